@@ -394,7 +394,7 @@ dco_status dco_stereo_agg_slices(dco_stereo* h, int view, int d0, int n, float* 
  * x 3 uint8) and outputs disp (device, H x W float), valid (device, H x W
  * uint8) are the caller's; every intermediate buffer (packed pixels, arms,
  * records, both aggregated volumes, disparity maps, the Eq. 1 tables) lives
- * in a static device array of 160 MiB that the library holds on each GPU it
+ * in a static device array of 172 MiB that the library holds on each GPU it
  * has run this call on until the process ends.  Shapes whose buffers do not
  * fit (beyond about 640 x 360 with D = 64) return DCO_ERR_SHAPE with the
  * bytes needed in dco_last_error(); argument and shape errors are the same

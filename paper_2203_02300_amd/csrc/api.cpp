@@ -166,17 +166,15 @@ static void free_handle_memory(dco_stereo* h) {
     for (void* p : ptrs) dev_free(p);
 }
 
-// Aggregation records with a zero apron and a zero extra row (zeroed once:
-// the geometry kernel writes only the interior).
+// Aggregation records with a zero apron and zero extra rows (zeroed once: the
+// geometry kernel writes only the interior).
 dco_status alloc_records(AggRecords* r, int W, int H) {
-    r->apron = kRecApronL;
-    r->Wp = W + kRecApronL + kRecApronR;
-    const size_t n = (size_t)r->Wp * (H + 1);
-    const size_t nb = (size_t)r->Wp * (H + kLMax + 1);
-    DCO_TRY(dev_alloc(&r->b, 4 * nb));
-    DCO_TRY(dev_alloc(&r->c, 4 * n));
-    DCO_HIP_CHECK(hipMemset(r->b, 0, 4 * nb * sizeof(uint32_t)));
-    DCO_HIP_CHECK(hipMemset(r->c, 0, 4 * n * sizeof(uint32_t)));
+    r->Wp = rec_wp(W);
+    const size_t nb = rec_b_words(W, H), nc = rec_c_words(W, H);
+    DCO_TRY(dev_alloc(&r->b, nb));
+    DCO_TRY(dev_alloc(&r->c, nc));
+    DCO_HIP_CHECK(hipMemset(r->b, 0, nb * sizeof(uint32_t)));
+    DCO_HIP_CHECK(hipMemset(r->c, 0, nc * sizeof(uint32_t)));
     return DCO_OK;
 }
 
@@ -186,7 +184,7 @@ static dco_status alloc_scratch(dco_stereo* h) {
     for (int v = 0; v < 2; ++v) {
         DCO_TRY(dev_alloc(&s.arms[v], P));
         DCO_TRY(alloc_records(&s.rec[v], h->W, h->H));
-        DCO_TRY(dev_alloc(&s.pix[v], P));
+        DCO_TRY(dev_alloc(&s.pix[v], pix_entries(h->W, h->H)));
         DCO_TRY(dev_alloc(&s.agg[v], V));
         DCO_TRY(dev_alloc(&s.dint[v], P));
     }
@@ -389,7 +387,7 @@ extern "C" dco_status dco_aggregate(dco_stereo* h, const float* cost, const uint
     }
     const uint32_t* arms = (const uint32_t*)arms_ref;
     DCO_HIP_CHECK(launch_geometry(arms, h->W, h->H, h->p.agg_iters, h->s.rec[0],
-                                  pair_rec_geom(h->p.agg_iters), h->stream));
+                                  h->stream));
     DCO_HIP_CHECK(launch_aggregate(cost, h->s.rec[0], h->W, h->H, h->D, h->p.agg_iters, agg,
                                    h->stream));
     return DCO_OK;
@@ -428,7 +426,7 @@ extern "C" dco_status dco_stereo_match(dco_stereo* h, const uint8_t* rgbL, const
     DCO_TRY(prof_mark(h));
     DCO_HIP_CHECK(launch_front2(img[0], img[1], h->W, h->H, p.census_w, p.census_h, p.arm_L1,
                                 p.arm_tau1, p.agg_iters, s.arms[0], s.arms[1], s.pix[0], s.pix[1],
-                                s.rec[0], s.rec[1], pair_rec_geom(p.agg_iters), h->stream));
+                                s.rec[0], s.rec[1], h->stream));
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
     DCO_HIP_CHECK(launch_cost_aggregate2(s.pix[0], s.pix[1], s.rec[0], s.rec[1], h->W, h->H, h->D,

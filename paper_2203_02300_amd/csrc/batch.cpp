@@ -60,10 +60,11 @@ dco_status alloc_pair(dco_batch* b, BatchPair& pr, int W, int H, int D) {
     pr.W = W;
     pr.H = H;
     pr.D = D;
-    pr.nstrips = (W + kStripOut - 1) / kStripOut;
+    const int sw = strip_out(b->p.agg_iters);
+    pr.nstrips = (W + sw - 1) / sw;
     for (int v = 0; v < 2; ++v) {
         DCO_TRY(balloc(b, &pr.arms[v], P));
-        DCO_TRY(balloc(b, &pr.pix[v], P));
+        DCO_TRY(balloc(b, &pr.pix[v], pix_entries(W, H)));
         const dco_status s = alloc_records(&pr.rec[v], W, H);
         for (void* q : {(void*)pr.rec[v].b, (void*)pr.rec[v].c})
             if (q) b->allocs.push_back(q);
@@ -322,7 +323,7 @@ dco_status tune_class(const dco_params& p, int W, int H, int D, hipStream_t st, 
     dco_status s = make_base(&tb, 1, p);
     int copies = 1;
     if (s == DCO_OK) {
-        const int nstrips = (W + kStripOut - 1) / kStripOut;
+        const int sw = strip_out(p.agg_iters), nstrips = (W + sw - 1) / sw;
         const long long slots = (long long)tb.cus * std::max(1, tb.per_cu[2]);
         copies = (int)std::min<long long>(16, std::max<long long>(
                                                    1, (4 * slots + 2LL * nstrips * D - 1) /
@@ -537,7 +538,7 @@ extern "C" dco_status dco_batch_tile(const dco_batch* b, int i, int* strip_w, in
         dco_set_error("dco_batch_tile: pair %d out of range", i);
         return DCO_ERR_ARG;
     }
-    if (strip_w) *strip_w = kStripOut;
+    if (strip_w) *strip_w = strip_out(b->p.agg_iters);
     if (band_h) *band_h = b->pairs[i].band;
     if (d_chunk) *d_chunk = b->pairs[i].dchunk;
     return DCO_OK;

@@ -108,7 +108,7 @@ template <int NT = 256>
 __device__ inline __attribute__((always_inline)) void census_tile(
     const uint8_t* __restrict__ rgb, int W, int H, int cw, int ch, int L1, int tau1,
     uint64_t* __restrict__ census, uint32_t* __restrict__ arms, uint32_t* __restrict__ rgb_packed,
-    uint4* __restrict__ pix, int x0, int y0, CensusLds& S) {
+    uint4* __restrict__ pix, bool planes, int x0, int y0, CensusLds& S) {
     static_assert(NT % 64 == 0 && (kCenTW * kCenTH) % NT == 0, "whole rows per pass");
     const int t = threadIdx.x;
     {   // stage the region: every load issued before any is stored
@@ -171,12 +171,22 @@ __device__ inline __attribute__((always_inline)) void census_tile(
         arms[(size_t)y * W + x] =
             (uint32_t)al | ((uint32_t)ar << 8) | ((uint32_t)au << 16) | ((uint32_t)ad << 24);
         if (rgb_packed) rgb_packed[(size_t)y * W + x] = cp;
-        // everything the fused raw cost needs of one pixel in one 16-byte
-        // load: census code, packed RGB, and 8 L_min (the byte offset of the
-        // pixel's (alpha, beta) pair)
-        if (pix)
-            pix[(size_t)y * W + x] = make_uint4((uint32_t)code, (uint32_t)(code >> 32), cp,
-                                                (uint32_t)(8 * min(min(al, ar), min(au, ad))));
+        // everything the fused raw cost needs of a pixel: census code, packed
+        // RGB and 8 L_min (the byte offset of the pixel's (alpha, beta) pair),
+        // in planes for the two-slice kernel or in one 16-byte word
+        const uint32_t lmin8 = (uint32_t)(8 * min(min(al, ar), min(au, ad)));
+        if (pix && planes) {
+            const PixPlanes px(W, H);
+            uint32_t* p = reinterpret_cast<uint32_t*>(pix);
+            const size_t i = (size_t)y * px.Wq + x;
+            p[kPixPad + i] = (uint32_t)code;
+            p[px.plane + kPixPad + i] = (uint32_t)(code >> 32);
+            p[2 * px.plane + kPixPad + i] = cp;
+            reinterpret_cast<uint8_t*>(p + 3 * px.plane)[i] = (uint8_t)lmin8;
+        } else if (pix) {
+            pix[(size_t)y * W + x] =
+                make_uint4((uint32_t)code, (uint32_t)(code >> 32), cp, lmin8);
+        }
     }
 }
 
@@ -185,25 +195,22 @@ __device__ inline __attribute__((always_inline)) void census_tile(
 // ===========================================================================
 //   N1 = sum over y' in [y-u, y+dn] of (l(x,y') + r(x,y') + 1)
 //   N2 = sum over x' in [x-l, x+r] of (u(x',y) + dn(x',y) + 1)
-// Stage-1 rounding uses sh = 31 + ceil(log2 N1) and m = ceil(2^sh / N1) <
-// 2^32, so floor(n / N1) = (n * m) >> sh for every 0 <= n < 2^31 (N1 <= 2^11).
 // A final division by N uses N' = N * 2^20 and y' = RN(1/N) * 2^-20 (both
 // exact scalings), so that it also removes the Q20 scale (div_q20 below).
 //
-// The streaming kernel keeps row r of a column-prefix ring in slot r mod R,
+// The streaming kernels keep row r of a column-prefix ring in slot r mod R,
 // so the byte offsets of the two prefix rows of a vertical range are fixed
 // per pixel and are stored here (16 bits each).
 
 constexpr int kAggK = kStripThreads / 64;             // rows per chunk = wavefronts (4)
 constexpr int kSeg = kStripThreads / 64;              // 64-column segments of a strip row
-constexpr int kRing1 = 2 * kLMax + 1 + kAggK;         // stage-1 prefix rows per column
-constexpr int kRing2 = 2 * kLMax + 2 + kAggK;         // stage 2 is read one chunk later
+constexpr int kRing1 = 2 * kLMax + 1 + kAggK;         // prefix rows per column (one stage)
 constexpr int kRingCols = kStripThreads - 2 * kLMax;  // columns with a ring: 222
 constexpr int kRingStride = 224;                      // a multiple of the 32 LDS banks
 constexpr uint32_t kSlotBytes = kRingStride * 4;
 constexpr int kPStride = 280;                         // prefix row: P(-1) at 0, P(i) at i + 1
 constexpr uint32_t kOOB = 0x7fffffffu;                // buffer offset that reads as 0
-static_assert(kRing2 * kSlotBytes < 65536, "ring offsets are stored in 16 bits");
+static_assert(kRing1 * kSlotBytes < 65536, "ring offsets are stored in 16 bits");
 static_assert(kStripThreads == 256 && kAggK == 4, "one row per wavefront per chunk");
 
 __device__ inline uint32_t ring_slot(int row, int ring) {
@@ -215,40 +222,57 @@ __device__ inline uint32_t ring_slot_bytes(int row, int ring) {
     return ring_slot(row, ring) * kSlotBytes;
 }
 
-// Records for the single-slice kernels (k_agg_stream, k_agg_pair<1>, the
-// batched path).
-constexpr RecGeom kRecPlain{kRing1, kRing2, kSlotBytes, kSlotBytes, 4};
+// Layout of the two-slice kernel (agg_stream_ws) that its records address.
+constexpr int kWsThreads = 3 * kStripThreads;
+constexpr int kWsSlices = 2;
+constexpr int kWsRing = 2 * kLMax + 2;
+constexpr int kWsI0 = 16;                             // first strip column with a ring
+constexpr int kWsCols = 224;                          // columns with a ring
+constexpr uint32_t kWsSlotBytes = kWsCols * 8;        // one ring row of both slices
+constexpr int kWsLanes = kWsCols / 4;                 // output lanes with columns
+constexpr uint32_t kWsPlaneBytes = kWsLanes * 8;      // a plane of an output row's prefixes
+constexpr uint32_t kWsOffBias = 64;                   // keeps the left offsets non-negative
+static_assert(kWsRing % kAggK == 0, "a chunk's slots are consecutive");
+static_assert(kWsApron % 4 == 0 && kWsOut % 4 == 0 && kWsI0 % 4 == 0 && kWsCols % 4 == 0,
+              "quads are aligned");
+static_assert(kWsI0 <= kWsApron - kLMax && kWsI0 + kWsCols >= kWsApron + kWsOut + kLMax &&
+                  kWsApron >= 2 * kLMax && kWsApron + kWsOut + 2 * kLMax <= kStripThreads,
+              "the strip's aprons");
+static_assert((kWsRing - 1) * kWsSlotBytes < 65536, "ring offsets are stored in 16 bits");
+static_assert(8 * (kLMax + 1) < 256, "arm offsets are stored in 8 bits");
 
-// Records of pixel (x, y) with arms word a and region counts n1, n2 (layout:
-// AggRecords).  The b row of the pixel's own row gets its horizontal arms
-// (low half of word 2); the b row kLMax rows below gets its stage-1 data.
-// ring1 and ring2 are the row counts of the two rings of the kernel that
-// reads the records.
+// Records of pixel (x, y) with arms word a and region counts n1, n2 (layouts:
+// AggRecords).  Entries of a b row come from up to three pixels of its
+// column: each writes its own words or halves.
 __device__ inline void write_records(const AggRecords& rec, int x, int y, int iters, uint32_t a,
-                                     uint32_t n1, uint32_t n2, const RecGeom& g) {
+                                     uint32_t n1, uint32_t n2, int H) {
     const uint32_t l = a & 0xff, r = (a >> 8) & 0xff, u = (a >> 16) & 0xff, dn = a >> 24;
-    const uint32_t lr = g.hw * (r + 1) | (g.hw * l) << 8;
-    const uint32_t hi = (uint32_t)y + dn, lo = (uint32_t)y - u - 1;
-    const size_t col = (size_t)x + rec.apron;
+    const int hi = y + (int)dn, lo = y - (int)u - 1;
+    const size_t col = (size_t)x + kRecApronL;
     uint32_t* bo = rec.b + 4 * ((size_t)y * rec.Wp + col);
-    reinterpret_cast<uint16_t*>(bo + 2)[0] = (uint16_t)lr;
     uint32_t* bv = rec.b + 4 * ((size_t)(y + kLMax) * rec.Wp + col);
-    bv[1] = ring_slot((int)hi, g.ring1) * g.step1 | ring_slot((int)lo, g.ring1) * g.step1 << 16;
     if (iters == 2) {
-        const uint32_t lg = n1 <= 1 ? 0u : 32u - (uint32_t)__clz((int)(n1 - 1));
-        const uint32_t sh = 31u + lg;
-        // m = ceil(2^sh / N1) from the correctly rounded double quotient:
-        // the quotient is below 2^32, so its rounding error is at most 2^-22,
-        // while a quotient that is not an integer is at least 1 / N1 > 2^-11
-        // away from one, so the ceiling is exact
-        bv[0] = (uint32_t)__builtin_ceil(__builtin_ldexp(1.0, (int)sh) / (double)n1);
-        reinterpret_cast<uint16_t*>(bv + 2)[1] = (uint16_t)((n1 >> 1) | sh << 10);
-        uint32_t* c = rec.c + 4 * ((size_t)y * rec.Wp + col);
-        c[0] = ring_slot((int)hi, g.ring2) * g.step2 | ring_slot((int)lo, g.ring2) * g.step2 << 16;
-        c[1] = __float_as_uint((1.0f / (float)n2) * 0x1p-20f);
-        c[2] = lr | n2 << 16;
-        c[3] = __float_as_uint((float)n2 * 0x1p20f);
+        constexpr int R = kWsRing;
+        reinterpret_cast<uint16_t*>(bo + 3)[0] = (uint16_t)(8 * (r + 1) | (8 * l) << 8);
+        bv[0] = __float_as_uint(1.0f / (float)n1);
+        bv[1] = ring_slot(hi, R) * kWsSlotBytes | ring_slot(lo, R) * kWsSlotBytes << 16;
+        reinterpret_cast<int16_t*>(bv + 3)[1] = (int16_t)(0 - (int)n1);
+        bv[4 * (size_t)kLMax * rec.Wp + 2] = ring_slot(hi + kLMax, R) * kWsSlotBytes |
+                                             ring_slot(lo + kLMax, R) * kWsSlotBytes << 16;
+        // byte offsets, from the lane's own entry, of columns x + r + 1 and
+        // x - l in a row of prefixes kept in four planes
+        const auto plane_off = [&](int k) {
+            return (uint32_t)(k & 3) * kWsPlaneBytes + (uint32_t)(8 * (k >> 2)) + kWsOffBias;
+        };
+        const int j = x & 3;
+        uint32_t* c = rec.c + (size_t)y * rec.Wp + col;
+        const size_t plane = (size_t)rec.Wp * H;
+        c[0] = plane_off(j + (int)r + 1) | plane_off(j - (int)l) << 16;
+        c[plane] = __float_as_uint((1.0f / (float)n2) * 0x1p-20f);
+        c[2 * plane] = __float_as_uint((float)n2 * 0x1p20f);
     } else {
+        reinterpret_cast<uint16_t*>(bo + 2)[0] = (uint16_t)(4 * (r + 1) | (4 * l) << 8);
+        bv[1] = ring_slot_bytes(hi, kRing1) | ring_slot_bytes(lo, kRing1) << 16;
         bv[0] = __float_as_uint((1.0f / (float)n1) * 0x1p-20f);
         reinterpret_cast<uint16_t*>(bv + 2)[1] = (uint16_t)n1;
     }
@@ -274,7 +298,7 @@ struct GeomLds {
 template <int NT = 256>
 __device__ inline __attribute__((always_inline)) void geometry_tile(
     const uint32_t* __restrict__ arms, int W, int H, int iters, const AggRecords& rec, int x0,
-    int y0, GeomLds& S, const RecGeom& g = kRecPlain) {
+    int y0, GeomLds& S) {
     static_assert(NT == 256 || NT == 1024, "256 or 1024 threads");
     const int t = threadIdx.x;
     {   // stage the arms: every load issued before any is used (clamped addresses)
@@ -378,49 +402,43 @@ __device__ inline __attribute__((always_inline)) void geometry_tile(
         const uint32_t a = (uint32_t)l | (uint32_t)r << 8 | (uint32_t)u << 16 | (uint32_t)dn << 24;
         const uint32_t n1 = S.cp[ty + kLMax + dn + 1][tx] - S.cp[ty + kLMax - u][tx];
         const uint32_t n2 = S.rp[ty][tx + kLMax + r + 1] - S.rp[ty][tx + kLMax - l];
-        write_records(rec, x, y, iters, a, n1, n2, g);
+        write_records(rec, x, y, iters, a, n1, n2, H);
     }
 }
 
 // ===========================================================================
-// Streaming two-stage aggregation (Eq. 2 twice), one slice x one column strip
+// Streaming one-stage aggregation (Eq. 2 once), one slice x one column strip
 // ===========================================================================
 //
 // A strip is 256 consecutive columns: 2 kLMax apron columns on each side and
 // kStripOut output columns in the middle.  The workgroup streams down the
-// rows in chunks of kAggK = 4 rows, in three steps per chunk:
+// rows in chunks of kAggK = 4 rows, in two steps per chunk:
 //   1 (wavefront w, row yc + w, all 256 columns as 4 segments of 64):
 //       raw cost q (fused: Eq. 1 from the images; staged: read), inclusive
 //       row prefix P1 by a wavefront scan per segment plus segment carries
 //   2 (thread t owns column t, rows yc .. yc + 3 in order):
 //       H1: E1 = P1(t + r) - P1(t - l - 1); push the column prefix of E1
-//       V1: S1 of row y - kLMax from two prefix rows of ring 1
-//           a1 = floor((S1 + N1/2) / N1) (multiply-shift), push into ring 2
-//   3 (wavefront w, output row y - 2 kLMax - 1 of row yc + w, 4 segments):
-//       V2: E2 from two prefix rows of ring 2; row prefix P2 as in step 1
-//       H2: S2 = P2(t + r) - P2(t - l - 1); out = RN(S2 / N2) * 2^-20
-// Two barriers per chunk: after step 1 (P1 rows) and after step 2 (ring 2,
-// and the end of step 2's reads of P1).  Row prefixes of steps 1 and 3 share
-// one LDS row per wavefront: only the wavefront that owns a row writes it.
-// Ring 1 holds kAggK - 1 rows more than a vertical range spans so that a
-// chunk's four pushes can precede its four range reads; ring 2 is read in
-// step 3, after all four pushes of step 2, so it holds kAggK rows more.
+//       V1: S1 of row y - kLMax from two prefix rows of the ring
+//           out = RN(S1 / N1) * 2^-20
+// Two barriers per chunk: after step 1 (P1 rows) and after step 2 (the end of
+// its reads of P1).  The ring holds kAggK - 1 rows more than a vertical range
+// spans so that a chunk's four pushes can precede its four range reads.
 //
 // Every sum is an integer and differences of prefix sums are taken mod 2^32
 // (every true range sum is below 2^31), so the result does not depend on the
 // summation order, and a band of output rows [y0, y1) can start from zero
-// prefixes 2 kLMax + 1 rows above y0: the rows before the start then shift
-// every prefix by the same constant.
+// prefixes kLMax rows above y0: the rows before the start then shift every
+// prefix by the same constant.
 //
-// Per-pixel data comes from padded records (zero apron, zero row H) through
-// buffer loads with a per-lane column offset and a uniform row offset, so the
-// chunk body has no bounds branches.
+// Per-pixel data comes from padded records (zero apron) through buffer loads
+// with a per-lane column offset and a uniform row offset, so the chunk body
+// has no bounds branches.
 
 // Every member starts below 64 KB, so LDS addresses fold into the 16-bit
 // instruction offsets.  Reads of a prefix row reach up to kLMax words before
 // it (apron lanes, results unused): `guard` and the tables keep them inside
 // the allocation.
-template <int ITERS, bool kFused>
+template <bool kFused>
 struct AggLds {
     float tabA[kFused ? 768 : 1];
     float tabC[kFused ? 68 : 1];
@@ -428,7 +446,6 @@ struct AggLds {
     uint32_t guard[32];
     uint32_t prow[kAggK][kPStride];
     uint32_t ring1[kRing1 * kRingStride];
-    uint32_t ring2[ITERS == 2 ? kRing2 * kRingStride : 1];
 };
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -506,8 +523,9 @@ __device__ inline float div_q20(uint32_t s, float n_scaled, float rcp_scaled) {
 
 struct AggArgs {
     const float* cost;         // staged: D x H x W raw costs
-    const uint4* pixL;         // fused: packed pixels of both views (H x W):
-    const uint4* pixR;         //   census lo, census hi, RGB, 8 L_min
+    const uint4* pixL;         // fused: packed pixels of both views: census lo,
+    const uint4* pixR;         //   census hi, RGB, 8 L_min (one stage: 16-byte words,
+                               //   H x W; two: planes, see PixPlanes)
     const float* tabA;         // fused: Eq. 1 tables
     const float* tabC;
     const float* alpha;
@@ -533,15 +551,14 @@ __device__ inline float paired_at(const float* __restrict__ vol, int P, int D, i
     return vol[(size_t)(e + 1) * P + i];
 }
 
-// Loads of one chunk.  Step 1 and step 3 loads are for this lane's four
-// segment columns of its wavefront's row; step 2 loads are for the owned
-// column and the chunk's four rows.
+// Loads of one chunk.  Step 1 loads are for this lane's four segment columns
+// of its wavefront's row; step 2 loads are for the owned column and the
+// chunk's four rows.
 template <bool kFused>
 struct ChunkIn {
     uint4 ref[kSeg];            // fused: reference pixel; staged: .x = raw cost bits
     uint4 par[kSeg];            // fused: partner pixel
     uint4 b2[kAggK];            // step 2: records b of rows yc + k
-    uint4 c3[kSeg];             // step 3: records c of the output row
 };
 
 // Per-lane constants of a strip.
@@ -550,26 +567,17 @@ struct AggLane {
                           // pixels: x16; cost slice: x4), or kOOB
     uint32_t par[kSeg];   // fused: the partner column's byte offset, or kOOB
     uint32_t inval[kSeg]; // fused: raw cost when the partner is outside (2^20; 0 off-image)
-    uint32_t recw;        // record column index x4 of segment 0 of this lane
     uint32_t reco;        // record column index x4 of the owned column
-    uint32_t cb1, cb2;    // ring byte offsets of the owned column
-    uint32_t cbs[kSeg];   // ring-2 byte offset of each segment column (column
-                          // kRingCols + 1, never written, for columns without a ring)
-    uint32_t vout[kSeg];  // output byte offset of each segment column, or kOOB
-    uint32_t vout_o;      // output byte offset of the owned column, or kOOB (one stage)
+    uint32_t cb1;         // ring byte offset of the owned column
+    uint32_t vout_o;      // output byte offset of the owned column, or kOOB
     bool pok[kSeg];       // fused: partner inside the image
 };
 
 struct AggRes {
-    rsrc_t rB, rC, rq, rIr, rIp, rOut;
-    uint32_t slice_bytes;  // two-slice kernel: distance between its output slices
-    uint32_t in_slice_bytes;  // staged two-slice kernel: distance between its input
-                              // slices (0 when only one slice is left: it is read twice)
-    int nout;              // two-slice kernel: slices that exist (the others are not stored)
-    bool paired;           // two-slice kernel: paired layout (AggArgs::paired)
+    rsrc_t rB, rq, rIr, rIp, rOut;
 };
 
-template <int ITERS, bool kFused>
+template <bool kFused>
 __device__ inline void load_chunk(const AggArgs& A, int yc, const AggLane& ln, const AggRes& R,
                                   ChunkIn<kFused>& in) {
     const int H = A.H;
@@ -594,19 +602,12 @@ __device__ inline void load_chunk(const AggArgs& A, int yc, const AggLane& ln, c
         const uint32_t rb = (uint32_t)min(y, H + kLMax);
         in.b2[k] = ld128(R.rB, ln.reco * 4, rb * Wp * 16);
     }
-    if (ITERS == 2) {  // step 3: output row yc + w - 2 kLMax - 1
-        const int y2 = yc + w - 2 * kLMax - 1;
-        const uint32_t rc = (uint32_t)(y2 >= 0 && y2 < H ? y2 : H);
-#pragma unroll
-        for (int j = 0; j < kSeg; ++j) in.c3[j] = ld128(R.rC, ln.recw * 4 + 1024 * j, rc * Wp * 16);
-    }
 }
 
-template <int ITERS, bool kFused>
+template <bool kFused>
 __device__ inline void process_chunk(const AggArgs& A, int yc, int y0, int y1, const AggLane& ln,
                                      const AggRes& R, const ChunkIn<kFused>& in,
-                                     uint32_t& cp1, uint32_t& cp2, uint32_t& s1off,
-                                     uint32_t& s2off, AggLds<ITERS, kFused>& S) {
+                                     uint32_t& cp1, uint32_t& s1off, AggLds<kFused>& S) {
     const int t = threadIdx.x, w = wave_id(), lane = t & 63;
     const int H = A.H, W = A.W;
     uint32_t* prow_w = S.prow[w];
@@ -642,7 +643,7 @@ __device__ inline void process_chunk(const AggArgs& A, int yc, int y0, int y1, c
         for (int j = 0; j < kSeg; ++j) prow_w[64 * j + lane + 1] = v[j];
     }
     __syncthreads();
-    // ---- step 2: column prefixes, stage-1 means of rows yc + k - kLMax ----
+    // ---- step 2: column prefixes, means of rows yc + k - kLMax ----
     // Ring 1 keeps kAggK - 1 rows more than a range needs, so the chunk's
     // four pushes can all go before its four range reads.
     uint32_t e1[kAggK], s1[kAggK];
@@ -668,54 +669,18 @@ __device__ inline void process_chunk(const AggArgs& A, int yc, int y0, int y1, c
 #pragma unroll
     for (int k = 0; k < kAggK; ++k) {
         const uint4 b = in.b2[k];
-        if (ITERS == 2) {
-            const uint64_t n = (uint64_t)(s1[k] + ((b.z >> 16) & 1023)) * b.x;
-            cp2 += (uint32_t)(n >> (b.z >> 26));
-            lds_st(S.ring2, ln.cb2 + s2off, cp2);
-            s2off = s2off + kSlotBytes == kRing2 * kSlotBytes ? 0u : s2off + kSlotBytes;
-        } else {
-            const int yv = yc + k - kLMax;
-            const float a1 = div_q20(s1[k], (float)(b.z >> 16) * 0x1p20f,
-                                     __builtin_bit_cast(float, b.x));
-            if (yv >= y0 && yv < y1) st32(a1, R.rOut, ln.vout_o, (uint32_t)(yv * W) * 4);
-        }
+        const int yv = yc + k - kLMax;
+        const float a1 = div_q20(s1[k], (float)(b.z >> 16) * 0x1p20f,
+                                 __builtin_bit_cast(float, b.x));
+        if (yv >= y0 && yv < y1) st32(a1, R.rOut, ln.vout_o, (uint32_t)(yv * W) * 4);
     }
     __syncthreads();
-    if (ITERS == 2) {
-        // ---- step 3: stage-2 means of output row yc + w - 2 kLMax - 1 ----
-        const int y2 = yc + w - 2 * kLMax - 1;
-        uint32_t v[kSeg];
-#pragma unroll
-        for (int j = 0; j < kSeg; ++j) {
-            const uint32_t o = in.c3[j].x;
-            v[j] = lds_ld(S.ring2, ln.cbs[j] + (o & 0xffff)) -
-                   lds_ld(S.ring2, ln.cbs[j] + (o >> 16));
-        }
-        wave_scan_segments(v);
-#pragma unroll
-        for (int j = 0; j < kSeg; ++j) prow_w[64 * j + lane + 1] = v[j];
-        // the row was written by this wavefront only: LDS keeps its order
-        float out[kSeg];
-        const uint32_t pbw = (uint32_t)(w * kPStride + lane) * 4;
-#pragma unroll
-        for (int j = 0; j < kSeg; ++j) {
-            const uint32_t lr = in.c3[j].z;
-            const uint32_t s2 = lds_ld(S.prow[0], pbw + 256 * j + (lr & 0xff)) -
-                                lds_ld(S.prow[0], pbw + 256 * j - ((lr >> 8) & 0xff));
-            out[j] = div_q20(s2, (float)(in.c3[j].z >> 16) * 0x1p20f,
-                             __builtin_bit_cast(float, in.c3[j].y));
-        }
-        if (y2 >= y0 && y2 < y1) {
-#pragma unroll
-            for (int j = 0; j < kSeg; ++j) st32(out[j], R.rOut, ln.vout[j], (uint32_t)(y2 * W) * 4);
-        }
-    }
 }
 
 // Output rows [y0, y1) of slice d and column strip `strip` (256 threads).
-template <int ITERS, bool kFused>
+template <bool kFused>
 __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, int y1,
-                                  AggLds<ITERS, kFused>& S) {
+                                  AggLds<kFused>& S) {
     const int W = A.W, H = A.H;
     const int t = threadIdx.x, lane = t & 63;
     const int x0 = strip * kStripOut;
@@ -732,8 +697,6 @@ __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, in
     if (t < kAggK) S.prow[t][0] = 0;  // P(-1) of every prefix row
     // zero column prefixes: rows before the start contribute nothing
     for (int i = t; i < kRing1 * kRingStride; i += kStripThreads) S.ring1[i] = 0;
-    if (ITERS == 2)
-        for (int i = t; i < kRing2 * kRingStride; i += kStripThreads) S.ring2[i] = 0;
 
     AggLane ln;
 #pragma unroll
@@ -747,30 +710,21 @@ __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, in
         ln.par[j] = pok ? (uint32_t)cp * 16 : kOOB;
         ln.pok[j] = pok;
         ln.inval[j] = in_img ? (1u << 20) : 0u;
-        const bool rok = i >= kLMax && i < kLMax + kRingCols;
-        ln.cbs[j] = (uint32_t)(rok ? i - kLMax : kRingCols + 1) * 4;
-        ln.vout[j] = i >= 2 * kLMax && i < 2 * kLMax + kStripOut && c < W ? (uint32_t)c * 4 : kOOB;
     }
     {
         const int c = x0 - 2 * kLMax + t;
         const int jj = t - kLMax;
         const bool ring = jj >= 0 && jj < kRingCols;
-        // owners without a ring column share one scratch column; column
-        // kRingCols + 1 stays zero
+        // owners without a ring column share one scratch column
         ln.cb1 = (uint32_t)(ring ? jj : kRingCols) * 4;
-        ln.cb2 = ln.cb1;
-        ln.reco = (uint32_t)(c + A.rec.apron) * 4;
-        ln.recw = (uint32_t)(x0 - 2 * kLMax + lane + A.rec.apron) * 4;
+        ln.reco = (uint32_t)(c + kRecApronL) * 4;
         ln.vout_o = t >= 2 * kLMax && t < 2 * kLMax + kStripOut && c < W ? (uint32_t)c * 4 : kOOB;
     }
-    const uint32_t recN = (uint32_t)(A.rec.Wp * (H + 1));
     const uint32_t P4 = (uint32_t)(slice * 4);
     const uint4* Iref = A.ref == 0 ? A.pixL : A.pixR;
     const uint4* Ipar = A.ref == 0 ? A.pixR : A.pixL;
     AggRes R;
     R.rB = make_rsrc(A.rec.b, (uint32_t)(A.rec.Wp * (H + kLMax + 1)) * 16);
-    R.rC = make_rsrc(ITERS == 2 ? (const void*)A.rec.c : (const void*)A.rec.b,
-                     ITERS == 2 ? recN * 16 : 0u);
     R.rq = make_rsrc(kFused ? (const void*)A.rec.b : (const void*)(A.cost + (size_t)d * slice),
                      kFused ? 0u : P4);
     R.rIr = make_rsrc(kFused ? (const void*)Iref : (const void*)A.rec.b, kFused ? 4 * P4 : 0u);
@@ -779,169 +733,169 @@ __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, in
     __syncthreads();
 
     // warm-up rows so that the first output row sees complete ranges
-    const int warm = ITERS == 2 ? 2 * kLMax + 1 : kLMax;
+    const int warm = kLMax;
     const int ys = max(0, y0 - warm);
     const int yend = y1 + warm;
-    uint32_t cp1 = 0, cp2 = 0;
+    uint32_t cp1 = 0;
     uint32_t s1off = ring_slot_bytes(ys, kRing1);
-    uint32_t s2off = ring_slot_bytes(ys - kLMax, kRing2);
     ChunkIn<kFused> ca, cb;
-    load_chunk<ITERS, kFused>(A, ys, ln, R, ca);
+    load_chunk<kFused>(A, ys, ln, R, ca);
     for (int yc = ys; yc < yend; yc += 2 * kAggK) {
         // the next chunk's loads are in flight while this chunk is processed
-        load_chunk<ITERS, kFused>(A, yc + kAggK, ln, R, cb);
-        process_chunk<ITERS, kFused>(A, yc, y0, y1, ln, R, ca, cp1, cp2, s1off, s2off, S);
+        load_chunk<kFused>(A, yc + kAggK, ln, R, cb);
+        process_chunk<kFused>(A, yc, y0, y1, ln, R, ca, cp1, s1off, S);
         if (yc + kAggK >= yend) break;
-        load_chunk<ITERS, kFused>(A, yc + 2 * kAggK, ln, R, ca);
-        process_chunk<ITERS, kFused>(A, yc + kAggK, y0, y1, ln, R, cb, cp1, cp2, s1off, s2off,
-                                     S);
+        load_chunk<kFused>(A, yc + 2 * kAggK, ln, R, ca);
+        process_chunk<kFused>(A, yc + kAggK, y0, y1, ln, R, cb, cp1, s1off, S);
     }
 }
 
 // ===========================================================================
-// Two-slice streaming aggregation with specialised wavefronts (one-call path)
+// Two-slice streaming aggregation with specialised wavefronts (two stages)
 // ===========================================================================
 //
-// One workgroup of 512 threads streams two adjacent disparity slices of one
-// column strip down the rows, in chunks of kAggK rows as above, with each
-// step done by a fixed set of wavefronts and the steps of three consecutive
-// chunks in flight:
-//   row wavefronts 0-3, phase p: step 3 of chunk p - 2 (its output row,
-//       both slices) and step 1 of chunk p (its row, both slices);
-//   column wavefronts 4-7 (thread 256 + t owns column t), phase p: step 2 of
-//       chunk p - 1 (both slices).
-// One barrier ends a phase.  Each step's reference pixels and records are
-// loaded once for both slices, and every LDS word holds the two slices'
-// values of one column (one 64-bit access serves both).
-//  * Prefix rows are double-buffered by chunk parity: step 1 of chunk p
-//    writes buffer p & 1 while step 2 of chunk p - 1 reads the other one.
-//    Step 3 uses its own wavefront's row of buffer p & 1 as scratch before
-//    step 1 of the same wavefront overwrites it.
-//  * Ring 1 is private to the column thread, which pushes a row and reads
-//    that row's range before the next push, so 2 kLMax + 2 rows suffice.
-//  * Ring 2 is pushed by step 2 of chunk p - 1 while step 3 of chunk p - 2
-//    reads it: it keeps 2 kLMax + 2 + 2 kAggK rows so that no push of the
-//    phase lands on a row still being read.
-constexpr int kWsThreads = 2 * kStripThreads;
-constexpr int kWsSlices = 2;
-static_assert(kWsSlices == 2 && kSeg == 4, "the step-1 register pin lists 2 x 4 values");
-constexpr int kWsRing1 = 2 * kLMax + 2;
-constexpr int kWsRing2 = 2 * kLMax + 2 + 2 * kAggK;
-constexpr uint32_t kWsSlotBytes = kRingStride * 8;  // one ring row of both slices
-// Prefix rows hold P(c) at index c + kWsP0 and P(-1) = 0 at kWsP0 - 1, so
-// that lane l's four columns 4 l .. 4 l + 3 form two aligned 16-byte words.
-constexpr int kWsP0 = 4;
-constexpr int kWsPStride = 260;  // P(-1) .. P(255)
-static_assert(kWsPStride % 2 == 0 && kWsP0 + 256 <= kWsPStride, "prefix row layout");
-// Records for this kernel: ring 1 offsets in bytes, ring 2 offsets in 8-byte
-// words (its byte offsets would not fit 16 bits), arm offsets in 8-byte words.
-constexpr RecGeom kRecWs{kWsRing1, kWsRing2, kWsSlotBytes, kRingStride, 8};
-static_assert((kWsRing1 - 1) * kWsSlotBytes < 65536 && (kWsRing2 - 1) * kRingStride < 65536,
-              "ring offsets are stored in 16 bits");
-
+// One workgroup of 768 threads streams two adjacent disparity slices of one
+// column strip down the rows, in chunks of kAggK rows, with each step done by
+// a fixed set of wavefronts and three consecutive chunks in flight.  Phase p:
+//   cost wavefronts 0-3 (wavefront w: row w of chunk p): the raw costs of
+//       Eq. 1 of both slices and their row prefixes;
+//   column wavefronts 4-7 (thread 256 + t owns ring column t), chunk p - 1,
+//       row by row: stage-1 horizontal range sums from the prefix rows, the
+//       vertical ones through ring 1, the stage-1 mean, the stage-2 vertical
+//       range sums through ring 2;
+//   output wavefronts 8-11 (wavefront w: row w of chunk p - 2): row prefixes
+//       of those sums, the horizontal range sums, the final division, stores.
+// One barrier ends a phase; a SIMD holds one wavefront of each kind.
+//
+// A strip is 256 input columns, kWsApron of them left of its kWsOut output
+// columns.  A cost or output lane owns four consecutive columns, so a row
+// prefix is three adds per lane and one wavefront scan of the lane totals,
+// every per-pixel input is a 16-byte load of four columns from a plane, and a
+// store is one 16-byte word.  The apron is 36 rather than 2 kLMax = 34, and
+// the strip 184 rather than 188, so that those quads are aligned to the
+// image's.  Every LDS word holds the two slices' values of one column (one
+// 64-bit access serves both).
+//  * Prefix rows are exclusive (entry i is the sum of the columns before i),
+//    so a range sum over [x - l, x + r] is entry x + r + 1 minus entry x - l
+//    and no entry is needed before the first column.
+//  * Both rings are private to the column thread, which pushes a row and
+//    reads that row's range before the next push, so 2 kLMax + 2 rows do.
+//    Stream row r lies in slot r mod 36 of ring 1, and so does the a1 row
+//    pushed with it, r - kLMax, in ring 2.
+//  * The output wavefront works in place on its row of the stage-2 sums: it
+//    takes four columns per lane as 16-byte words and writes the prefixes
+//    back in four planes (column mod 4), in which the lanes' range reads are
+//    consecutive.
+//
+// What bounds it: between two barriers a SIMD's three wavefronts share VALU
+// and LDS (busy 65 % and 53 %), and the rings fill a CU's LDS, so there is no
+// fourth.  Two kinds of wavefront on 512 threads, a column per lane and
+// segment, took 0.829 ms for both views at 1280 x 720, D = 128; this form
+// takes 0.579 ms (row prefixes without a pass through LDS, a third wavefront
+// per SIMD, no 64-bit multiply in the mean, 16-byte stores).
 struct AggLdsWs {
     float tabA[768];
     float tabC[68];
     float2 ab[kLMax + 1];
-    uint32_t guard[32];
-    alignas(16) uint2 prow[2][kAggK][kWsPStride];  // [buffer][row][index]: both slices
-    uint2 ring1[kWsRing1 * kRingStride];            // [slot][column]: both slices
-    uint2 ring2[kWsRing2 * kRingStride];
+    alignas(16) uint2 x1[2][kAggK][kStripThreads];  // stage-1 row prefixes, by chunk parity
+    alignas(16) uint2 e2[2][kAggK][kWsCols];        // stage-2 vertical sums, by chunk parity
+    uint2 ring1[kWsRing * kWsCols];                 // [slot][column]
+    uint2 ring2[kWsRing * kWsCols];
 };
 static_assert(sizeof(AggLdsWs) <= 160 * 1024, "one workgroup per CU");
 
-__device__ inline uint2 lds_ld2(const uint2* base, uint32_t byte_off) {
-    return *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(base) + byte_off);
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ inline uint2 lds_ld2(const void* base, uint32_t byte_off) {
+    return *reinterpret_cast<const uint2*>(static_cast<const char*>(base) + byte_off);
 }
-__device__ inline void lds_st2(uint2* base, uint32_t byte_off, uint2 v) {
-    *reinterpret_cast<uint2*>(reinterpret_cast<char*>(base) + byte_off) = v;
+__device__ inline void lds_st2(void* base, uint32_t byte_off, uint2 v) {
+    *reinterpret_cast<uint2*>(static_cast<char*>(base) + byte_off) = v;
+}
+// A 16-byte buffer store reads its data registers late: a vector instruction
+// right behind it that writes one of them changed the stored words on gfx950
+// (the compiler expects this only of stores without a register offset).  The
+// wait state that names the data keeps the registers until it has passed.
+__device__ inline void st128(u32x4 v, rsrc_t r, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 0" : : "v"(v));
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// Loads of a row wavefront for one phase: the pixels of step 1's row and the
-// c records of step 3's output row.
-struct WsRowIn {
-    uint4 ref[kSeg];
-    uint4 par[kWsSlices][kSeg];
-    uint4 c3[kSeg];
+// What the wavefronts of a workgroup share: the item and its buffers.
+struct WsItem {
+    rsrc_t rB, rC, rRef, rPar, rCost, rOut;
+    uint32_t Wq4, plane4, lm;      // pixel planes: bytes of a row and of a plane, L_min plane
+    uint32_t slice_bytes;          // distance between the output slices
+    uint32_t in_slice_bytes;       // ... and the cost volume's (0 when one slice is left)
+    int nout;                      // slices that exist (the others are not stored)
+    bool paired;                   // paired layout (see paired_at)
+    bool quads;                    // W % 4 == 0: rows of the volumes keep quads aligned
+    int x0, ys, y0, y1, nch;       // strip, first stream row (a multiple of 4), band, chunks
 };
 
-// Loads of a column thread for one phase: the b records of step 2's rows.
+// Loads of a cost wavefront for one chunk.  Fused: the lane's four reference
+// pixels and the five partner pixels of its columns in both slices; staged:
+// the two slices' raw costs in ref[0] and ref[1].
+struct WsCostIn {
+    uint4 ref[3], par[3];   // census lo, census hi, RGB
+    uint32_t lmin, par4[3];
+};
 struct WsColIn {
-    uint4 b2[kAggK];
+    uint4 b[kAggK];
+};
+struct WsOutIn {
+    uint4 off, rcp, n;
 };
 
-struct WsRowLane {
-    uint32_t img[kSeg], col4[kSeg], par[kWsSlices][kSeg], inval[kSeg], cbs[kSeg], vout[kSeg], recw;
-    bool pok[kWsSlices][kSeg];
+struct WsCostLane {
+    uint32_t vref, vlm, vpar;      // byte offsets of the lane's columns in a plane row
+    uint32_t vq[4];                // staged: byte offsets in a cost row, or kOOB
+    bool ok[kWsSlices][4];         // fused: partner inside the image
 };
 
-// Row wavefront: loads for phase p (step 1 of chunk p, step 3 of chunk p - 2).
-// kFused: the pixels of both views for the raw cost; else the two slices'
-// raw costs of the row from the cost volume (in the x words of in.par).
 template <bool kFused>
-__device__ inline void ws_row_load(const AggArgs& A, int ys, int p, int w, const WsRowLane& ln,
-                                   const AggRes& R, WsRowIn& in) {
-    const uint32_t W = (uint32_t)A.W, Wp = (uint32_t)A.rec.Wp;
-    const uint32_t yq = (uint32_t)min(ys + kAggK * p + w, A.H - 1);
+__device__ inline void ws_cost_load(const WsItem& I, int H, int W, int p, int w,
+                                    const WsCostLane& ln, WsCostIn& in) {
+    const uint32_t y = (uint32_t)min(I.ys + kAggK * p + w, H - 1);
+    if constexpr (kFused) {
+        const uint32_t row = y * I.Wq4;
 #pragma unroll
-    for (int j = 0; j < kSeg; ++j) {
-        if constexpr (kFused) {
-            in.ref[j] = ld128(R.rIr, ln.img[j], yq * W * 16);
+        for (int k = 0; k < 3; ++k) {
+            in.ref[k] = ld128(I.rRef, ln.vref, row + k * I.plane4);
+            in.par[k] = ld128(I.rPar, ln.vpar, row + k * I.plane4);
+            in.par4[k] = ld32(I.rPar, ln.vpar + 16, row + k * I.plane4);
+        }
+        in.lmin = ld32(I.rRef, ln.vlm, I.lm + (row >> 2));
+    } else {
+        const uint32_t row = y * (uint32_t)W * 4;
 #pragma unroll
-            for (int s = 0; s < kWsSlices; ++s)
-                in.par[s][j] = ld128(R.rIp, ln.par[s][j], yq * W * 16);
-        } else {
-#pragma unroll
-            for (int s = 0; s < kWsSlices; ++s)
-                in.par[s][j].x = ld32(R.rq, ln.col4[j], yq * W * 4 + s * R.in_slice_bytes);
+        for (int s = 0; s < kWsSlices; ++s) {
+            const uint32_t o = row + s * I.in_slice_bytes;
+            if (I.quads)  // uniform
+                in.ref[s] = ld128(I.rCost, ln.vq[0], o);
+            else
+                in.ref[s] = make_uint4(ld32(I.rCost, ln.vq[0], o), ld32(I.rCost, ln.vq[1], o),
+                                       ld32(I.rCost, ln.vq[2], o), ld32(I.rCost, ln.vq[3], o));
         }
     }
-    const int y2 = ys + kAggK * (p - 2) + w - 2 * kLMax - 1;
-    const uint32_t rc = (uint32_t)(y2 >= 0 && y2 < A.H ? y2 : A.H);
-#pragma unroll
-    for (int j = 0; j < kSeg; ++j) in.c3[j] = ld128(R.rC, ln.recw * 4 + 1024 * j, rc * Wp * 16);
 }
 
-// Column thread: loads for step 2 of chunk q (b rows ys + kAggK q + k).
-__device__ inline void ws_col_load(const AggArgs& A, int ys, int q, uint32_t reco,
-                                   const AggRes& R, WsColIn& in) {
-    const uint32_t Wp = (uint32_t)A.rec.Wp;
-#pragma unroll
-    for (int k = 0; k < kAggK; ++k) {
-        const uint32_t rb = (uint32_t)min(ys + kAggK * q + k, A.H + kLMax);
-        in.b2[k] = ld128(R.rB, reco * 4, rb * Wp * 16);
-    }
-}
-
-// Inclusive row prefixes of the two rows of 256 values the wavefront holds
-// in segment layout (lane l, segment j: column 64 j + l), written to its own
-// LDS row as P(c) at index c + kWsP0.  The values pass through that row so
-// that lane l takes the four consecutive columns 4 l .. 4 l + 3: it adds them
-// up in order, one wavefront scan of the lane totals (DPP row shifts 1, 2, 4,
-// 8 and row broadcasts 15 and 31) gives each lane the sum of the columns
-// before its four, and the prefixes go back as two 16-byte stores.  Sums are
-// mod 2^32; only differences of them are used.
-__device__ inline void ws_scan_row(const uint32_t (&v)[kWsSlices][kSeg], uint2* row) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int j = 0; j < kSeg; ++j) row[64 * j + lane + kWsP0] = make_uint2(v[0][j], v[1][j]);
-    __builtin_amdgcn_wave_barrier();  // the row is this wavefront's own
-    uint32_t a[kWsSlices][4];
-    uint4 lo, hi;  // columns 4 l, 4 l + 1 and 4 l + 2, 4 l + 3, both slices each
-    __builtin_memcpy(&lo, __builtin_assume_aligned(row + kWsP0 + 4 * lane, 16), 16);
-    __builtin_memcpy(&hi, __builtin_assume_aligned(row + kWsP0 + 4 * lane + 2, 16), 16);
-    a[0][0] = lo.x, a[1][0] = lo.y, a[0][1] = lo.z, a[1][1] = lo.w;
-    a[0][2] = hi.x, a[1][2] = hi.y, a[0][3] = hi.z, a[1][3] = hi.w;
-    uint32_t tot[kWsSlices];
+// Exclusive prefixes across the wavefront of four columns per lane: v[s][i]
+// becomes the sum of slice s over all columns before the lane's column i
+// (mod 2^32; only differences are used).  One DPP scan of the lane totals:
+// row shifts 1, 2, 4, 8 and row broadcasts 15 and 31.
+__device__ inline void ws_scan(uint32_t (&v)[kWsSlices][4]) {
+    uint32_t tot[kWsSlices], inc[kWsSlices];
 #pragma unroll
     for (int s = 0; s < kWsSlices; ++s) {
-        a[s][1] += a[s][0];
-        a[s][2] += a[s][1];
-        a[s][3] += a[s][2];
-        tot[s] = a[s][3];
+        v[s][1] += v[s][0];
+        v[s][2] += v[s][1];
+        tot[s] = inc[s] = v[s][2] + v[s][3];
     }
 #define DCO_WS_SCAN(CTRL, MASK) \
-    _Pragma("unroll") for (int s = 0; s < kWsSlices; ++s) tot[s] += dpp<CTRL, MASK>(tot[s]);
+    _Pragma("unroll") for (int s = 0; s < kWsSlices; ++s) inc[s] += dpp<CTRL, MASK>(inc[s]);
     DCO_WS_SCAN(0x111, 0xf)
     DCO_WS_SCAN(0x112, 0xf)
     DCO_WS_SCAN(0x114, 0xf)
@@ -951,168 +905,278 @@ __device__ inline void ws_scan_row(const uint32_t (&v)[kWsSlices][kSeg], uint2* 
 #undef DCO_WS_SCAN
 #pragma unroll
     for (int s = 0; s < kWsSlices; ++s) {
-        const uint32_t before = tot[s] - a[s][3];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[s][i] += before;
+        const uint32_t before = inc[s] - tot[s];
+        v[s][3] = before + v[s][2];
+        v[s][2] = before + v[s][1];
+        v[s][1] = before + v[s][0];
+        v[s][0] = before;
     }
-    lo = make_uint4(a[0][0], a[1][0], a[0][1], a[1][1]);
-    hi = make_uint4(a[0][2], a[1][2], a[0][3], a[1][3]);
-    __builtin_memcpy(__builtin_assume_aligned(row + kWsP0 + 4 * lane, 16), &lo, 16);
-    __builtin_memcpy(__builtin_assume_aligned(row + kWsP0 + 4 * lane + 2, 16), &hi, 16);
-    __builtin_amdgcn_wave_barrier();
 }
 
-// Row wavefront w, phase p: step 3 of chunk p - 2 and step 1 of chunk p.
+// Cost wavefront: raw costs and row prefixes of one row.  Rows below the
+// image load row H - 1 and columns outside it whatever their address holds:
+// prefixes are modular and every range of a stored output ends inside the
+// image (arms stop at the border), so neither reaches a stored output.
 template <bool kFused>
-__device__ inline void ws_row_phase(const AggArgs& A, int ys, int y0, int y1, int p, int w,
-                                    const WsRowLane& ln, const AggRes& R, const WsRowIn& in,
-                                    AggLdsWs& S) {
-    // Both steps run as one straight block so that their LDS round trips
-    // overlap; in the phases where a step has no chunk its LDS writes land in
-    // rows nobody reads and its stores are skipped.
-    const int lane = threadIdx.x & 63;
-    const int W = A.W;
-    uint2* row = S.prow[p & 1][w];
-    // step 3 of chunk p - 2: vertical range sums of ring 2 (E2)
-    uint32_t e2[kWsSlices][kSeg];
+__device__ inline void ws_cost_phase(const WsCostLane& ln, const WsCostIn& in, uint2* row,
+                                     AggLdsWs& S) {
+    uint32_t q[kWsSlices][4];
+    if constexpr (kFused) {
+        const uint32_t rlo[4] = {in.ref[0].x, in.ref[0].y, in.ref[0].z, in.ref[0].w};
+        const uint32_t rhi[4] = {in.ref[1].x, in.ref[1].y, in.ref[1].z, in.ref[1].w};
+        const uint32_t rc[4] = {in.ref[2].x, in.ref[2].y, in.ref[2].z, in.ref[2].w};
+        const uint32_t plo[5] = {in.par[0].x, in.par[0].y, in.par[0].z, in.par[0].w, in.par4[0]};
+        const uint32_t phi[5] = {in.par[1].x, in.par[1].y, in.par[1].z, in.par[1].w, in.par4[1]};
+        const uint32_t pc[5] = {in.par[2].x, in.par[2].y, in.par[2].z, in.par[2].w, in.par4[2]};
 #pragma unroll
-    for (int j = 0; j < kSeg; ++j) {
-        const uint32_t o = in.c3[j].x;  // ring 2 offsets in 8-byte words
-        const uint2 a = S.ring2[ln.cbs[j] + (o & 0xffff)], b = S.ring2[ln.cbs[j] + (o >> 16)];
-        e2[0][j] = a.x - b.x;
-        e2[1][j] = a.y - b.y;
-    }
-    // step 1 of chunk p: raw costs of Eq. 1.  Rows below the image load row
-    // H - 1 and are not masked: prefixes are modular and every range of a
-    // stored output ends inside the image (arms stop at the border), so those
-    // rows only change prefixes past the last row any stored output reads.
-    uint32_t q[kWsSlices][kSeg];
-    if constexpr (!kFused) {
-        // the volume holds q 2^-20 exactly (1.0 where the partner is outside
-        // the image); columns outside the image load 0
+        for (int j = 0; j < 4; ++j) {
+            const float2 ab = *reinterpret_cast<const float2*>(
+                reinterpret_cast<const char*>(S.ab) + ((in.lmin >> 8 * j) & 0xff));
 #pragma unroll
-        for (int j = 0; j < kSeg; ++j)
-#pragma unroll
-            for (int s = 0; s < kWsSlices; ++s)
-                q[s][j] = (uint32_t)(__builtin_bit_cast(float, in.par[s][j].x) * 0x1p20f);
-    } else {
-#pragma unroll
-    for (int j = 0; j < kSeg; ++j) {
-        const uint64_t rc = (uint64_t)in.ref[j].y << 32 | in.ref[j].x;
-        const float2 ab = *reinterpret_cast<const float2*>(
-            reinterpret_cast<const char*>(S.ab) + in.ref[j].w);
-#pragma unroll
-        for (int s = 0; s < kWsSlices; ++s) {
-            const uint32_t sad = __builtin_amdgcn_sad_u8(in.ref[j].z, in.par[s][j].z, 0u);
-            const uint64_t x = rc ^ ((uint64_t)in.par[s][j].y << 32 | in.par[s][j].x);
-            const uint32_t h = (uint32_t)__popcll(x);
-            q[s][j] = q20_term(ab.x, S.tabA[sad]) + q20_term(ab.y, S.tabC[h]);
-        }
-    }
-    // every lookup stays unconditional; the selects are lane-mask cndmasks
-    asm volatile(""
-                 : "+v"(q[0][0]), "+v"(q[0][1]), "+v"(q[0][2]), "+v"(q[0][3]), "+v"(q[1][0]),
-                   "+v"(q[1][1]), "+v"(q[1][2]), "+v"(q[1][3]));
-#pragma unroll
-    for (int j = 0; j < kSeg; ++j)
-#pragma unroll
-        for (int s = 0; s < kWsSlices; ++s) q[s][j] = ln.pok[s][j] ? q[s][j] : ln.inval[j];
-    }
-    // step 3: row prefixes of E2 in this wavefront's row, then the horizontal
-    // range sums and the final division
-    ws_scan_row(e2, row);
-    float out[kWsSlices][kSeg];
-    const uint32_t pbw = (uint32_t)(lane + kWsP0 - 1) * 8;
-#pragma unroll
-    for (int j = 0; j < kSeg; ++j) {
-        const uint32_t lr = in.c3[j].z;  // arm offsets in 8-byte words
-        const uint2 a = lds_ld2(row, pbw + 512 * j + (lr & 0xff));
-        const uint2 b = lds_ld2(row, pbw + 512 * j - ((lr >> 8) & 0xff));
-        const float nf = __builtin_bit_cast(float, in.c3[j].w);
-        const float rcp = __builtin_bit_cast(float, in.c3[j].y);
-        out[0][j] = div_q20(a.x - b.x, nf, rcp);
-        out[1][j] = div_q20(a.y - b.y, nf, rcp);
-    }
-    // step 1: its row prefixes replace step 3's in the same row (LDS keeps
-    // this wavefront's order, so step 3's reads above see the old values)
-    ws_scan_row(q, row);
-    const int y2 = ys + kAggK * (p - 2) + w - 2 * kLMax - 1;
-    if (p >= 2 && y2 >= y0 && y2 < y1) {  // uniform
-        if (R.paired && R.nout == kWsSlices) {  // uniform: the pair's minimum first
-            // div_q20 of an unsigned sum is never negative nor -0, so the bits
-            // order like the values, and bit 31 of b1 - b0 is set exactly when
-            // b1 < b0 (the second slice strictly smaller)
-#pragma unroll
-            for (int j = 0; j < kSeg; ++j) {
-                const uint32_t b0 = __builtin_bit_cast(uint32_t, out[0][j]);
-                const uint32_t b1 = __builtin_bit_cast(uint32_t, out[1][j]);
-                out[0][j] = __builtin_bit_cast(float, ((b1 - b0) & 0x80000000u) | min(b0, b1));
-                out[1][j] = __builtin_bit_cast(float, max(b0, b1));
+            for (int s = 0; s < kWsSlices; ++s) {
+                const uint32_t sad = __builtin_amdgcn_sad_u8(rc[j], pc[j + s], 0u);
+                const uint32_t h = (uint32_t)__popc(rlo[j] ^ plo[j + s]) +
+                                   (uint32_t)__popc(rhi[j] ^ phi[j + s]);
+                q[s][j] = q20_term(ab.x, S.tabA[sad]) + q20_term(ab.y, S.tabC[h]);
             }
         }
+        // every lookup stays unconditional; the selects are lane-mask cndmasks
+        asm volatile(""
+                     : "+v"(q[0][0]), "+v"(q[0][1]), "+v"(q[0][2]), "+v"(q[0][3]), "+v"(q[1][0]),
+                       "+v"(q[1][1]), "+v"(q[1][2]), "+v"(q[1][3]));
 #pragma unroll
-        for (int s = 0; s < kWsSlices; ++s)
-            if (s < R.nout)  // uniform
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int j = 0; j < kSeg; ++j)
-                    st32(out[s][j], R.rOut, ln.vout[j], (uint32_t)(y2 * W) * 4 + s * R.slice_bytes);
+            for (int s = 0; s < kWsSlices; ++s) q[s][j] = ln.ok[s][j] ? q[s][j] : 1u << 20;
+    } else {
+        // the volume holds q 2^-20 exactly (1.0 where the partner is outside)
+#pragma unroll
+        for (int s = 0; s < kWsSlices; ++s) {
+            const uint32_t c[4] = {in.ref[s].x, in.ref[s].y, in.ref[s].z, in.ref[s].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                q[s][j] = (uint32_t)(__builtin_bit_cast(float, c[j]) * 0x1p20f);
+        }
+    }
+    ws_scan(q);
+    const uint4 lo = make_uint4(q[0][0], q[1][0], q[0][1], q[1][1]);
+    const uint4 hi = make_uint4(q[0][2], q[1][2], q[0][3], q[1][3]);
+    uint2* dst = row + 4 * (threadIdx.x & 63);
+    __builtin_memcpy(__builtin_assume_aligned(dst, 16), &lo, 16);
+    __builtin_memcpy(__builtin_assume_aligned(dst + 2, 16), &hi, 16);
+}
+
+// Column thread: the b records of chunk q.
+__device__ inline void ws_col_load(const WsItem& I, int H, uint32_t Wp16, int q, uint32_t vcol,
+                                   WsColIn& in) {
+#pragma unroll
+    for (int k = 0; k < kAggK; ++k) {
+        const uint32_t r = (uint32_t)min(I.ys + kAggK * q + k, H + kWsRecRows - 1);
+        in.b[k] = ld128(I.rB, vcol, r * Wp16);
     }
 }
 
-// Column thread ct (its column's ring byte offset cb), step 2 of chunk q.
-__device__ inline void ws_col_phase(int q, int nch, int ct, uint32_t cb, const WsColIn& in,
-                                    uint32_t (&cp1)[kWsSlices], uint32_t (&cp2)[kWsSlices],
-                                    uint32_t& off1, uint32_t& off2, AggLdsWs& S) {
-    if (q >= nch) return;  // uniform
-    const uint2* rows = S.prow[q & 1][0];
-    uint32_t e1[kWsSlices][kAggK];
+// floor((s + floor(n / 2)) / n) for 0 <= s <= n 2^20, 1 <= n <= 1225, given
+// rcp = RN(1 / n) and neg_n = -n.  (float)s, rcp and the fused multiply-add
+// round, together by less than 0.19 of a quotient of at most 2^20, so
+// q = trunc(s / n + 0.25 -+ 0.19) is the result or one less; the remainder
+// s - q n (24-bit multiply, 32-bit sum) decides: one more when it is at
+// least ceil(n / 2).
+__device__ inline uint32_t mean_q20(uint32_t s, float rcp, int neg_n, int half_up) {
+    const uint32_t q = (uint32_t)__builtin_fmaf((float)s, rcp, 0.25f);
+    const int r = (int)s + __mul24((int)q, neg_n);
+    return q + (r >= half_up ? 1u : 0u);
+}
+
+// Column thread of ring column ct (byte offset cb in a ring row), one chunk:
+// x = its entry of the chunk's first prefix row, e = its entry of the first
+// output row, slot = the ring byte offset of the chunk's first row.
+__device__ inline void ws_col_phase(const uint2* x, uint2* e, uint32_t cb, uint32_t slot,
+                                    const WsColIn& in, uint32_t (&cp1)[kWsSlices],
+                                    uint32_t (&cp2)[kWsSlices], AggLdsWs& S) {
+    uint32_t e1[kWsSlices][kAggK], s1[kWsSlices][kAggK];
 #pragma unroll
     for (int k = 0; k < kAggK; ++k) {
-        const uint32_t a = in.b2[k].z;  // arm offsets in 8-byte words
-        const uint32_t pb = (uint32_t)(k * kWsPStride + ct + kWsP0 - 1) * 8;
-        const uint2 hi = lds_ld2(rows, pb + (a & 0xff)), lo = lds_ld2(rows, pb - ((a >> 8) & 0xff));
+        const uint32_t a = in.b[k].w;
+        const uint2* xk = x + k * kStripThreads;
+        const uint2 hi = lds_ld2(xk, a & 0xff);
+        const uint2 lo = lds_ld2(xk, 0u - ((a >> 8) & 0xff));
         e1[0][k] = hi.x - lo.x;
         e1[1][k] = hi.y - lo.y;
     }
-    // push a row, then read that row's range, before the next push
-    uint32_t s1[kWsSlices][kAggK];
 #pragma unroll
-    for (int k = 0; k < kAggK; ++k) {
+    for (int k = 0; k < kAggK; ++k) {  // push a row, then read its range
         cp1[0] += e1[0][k];
         cp1[1] += e1[1][k];
-        lds_st2(S.ring1, cb + off1, make_uint2(cp1[0], cp1[1]));
-        const uint32_t r = in.b2[k].y;  // ring 1 offsets in bytes
-        const uint2 hi = lds_ld2(S.ring1, cb + (r & 0xffff)), lo = lds_ld2(S.ring1, cb + (r >> 16));
+        lds_st2(S.ring1, cb + slot + k * kWsSlotBytes, make_uint2(cp1[0], cp1[1]));
+        const uint32_t o = in.b[k].y;
+        const uint2 hi = lds_ld2(S.ring1, cb + (o & 0xffff));
+        const uint2 lo = lds_ld2(S.ring1, cb + (o >> 16));
         s1[0][k] = hi.x - lo.x;
         s1[1][k] = hi.y - lo.y;
-        off1 = off1 + kWsSlotBytes == kWsRing1 * kWsSlotBytes ? 0u : off1 + kWsSlotBytes;
     }
 #pragma unroll
     for (int k = 0; k < kAggK; ++k) {
-        const uint4 b = in.b2[k];
-        const uint32_t half = (b.z >> 16) & 1023, sh = b.z >> 26;
+        const float rcp = __builtin_bit_cast(float, in.b[k].x);
+        const int neg_n = (int)in.b[k].w >> 16, half_up = (1 - neg_n) >> 1;
 #pragma unroll
-        for (int s = 0; s < kWsSlices; ++s) {
-            const uint64_t n = (uint64_t)(s1[s][k] + half) * b.x;
-            cp2[s] += (uint32_t)(n >> sh);
+        for (int s = 0; s < kWsSlices; ++s) cp2[s] += mean_q20(s1[s][k], rcp, neg_n, half_up);
+        lds_st2(S.ring2, cb + slot + k * kWsSlotBytes, make_uint2(cp2[0], cp2[1]));
+        const uint32_t o = in.b[k].z;
+        const uint2 hi = lds_ld2(S.ring2, cb + (o & 0xffff));
+        const uint2 lo = lds_ld2(S.ring2, cb + (o >> 16));
+        e[k * kWsCols] = make_uint2(hi.x - lo.x, hi.y - lo.y);
+    }
+}
+
+// Output wavefront: the c records of its row of chunk q.
+__device__ inline int ws_out_row(const WsItem& I, int q, int w) {
+    return I.ys + kAggK * q + w - 2 * kLMax;
+}
+__device__ inline void ws_out_load(const WsItem& I, int H, uint32_t Wp4, uint32_t cplane4, int q,
+                                   int w, uint32_t vcol, WsOutIn& in) {
+    const uint32_t row = (uint32_t)min(max(ws_out_row(I, q, w), 0), H - 1) * Wp4;
+    in.off = ld128(I.rC, vcol, row);
+    in.rcp = ld128(I.rC, vcol, row + cplane4);
+    in.n = ld128(I.rC, vcol, row + 2 * cplane4);
+}
+
+// Output wavefront: its row's prefixes, horizontal range sums, division and
+// stores.  Slot s of a lane's values is slice s for the right view and slice
+// 1 - s for the left (kRef = 0), whose partners lie the other way.  Every call
+// issues the same number of stores (the hardware drops those out of range):
+// loads and stores complete in order, so with a fixed count the next chunk's
+// records are waited for without waiting for this chunk's stores.
+template <int kRef, bool kQuads>
+__device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
+                                    const uint32_t (&vout)[4], const WsOutIn& in) {
+    const int lane = threadIdx.x & 63;
+    uint32_t v[kWsSlices][4];
+    {
+        uint4 lo, hi;
+        const uint2* src = row + 4 * min(lane, kWsLanes - 1);
+        __builtin_memcpy(&lo, __builtin_assume_aligned(src, 16), 16);
+        __builtin_memcpy(&hi, __builtin_assume_aligned(src + 2, 16), 16);
+        v[0][0] = lo.x, v[1][0] = lo.y, v[0][1] = lo.z, v[1][1] = lo.w;
+        v[0][2] = hi.x, v[1][2] = hi.y, v[0][3] = hi.z, v[1][3] = hi.w;
+    }
+    ws_scan(v);
+    __builtin_amdgcn_wave_barrier();  // the row is this wavefront's own
+    if (lane < kWsLanes) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) row[j * kWsLanes + lane] = make_uint2(v[0][j], v[1][j]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t off[4] = {in.off.x, in.off.y, in.off.z, in.off.w};
+    const uint32_t rcp[4] = {in.rcp.x, in.rcp.y, in.rcp.z, in.rcp.w};
+    const uint32_t n[4] = {in.n.x, in.n.y, in.n.z, in.n.w};
+    uint32_t out[kWsSlices][4];
+    const char* base = reinterpret_cast<const char*>(row) + 8 * lane - kWsOffBias;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint2 a = lds_ld2(base, off[j] & 0xffff), b = lds_ld2(base, off[j] >> 16);
+        const float nf = __builtin_bit_cast(float, n[j]), rf = __builtin_bit_cast(float, rcp[j]);
+        out[0][j] = __builtin_bit_cast(uint32_t, div_q20(a.x - b.x, nf, rf));
+        out[1][j] = __builtin_bit_cast(uint32_t, div_q20(a.y - b.y, nf, rf));
+    }
+    constexpr int kLo = kRef == 0 ? 1 : 0, kHi = 1 - kLo;  // slots of slices d and d + 1
+    if (I.paired && I.nout == kWsSlices) {                 // uniform: the pair's minimum first
+        // div_q20 of an unsigned sum is never negative nor -0, so the bits
+        // order like the values, and bit 31 of b1 - b0 is set exactly when
+        // b1 < b0 (the second slice strictly smaller)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t b0 = out[kLo][j], b1 = out[kHi][j];
+            out[kLo][j] = ((b1 - b0) & 0x80000000u) | min(b0, b1);
+            out[kHi][j] = max(b0, b1);
         }
-        lds_st2(S.ring2, cb + off2, make_uint2(cp2[0], cp2[1]));
-        off2 = off2 + kWsSlotBytes == kWsRing2 * kWsSlotBytes ? 0u : off2 + kWsSlotBytes;
+    }
+    const bool live = y2 >= I.y0 && y2 < I.y1;  // uniform
+    const uint32_t row4 = live ? (uint32_t)(y2 * W) * 4 : 0u;
+#pragma unroll
+    for (int k = 0; k < kWsSlices; ++k) {
+        const uint32_t(&o)[4] = out[k ? kHi : kLo];
+        const bool keep = live && k < I.nout;
+        const uint32_t so = keep ? row4 + k * I.slice_bytes : 0u;
+        if constexpr (kQuads) {
+            st128(u32x4{o[0], o[1], o[2], o[3]}, I.rOut, keep ? vout[0] : kOOB, so);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                st32(__builtin_bit_cast(float, o[j]), I.rOut, keep ? vout[j] : kOOB, so);
+        }
+    }
+}
+
+// kQuads: rows of the output volume keep the lanes' quads 16-byte aligned.
+template <int kRef, bool kQuads>
+__device__ inline void ws_out_loop(const AggArgs& A, const WsItem& I, int w, AggLdsWs& S) {
+    const int lane = threadIdx.x & 63, W = A.W, H = A.H;
+    const uint32_t Wp4 = (uint32_t)A.rec.Wp * 4, cplane4 = Wp4 * (uint32_t)H;
+    const int c = I.x0 - kWsApron + kWsI0 + 4 * lane;  // image column of the lane's first
+    const uint32_t vcol = (uint32_t)(c + kRecApronL) * 4;
+    uint32_t vout[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        vout[j] = c >= I.x0 && c < I.x0 + kWsOut && c + j < W ? (uint32_t)(c + j) * 4 : kOOB;
+    // the first chunk, even, with an output row of the band: before it there
+    // is nothing to do but keep the phases
+    const int q0 = max(0, I.y0 + 2 * kLMax - I.ys) / kAggK & ~1;
+    WsOutIn ia, ib;
+    ws_out_load(I, H, Wp4, cplane4, q0, w, vcol, ia);
+    for (int p = 0; p < q0 + 2; ++p) __syncthreads();  // phases without a chunk to finish
+    for (int q = q0;; q += 2) {
+        ws_out_load(I, H, Wp4, cplane4, q + 1, w, vcol, ib);
+        ws_out_phase<kRef, kQuads>(I, W, ws_out_row(I, q, w), S.e2[0][w], vout, ia);
+        __syncthreads();
+        if (q + 1 >= I.nch) break;
+        ws_out_load(I, H, Wp4, cplane4, q + 2, w, vcol, ia);
+        ws_out_phase<kRef, kQuads>(I, W, ws_out_row(I, q + 1, w), S.e2[1][w], vout, ib);
+        __syncthreads();
+        if (q + 2 >= I.nch) break;
     }
 }
 
 // Output rows [y0, y1) of slices d and d + 1 and column strip `strip`
-// (512 threads; two stages); slices at or past dend are computed but not
+// (768 threads; two stages); slices at or past dend are computed but not
 // stored.  kFused: the raw cost computed from the packed pixels; else read
-// from the cost volume A.cost.  The records must be written with kRecWs.
+// from the cost volume A.cost.
 template <bool kFused = true>
 __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int strip, int y0, int y1,
                                      AggLdsWs& S) {
     const int W = A.W, H = A.H;
     const int t = threadIdx.x, lane = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int x0 = strip * kStripOut;
+    const int kind = __builtin_amdgcn_readfirstlane(t >> 8);  // 0 cost, 1 column, 2 output
+    const int w = __builtin_amdgcn_readfirstlane((t >> 6) & 3);
     const size_t slice = (size_t)W * H;
+    const uint32_t P4 = (uint32_t)(slice * 4);
+
+    WsItem I;
+    I.x0 = strip * kWsOut;
+    I.y0 = y0;
+    I.y1 = y1;
+    I.ys = max(0, y0 - 2 * kLMax) & ~3;  // warm-up rows so that every range is complete
+    I.nch = (y1 + 2 * kLMax - I.ys + kAggK - 1) / kAggK;
+    I.nout = min(kWsSlices, min(A.D, dend) - d);
+    I.paired = A.paired;
+    I.quads = W % 4 == 0 && (reinterpret_cast<uintptr_t>(A.out) & 15) == 0 &&
+              (kFused || (reinterpret_cast<uintptr_t>(A.cost) & 15) == 0);
+    const PixPlanes px(W, H);
+    const uint32_t pixbytes = px.bytes();
+    I.Wq4 = px.Wq * 4;
+    I.plane4 = px.plane * 4;
+    I.lm = 3 * I.plane4;
+    I.rB = make_rsrc(A.rec.b, (uint32_t)(A.rec.Wp * (H + kWsRecRows)) * 16);
+    I.rC = make_rsrc(A.rec.c, (uint32_t)(A.rec.Wp * H) * 12);
+    I.rRef = kFused ? make_rsrc(A.ref == 0 ? A.pixL : A.pixR, pixbytes) : I.rB;
+    I.rPar = kFused ? make_rsrc(A.ref == 0 ? A.pixR : A.pixL, pixbytes) : I.rB;
+    // raw costs of slices d and d + 1; past the last slice, slice d again
+    I.rCost = kFused ? I.rB
+                     : make_rsrc(A.cost + (size_t)d * slice,
+                                 (uint32_t)min(kWsSlices, A.D - d) * P4);
+    I.in_slice_bytes = A.D - d >= 2 ? P4 : 0u;
+    I.rOut = make_rsrc(A.out + (size_t)d * slice, (uint32_t)I.nout * P4);
+    I.slice_bytes = P4;
 
     if constexpr (kFused) {
         for (int i = t; i < 766; i += kWsThreads) S.tabA[i] = A.tabA[i];
@@ -1122,101 +1186,83 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
             S.ab[t] = make_float2(A.alpha[L], A.beta[L]);
         }
     }
-    if (t < 2 * kAggK * kWsP0) {  // P(-1) and the entries before it, every row
-        const int r = t / kWsP0;
-        S.prow[r / kAggK][r % kAggK][t % kWsP0] = make_uint2(0u, 0u);
-    }
-    // zero column prefixes: rows before the start contribute nothing
-    for (int i = t; i < kWsRing1 * kRingStride; i += kWsThreads) S.ring1[i] = make_uint2(0u, 0u);
-    for (int i = t; i < kWsRing2 * kRingStride; i += kWsThreads) S.ring2[i] = make_uint2(0u, 0u);
-
-    const uint32_t P4 = (uint32_t)(slice * 4);
-    AggRes R;
-    const uint4* Iref = A.ref == 0 ? A.pixL : A.pixR;
-    const uint4* Ipar = A.ref == 0 ? A.pixR : A.pixL;
-    R.rB = make_rsrc(A.rec.b, (uint32_t)(A.rec.Wp * (H + kLMax + 1)) * 16);
-    R.rC = make_rsrc(A.rec.c, (uint32_t)(A.rec.Wp * (H + 1)) * 16);
-    R.rIr = make_rsrc(Iref, 4 * P4);
-    R.rIp = make_rsrc(Ipar, 4 * P4);
-    const int nout = min(kWsSlices, min(A.D, dend) - d);  // slices to store
-    // raw costs of slices d and d + 1; past the last slice, slice d again
-    R.rq = kFused ? R.rB
-                  : make_rsrc(A.cost + (size_t)d * slice, (uint32_t)min(kWsSlices, A.D - d) * P4);
-    R.in_slice_bytes = A.D - d >= 2 ? P4 : 0u;
-    R.rOut = make_rsrc(A.out + (size_t)d * slice, (uint32_t)nout * P4);
-    R.slice_bytes = P4;
-    R.nout = nout;
-    R.paired = A.paired;
-
-    const int warm = 2 * kLMax + 1;
-    const int ys = max(0, y0 - warm);
-    const int nch = (y1 + warm - ys + kAggK - 1) / kAggK;
-    const int last = nch + 1;  // phases 0 .. nch + 1
+    // the prefix before the first stream row is zero; rings hold nothing else
+    // that a stored output reads before it is written
+    const uint32_t slot0 = (uint32_t)(I.ys % kWsRing);
+    if (t < kWsCols) S.ring1[(slot0 + kWsRing - 1) % kWsRing * kWsCols + t] = make_uint2(0u, 0u);
     __syncthreads();
 
-    if (w < kAggK) {  // row wavefronts
-        // the row wavefronts carry the longer chain of each phase; issuing
-        // their instructions first when both kinds are ready helps slightly
-        __builtin_amdgcn_s_setprio(1);
-        WsRowLane ln;
+    if (kind == 0) {
+        WsCostLane ln;
+        const int c = I.x0 - kWsApron + 4 * lane;  // image column of the lane's first
+        if constexpr (kFused) {
+            const bool in_img = c >= 0 && c < px.Wq;
+            ln.vref = (uint32_t)(kPixPad + (in_img ? c : 0)) * 4;
+            ln.vlm = (uint32_t)(in_img ? c : 0);
+            // partner columns b .. b + 4: slot s of column j takes b + j + s
+            const int b = A.ref == 0 ? c - d - 1 : c + d;
+            ln.vpar = (uint32_t)(b > -5 && b < W ? b + kPixPad : 0) * 4;
 #pragma unroll
-        for (int j = 0; j < kSeg; ++j) {
-            const int i = 64 * j + lane;            // strip column of segment j
-            const int c = x0 - 2 * kLMax + i;       // image column
-            const bool in_img = c >= 0 && c < W;
-            ln.img[j] = in_img ? (uint32_t)c * 16 : kOOB;
-            ln.col4[j] = in_img ? (uint32_t)c * 4 : kOOB;
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int s = 0; s < kWsSlices; ++s) {
-                const int cp = A.ref == 0 ? c - d - s : c + d + s;
-                const bool pok = in_img && cp >= 0 && cp < W;
-                ln.par[s][j] = pok ? (uint32_t)cp * 16 : kOOB;
-                ln.pok[s][j] = pok;
-            }
-            ln.inval[j] = in_img ? (1u << 20) : 0u;
-            // ring-2 column (kRingCols + 1, never written, for columns without one)
-            const bool rok = i >= kLMax && i < kLMax + kRingCols;
-            ln.cbs[j] = (uint32_t)(rok ? i - kLMax : kRingCols + 1);
-            ln.vout[j] =
-                i >= 2 * kLMax && i < 2 * kLMax + kStripOut && c < W ? (uint32_t)c * 4 : kOOB;
+                for (int s = 0; s < kWsSlices; ++s)
+                    ln.ok[s][j] = b + j + s >= 0 && b + j + s < W;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                ln.vq[j] = c + j >= 0 && c + j < W ? (uint32_t)(c + j) * 4 : kOOB;
         }
-        ln.recw = (uint32_t)(x0 - 2 * kLMax + lane + A.rec.apron) * 4;
-        WsRowIn ia, ib;
-        ws_row_load<kFused>(A, ys, 0, w, ln, R, ia);
+        const int last = I.nch + 1;  // phases 0 .. nch + 1
+        WsCostIn ia, ib;
+        ws_cost_load<kFused>(I, H, W, 0, w, ln, ia);
         for (int p = 0;; p += 2) {
-            ws_row_load<kFused>(A, ys, p + 1, w, ln, R, ib);
-            ws_row_phase<kFused>(A, ys, y0, y1, p, w, ln, R, ia, S);
+            ws_cost_load<kFused>(I, H, W, p + 1, w, ln, ib);
+            ws_cost_phase<kFused>(ln, ia, S.x1[0][w], S);
             __syncthreads();
             if (p + 1 > last) break;
-            ws_row_load<kFused>(A, ys, p + 2, w, ln, R, ia);
-            ws_row_phase<kFused>(A, ys, y0, y1, p + 1, w, ln, R, ib, S);
+            ws_cost_load<kFused>(I, H, W, p + 2, w, ln, ia);
+            ws_cost_phase<kFused>(ln, ib, S.x1[1][w], S);
             __syncthreads();
             if (p + 2 > last) break;
         }
-    } else {  // column threads
+    } else if (kind == 1) {
+        __builtin_amdgcn_s_setprio(1);
         const int ct = t - kStripThreads;
-        const int c = x0 - 2 * kLMax + ct;
-        const int jj = ct - kLMax;
-        // threads without a ring column share one scratch column; column
-        // kRingCols + 1 stays zero
-        const uint32_t cb = (uint32_t)(jj >= 0 && jj < kRingCols ? jj : kRingCols) * 8;
-        const uint32_t reco = (uint32_t)(c + A.rec.apron) * 4;
+        const bool owns = ct < kWsCols;
+        const uint32_t cb = (uint32_t)ct * 8;
+        const uint32_t vcol = (uint32_t)(I.x0 + kWsI0 + ct - kWsApron + kRecApronL) * 16;
+        const uint32_t Wp16 = (uint32_t)A.rec.Wp * 16;
         uint32_t cp1[kWsSlices] = {0, 0}, cp2[kWsSlices] = {0, 0};
-        uint32_t off1 = ring_slot(ys, kWsRing1) * kWsSlotBytes;
-        uint32_t off2 = ring_slot(ys - kLMax, kWsRing2) * kWsSlotBytes;
+        uint32_t slot = slot0 * kWsSlotBytes;
+        constexpr uint32_t kStep = kAggK * kWsSlotBytes, kTurn = kWsRing * kWsSlotBytes;
         WsColIn ja, jb;
-        ws_col_load(A, ys, 0, reco, R, ja);
-        __syncthreads();  // phase 0: no step 2 yet
-        for (int p = 1;; p += 2) {
-            if (p > last) break;
-            ws_col_load(A, ys, p, reco, R, jb);
-            ws_col_phase(p - 1, nch, ct, cb, ja, cp1, cp2, off1, off2, S);
+        ws_col_load(I, H, Wp16, 0, vcol, ja);
+        __syncthreads();  // phase 0: no chunk yet
+        for (int q = 0;; q += 2) {
+            ws_col_load(I, H, Wp16, q + 1, vcol, jb);
+            if (owns)
+                ws_col_phase(&S.x1[0][0][kWsI0 + ct], &S.e2[0][0][ct], cb, slot, ja, cp1, cp2, S);
+            slot = slot + kStep == kTurn ? 0u : slot + kStep;
             __syncthreads();
-            if (p + 1 > last) break;
-            ws_col_load(A, ys, p + 1, reco, R, ja);
-            ws_col_phase(p, nch, ct, cb, jb, cp1, cp2, off1, off2, S);
+            if (q + 1 >= I.nch) break;
+            ws_col_load(I, H, Wp16, q + 2, vcol, ja);
+            if (owns)
+                ws_col_phase(&S.x1[1][0][kWsI0 + ct], &S.e2[1][0][ct], cb, slot, jb, cp1, cp2, S);
+            slot = slot + kStep == kTurn ? 0u : slot + kStep;
             __syncthreads();
+            if (q + 2 >= I.nch) break;
         }
+        __syncthreads();  // the last phase: output wavefronts only
+    } else {
+        const bool right = !kFused || A.ref != 0;
+        if (right && I.quads)
+            ws_out_loop<1, true>(A, I, w, S);
+        else if (right)
+            ws_out_loop<1, false>(A, I, w, S);
+        else if (I.quads)
+            ws_out_loop<0, true>(A, I, w, S);
+        else
+            ws_out_loop<0, false>(A, I, w, S);
     }
 }
 
@@ -1380,8 +1426,6 @@ __device__ inline void wta_pairs_pixel(const float* __restrict__ vol, int P, int
     *dout = (int16_t)bd;
     if (delta_out) *delta_out = subpixel ? wta_pair_delta(vol, P, D, i, best, bd) : 0.f;
 }
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Pair step that also keeps, for the left view's parabola, the word of the
 // pair before the best one (prevw) and of the pair after it (nextw): the

@@ -20,6 +20,7 @@ struct dco_scratch {
     uint32_t* arms[2];
     AggRecords rec[2];
     uint4* pix[2];      // packed pixels of both views: census lo, census hi, RGB, 8 L_min
+                        // (two stages: in planes, PixPlanes; pix_entries 16-byte words)
     float* agg[2];      // aggregated volumes of both views (D x H x W)
     bool agg_paired;    // ... written in the paired layout (two-stage aggregation)
     int16_t* dint[2];
@@ -241,17 +242,14 @@ hipError_t launch_census_pairs(const uint8_t* rgbL, const uint8_t* rgbR, int B, 
                                int cw, int ch, int L1, int tau1, uint32_t* armsL, uint32_t* armsR,
                                uint4* pixL, uint4* pixR, hipStream_t st);
 // Census + arms + packed pixels, then region counts + records, of both views
-// (the one-call path): two launches.  The records address the LDS of the
-// aggregation kernel that launch_cost_aggregate2 runs (pair_rec_geom).
+// (the one-call path): two launches.  With two stages the packed pixels are
+// written in planes (PixPlanes), with one in 16-byte words.
 hipError_t launch_front2(const uint8_t* rgbL, const uint8_t* rgbR, int W, int H, int cw, int ch,
                          int L1, int tau1, int iters, uint32_t* armsL, uint32_t* armsR,
                          uint4* pixL, uint4* pixR, const AggRecords& recL, const AggRecords& recR,
-                         const RecGeom& g, hipStream_t st);
-RecGeom pair_rec_geom(int iters);
-// Records for the aggregation kernels; g = pair_rec_geom(iters) for the
-// kernels of dco_aggregate and dco_stereo_match.
+                         hipStream_t st);
 hipError_t launch_geometry(const uint32_t* arms, int W, int H, int iters, const AggRecords& rec,
-                           const RecGeom& g, hipStream_t st);
+                           hipStream_t st);
 hipError_t launch_cost(int ref, const uint8_t* rgbL, const uint8_t* rgbR, const uint64_t* cenL,
                        const uint64_t* cenR, const uint32_t* arms_ref, int W, int H, int D,
                        const float* tabA, const float* tabC, const float* alpha,
@@ -266,10 +264,6 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
                                   const float* tabA, const float* tabC, const float* alpha,
                                   const float* beta, int L1, float* outL, float* outR,
                                   bool paired, hipStream_t st);
-hipError_t launch_cost_aggregate(int ref, const uint4* pixL, const uint4* pixR,
-                                 const AggRecords& rec, int W, int H, int D, int iters,
-                                 const float* tabA, const float* tabC, const float* alpha,
-                                 const float* beta, int L1, float* out, hipStream_t st);
 hipError_t launch_wta2(const float* aggL, const float* aggR, int W, int H, int D, int subpixel,
                        int16_t* dL, float* deltaL, int16_t* dR, hipStream_t st);
 // The same outputs from volumes in the paired layout (even slices only).

@@ -3,6 +3,7 @@
 // ABI).
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 // Largest arm length the kernels are built for.  The aggregation halo is
@@ -10,36 +11,59 @@
 constexpr int kLMax = 17;
 // Threads of a streaming-aggregation workgroup = input columns of a strip.
 constexpr int kStripThreads = 256;
-// Output columns of one strip.
+// Output columns of one strip of the one-stage kernels.
 constexpr int kStripOut = kStripThreads - 4 * kLMax;
+// The two-stage kernel: columns of a strip left of its output columns, and
+// output columns (multiples of four: its lanes own aligned quads).
+constexpr int kWsApron = 36;
+constexpr int kWsOut = 184;
+constexpr int strip_out(int iters) { return iters == 2 ? kWsOut : kStripOut; }
 
 // Packed per-pixel records of one view for the aggregation kernels, written
-// by k_geometry.  Both arrays hold 4-word entries (the fourth of b is unused:
-// one 16-byte load per pixel is cheaper than a 12-byte one), Wp per row; column x
-// sits at x + apron, and the apron columns are zero.  With hw(p) = 4 (r + 1) | 4 l << 8
-// (horizontal arms as byte offsets) and ring offsets rb(p) = the byte offsets
-// of prefix rows y + dn and y - u - 1 in a ring (16 bits each):
-//   b row r (H + kLMax + 1 rows; the last is zero), read at stream row r:
-//     two stages: m, rb1, hw(x, r) | (N1/2 | sh << 10) << 16    of pixel (x, r - kLMax)
-//                 for its stage-1 rounding floor((S1 + N1/2) / N1) = ((S1 + N1/2) m) >> sh
-//     one stage:  RN(1/N1) 2^-20, rb1, hw(x, r) | N1 << 16
-//     (hw of row r is 0 from row H on; the rest is 0 above row kLMax)
-//   c row y (H + 1 rows; row H is zero), two stages only:
-//     rb2, RN(1/N2) 2^-20, hw | N2 << 16, N2 2^20 (float)        of pixel (x, y)
+// by k_geometry.  Entries of rows and columns outside the image are zero
+// (zeroed once; only the image's are written).  Wp entries per row (a
+// multiple of four); column x sits at x + kRecApronL.
+// Two stages, with slot(r) = r mod 36 times the bytes of a ring row:
+//   b row r (H + 2 kLMax rows of 16-byte entries), read at stream row r:
+//     RN(1/N1), slots of rows y + dn and y - u - 1 (16 bits each)  of y = r - kLMax
+//     the same slots + kLMax rows                                  of y = r - 2 kLMax
+//     8 (r + 1) | 8 l << 8 (low half)                              of y = r
+//     -N1 (high half)                                              of y = r - kLMax
+//   c (three planes of H rows of words), read at output row y:
+//     offsets of columns x + r + 1 and x - l in a row of prefixes (16 bits
+//     each), RN(1/N2) 2^-20, N2 2^20 (floats)
+// One stage, with hw = 4 (r + 1) | 4 l << 8 and rb the ring's byte offsets:
+//   b row r: RN(1/N1) 2^-20, rb, hw | N1 << 16 (the fourth word is unused:
+//     one 16-byte load per pixel is cheaper than a 12-byte one); hw of y = r,
+//     the rest of y = r - kLMax
 struct AggRecords {
     uint32_t* b;
     uint32_t* c;
-    int Wp, apron;
+    int Wp;
 };
-constexpr int kRecApronL = 2 * kLMax;        // left apron of the records
+constexpr int kRecApronL = kWsApron;         // left apron of the records
 constexpr int kRecApronR = kStripThreads;    // right apron (covers a strip's overhang)
+constexpr int kWsRecRows = 2 * kLMax;        // rows of b past the image's
+constexpr int rec_wp(int W) { return (W + kRecApronL + kRecApronR + 3) & ~3; }
+constexpr size_t rec_b_words(int W, int H) { return 4 * (size_t)rec_wp(W) * (H + kWsRecRows); }
+constexpr size_t rec_c_words(int W, int H) { return 3 * (size_t)rec_wp(W) * H; }
 
-// How the records address the LDS of the kernel that reads them: the row
-// counts of its two rings, the value stored per ring slot (ring 1 in bytes,
-// ring 2 in bytes or in 8-byte words) and the bytes of one prefix-row entry
-// (the scale of the arm offsets in hw).  Slot value x (rows - 1) and
-// hw x (kLMax + 1) must fit 16 and 8 bits.
-struct RecGeom {
-    int ring1, ring2;
-    uint32_t step1, step2, hw;
+// Packed pixels of one view in planes, for the two-stage kernel: census lo,
+// census hi and RGB words, then a plane of bytes holding 8 L_min.  Rows hold
+// Wq = W rounded up to a multiple of four entries; kPixPad words before and
+// after each word plane keep a quad that starts up to four columns before the
+// image, or ends after it, inside the buffer (the values there are not used).
+constexpr int kPixPad = 4;
+struct PixPlanes {
+    int Wq;
+    uint32_t plane, H;  // words from one plane to the next, rows
+    constexpr PixPlanes(int W, int rows)
+        : Wq((W + 3) & ~3), plane((uint32_t)rows * ((W + 3) & ~3) + 2 * kPixPad),
+          H((uint32_t)rows) {}
+    constexpr uint32_t bytes() const { return 12 * plane + H * (uint32_t)Wq; }
 };
+// 16-byte entries of a view's packed pixels: the planes, or one word a pixel.
+constexpr size_t pix_entries(int W, int H) {
+    const size_t a = (size_t)W * H, b = (PixPlanes(W, H).bytes() + 15) / 16;
+    return a > b ? a : b;
+}

@@ -13,15 +13,14 @@
 
 namespace {
 
-template <int ITERS, bool kFused>
 __global__ __launch_bounds__(kStripThreads, 2) void k_agg_stream(dco::AggArgs A) {
-    __shared__ dco::AggLds<ITERS, kFused> S;
+    __shared__ dco::AggLds<false> S;
     // strip-major items, consecutive per XCD: the workgroups one XCD runs at
     // a time share a strip (its records and reference pixels) and read
     // overlapping partner columns, so most loads hit that XCD's L2
     const int work = dco::xcd_work_item(blockIdx.x, A.nstrips * A.D);
     const int strip = work / A.D, d = work - strip * A.D;
-    dco::agg_stream<ITERS, kFused>(A, d, strip, 0, A.H, S);
+    dco::agg_stream<false>(A, d, strip, 0, A.H, S);
 }
 
 // Blocks of XCD x in the two-view launch: its nx items (a contiguous,
@@ -45,13 +44,12 @@ __host__ __device__ inline void pair_part(int N, int x, int s8, int H, int& star
     }
 }
 
-// Cost + two-stage aggregation of both views in one launch (one-call path).
+// Cost + one-stage aggregation of both views in one launch (one-call path).
 // Items: view, then strip, then disparity (strip-major); each XCD runs a
 // contiguous part of them.
-template <int ITERS>
 __global__ __launch_bounds__(kStripThreads, 2) void k_agg_pair(dco::AggArgs A0, AggRecords rec1,
                                                               float* out1, int s8) {
-    __shared__ dco::AggLds<ITERS, true> S;
+    __shared__ dco::AggLds<true> S;
     const int per_view = A0.nstrips * A0.D, N = 2 * per_view;
     const int x = blockIdx.x % 8, i = blockIdx.x / 8;
     int start, nx, m;
@@ -76,11 +74,11 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_agg_pair(dco::AggArgs A0, 
         A.rec = rec1;
         A.out = out1;
     }
-    dco::agg_stream<ITERS, true>(A, d, strip, y0, y1, S);
+    dco::agg_stream<true>(A, d, strip, y0, y1, S);
 }
 
 // Two stages: the same items with two adjacent disparities per item, one
-// 512-thread workgroup per CU (dco::agg_stream_ws).  kFused: both views, the
+// 768-thread workgroup per CU (dco::agg_stream_ws).  kFused: both views, the
 // raw cost computed on the fly; else one view (nviews = 1) from its cost
 // volume A0.cost (the staged dco_aggregate).
 template <bool kFused>
@@ -157,28 +155,12 @@ hipError_t launch_pair_ws(const dco::AggArgs& a0, const AggRecords& rec1, float*
     return hipGetLastError();
 }
 
-template <int ITERS>
 hipError_t launch_pair(const dco::AggArgs& a0, const AggRecords& rec1, float* out1,
                        hipStream_t st) {
-    // resident workgroups of the whole device, per device (queried once each;
-    // concurrent first calls store the same value)
-    constexpr int kMaxDev = 64;
-    static std::atomic<int> slots[kMaxDev];
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    static std::atomic<int> slots[64];
+    int s8 = 0;
+    const hipError_t e = xcd_slots(k_agg_pair, kStripThreads, slots, &s8);
     if (e != hipSuccess) return e;
-    int total = dev < kMaxDev ? slots[dev].load(std::memory_order_relaxed) : 0;
-    if (!total) {
-        int cus = 0, nb = 0;
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_agg_pair<ITERS>,
-                                                             kStripThreads, 0);
-        if (e != hipSuccess) return e;
-        total = (nb > 0 ? nb : 1) * (cus > 0 ? cus : 1);
-        if (dev < kMaxDev) slots[dev].store(total, std::memory_order_relaxed);
-    }
-    const int s8 = total / 8;
     const int N = 2 * a0.nstrips * a0.D;
     int most = 1;
     for (int x = 0; x < 8; ++x) {
@@ -186,15 +168,13 @@ hipError_t launch_pair(const dco::AggArgs& a0, const AggRecords& rec1, float* ou
         pair_part(N, x, s8, a0.H, start, nx, m);
         most = nx + m > most ? nx + m : most;
     }
-    hipLaunchKernelGGL((k_agg_pair<ITERS>), dim3(8 * most), dim3(kStripThreads), 0, st, a0, rec1,
-                       out1, s8);
+    hipLaunchKernelGGL(k_agg_pair, dim3(8 * most), dim3(kStripThreads), 0, st, a0, rec1, out1,
+                       s8);
     return hipGetLastError();
 }
 
-template <int ITERS, bool kFused>
 hipError_t launch_stream(const dco::AggArgs& a, hipStream_t st) {
-    const int nblk = a.nstrips * a.D;
-    hipLaunchKernelGGL((k_agg_stream<ITERS, kFused>), dim3(nblk), dim3(kStripThreads), 0, st, a);
+    hipLaunchKernelGGL(k_agg_stream, dim3(a.nstrips * a.D), dim3(kStripThreads), 0, st, a);
     return hipGetLastError();
 }
 
@@ -209,11 +189,9 @@ hipError_t launch_aggregate(const float* cost, const AggRecords& rec, int W, int
     a.W = W;
     a.H = H;
     a.D = D;
-    a.nstrips = (W + kStripOut - 1) / kStripOut;
-    // two stages: the two-slice kernel on the volume (records written with
-    // kRecWs, plain slice order)
-    return iters == 1 ? launch_stream<1, false>(a, st)
-                      : launch_pair_ws<false>(a, rec, out, 1, st);
+    a.nstrips = (W + strip_out(iters) - 1) / strip_out(iters);
+    // two stages: the two-slice kernel on the volume (plain slice order)
+    return iters == 1 ? launch_stream(a, st) : launch_pair_ws<false>(a, rec, out, 1, st);
 }
 
 hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const AggRecords& recL,
@@ -232,35 +210,11 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
     a.H = H;
     a.D = D;
     a.L1 = L1;
-    a.nstrips = (W + kStripOut - 1) / kStripOut;
+    a.nstrips = (W + strip_out(iters) - 1) / strip_out(iters);
     a.ref = 0;
     a.rec = recL;
     a.out = outL;
     a.paired = paired && iters == 2;
-    return iters == 1 ? launch_pair<1>(a, recR, outR, st)
+    return iters == 1 ? launch_pair(a, recR, outR, st)
                       : launch_pair_ws<true>(a, recR, outR, 2, st);
-}
-
-RecGeom pair_rec_geom(int iters) { return iters == 2 ? dco::kRecWs : dco::kRecPlain; }
-
-hipError_t launch_cost_aggregate(int ref, const uint4* pixL, const uint4* pixR,
-                                 const AggRecords& rec, int W, int H, int D, int iters,
-                                 const float* tabA, const float* tabC, const float* alpha,
-                                 const float* beta, int L1, float* out, hipStream_t st) {
-    dco::AggArgs a{};
-    a.pixL = pixL;
-    a.pixR = pixR;
-    a.tabA = tabA;
-    a.tabC = tabC;
-    a.alpha = alpha;
-    a.beta = beta;
-    a.rec = rec;
-    a.out = out;
-    a.W = W;
-    a.H = H;
-    a.D = D;
-    a.ref = ref;
-    a.L1 = L1;
-    a.nstrips = (W + kStripOut - 1) / kStripOut;
-    return iters == 1 ? launch_stream<1, true>(a, st) : launch_stream<2, true>(a, st);
 }

@@ -25,7 +25,7 @@ struct NoLds {
 };
 
 // Stage 2 with two aggregation stages: slices a .. a + dchunk - 1 of strip b,
-// row band c, two adjacent disparities per pass of dco::agg_stream_ws (512
+// row band c, two adjacent disparities per pass of dco::agg_stream_ws (768
 // threads, one workgroup per CU).  The workgroups of XCD x take that XCD's
 // contiguous part of the list, one item each.
 __global__ __launch_bounds__(dco::kWsThreads, 1) void k_batch_agg_ws(BatchArgs B, int first) {
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
                 const int y0 = I.b * 64 + r * dco::kCenTH;
                 if (y0 >= H) break;
                 dco::census_tile<1024>(img, W, H, B.cw, B.ch, B.L1, B.tau1, nullptr,
-                                       pr.arms[I.view], nullptr, pr.pix[I.view],
+                                       pr.arms[I.view], nullptr, pr.pix[I.view], ITERS == 2,
                                        I.a * dco::kCenTW, y0, S);
                 __syncthreads();
             }
@@ -87,8 +87,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
                 const int y0 = I.b * 64 + r * dco::kGeoTH;
                 if (y0 >= H) break;
                 dco::geometry_tile<1024>(pr.arms[I.view], W, H, ITERS, pr.rec[I.view],
-                                         I.a * dco::kGeoTW, y0, S,
-                                         ITERS == 2 ? dco::kRecWs : dco::kRecPlain);
+                                         I.a * dco::kGeoTW, y0, S);
                 __syncthreads();
             }
         }
@@ -96,13 +95,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 }
 
 // LDS of stages 2 (one aggregation stage), 3 and 4: aggregation rings or none.
-template <int ITERS, int STAGE>
+template <int STAGE>
 using StageLds =
-    typename std::conditional<STAGE == 2, dco::AggLds<ITERS, true>, NoLds>::type;
+    typename std::conditional<STAGE == 2, dco::AggLds<true>, NoLds>::type;
 
 template <int ITERS, int STAGE>
 __global__ __launch_bounds__(256, 2) void k_batch_stage(BatchArgs B, int first, int count) {
-    __shared__ StageLds<ITERS, STAGE> S;
+    __shared__ StageLds<STAGE> S;
     const int t = threadIdx.x;
     // stage 2: one item per workgroup, the workgroups of XCD x (blockIdx %
     // kXcds, dispatched in order) taking that XCD's contiguous part of the
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_stage(BatchArgs B, int first, 
             const int y0 = I.c * pr.band, y1 = min(H, y0 + pr.band);
             const int dend = min(pr.D, I.a + pr.dchunk);
             for (int d = I.a; d < dend; ++d) {
-                dco::agg_stream<ITERS, true>(A, d, I.b, y0, y1, S);
+                dco::agg_stream<true>(A, d, I.b, y0, y1, S);
                 __syncthreads();
             }
         } else if constexpr (STAGE == 3) {  // WTA of both views for pixels [a, a + kWtaPx)

@@ -12,15 +12,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     uint64_t* __restrict__ census, uint32_t* __restrict__ arms, uint32_t* __restrict__ rgb_packed,
     uint4* __restrict__ pix) {
     __shared__ dco::CensusLds S;
-    dco::census_tile<1024>(rgb, W, H, cw, ch, L1, tau1, census, arms, rgb_packed, pix,
+    dco::census_tile<1024>(rgb, W, H, cw, ch, L1, tau1, census, arms, rgb_packed, pix, false,
                            blockIdx.x * dco::kCenTW, blockIdx.y * dco::kCenTH, S);
 }
 
 __global__ __launch_bounds__(1024) void k_geometry(const uint32_t* __restrict__ arms, int W, int H,
-                                                   int iters, AggRecords rec, RecGeom g) {
+                                                   int iters, AggRecords rec) {
     __shared__ dco::GeomLds S;
     dco::geometry_tile<1024>(arms, W, H, iters, rec, blockIdx.x * dco::kGeoTW,
-                             blockIdx.y * dco::kGeoTH, S, g);
+                             blockIdx.y * dco::kGeoTH, S);
 }
 
 // Both views of the one-call path in one launch each (blockIdx.z = view);
@@ -28,22 +28,22 @@ __global__ __launch_bounds__(1024) void k_geometry(const uint32_t* __restrict__ 
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_census_arms2(
     const uint8_t* __restrict__ rgbL, const uint8_t* __restrict__ rgbR, int W, int H, int cw,
     int ch, int L1, int tau1, uint32_t* __restrict__ armsL, uint32_t* __restrict__ armsR,
-    uint4* __restrict__ pixL, uint4* __restrict__ pixR) {
+    uint4* __restrict__ pixL, uint4* __restrict__ pixR, bool planes) {
     __shared__ dco::CensusLds S;
     const bool r = blockIdx.z != 0;
     dco::census_tile<1024>(r ? rgbR : rgbL, W, H, cw, ch, L1, tau1, nullptr, r ? armsR : armsL,
-                           nullptr, r ? pixR : pixL, blockIdx.x * dco::kCenTW,
+                           nullptr, r ? pixR : pixL, planes, blockIdx.x * dco::kCenTW,
                            blockIdx.y * dco::kCenTH, S);
 }
 
 __global__ __launch_bounds__(1024) void k_geometry2(const uint32_t* __restrict__ armsL,
                                                    const uint32_t* __restrict__ armsR, int W,
                                                    int H, int iters, AggRecords recL,
-                                                   AggRecords recR, RecGeom g) {
+                                                   AggRecords recR) {
     __shared__ dco::GeomLds S;
     const bool r = blockIdx.z != 0;
     dco::geometry_tile<1024>(r ? armsR : armsL, W, H, iters, r ? recR : recL,
-                             blockIdx.x * dco::kGeoTW, blockIdx.y * dco::kGeoTH, S, g);
+                             blockIdx.x * dco::kGeoTW, blockIdx.y * dco::kGeoTH, S);
 }
 
 // Every view of a batch of pairs in one launch (blockIdx.z = 2 * pair + view),
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     const bool r = (blockIdx.z & 1) != 0;
     const size_t P = (size_t)W * H, o = P * (blockIdx.z >> 1);
     dco::census_tile<1024>((r ? rgbR : rgbL) + 3 * o, W, H, cw, ch, L1, tau1, nullptr,
-                           (r ? armsR : armsL) + o, nullptr, (r ? pixR : pixL) + o,
+                           (r ? armsR : armsL) + o, nullptr, (r ? pixR : pixL) + o, false,
                            blockIdx.x * dco::kCenTW, blockIdx.y * dco::kCenTH, S);
 }
 
@@ -80,13 +80,12 @@ hipError_t launch_census_pairs(const uint8_t* rgbL, const uint8_t* rgbR, int B, 
 hipError_t launch_front2(const uint8_t* rgbL, const uint8_t* rgbR, int W, int H, int cw, int ch,
                          int L1, int tau1, int iters, uint32_t* armsL, uint32_t* armsR,
                          uint4* pixL, uint4* pixR, const AggRecords& recL, const AggRecords& recR,
-                         const RecGeom& g, hipStream_t st) {
+                         hipStream_t st) {
     dim3 g1((W + dco::kCenTW - 1) / dco::kCenTW, (H + dco::kCenTH - 1) / dco::kCenTH, 2);
     hipLaunchKernelGGL(k_census_arms2, g1, dim3(1024), 0, st, rgbL, rgbR, W, H, cw, ch, L1, tau1,
-                       armsL, armsR, pixL, pixR);
+                       armsL, armsR, pixL, pixR, iters == 2);
     dim3 g2((W + dco::kGeoTW - 1) / dco::kGeoTW, (H + dco::kGeoTH - 1) / dco::kGeoTH, 2);
-    hipLaunchKernelGGL(k_geometry2, g2, dim3(1024), 0, st, armsL, armsR, W, H, iters, recL, recR,
-                       g);
+    hipLaunchKernelGGL(k_geometry2, g2, dim3(1024), 0, st, armsL, armsR, W, H, iters, recL, recR);
     return hipGetLastError();
 }
 
@@ -100,8 +99,8 @@ hipError_t launch_census_arms(const uint8_t* rgb, int W, int H, int cw, int ch, 
 }
 
 hipError_t launch_geometry(const uint32_t* arms, int W, int H, int iters, const AggRecords& rec,
-                           const RecGeom& g, hipStream_t st) {
+                           hipStream_t st) {
     dim3 grid((W + dco::kGeoTW - 1) / dco::kGeoTW, (H + dco::kGeoTH - 1) / dco::kGeoTH);
-    hipLaunchKernelGGL(k_geometry, grid, dim3(1024), 0, st, arms, W, H, iters, rec, g);
+    hipLaunchKernelGGL(k_geometry, grid, dim3(1024), 0, st, arms, W, H, iters, rec);
     return hipGetLastError();
 }

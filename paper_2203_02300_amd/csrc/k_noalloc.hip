@@ -20,10 +20,15 @@
 
 namespace {
 
+// The shapes the call takes are those whose budget (budget_bytes) is at most
 // 160 MiB: the paper's operating point, a 640 x 360 pair with D = 64 and two
 // vote passes, needs about 152 MB (both 59 MB aggregated volumes, the
-// records, the packed pixels and the disparity maps).
-constexpr size_t kStaticScratchBytes = size_t(160) << 20;
+// records, the packed pixels and the disparity maps).  The array is larger by
+// the most that the buffers of such a shape exceed its budget: their records
+// have 34 rows past the image where the budget counts 18, at most
+// 16 * 16 * 16672 bytes more per view.
+constexpr size_t kStaticBudgetBytes = size_t(160) << 20;
+constexpr size_t kStaticScratchBytes = size_t(172) << 20;
 
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -84,7 +89,7 @@ struct StaticBufs {
     uint4* pix[2];
     uint32_t* arms[2];
     AggRecords rec[2];
-    size_t rec_words[2][2];  // 4-word entries of b and c
+    size_t rec_words[2];  // words of b and c
     float* agg[2];
     int16_t* dint[2];
     float* delta;
@@ -101,20 +106,43 @@ size_t layout(unsigned char* base, int W, int H, int D, StaticBufs& b) {
     b.alpha = c.take<float>(kLMax + 1);
     b.beta = c.take<float>(kLMax + 1);
     for (int v = 0; v < 2; ++v) {
-        b.pix[v] = c.take<uint4>(P);
+        b.pix[v] = c.take<uint4>(pix_entries(W, H));
         b.arms[v] = c.take<uint32_t>(P);
         AggRecords& r = b.rec[v];
-        r.apron = kRecApronL;
-        r.Wp = W + kRecApronL + kRecApronR;
-        b.rec_words[v][0] = (size_t)r.Wp * (H + kLMax + 1);
-        b.rec_words[v][1] = (size_t)r.Wp * (H + 1);
-        r.b = c.take<uint32_t>(4 * b.rec_words[v][0]);
-        r.c = c.take<uint32_t>(4 * b.rec_words[v][1]);
+        r.Wp = rec_wp(W);
+        b.rec_words[0] = rec_b_words(W, H);
+        b.rec_words[1] = rec_c_words(W, H);
+        r.b = c.take<uint32_t>(b.rec_words[0]);
+        r.c = c.take<uint32_t>(b.rec_words[1]);
         b.agg[v] = c.take<float>(V);
         b.dint[v] = c.take<int16_t>(P);
         b.vote[v] = c.take<int16_t>(P);
     }
     b.delta = c.take<float>(P);
+    return (c.used + 255) & ~size_t(255);
+}
+
+// Bytes a shape is counted as, which decide whether it is taken: 32 bytes of
+// records per pixel with 290 columns and 18 + 1 rows of apron, 16 of packed
+// pixels, 4 of arms, 4 of maps, 4 of offsets and both volumes, every buffer
+// 256-byte aligned.
+size_t budget_bytes(int W, int H, int D) {
+    const size_t P = (size_t)W * H, Wp = (size_t)W + 290;
+    Carve c{nullptr, 0};
+    c.take<float>(768);
+    c.take<float>(68);
+    c.take<float>(kLMax + 1);
+    c.take<float>(kLMax + 1);
+    for (int v = 0; v < 2; ++v) {
+        c.take<uint4>(P);
+        c.take<uint32_t>(P);
+        c.take<uint4>(Wp * (H + 18));
+        c.take<uint4>(Wp * (H + 1));
+        c.take<float>(P * D);
+        c.take<int16_t>(P);
+        c.take<int16_t>(P);
+    }
+    c.take<float>(P);
     return (c.used + 255) & ~size_t(255);
 }
 
@@ -160,11 +188,12 @@ extern "C" dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_pa
     DCO_TRY(need(disp, "disp"));
     DCO_TRY(need(valid, "valid"));
     StaticBufs b{};
-    const size_t need_bytes = layout(nullptr, W, H, D, b);
-    if (need_bytes > kStaticScratchBytes) {
+    const size_t need_bytes = budget_bytes(W, H, D);
+    if (need_bytes > kStaticBudgetBytes ||
+        layout(nullptr, W, H, D, b) > kStaticScratchBytes) {
         dco_set_error("dco_stereo_match_noalloc: W=%d H=%d D=%d needs %zu bytes of static "
                       "scratch, %zu available (up to 640 x 360 with D = 64)",
-                      W, H, D, need_bytes, kStaticScratchBytes);
+                      W, H, D, need_bytes, kStaticBudgetBytes);
         return DCO_ERR_SHAPE;
     }
     unsigned char* base = nullptr;
@@ -184,14 +213,14 @@ extern "C" dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_pa
     for (int v = 0; v < 2; ++v)
         for (int k = 0; k < 2; ++k) {
             uint4* r = reinterpret_cast<uint4*>(k ? b.rec[v].c : b.rec[v].b);
-            hipLaunchKernelGGL(k_zero16, dim3(1024), dim3(256), 0, st, r, b.rec_words[v][k]);
+            hipLaunchKernelGGL(k_zero16, dim3(1024), dim3(256), 0, st, r, b.rec_words[k] / 4);
         }
     DCO_HIP_CHECK(hipGetLastError());
 
     // the same kernel sequence as dco_stereo_match
     DCO_HIP_CHECK(launch_front2(rgbL, rgbR, W, H, p.census_w, p.census_h, p.arm_L1, p.arm_tau1,
                                 p.agg_iters, b.arms[0], b.arms[1], b.pix[0], b.pix[1], b.rec[0],
-                                b.rec[1], pair_rec_geom(p.agg_iters), st));
+                                b.rec[1], st));
     DCO_HIP_CHECK(launch_cost_aggregate2(b.pix[0], b.pix[1], b.rec[0], b.rec[1], W, H, D,
                                          p.agg_iters, b.tabA, b.tabC, b.alpha, b.beta, p.arm_L1,
                                          b.agg[0], b.agg[1], true, st));
