@@ -29,10 +29,12 @@ FLAGS = [
 # scheduler that maximises instruction-level parallelism interleaves the
 # independent chains of its two slices: the 1280x720, D = 128 frame takes
 # 0.782 ms with it and 0.889 ms with the default one, with the same results
-# bit for bit.  The WTA and the batched work-list kernels are a little slower
-# under it, so it is not global.
+# bit for bit.  The WTA and the other batched work-list kernels are a little
+# slower under it, so it is not global.
+_MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 FILE_FLAGS = {
-    "k_aggregate.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "k_aggregate.hip": _MAX_ILP,
+    "k_batch_agg.hip": _MAX_ILP,
 }
 
 

@@ -60,8 +60,7 @@ dco_status alloc_pair(dco_batch* b, BatchPair& pr, int W, int H, int D) {
     pr.W = W;
     pr.H = H;
     pr.D = D;
-    const int sw = strip_out(b->p.agg_iters);
-    pr.nstrips = (W + sw - 1) / sw;
+    pr.nstrips = agg_strips(W, b->p.agg_iters);
     for (int v = 0; v < 2; ++v) {
         DCO_TRY(balloc(b, &pr.arms[v], P));
         DCO_TRY(balloc(b, &pr.pix[v], pix_entries(W, H)));
@@ -323,7 +322,7 @@ dco_status tune_class(const dco_params& p, int W, int H, int D, hipStream_t st, 
     dco_status s = make_base(&tb, 1, p);
     int copies = 1;
     if (s == DCO_OK) {
-        const int sw = strip_out(p.agg_iters), nstrips = (W + sw - 1) / sw;
+        const int nstrips = agg_strips(W, p.agg_iters);
         const long long slots = (long long)tb.cus * std::max(1, tb.per_cu[2]);
         copies = (int)std::min<long long>(16, std::max<long long>(
                                                    1, (4 * slots + 2LL * nstrips * D - 1) /
@@ -538,7 +537,7 @@ extern "C" dco_status dco_batch_tile(const dco_batch* b, int i, int* strip_w, in
         dco_set_error("dco_batch_tile: pair %d out of range", i);
         return DCO_ERR_ARG;
     }
-    if (strip_w) *strip_w = strip_out(b->p.agg_iters);
+    if (strip_w) *strip_w = b->p.agg_iters == 2 ? kWsOut : kStripOut;
     if (band_h) *band_h = b->pairs[i].band;
     if (d_chunk) *d_chunk = b->pairs[i].dchunk;
     return DCO_OK;

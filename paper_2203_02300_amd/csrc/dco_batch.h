@@ -57,3 +57,7 @@ hipError_t launch_batch(const BatchArgs& a, int iters, const int* first, const i
                         hipStream_t st);
 // Resident workgroups per CU of each stage kernel.
 void batch_blocks_per_cu(int iters, int* per_stage);
+// Stage 2 with two aggregation stages (k_batch_agg.hip): items from index
+// `first`, one workgroup each; and its resident workgroups per CU.
+void launch_batch_agg_ws(const BatchArgs& a, int first, int grid, hipStream_t st);
+int batch_agg_ws_per_cu();

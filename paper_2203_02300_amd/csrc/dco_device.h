@@ -226,18 +226,21 @@ __device__ inline uint32_t ring_slot_bytes(int row, int ring) {
 constexpr int kWsThreads = 3 * kStripThreads;
 constexpr int kWsSlices = 2;
 constexpr int kWsRing = 2 * kLMax + 2;
-constexpr int kWsI0 = 16;                             // first strip column with a ring
-constexpr int kWsCols = 224;                          // columns with a ring
+constexpr int kWsCols = 224;                          // columns with a ring, from kWsI0 on
 constexpr uint32_t kWsSlotBytes = kWsCols * 8;        // one ring row of both slices
 constexpr int kWsLanes = kWsCols / 4;                 // output lanes with columns
-constexpr uint32_t kWsPlaneBytes = kWsLanes * 8;      // a plane of an output row's prefixes
+constexpr int kWsPlane = kWsLanes + 1;                // entries of a plane of an output row's
+                                                      // prefixes (with the sum of all columns)
+constexpr uint32_t kWsPlaneBytes = kWsPlane * 8;
 constexpr uint32_t kWsOffBias = 64;                   // keeps the left offsets non-negative
 static_assert(kWsRing % kAggK == 0, "a chunk's slots are consecutive");
 static_assert(kWsApron % 4 == 0 && kWsOut % 4 == 0 && kWsI0 % 4 == 0 && kWsCols % 4 == 0,
               "quads are aligned");
 static_assert(kWsI0 <= kWsApron - kLMax && kWsI0 + kWsCols >= kWsApron + kWsOut + kLMax &&
-                  kWsApron >= 2 * kLMax && kWsApron + kWsOut + 2 * kLMax <= kStripThreads,
+                  kWsApron >= 2 * kLMax && kWsApron + kWsOut + 2 * kLMax <= kStripThreads &&
+                  kWsI0 + kWsCols >= kWsApron + kWsOut + kWsEdge,
               "the strip's aprons");
+static_assert((4 * kWsPlane) % 2 == 0, "16-byte rows");
 static_assert((kWsRing - 1) * kWsSlotBytes < 65536, "ring offsets are stored in 16 bits");
 static_assert(8 * (kLMax + 1) < 256, "arm offsets are stored in 8 bits");
 
@@ -773,8 +776,11 @@ __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, in
 // every per-pixel input is a 16-byte load of four columns from a plane, and a
 // store is one 16-byte word.  The apron is 36 rather than 2 kLMax = 34, and
 // the strip 184 rather than 188, so that those quads are aligned to the
-// image's.  Every LDS word holds the two slices' values of one column (one
-// 64-bit access serves both).
+// image's.  The first and last strip have no apron at the image's border and
+// take 20 columns more, so that narrower strips do not mean more of them (960
+// columns are five strips, not six: 960 x 540 with D = 96 and two vote passes
+// takes 0.445 ms instead of 0.491).  Every LDS word holds the two slices' values
+// of one column (one 64-bit access serves both).
 //  * Prefix rows are exclusive (entry i is the sum of the columns before i),
 //    so a range sum over [x - l, x + r] is entry x + r + 1 minus entry x - l
 //    and no entry is needed before the first column.
@@ -798,7 +804,7 @@ struct AggLdsWs {
     float tabC[68];
     float2 ab[kLMax + 1];
     alignas(16) uint2 x1[2][kAggK][kStripThreads];  // stage-1 row prefixes, by chunk parity
-    alignas(16) uint2 e2[2][kAggK][kWsCols];        // stage-2 vertical sums, by chunk parity
+    alignas(16) uint2 e2[2][kAggK][4 * kWsPlane];   // stage-2 vertical sums, by chunk parity
     uint2 ring1[kWsRing * kWsCols];                 // [slot][column]
     uint2 ring2[kWsRing * kWsCols];
 };
@@ -832,7 +838,8 @@ struct WsItem {
     int nout;                      // slices that exist (the others are not stored)
     bool paired;                   // paired layout (see paired_at)
     bool quads;                    // W % 4 == 0: rows of the volumes keep quads aligned
-    int x0, ys, y0, y1, nch;       // strip, first stream row (a multiple of 4), band, chunks
+    int base, o0, o1;              // image columns of the strip's first, of its output range
+    int ys, y0, y1, nch;           // first stream row (a multiple of 4), band, chunks
 };
 
 // Loads of a cost wavefront for one chunk.  Fused: the lane's four reference
@@ -1025,7 +1032,7 @@ __device__ inline void ws_col_phase(const uint2* x, uint2* e, uint32_t cb, uint3
         const uint32_t o = in.b[k].z;
         const uint2 hi = lds_ld2(S.ring2, cb + (o & 0xffff));
         const uint2 lo = lds_ld2(S.ring2, cb + (o >> 16));
-        e[k * kWsCols] = make_uint2(hi.x - lo.x, hi.y - lo.y);
+        e[k * 4 * kWsPlane] = make_uint2(hi.x - lo.x, hi.y - lo.y);
     }
 }
 
@@ -1062,9 +1069,9 @@ __device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
     }
     ws_scan(v);
     __builtin_amdgcn_wave_barrier();  // the row is this wavefront's own
-    if (lane < kWsLanes) {
+    if (lane < kWsPlane) {  // the lane past the last: its first prefix is the sum of all
 #pragma unroll
-        for (int j = 0; j < 4; ++j) row[j * kWsLanes + lane] = make_uint2(v[0][j], v[1][j]);
+        for (int j = 0; j < 4; ++j) row[j * kWsPlane + lane] = make_uint2(v[0][j], v[1][j]);
     }
     __builtin_amdgcn_wave_barrier();
     const uint32_t off[4] = {in.off.x, in.off.y, in.off.z, in.off.w};
@@ -1113,12 +1120,12 @@ template <int kRef, bool kQuads>
 __device__ inline void ws_out_loop(const AggArgs& A, const WsItem& I, int w, AggLdsWs& S) {
     const int lane = threadIdx.x & 63, W = A.W, H = A.H;
     const uint32_t Wp4 = (uint32_t)A.rec.Wp * 4, cplane4 = Wp4 * (uint32_t)H;
-    const int c = I.x0 - kWsApron + kWsI0 + 4 * lane;  // image column of the lane's first
+    const int c = I.base + kWsI0 + 4 * lane;  // image column of the lane's first
     const uint32_t vcol = (uint32_t)(c + kRecApronL) * 4;
     uint32_t vout[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        vout[j] = c >= I.x0 && c < I.x0 + kWsOut && c + j < W ? (uint32_t)(c + j) * 4 : kOOB;
+        vout[j] = c >= I.o0 && c + j < I.o1 && lane < kWsLanes ? (uint32_t)(c + j) * 4 : kOOB;
     // the first chunk, even, with an output row of the band: before it there
     // is nothing to do but keep the phases
     const int q0 = max(0, I.y0 + 2 * kLMax - I.ys) / kAggK & ~1;
@@ -1152,7 +1159,9 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
     const uint32_t P4 = (uint32_t)(slice * 4);
 
     WsItem I;
-    I.x0 = strip * kWsOut;
+    I.base = strip * kWsOut - kWsI0;
+    I.o0 = strip == 0 ? 0 : I.base + kWsApron;
+    I.o1 = strip == A.nstrips - 1 ? W : I.base + kWsApron + kWsOut;
     I.y0 = y0;
     I.y1 = y1;
     I.ys = max(0, y0 - 2 * kLMax) & ~3;  // warm-up rows so that every range is complete
@@ -1194,7 +1203,7 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
 
     if (kind == 0) {
         WsCostLane ln;
-        const int c = I.x0 - kWsApron + 4 * lane;  // image column of the lane's first
+        const int c = I.base + 4 * lane;  // image column of the lane's first
         if constexpr (kFused) {
             const bool in_img = c >= 0 && c < px.Wq;
             ln.vref = (uint32_t)(kPixPad + (in_img ? c : 0)) * 4;
@@ -1230,7 +1239,7 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
         const int ct = t - kStripThreads;
         const bool owns = ct < kWsCols;
         const uint32_t cb = (uint32_t)ct * 8;
-        const uint32_t vcol = (uint32_t)(I.x0 + kWsI0 + ct - kWsApron + kRecApronL) * 16;
+        const uint32_t vcol = (uint32_t)(I.base + kWsI0 + ct + kRecApronL) * 16;
         const uint32_t Wp16 = (uint32_t)A.rec.Wp * 16;
         uint32_t cp1[kWsSlices] = {0, 0}, cp2[kWsSlices] = {0, 0};
         uint32_t slot = slot0 * kWsSlotBytes;

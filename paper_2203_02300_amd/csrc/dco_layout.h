@@ -13,11 +13,23 @@ constexpr int kLMax = 17;
 constexpr int kStripThreads = 256;
 // Output columns of one strip of the one-stage kernels.
 constexpr int kStripOut = kStripThreads - 4 * kLMax;
-// The two-stage kernel: columns of a strip left of its output columns, and
-// output columns (multiples of four: its lanes own aligned quads).
+// The two-stage kernel: a strip's 256 input columns start kWsI0 columns before
+// image column kWsOut * s.  An inner strip has kWsOut output columns after an
+// apron of kWsApron; the first and the last need no apron at the image's
+// border and take kWsEdge more.  (All multiples of four: the kernel's lanes
+// own aligned quads.)
+constexpr int kWsI0 = 16;
 constexpr int kWsApron = 36;
 constexpr int kWsOut = 184;
-constexpr int strip_out(int iters) { return iters == 2 ? kWsOut : kStripOut; }
+constexpr int kWsEdge = kWsApron - kWsI0;
+// Strips of an image W columns wide.  With the wider ones at the borders there
+// are never more than the 188-column strips of the one-stage kernels give, up
+// to W = 2064.
+constexpr int agg_strips(int W, int iters) {
+    if (iters != 2) return (W + kStripOut - 1) / kStripOut;
+    const int n = (W - 2 * kWsEdge + kWsOut - 1) / kWsOut;
+    return n > 0 && W > kWsOut + 2 * kWsEdge ? n : 1;
+}
 
 // Packed per-pixel records of one view for the aggregation kernels, written
 // by k_geometry.  Entries of rows and columns outside the image are zero
@@ -41,7 +53,7 @@ struct AggRecords {
     uint32_t* c;
     int Wp;
 };
-constexpr int kRecApronL = kWsApron;         // left apron of the records
+constexpr int kRecApronL = kWsApron;         // left apron of the records (2 kLMax at least)
 constexpr int kRecApronR = kStripThreads;    // right apron (covers a strip's overhang)
 constexpr int kWsRecRows = 2 * kLMax;        // rows of b past the image's
 constexpr int rec_wp(int W) { return (W + kRecApronL + kRecApronR + 3) & ~3; }

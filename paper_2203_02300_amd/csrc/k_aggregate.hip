@@ -189,7 +189,7 @@ hipError_t launch_aggregate(const float* cost, const AggRecords& rec, int W, int
     a.W = W;
     a.H = H;
     a.D = D;
-    a.nstrips = (W + strip_out(iters) - 1) / strip_out(iters);
+    a.nstrips = agg_strips(W, iters);
     // two stages: the two-slice kernel on the volume (plain slice order)
     return iters == 1 ? launch_stream(a, st) : launch_pair_ws<false>(a, rec, out, 1, st);
 }
@@ -210,7 +210,7 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
     a.H = H;
     a.D = D;
     a.L1 = L1;
-    a.nstrips = (W + strip_out(iters) - 1) / strip_out(iters);
+    a.nstrips = agg_strips(W, iters);
     a.ref = 0;
     a.rec = recL;
     a.out = outL;

@@ -24,43 +24,6 @@ struct NoLds {
     int unused;
 };
 
-// Stage 2 with two aggregation stages: slices a .. a + dchunk - 1 of strip b,
-// row band c, two adjacent disparities per pass of dco::agg_stream_ws (768
-// threads, one workgroup per CU).  The workgroups of XCD x take that XCD's
-// contiguous part of the list, one item each.
-__global__ __launch_bounds__(dco::kWsThreads, 1) void k_batch_agg_ws(BatchArgs B, int first) {
-    __shared__ dco::AggLdsWs S;
-    const int x = blockIdx.x % kXcds;
-    const int k = B.xsplit[x] - first + blockIdx.x / kXcds;
-    if (k >= B.xsplit[x + 1] - first) return;  // uniform
-    const BatchItem I = B.items[first + k];
-    const BatchPair& pr = B.pairs[I.pair];
-    dco::AggArgs A{};
-    A.pixL = pr.pix[0];
-    A.pixR = pr.pix[1];
-    A.tabA = B.tabA;
-    A.tabC = B.tabC;
-    A.alpha = B.alpha;
-    A.beta = B.beta;
-    A.rec = pr.rec[I.view];
-    A.out = pr.agg[I.view];
-    A.W = pr.W;
-    A.H = pr.H;
-    A.D = pr.D;
-    A.nstrips = pr.nstrips;
-    A.ref = I.view;
-    A.L1 = B.L1;
-    // with an even chunk every pass starts at an even slice, so the passes'
-    // slice pairs are the layout's pairs; stage 3 reads the even slices
-    A.paired = pr.dchunk % 2 == 0;
-    const int y0 = I.c * pr.band, y1 = min(pr.H, y0 + pr.band);
-    const int dend = min(pr.D, I.a + pr.dchunk);
-    for (int d = I.a; d < dend; d += dco::kWsSlices) {
-        dco::agg_stream_ws(A, d, dend, I.b, y0, y1, S);
-        __syncthreads();
-    }
-}
-
 // Stages 0 and 1 with one thread per pixel of a tile (1024 threads), the
 // same tiles as the one-call front end: census + arms + packed pixels, then
 // region counts and records, of 64 x 64 blocks; persistent over the items.
@@ -202,8 +165,7 @@ hipError_t launch_all(const BatchArgs& a, const int* first, const int* grid, hip
     hipLaunchKernelGGL((k_batch_front<ITERS, 1>), dim3(grid[1]), dim3(1024), 0, st, a, first[1],
                        first[2] - first[1]);
     if constexpr (ITERS == 2)
-        hipLaunchKernelGGL(k_batch_agg_ws, dim3(grid[2]), dim3(dco::kWsThreads), 0, st, a,
-                           first[2]);
+        launch_batch_agg_ws(a, first[2], grid[2], st);
     else
         hipLaunchKernelGGL((k_batch_stage<ITERS, 2>), dim3(grid[2]), dim3(256), 0, st, a,
                            first[2], first[3] - first[2]);
@@ -223,10 +185,7 @@ void blocks_per_cu(int* per_stage) {
         per_stage[k] = e == hipSuccess && nb > 0 ? nb : 1;
     }
     if constexpr (ITERS == 2) {
-        int nb = 0;
-        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, k_batch_agg_ws, dco::kWsThreads, 0);
-        per_stage[2] = e == hipSuccess && nb > 0 ? nb : 1;
+        per_stage[2] = batch_agg_ws_per_cu();
     } else {
         per_stage[2] = stage_blocks_per_cu<ITERS, 2>();
     }

@@ -9,19 +9,22 @@ from gpu_util import dev, host
 
 pytestmark = pytest.mark.gpu
 
-# a strip is 184 output columns (aprons of 36), lanes own aligned quads of
-# columns, rows go in chunks of four, rings hold 36 rows; small frames are
-# split into a top and a bottom half
+# inner strips are 184 output columns (aprons of 36), the first and the last
+# 20 more, a lone one 224; lanes own aligned quads of columns, rows go in
+# chunks of four, rings hold 36 rows; small frames are split into a top and a
+# bottom half
 SHAPES = [
     (9, 7, 3),        # the smallest frame: one quad and one column
-    (183, 8, 2),      # one strip, its last column missing
-    (184, 37, 5),     # one strip exactly, an odd range (a lone last slice)
-    (185, 36, 4),     # a second strip of one column
-    (186, 35, 1),     # one slice only
-    (187, 34, 7),
-    (188, 33, 8),     # a second strip of one quad
-    (369, 71, 6),     # three strips, a ragged last quad
-    (552, 70, 16),    # three strips exactly
+    (184, 37, 5),     # one strip, an odd range (a lone last slice)
+    (223, 36, 4),     # one strip, its last column missing
+    (224, 35, 1),     # one strip exactly, one slice only
+    (225, 34, 7),     # two strips, the second of 21 columns
+    (226, 8, 2),
+    (407, 33, 8),     # two strips, the last column missing
+    (408, 71, 6),     # two strips exactly
+    (409, 38, 3),     # three strips
+    (592, 70, 16),    # three strips exactly
+    (593, 39, 2),
 ]
 
 
@@ -52,7 +55,7 @@ def test_one_call_volumes_and_maps(W, H, D):
 
 
 @pytest.mark.parametrize("offset", [0, 1])
-@pytest.mark.parametrize("W,H,D", [(184, 37, 5), (185, 36, 4), (369, 71, 6)])
+@pytest.mark.parametrize("W,H,D", [(184, 37, 5), (225, 34, 7), (408, 71, 6)])
 def test_staged_aggregation_any_alignment(W, H, D, offset):
     """Volumes that start `offset` floats into their buffers: only 4-byte
     aligned, so the rows are read and written word by word."""
