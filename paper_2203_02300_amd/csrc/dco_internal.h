@@ -203,9 +203,21 @@ struct DensifyBufs {
     double *cr, *cd, *diag, *invdiag;  // edge coefficients (p, p + x), (p, p + y); diagonal
     double *x, *r, *q, *p[2];          // solution, residual, A p, search directions
     double *rz[2], *rr[2], *pq, *bb;   // block partial sums
-    int* flags;                        // [0] converged, [1] iterations done
+    int* flags;                        // [0] converged, [1] iterations done, [2] abort
+    // one-launch solve
+    uint64_t* words;                   // what its workgroups exchange
+    double* res;                       // [0] r.r, [1] b.b
 };
 int densify_blocks(int W, int H);
+constexpr int kDensifyMaxK = 4;
+int densify_solve_k(int W, int H, int cus);
+size_t densify_solve_words(int W, int H, int k);
+// The whole solve in one launch (k = densify_solve_k; `ticks` of the 100 MHz
+// clock bound each of its waits): D, flags and res are its results; with flags[2] set it was given up and D holds nothing.
+hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
+                                const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
+                                int H, double lam_d, double lam_s, double lam_s2, double tol,
+                                int limit, uint64_t ticks, float* D, hipStream_t st);
 hipError_t launch_densify_setup(const DensifyBufs& b, const float* Ds, const float* Dpre,
                                 const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
                                 int H, double lam_d, double lam_s, double lam_s2, hipStream_t st);

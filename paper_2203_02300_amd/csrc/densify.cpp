@@ -1,7 +1,9 @@
 // densify.cpp -- host side of the depth densification (Sec. 6, Eq. 13-20):
 // buffers, the captured iteration graph and the convergence loop.
+#include <climits>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -15,7 +17,18 @@ struct dco_densify {
     hipGraphExec_t exec = nullptr;
     int* flags_host = nullptr;  // pinned copy of b.flags
     int launches = 0;           // graph launches of the last run
+    int device = 0;
+    int solve_k = 0;            // pixels per thread of the one-launch solve (0: not possible)
+    bool one_launch = false;    // the last run was one
+    // longest wait of its workgroups for each other, in 10 ns (0.2 s); the
+    // environment variable DCO_DENSIFY_WAIT, read at create, lets a test
+    // force a solve to be given up
+    unsigned long long ticks = 20000000;
 };
+
+// One-launch solves of a process take turns on a device: two of them at once
+// could each hold CUs that the other's workgroups wait for.
+static std::mutex g_solve_turn[64];
 
 extern "C" dco_status dco_densify_default_params(dco_densify_params* out) {
     if (!out) {
@@ -34,7 +47,8 @@ extern "C" dco_status dco_densify_default_params(dco_densify_params* out) {
 static void free_densify(dco_densify* h) {
     DensifyBufs& b = h->b;
     void* ptrs[] = {b.cr, b.cd, b.diag, b.invdiag, b.x,  b.r,     b.q,  b.p[0],
-                    b.p[1], b.rz[0], b.rz[1], b.rr[0], b.rr[1], b.pq, b.bb, b.flags};
+                    b.p[1], b.rz[0], b.rz[1], b.rr[0], b.rr[1], b.pq, b.bb, b.flags,
+                    b.words, b.res};
     for (void* q : ptrs) dev_free(q);
     if (h->exec) (void)hipGraphExecDestroy(h->exec);
     pinned_free(h->flags_host);
@@ -98,8 +112,23 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
     double** parts[] = {&b.rz[0], &b.rz[1], &b.rr[0], &b.rr[1], &b.pq, &b.bb};
     for (double** v : parts)
         if ((st = dev_alloc(v, nb)) != DCO_OK) return fail(st);
-    if ((st = dev_alloc(&b.flags, 2)) != DCO_OK) return fail(st);
-    if ((st = pinned_alloc((void**)&h->flags_host, 2 * sizeof(int))) != DCO_OK) return fail(st);
+    if ((st = dev_alloc(&b.flags, 3)) != DCO_OK) return fail(st);
+    if ((st = pinned_alloc((void**)&h->flags_host, 3 * sizeof(int))) != DCO_OK) return fail(st);
+    int cus = 0;
+    if (hipGetDevice(&h->device) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) !=
+            hipSuccess) {
+        (void)hipGetLastError();
+        dco_set_error("hipGetDevice failed: no usable GPU");
+        return fail(DCO_ERR_HIP);
+    }
+    if (const char* w = getenv("DCO_DENSIFY_WAIT")) h->ticks = strtoull(w, nullptr, 10);
+    h->solve_k = h->device < 64 ? densify_solve_k(W, H, cus) : 0;
+    if (h->solve_k) {
+        if ((st = dev_alloc(&b.words, densify_solve_words(W, H, h->solve_k))) != DCO_OK)
+            return fail(st);
+        if ((st = dev_alloc(&b.res, 2)) != DCO_OK) return fail(st);
+    }
     // one launch = iters_per_launch iterations (two kernels each), captured
     // once on a private stream of default priority; no memset nodes
     hipStream_t cap;
@@ -137,6 +166,25 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
     DCO_TRY(need(MI, "MI"));
     DCO_TRY(need(D, "D"));
     const dco_densify_params& p = h->p;
+    h->one_launch = false;
+    if (h->solve_k) {
+        // whole groups of iters_per_launch iterations, as the launches below run
+        const long long groups = ((long long)p.max_iters + p.iters_per_launch - 1) /
+                                 p.iters_per_launch;
+        const long long limit = groups * p.iters_per_launch;
+        std::lock_guard<std::mutex> turn(g_solve_turn[h->device]);
+        DCO_HIP_CHECK(launch_densify_solve(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
+                                           p.lambda_d, p.lambda_s, p.lambda_s2, p.tol,
+                                           (int)(limit < INT_MAX ? limit : INT_MAX), h->ticks, D,
+                                           h->stream));
+        DCO_HIP_CHECK(hipMemcpyAsync(h->flags_host, h->b.flags, 3 * sizeof(int),
+                                     hipMemcpyDeviceToHost, h->stream));
+        DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
+        h->one_launch = h->flags_host[2] == 0;
+        if (h->one_launch) return DCO_OK;
+        // given up: its workgroups could not all run (another process held the
+        // CUs); the launches below need nothing to run at the same time
+    }
     DCO_HIP_CHECK(launch_densify_setup(h->b, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H, p.lambda_d,
                                        p.lambda_s, p.lambda_s2, h->stream));
     h->launches = 0;
@@ -158,7 +206,11 @@ extern "C" dco_status dco_densify_stats(dco_densify* h, int* iters, double* rel_
     int f[2];
     DCO_HIP_CHECK(hipMemcpy(f, h->b.flags, sizeof(f), hipMemcpyDeviceToHost));
     if (iters) *iters = f[1];
-    if (rel_residual) {
+    if (rel_residual && h->one_launch) {
+        double res[2];
+        DCO_HIP_CHECK(hipMemcpy(res, h->b.res, sizeof(res), hipMemcpyDeviceToHost));
+        *rel_residual = res[1] > 0.0 ? std::sqrt(res[0] / res[1]) : 0.0;
+    } else if (rel_residual) {
         // the newest r.r block sums: iteration k writes parity k & 1; setup parity 1
         const double* rr = f[1] > 0 ? h->b.rr[(f[1] - 1) & 1] : h->b.rr[1];
         std::vector<double> a((size_t)h->nblk), c((size_t)h->nblk);

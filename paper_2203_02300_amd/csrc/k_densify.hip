@@ -18,6 +18,12 @@
 // whole solve is deterministic without grid-wide synchronisation.  When
 // r.r <= tol^2 b.b the update launch sets a flag and every later launch
 // returns at once (no pixel is touched).
+//
+// Grids of up to about a million pixels run the whole solve in one launch
+// instead (k_dz_solve, below); the launches above serve larger grids, and a
+// solve whose workgroups could not all run at once.
+#include <climits>
+
 #include "dco_internal.h"
 
 namespace {
@@ -228,6 +234,346 @@ __global__ __launch_bounds__(kDzThreads) void k_dz_out(const double* __restrict_
     if (i < P) D[i] = (float)x[i];
 }
 
+// ---------------------------------------------------------------------------
+// The whole solve in one launch
+// ---------------------------------------------------------------------------
+//
+// One workgroup of 1024 threads per tile of 32 x 32 K pixels, at most one per
+// CU, so that all of them run at once.  A pixel's state (x, r, p, its
+// coefficients) stays in its thread's registers for the whole solve and p
+// passes to the neighbours through an LDS tile; the arithmetic per pixel is
+// that of the launches above.  Per iteration the workgroups exchange two
+// things through memory, and wait for nothing else:
+//   after the update: the partial sums of r.z and r.r, and z along the tile's
+//       edges, from which the neighbours keep p on their halo themselves;
+//   after q = A p: the partial sum of p.q.
+// A double travels as two 64-bit words that each carry 32 of its bits and the
+// iteration's number, written and read as single (relaxed, device-scope)
+// atomics: a reader takes a word as soon as it bears the number it waits for,
+// so no fence, counter or barrier is needed.  Words of one iteration are
+// written over in the next: a workgroup writes its sums of p.q for iteration
+// k + 1 only after it has read everybody's update of iteration k, which
+// everybody writes after reading the sums of p.q of iteration k, and so on in
+// turn.  Every workgroup adds all partial sums itself in the same order, so
+// all hold the same alpha and beta bits.
+//
+// A wait ends after `ticks` (0.2 s) without the awaited word (workgroups that do
+// not run: another process holds the CUs): the workgroup raises an abort flag
+// that every wait looks at, all leave, and the host repeats the solve with
+// the launches above.
+//
+// What bounds it: the two exchanges of an iteration (a store to memory and
+// loads from it across the XCDs, 1.3 us each, more with the tiles polled) and
+// the sums within a workgroup.  640 x 360: 0.42 ms (62 iterations) where the
+// launches above took 1.42; 1280 x 720: 0.77 ms (67) instead of 2.88.
+
+constexpr int kSolveThreads = 1024, kSolveWaves = kSolveThreads / 64;
+constexpr int kTileW = 32, kTileRows = 32;           // a tile is 32 x 32 K pixels
+constexpr int kLineWords = 32;                       // a tile's sums, 256 bytes apart: every
+                                                     // workgroup polls them
+
+struct SolveArgs {
+    const float *Ds, *Dpre;
+    const uint8_t* Bdp;
+    const float *Mfuse, *MI;
+    float* D;
+    int W, H, tx, ntiles, limit;  // tiles per row, tiles, iterations at most
+    double lam_d, lam_s, lam_s2, tol2;
+    uint64_t ticks;  // longest wait, in ticks of the 100 MHz clock
+    uint64_t* pq;    // ntiles lines: p.q (two words)
+    uint64_t* rzr;   // ntiles lines: r.z, r.r (two words each)
+    uint64_t* edge;  // ntiles x (64 + 64 K) x 2 words: top, bottom, left, right
+    int* flags;      // [0] converged, [1] iterations done, [2] abort
+    double* res;     // [0] r.r, [1] b.b
+};
+
+__device__ inline void put_word(uint64_t* p, uint32_t v, uint32_t epoch) {
+    __hip_atomic_store(p, (uint64_t)epoch << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void put_double(uint64_t* p, double v, uint32_t epoch) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    put_word(p, (uint32_t)b, epoch);
+    put_word(p + 1, (uint32_t)(b >> 32), epoch);
+}
+
+// The N doubles at p once all their words bear the epoch; false if the wait
+// was given up (the abort flag is then set).
+template <int N>
+__device__ inline bool get_doubles(const uint64_t* p, uint32_t epoch, uint64_t ticks,
+                                   int* abort_flag, double (&v)[N]) {
+    uint64_t w[2 * N];
+    uint64_t t0 = 0;
+    for (uint32_t n = 0;; ++n) {
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < 2 * N; ++k)
+            w[k] = __hip_atomic_load(p + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int k = 0; k < 2 * N; ++k) all = all && (uint32_t)(w[k] >> 32) == epoch;
+        if (all) break;
+        if ((n & 63) == 63 || !ticks) {  // now and then: is it time to give up, has somebody?
+            const uint64_t t = __builtin_amdgcn_s_memrealtime();
+            if (!t0) t0 = t;
+            const bool late = t - t0 >= ticks;
+            if (late) __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (late ||
+                __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                return false;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        v[k] = __builtin_bit_cast(double, (uint64_t)(uint32_t)w[2 * k] | w[2 * k + 1] << 32);
+    return true;
+}
+
+// Sum of a double over the wavefront's lanes 16 r .. 16 r + 15 in lane 15 of
+// each such row (kAll: over the whole wavefront, in lane 63), in a fixed
+// order: DPP row shifts 1, 2, 4, 8, then the row broadcasts 15 and 31.  Lanes
+// without a source add nothing.
+template <unsigned Ctrl, unsigned RowMask>
+__device__ inline double dpp_f64(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, Ctrl, RowMask,
+                                                              0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), Ctrl,
+                                                              RowMask, 0xf, false);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <bool kAll>
+__device__ inline double lane_sum(double v) {
+    v += dpp_f64<0x111, 0xf>(v);
+    v += dpp_f64<0x112, 0xf>(v);
+    v += dpp_f64<0x114, 0xf>(v);
+    v += dpp_f64<0x118, 0xf>(v);
+    if constexpr (kAll) {
+        v += dpp_f64<0x142, 0xa>(v);
+        v += dpp_f64<0x143, 0xc>(v);
+    }
+    return v;
+}
+
+// Clears what k_dz_solve waits on (words of an earlier solve bear the same
+// iteration numbers) and the flags.
+__global__ __launch_bounds__(256) void k_dz_clear(uint64_t* __restrict__ words, size_t n,
+                                                  int* __restrict__ flags) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) words[i] = 0;
+    if (i < 3) flags[i] = 0;
+}
+
+template <int K>
+__global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
+    constexpr int TH = kTileRows * K, E = 2 * kTileW + 2 * TH;
+    __shared__ double P[TH + 2][kTileW + 2];
+    __shared__ double red[2][kSolveWaves];  // wavefront sums of this tile
+    __shared__ double all[2][4];            // wavefront sums over the tiles
+    __shared__ int gave_up;
+    const int t = threadIdx.x, lx = t & 31, ly = t >> 5;
+    const int tile = blockIdx.x, ty0 = tile / A.tx, tx0 = tile - ty0 * A.tx;
+    const int x0 = tx0 * kTileW, y0 = ty0 * TH, W = A.W, H = A.H;
+    if (t == 0) gave_up = 0;
+
+    // own pixels: rows ly + 32 k of the tile; outside the image all is zero
+    double x[K], r[K], p[K], id[K], dg[K], cr[K], cd[K], cl[K], cu[K];
+    double rz = 0.0, rr = 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int xx = x0 + lx, y = y0 + ly + kTileRows * k;
+        x[k] = r[k] = p[k] = id[k] = dg[k] = cr[k] = cd[k] = cl[k] = cu[k] = 0.0;
+        if (xx >= W || y >= H) continue;
+        const int i = y * W + xx;
+        const double s = (double)A.Mfuse[i] * (double)A.MI[i];
+        const int b = A.Bdp[i] != 0;
+        auto w = [&](int j) {
+            const int bj = A.Bdp[j] != 0;
+            if (b + bj == 1) return 0.0;
+            const double sj = (double)A.Mfuse[j] * (double)A.MI[j];
+            return fmax(1.0 - fmin(s, sj), 0.0);
+        };
+        cr[k] = xx + 1 < W ? 2.0 * A.lam_s * w(i + 1) : 0.0;
+        cd[k] = y + 1 < H ? 2.0 * A.lam_s * w(i + W) : 0.0;
+        cl[k] = xx > 0 ? 2.0 * A.lam_s * w(i - 1) : 0.0;
+        cu[k] = y > 0 ? 2.0 * A.lam_s * w(i - W) : 0.0;
+        const double ds = A.Ds[i], dp = A.Dpre ? (double)A.Dpre[i] : 0.0;
+        const double wsp = ds > 0.0 ? 1.0 : 0.0, wst = dp > 0.0 ? 1.0 : 0.0;
+        dg[k] = A.lam_d * wsp + A.lam_s2 * wst + cr[k] + cd[k] + cl[k] + cu[k];
+        r[k] = A.lam_d * wsp * ds + A.lam_s2 * wst * dp;
+        id[k] = dg[k] > 0.0 ? 1.0 / dg[k] : 0.0;
+        rz += r[k] * r[k] * id[k];
+        rr += r[k] * r[k];
+    }
+    // halo cell of threads 256 .. 256 + E - 1: whose edge entry it is and
+    // where its p goes (corners are never read)
+    uint64_t* const my_edge = A.edge + (size_t)tile * E * 2;
+    const int e = t - 256;
+    const uint64_t* src = nullptr;
+    double* dst = nullptr;
+    if (e >= 0 && e < E) {
+        int nb = -1, idx = 0;  // neighbour tile, its edge entry
+        if (e < kTileW) {  // row above: the upper tile's bottom row
+            nb = ty0 > 0 ? tile - A.tx : -1;
+            idx = kTileW + e;
+            dst = &P[0][e + 1];
+        } else if (e < 2 * kTileW) {  // row below: the lower tile's top row
+            nb = y0 + TH < H ? tile + A.tx : -1;
+            idx = e - kTileW;
+            dst = &P[TH + 1][e - kTileW + 1];
+        } else if (e < 2 * kTileW + TH) {  // column left: the left tile's right column
+            nb = tx0 > 0 ? tile - 1 : -1;
+            idx = e + TH;
+            dst = &P[e - 2 * kTileW + 1][0];
+        } else {  // column right: the right tile's left column
+            nb = tx0 + 1 < A.tx ? tile + 1 : -1;
+            idx = e - TH;
+            dst = &P[e - 2 * kTileW - TH + 1][kTileW + 1];
+        }
+        if (nb >= 0) src = A.edge + ((size_t)nb * E + idx) * 2;
+        *dst = 0.0;
+    }
+    double ph = 0.0;
+
+    // Block sum of N values per thread in a fixed order, then published by one
+    // thread as this tile's words at `at`.
+    const auto publish = [&](auto& v, uint64_t* at, uint32_t epoch) {
+        constexpr int N = sizeof(v) / sizeof(double);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            v[j] = lane_sum<true>(v[j]);
+            if ((t & 63) == 63) red[j][t >> 6] = v[j];
+        }
+        __syncthreads();
+        static_assert(kSolveWaves == 16, "one wavefront total per lane of a DPP row");
+        if (t < kSolveWaves) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const double u = lane_sum<false>(red[j][t]);
+                if (t == kSolveWaves - 1) put_double(at + 2 * j, u, epoch);
+            }
+        }
+    };
+    // All tiles' sums (N doubles of every tile), added in a
+    // fixed order, in every thread's v; with halo, also z of the thread's halo
+    // cell.  False, in the whole workgroup, when a wait was given up.
+    const auto collect = [&](auto& v, const uint64_t* words, uint32_t epoch, bool halo,
+                             double& zh) {
+        constexpr int N = sizeof(v) / sizeof(double);
+        bool ok = true;
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] = 0.0;
+        for (int i = t; i < A.ntiles && t < 256; i += 256) {
+            double u[N];
+            ok = ok && get_doubles<N>(words + (size_t)i * kLineWords, epoch, A.ticks, A.flags + 2,
+                                       u);
+            if (!ok) break;
+#pragma unroll
+            for (int j = 0; j < N; ++j) v[j] += u[j];
+        }
+        if (halo && src) {
+            double u[1];
+            ok = get_doubles<1>(src, epoch, A.ticks, A.flags + 2, u);
+            zh = u[0];
+        }
+        if (!ok) gave_up = 1;
+        if (t < 256) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                v[j] = lane_sum<true>(v[j]);
+                if ((t & 63) == 63) all[j][t >> 6] = v[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] = (all[j][0] + all[j][1]) + (all[j][2] + all[j][3]);
+        const bool stop = gave_up != 0;
+        __syncthreads();  // all[] may be reused
+        return !stop;
+    };
+    const auto publish_update = [&](uint32_t epoch) {
+        // z along the edges, then the sums
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int row = ly + kTileRows * k;
+            const double z = r[k] * id[k];
+            if (row == 0) put_double(my_edge + 2 * lx, z, epoch);
+            if (row == TH - 1) put_double(my_edge + 2 * (kTileW + lx), z, epoch);
+            if (lx == 0) put_double(my_edge + 2 * (2 * kTileW + row), z, epoch);
+            if (lx == kTileW - 1) put_double(my_edge + 2 * (2 * kTileW + TH + row), z, epoch);
+        }
+        double v[2] = {rz, rr};
+        publish(v, A.rzr + (size_t)tile * kLineWords, epoch);
+    };
+
+    uint32_t epoch = 1;
+    publish_update(epoch);
+    double bb = 0.0, rz_old = 1.0, rr_all = 0.0;
+    int it = 0, converged = 0;
+    bool ok = true;
+    for (;; ++it) {
+        double s2[2], zh = 0.0;
+        ok = collect(s2, A.rzr, epoch, true, zh);
+        if (!ok) break;
+        const double rz_all = s2[0];
+        rr_all = s2[1];
+        if (it == 0) bb = rr_all;
+        if (rr_all <= A.tol2 * bb) {  // the same decision in every workgroup
+            converged = 1;
+            break;
+        }
+        if (it >= A.limit) break;
+        const double beta = it ? rz_all / rz_old : 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            p[k] = r[k] * id[k] + beta * p[k];
+            P[ly + kTileRows * k + 1][lx + 1] = p[k];
+        }
+        if (src) {
+            ph = zh + beta * ph;
+            *dst = ph;
+        }
+        __syncthreads();
+        double q[K], pq = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int py = ly + kTileRows * k + 1, px = lx + 1;
+            double off = 0.0;  // right, left, below, above, as in k_dz_dir
+            off += cr[k] * P[py][px + 1];
+            off += cl[k] * P[py][px - 1];
+            off += cd[k] * P[py + 1][px];
+            off += cu[k] * P[py - 1][px];
+            q[k] = dg[k] * p[k] - off;
+            pq += p[k] * q[k];
+        }
+        double s1[1] = {pq};
+        publish(s1, A.pq + (size_t)tile * kLineWords, epoch);
+        ok = collect(s1, A.pq, epoch, false, zh);
+        if (!ok) break;
+        const double alpha = s1[0] > 0.0 ? rz_all / s1[0] : 0.0;
+        rz = rr = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            x[k] += alpha * p[k];
+            r[k] = r[k] - alpha * q[k];
+            rz += r[k] * r[k] * id[k];
+            rr += r[k] * r[k];
+        }
+        rz_old = rz_all;
+        publish_update(++epoch);
+    }
+    if (!ok) return;  // uniform
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int xx = x0 + lx, y = y0 + ly + kTileRows * k;
+        if (xx < W && y < H) A.D[(size_t)y * W + xx] = (float)x[k];
+    }
+    if (tile == 0 && t == 0) {
+        A.flags[0] = converged;
+        A.flags[1] = it;
+        A.res[0] = rr_all;
+        A.res[1] = bb;
+    }
+}
+
 }  // namespace
 
 int densify_blocks(int W, int H) {
@@ -263,5 +609,52 @@ hipError_t launch_densify_out(const DensifyBufs& b, int W, int H, float* D, hipS
     const int P = W * H;
     hipLaunchKernelGGL(k_dz_out, dim3((P + kDzThreads - 1) / kDzThreads), dim3(kDzThreads), 0, st,
                        b.x, P, D);
+    return hipGetLastError();
+}
+
+static int solve_tiles(int W, int H, int k) {
+    const long long n = (long long)((W + kTileW - 1) / kTileW) *
+                        ((H + kTileRows * k - 1) / (kTileRows * k));
+    return n < INT_MAX ? (int)n : INT_MAX;
+}
+
+// Pixels per thread of the one-launch solve on a device with `cus` CUs, or 0
+// when the grid does not fit: its tiles must all run at once, one per CU.
+// An iteration takes about 3.3 us, 0.55 us per pixel of a thread and 23.5 ns
+// per tile that every workgroup polls (measured per iteration: 240 tiles of
+// one pixel 9.7 us, 120 of two 6.9, 80 of three 6.3, 60 of four 6.6 at
+// 640 x 360; 35 of one 4.5, 21 of two 4.8, 14 of three 5.3 at 200 x 150), so
+// the k with the least 23 k + tiles is taken.
+int densify_solve_k(int W, int H, int cus) {
+    int best = 0;
+    for (int k = 1; k <= kDensifyMaxK; ++k)
+        if (solve_tiles(W, H, k) <= cus &&
+            (!best || 23 * k + solve_tiles(W, H, k) < 23 * best + solve_tiles(W, H, best)))
+            best = k;
+    return best;
+}
+
+size_t densify_solve_words(int W, int H, int k) {
+    const size_t tiles = solve_tiles(W, H, k);
+    return tiles * (2 * kLineWords + 2 * (size_t)(2 * kTileW + 2 * kTileRows * k));
+}
+
+hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
+                                const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
+                                int H, double lam_d, double lam_s, double lam_s2, double tol,
+                                int limit, uint64_t ticks, float* D, hipStream_t st) {
+    const int tx = (W + kTileW - 1) / kTileW, tiles = solve_tiles(W, H, k);
+    SolveArgs A{Ds, Dpre, Bdp, Mfuse, MI, D, W, H, tx, tiles, limit, lam_d, lam_s, lam_s2,
+                tol * tol, ticks, b.words, b.words + (size_t)tiles * kLineWords,
+                b.words + 2 * (size_t)tiles * kLineWords, b.flags, b.res};
+    const size_t n = densify_solve_words(W, H, k);
+    hipLaunchKernelGGL(k_dz_clear, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, b.words, n,
+                       b.flags);
+    switch (k) {
+        case 1: hipLaunchKernelGGL(k_dz_solve<1>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
+        case 2: hipLaunchKernelGGL(k_dz_solve<2>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
+        case 3: hipLaunchKernelGGL(k_dz_solve<3>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
+        default: hipLaunchKernelGGL(k_dz_solve<4>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
+    }
     return hipGetLastError();
 }
