@@ -40,7 +40,8 @@ namespace {
 
 struct SoftGeom {
     const uint32_t* arms;  // B x H x W packed arms of the left view
-    const float* n1;       // B x H x W stage-1 region counts
+    const uint32_t* vrec;  // B x H x W column records (col_record)
+    const float* rn1;      // B x H x W 1 / stage-1 region counts
     const float* n2;       // B x H x W stage-2 region counts
     int B, W, H, D;
 };
@@ -66,13 +67,23 @@ __global__ void k_soft_tables(const float* __restrict__ theta, float* __restrict
     }
 }
 
+// Column record of a pixel: dn in bits 9 .. 13 and kLMax - u in bits 4 .. 8
+// (so that one mask and or give the LDS offset of a ring row, 512 bytes each),
+// -N1 as a 16-bit float (exact: N1 <= (2 kLMax + 1)^2) in the high half.
+__device__ inline uint32_t col_record(uint32_t a, int n1) {
+    const _Float16 n = (_Float16)(-n1);
+    return (uint32_t)arm(a, 3) << 9 | (uint32_t)(kLMax - arm(a, 2)) << 4 |
+           (uint32_t)__builtin_bit_cast(uint16_t, n) << 16;
+}
+
 // Region pixel counts of the left view (as floats) for every pair: one
 // block per 64 x 4 tile.  The row lengths l + r + 1 of the tile's columns
 // over kLMax rows above and below, and the column lengths u + dn + 1 of the
 // tile's rows over kLMax columns left and right, go to LDS (0 outside the
 // image, where no arm reaches); each count is then a sum of LDS entries.
 constexpr int kCntTW = 64, kCntTH = 4;
-__global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, float* __restrict__ n1,
+__global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, uint32_t* __restrict__ vrec,
+                                                     float* __restrict__ rn1,
                                                      float* __restrict__ n2) {
     constexpr int CH = kCntTH + 2 * kLMax, RW = kCntTW + 2 * kLMax;
     __shared__ uint8_t hl[CH][kCntTW];  // l + r + 1 down each tile column
@@ -103,7 +114,8 @@ __global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, float* __restri
     for (int k = -arm(a, 2); k <= arm(a, 3); ++k) s1 += hl[ty + kLMax + k][tx];
     for (int k = -arm(a, 0); k <= arm(a, 1); ++k) s2 += vl[ty][tx + kLMax + k];
     const size_t i = (size_t)b * g.W * g.H + (size_t)y * g.W + x;
-    n1[i] = (float)s1;
+    vrec[i] = col_record(a, s1);
+    rn1[i] = 1.0f / (float)s1;
     n2[i] = (float)s2;
 }
 
@@ -618,232 +630,232 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_soft_seed_adj(
     }
 }
 
-// Column passes, streamed down each column: one thread per column, kSoftCols
-// columns per workgroup, rows in batches of kSoftPre.  FP64 running sums in an
-// LDS ring of kSoftRing rows per column keep every range sum exact to FP32
-// rounding of the final value, and each thread touches only its own column,
-// so the result does not depend on scheduling.  A batch makes all its ring
-// writes before its ring reads: one LDS round trip per batch, not per row.
+// Column passes: both column sums of the forward (a1 = (column sum of E1) / N1,
+// E2 = column sum of a1), or both of their adjoints, in one pass over the
+// volume.  One thread per column, kSoftCols columns and one plane (or one of
+// S row segments of it) per wavefront, rows in batches of kSoftPre.  Each of
+// the two sums keeps FP64 running sums in an LDS ring of kSoftRing rows per
+// column, so every range sum is exact to FP32 rounding of the final value,
+// and each thread touches only its own column, so the result does not depend
+// on scheduling; the first sum's rows go to the second in registers, rounded
+// to FP32.
 //
-// The ring (20 KB per workgroup) bounds a CU to eight such workgroups, so
-// the loads of one wavefront have to cover the memory latency by themselves:
-// each thread keeps kSoftDepth batches of inputs in registers and loads
-// kSoftDepth - 1 batches ahead of the one it processes.  The row loop is
-// unrolled over one turn of the ring (kSoftTurn batches), so every ring slot
-// and every buffer index is a compile-time constant: slots are immediate LDS
-// offsets, and the wrap of a per-pixel range end around the ring is tested
-// only in the batches where it can happen.  The loop body has no branch:
-// loads read clamped rows, stores of rows outside the image get an
-// out-of-range buffer offset (the hardware drops them), and the row count is
-// rounded up to whole turns.
+// The two rings (40 KB) leave a CU four wavefronts, one per SIMD, so the
+// instruction stream of one wavefront has to cover every latency by itself:
+//   - inputs are loaded kSoftLead batches ahead of their use;
+//   - the LDS reads of one batch are issued in one step and used in the next
+//     (a step works on batch j of the first sum's reads, on batch j - 1's
+//     result, and on the second sum's reads, whose rows are stored one step
+//     later);
+//   - the row loop is unrolled over one turn of the ring (kSoftTurn batches),
+//     so every ring slot and buffer index is a compile-time constant: slots
+//     are immediate LDS offsets, and the wrap of a range end around the ring
+//     is tested only in the batches where it can happen;
+//   - no row is clamped or branched on: buffer loads outside the plane return
+//     zero and stores outside the segment are dropped by the buffer's bounds.
+// A plane's rows below 0 and past H then hold v = 0 and a record of N = 0,
+// 1/N = 0: they add zero to both sums.
+//
+// Measured at 8 x 64 planes of 640 x 480 (1.26 GB in and out; a copy of that
+// size takes about 0.25 ms): 0.35 ms forward and 0.36 ms adjoint, bound by the
+// issue of the four wavefronts (33 instructions per row); as two passes over
+// the volume, each at the copy's rate, 0.58 ms each.  Loading 2, 5 or 7
+// batches ahead instead of 3: 0.37, 0.35, 0.35 ms.  At 32 planes of 320 x 240
+// (160 wavefronts, six segments each) 19 us, was 53 us.
 constexpr int kSoftCols = 64;
 constexpr int kSoftPre = 5;                       // rows per batch
 constexpr int kSoftRing = 2 * kLMax + 1 + kSoftPre;  // 40 rows
 constexpr int kSoftTurn = kSoftRing / kSoftPre;   // batches per turn of the ring
-constexpr int kSoftDepth = 4;                     // batches held per thread
-constexpr int kSoftLead = (kSoftDepth - 1) * kSoftPre;  // rows streamed before row 0
+constexpr int kSoftLead = 3;                      // batches loaded ahead
+constexpr int kSoftBufs = kSoftLead < 4 ? 4 : 8;  // batches held per thread
+constexpr int kSoftLag = 2 * kLMax + 2 * kSoftPre;  // rows from a row's input to its output
+constexpr int kSoftSlots = 4 * 256;               // wavefronts the device holds at once
 constexpr uint32_t kSoftDrop = 0x80000000u;       // buffer offset past any plane (W H <= 2^27)
-static_assert(kSoftRing % kSoftPre == 0 && kSoftTurn % kSoftDepth == 0,
+static_assert(kSoftRing % kSoftPre == 0 && kSoftTurn % kSoftBufs == 0 && kSoftLead < kSoftBufs,
               "a turn of the ring is a whole number of batches and of buffer rotations");
-static_assert(kSoftLead < kSoftRing, "the lead-in rows fit in the ring");
 
-// kSoftPre rows of a column pass's per-row inputs.
-struct ColBatch {
-    float v[kSoftPre];     // input of row y
-    uint32_t a[kSoftPre];  // arms of row y (adjoint) or of row y - kLMax (forward)
-    float s[kSoftPre];     // scale of row y - kLMax
-};
-
-// Per-column state of a column pass: buffer resources over one plane of the
-// input, output, arms and scale, and the running state.
-struct ColPass {
-    double (*ring)[kSoftCols];  // the workgroup's LDS ring
-    __amdgpu_buffer_rsrc_t src, arms, sc, dst;
-    uint32_t x4, W4;  // byte offset of the (clamped) column, bytes per row
-    int t, H, rows;
-    bool ok;
-    double acc;  // running prefix (forward) or running sum of differences (adjoint)
-};
-
-template <bool kScale, bool kAdj>
-__device__ inline void col_load(const ColPass& c, int y0, ColBatch& b) {
-#pragma unroll
-    for (int k = 0; k < kSoftPre; ++k) {
-        const int y = y0 + k, yo = y - kLMax;
-        const uint32_t yq = (uint32_t)min(y, c.H - 1);  // y >= 0
-        const uint32_t oq = (uint32_t)min(max(yo, 0), c.H - 1);
-        b.v[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(c.src, c.x4,
-                                                                                 yq * c.W4, 0));
-        b.a[k] = __builtin_amdgcn_raw_buffer_load_b32(c.arms, c.x4, (kAdj ? yq : oq) * c.W4, 0);
-        b.s[k] = kScale ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                        c.sc, c.x4, oq * c.W4, 0))
-                        : 1.0f;
-    }
+// r / N1 from the record and 1/N1 (correctly rounded): the quotient's
+// remainder is exact, so its correction rounds correctly (Markstein).
+__device__ inline float col_div(float r, uint32_t rec, float rn) {
+    const float n = (float)__builtin_bit_cast(_Float16, (uint16_t)(rec >> 16));
+    const float q = r * rn;
+    return __builtin_fmaf(__builtin_fmaf(n, q, r), rn, q);
 }
 
-// Stores r as row yo of the column; dropped for rows outside the image and
-// for lanes past the last column.
-__device__ inline void col_store(const ColPass& c, int yo, float r) {
-    const bool in = c.ok && yo >= 0 && yo < c.H;
-    const uint32_t off = in ? (uint32_t)yo * c.W4 + c.x4 : kSoftDrop;
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, r), c.dst, off, 0, 0);
-}
-
-// Ring slot `base + v` and `base - v` (mod kSoftRing) for a compile-time
-// base in [0, kSoftRing) and a per-pixel 0 <= v <= kLMax + 1 (arm lengths
-// never exceed kLMax): the wrap test folds away where it cannot happen.
-__device__ inline int ring_up(int base, int v) {
-    const int r = base + v;
-    return base + kLMax + 1 < kSoftRing ? r : (r >= kSoftRing ? r - kSoftRing : r);
-}
-__device__ inline int ring_down(int base, int v) {
-    const int r = base - v;
-    return base >= kLMax + 1 ? r : (r < 0 ? r + kSoftRing : r);
-}
 constexpr int ring_mod(int s) { return ((s % kSoftRing) + kSoftRing) % kSoftRing; }
 
-template <bool kScale>
-__device__ inline ColPass col_setup(const SoftGeom& g, const float* in, const float* scale,
-                                    float* out, double (*ring)[kSoftCols]) {
-    ColPass c;
-    c.t = threadIdx.x;
-    const int x = blockIdx.x * kSoftCols + c.t;
-    const int bd = blockIdx.y, b = bd / g.D;
-    c.ok = x < g.W;
-    const size_t P = (size_t)g.W * g.H;
-    const int bytes = (int)(P * 4);
-    c.src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + (size_t)bd * P), (short)0,
-                                              bytes, 0x00020000);
-    c.arms = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(g.arms + (size_t)b * P),
-                                               (short)0, bytes, 0x00020000);
-    c.sc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>((kScale ? scale : in) + (size_t)b * P), (short)0, bytes, 0x00020000);
-    c.dst = __builtin_amdgcn_make_buffer_rsrc(out + (size_t)bd * P, (short)0, bytes, 0x00020000);
-    c.x4 = 4u * (uint32_t)(c.ok ? x : 0);
-    c.W4 = 4u * (uint32_t)g.W;
-    c.ring = ring;
-    c.H = g.H;
-    c.rows = g.H + kLMax;
-    c.acc = 0.0;
-    return c;
+// LDS byte offset of ring row base + v (mod kSoftRing) of this thread's column,
+// for a compile-time base in [0, kSoftRing), from o = 512 v + 8 t with
+// 0 <= v <= span: the wrap folds away where it cannot happen (min picks the
+// wrapped offset only where it does not go below zero).
+__device__ inline uint32_t ring_at(int base, uint32_t o, int span) {
+    const uint32_t r = (uint32_t)(base * (kSoftCols * 8)) + o;
+    return base + span < kSoftRing ? r : min(r, r - (uint32_t)(kSoftRing * kSoftCols * 8));
 }
 
-// Streams the column through `step(c, batch, y0, s0)`: rows y0 .. y0 +
-// kSoftPre - 1, whose first row sits in ring slot s0 (a compile-time
-// constant once unrolled).  The stream starts kSoftLead rows before row 0
-// on zeroed buffers, so the loop needs no prologue of loads (whose registers
-// the compiler would copy, and wait for, at the loop's entry); those rows
-// add zero and store nothing, and row 0 sits in slot 0.
-template <bool kScale, bool kAdj, typename Step>
-__device__ inline void col_stream(ColPass& c, Step step) {
-    ColBatch buf[kSoftDepth];
+// LDS add that returns nothing (a thread's adds to its own column stay in
+// program order).
+__device__ inline void lds_add(double* p, double v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <bool kAdj>
+__global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* __restrict__ in,
+                                                       float* __restrict__ out, int seg_rows) {
+    __shared__ __align__(16) double rings[2][kSoftRing][kSoftCols];
+    const int t = threadIdx.x, x = blockIdx.x * kSoftCols + t;
+    const int bd = blockIdx.y, b = bd / g.D;
+    const size_t P = (size_t)g.W * g.H;
+    const int r0 = blockIdx.z * seg_rows, r1 = min(r0 + seg_rows, g.H);
+    const int plane = (int)(P * 4);
+    const uint32_t W4 = 4u * (uint32_t)g.W;
+    const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + (size_t)bd * P),
+                                                       (short)0, plane, 0x00020000);
+    const auto rec = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint32_t*>(g.vrec + (size_t)b * P), (short)0, plane, 0x00020000);
+    const auto rni = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.rn1 + (size_t)b * P),
+                                                       (short)0, plane, 0x00020000);
+    const auto dst = __builtin_amdgcn_make_buffer_rsrc(
+        out + (size_t)bd * P + (size_t)r0 * g.W, (short)0, (int)((uint32_t)(r1 - r0) * W4),
+        0x00020000);
+    const uint32_t x4 = x < g.W ? 4u * (uint32_t)x : kSoftDrop;
+    const uint32_t t8 = 8u * t;
+    char* const R1 = reinterpret_cast<char*>(&rings[0][0][0]);
+    char* const R2 = reinterpret_cast<char*>(&rings[1][0][0]);
+    for (int i = 0; i < kSoftRing; ++i) rings[0][i][t] = rings[1][i][t] = 0.0;
+    // first input row that the segment's outputs need; the stream starts
+    // kSoftLead batches before it on zeroed buffers
+    const int first = max(r0 - 2 * kLMax, 0);
+    const int last = r1 + kSoftLag;
+    uint32_t v_off = x4 + (uint32_t)first * W4;                     // row y + lead
+    uint32_t n_off = v_off - (uint32_t)kLMax * W4;                  // row y - kLMax + lead
+    uint32_t d_off = x4 + (uint32_t)(first - r0 - kSoftLead * kSoftPre - kSoftLag) * W4;
+    float v[kSoftBufs][kSoftPre], rn[kSoftBufs][kSoftPre];
+    uint32_t p[kSoftBufs][kSoftPre], p2[kSoftTurn][kSoftPre];
+    double h1[kSoftPre], l1[kSoftPre], h2[kSoftPre], l2[kSoftPre];
 #pragma unroll
-    for (int j = 0; j < kSoftDepth; ++j)
+    for (int k = 0; k < kSoftPre; ++k) {
 #pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) {
-            buf[j].v[k] = 0.0f;
-            buf[j].a[k] = 0u;
-            buf[j].s[k] = 1.0f;
-        }
-    for (int y0 = -kSoftLead; y0 < c.rows; y0 += kSoftRing) {
+        for (int j = 0; j < kSoftBufs; ++j) v[j][k] = rn[j][k] = 0.0f, p[j][k] = 0u;
+#pragma unroll
+        for (int j = 0; j < kSoftTurn; ++j) p2[j][k] = 0u;
+        h1[k] = l1[k] = h2[k] = l2[k] = 0.0;
+    }
+    double acc1 = 0.0, acc2 = 0.0;
+    const auto up = [&](uint32_t q) { return (q & 0x3e00u) | t8; };           // 512 dn + 8 t
+    const auto dn = [&](uint32_t q) { return (q << 5 & 0x3e00u) | t8; };      // 512 (kLMax - u) + 8 t
+    const auto at = [](char* r, uint32_t o) { return reinterpret_cast<double*>(r + o); };
+    for (int y0 = first - kSoftLead * kSoftPre; y0 < last; y0 += kSoftRing) {
 #pragma unroll
         for (int j = 0; j < kSoftTurn; ++j) {
-            const int yb = y0 + j * kSoftPre;
-            col_load<kScale, kAdj>(c, yb + kSoftLead, buf[(j + kSoftDepth - 1) % kSoftDepth]);
-            ColBatch& cur = buf[j % kSoftDepth];
+            const int s1 = ring_mod((j - kSoftLead) * kSoftPre);       // slot of row y0 + 5 j
+            const int s2 = ring_mod((j - kSoftLead - 1) * kSoftPre);   // and of the batch before
+            float (&cv)[kSoftPre] = v[j % kSoftBufs];
+            uint32_t (&cp)[kSoftPre] = p[j % kSoftBufs];
+            float (&crn)[kSoftPre] = rn[(j + kSoftBufs - 1) % kSoftBufs];  // of the batch before
             // The batch's values are used from here on: without this pin the
             // compiler starts converting a later batch early, which waits for
             // loads that should still be in flight.
 #pragma unroll
+            for (int k = 0; k < kSoftPre; ++k)
+                asm volatile("" : "+v"(cv[k]), "+v"(cp[k]), "+v"(crn[k]));
+            // the second sum's finished rows, read in the step before
+#pragma unroll
             for (int k = 0; k < kSoftPre; ++k) {
-                asm volatile("" : "+v"(cur.v[k]), "+v"(cur.a[k]));
-                if (kScale) asm volatile("" : "+v"(cur.s[k]));
+                float o;
+                if (kAdj) {
+                    acc2 += h2[k];
+                    o = (float)acc2;
+                } else {
+                    o = (float)(h2[k] - l2[k]);
+                }
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, o), dst, d_off,
+                                                      0, 0);
+                d_off += W4;
             }
-            step(c, cur, yb, ring_mod(j * kSoftPre - kSoftLead));
+            // the first sum's rows, read in the step before, into the second
+            // (row record q of stream row y0 - kSoftPre + k - kLMax)
+            float a1[kSoftPre];
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) {
+                const uint32_t q = kAdj ? (k < 2 ? p2[(j + 3) % kSoftTurn][k + 3]
+                                                 : p2[(j + 4) % kSoftTurn][k - 2])
+                                        : p2[(j + kSoftTurn - 1) % kSoftTurn][k];
+                float r;
+                if (kAdj) {
+                    acc1 += h1[k];
+                    r = (float)acc1;
+                } else {
+                    r = (float)(h1[k] - l1[k]);
+                }
+                a1[k] = col_div(r, q, crn[k]);
+            }
+            // first sum, batch j
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) {
+                if (kAdj) {
+                    const double e = (double)cv[k];
+                    lds_add(at(R1, ring_at(ring_mod(s1 + k - kLMax), dn(cp[k]), kLMax)), e);
+                    lds_add(at(R1, ring_at(ring_mod(s1 + k + 1), up(cp[k]), kLMax)), -e);
+                } else {
+                    acc1 += (double)cv[k];
+                    *at(R1, (uint32_t)(ring_mod(s1 + k) * kSoftCols * 8) + t8) = acc1;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) {
+                if (kAdj) {
+                    h1[k] = __hip_atomic_exchange(
+                        at(R1, (uint32_t)(ring_mod(s1 + k - kLMax) * kSoftCols * 8) + t8), 0.0,
+                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                } else {
+                    h1[k] = *at(R1, ring_at(ring_mod(s1 + k - kLMax), up(cp[k]), kLMax));
+                    l1[k] = *at(R1, ring_at(ring_mod(s1 + k - 2 * kLMax - 1), dn(cp[k]), kLMax));
+                }
+            }
+            // second sum, batch j - 1
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) {
+                if (kAdj) {
+                    const uint32_t q = k < 2 ? p2[(j + 3) % kSoftTurn][k + 3]
+                                             : p2[(j + 4) % kSoftTurn][k - 2];
+                    const double e = (double)a1[k];
+                    lds_add(at(R2, ring_at(ring_mod(s2 + k - kLMax), dn(q), kLMax)), e);
+                    lds_add(at(R2, ring_at(ring_mod(s2 + k + 1), up(q), kLMax)), -e);
+                } else {
+                    acc2 += (double)a1[k];
+                    *at(R2, (uint32_t)(ring_mod(s2 + k) * kSoftCols * 8) + t8) = acc2;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) {
+                if (kAdj) {
+                    h2[k] = __hip_atomic_exchange(
+                        at(R2, (uint32_t)(ring_mod(s2 + k - kLMax) * kSoftCols * 8) + t8), 0.0,
+                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                } else {
+                    const uint32_t q = k < 2 ? p2[(j + 3) % kSoftTurn][k + 3]
+                                             : p2[(j + 4) % kSoftTurn][k - 2];
+                    h2[k] = *at(R2, ring_at(ring_mod(s2 + k - kLMax), up(q), kLMax));
+                    l2[k] = *at(R2, ring_at(ring_mod(s2 + k - 2 * kLMax - 1), dn(q), kLMax));
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) p2[j][k] = cp[k];
+            // the batch kSoftLead ahead
+#pragma unroll
+            for (int k = 0; k < kSoftPre; ++k) {
+                const int f = (j + kSoftLead) % kSoftBufs;
+                v[f][k] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(src, v_off, 0, 0));
+                p[f][k] = __builtin_amdgcn_raw_buffer_load_b32(rec, kAdj ? v_off : n_off, 0, 0);
+                rn[f][k] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(rni, n_off, 0, 0));
+                v_off += W4;
+                n_off += W4;
+            }
         }
     }
-}
-
-// out(y) = (sum of in over the vertical range of pixel y) [/ scale(y)], with
-// the running column prefix P: out(y) = P(y + dn) - P(y - u - 1).  The batch
-// of rows y0 .. y0 + kSoftPre - 1 (outputs kLMax rows behind) reads prefixes
-// from row y0 - 2 kLMax - 1 on; its writes land in the slots of rows
-// y0 - kSoftRing ... y0 + kSoftPre - 1 - kSoftRing, which are older.  The
-// lead-in rows hold P = 0, which is the prefix before row 0 (read as row -1
-// by a range that starts at row 0); rows past the image only feed outputs
-// that are dropped.
-template <bool kScale>
-__global__ __launch_bounds__(kSoftCols) void k_soft_vs(SoftGeom g, const float* __restrict__ in,
-                                                       const float* __restrict__ scale,
-                                                       float* __restrict__ out) {
-    __shared__ double ring[kSoftRing][kSoftCols];
-    ColPass c = col_setup<kScale>(g, in, scale, out, ring);
-    col_stream<kScale, false>(c, [](ColPass& c, const ColBatch& cur, int y0, int s0) {
-        const int t = c.t;
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) {
-            c.acc += (double)cur.v[k];
-            c.ring[ring_mod(s0 + k)][t] = c.acc;
-        }
-        double hi[kSoftPre], lo[kSoftPre];
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) {
-            const int u = arm(cur.a[k], 2), dn = arm(cur.a[k], 3);
-            hi[k] = c.ring[ring_up(ring_mod(s0 + k - kLMax), dn)][t];
-            lo[k] = c.ring[ring_down(ring_mod(s0 + k - kLMax - 1), u)][t];
-        }
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) {
-            const float r = (float)(hi[k] - lo[k]);
-            col_store(c, y0 + k - kLMax, kScale ? r / cur.s[k] : r);
-        }
-    });
-}
-
-// Adjoint of k_soft_vs: out(y') = sum over pixels y whose vertical range
-// covers y' of in(y), [/ scale(y')].  Each y adds in(y) at row y - u and
-// subtracts it after row y + dn in a ring of differences (LDS FP64 adds that
-// return nothing, in program order per column); row y' is final kLMax rows
-// later and its running sum is the output.  A batch first makes all its
-// adds, into rows y0 - kLMax ... y0 + kSoftPre + kLMax, then finishes (reads
-// and clears) rows y0 - kLMax ... y0 + kSoftPre - 1 - kLMax: that span is
-// kSoftRing rows, so no add lands in the slot of a row still to be finished,
-// and every slot it lands in was cleared when its previous row finished.
-// Rows outside the image add zero.
-template <bool kScale>
-__global__ __launch_bounds__(kSoftCols) void k_soft_vsa(SoftGeom g, const float* __restrict__ in,
-                                                        const float* __restrict__ scale,
-                                                        float* __restrict__ out) {
-    __shared__ double ring[kSoftRing][kSoftCols];
-    ColPass c = col_setup<kScale>(g, in, scale, out, ring);
-    for (int i = 0; i < kSoftRing; ++i) ring[i][c.t] = 0.0;
-    col_stream<kScale, true>(c, [](ColPass& c, const ColBatch& cur, int y0, int s0) {
-        const int t = c.t;
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) {
-            const int u = arm(cur.a[k], 2), dn = arm(cur.a[k], 3);
-            const float vf = (unsigned)(y0 + k) < (unsigned)c.H ? cur.v[k] : 0.0f;
-            const double v = (double)vf;
-            __hip_atomic_fetch_add(&c.ring[ring_down(ring_mod(s0 + k), u)][t], v,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_add(&c.ring[ring_up(ring_mod(s0 + k + 1), dn)][t], -v,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        double dv[kSoftPre];
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k)
-            dv[k] = __hip_atomic_exchange(&c.ring[ring_mod(s0 + k - kLMax)][t], 0.0,
-                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        // all the batch's exchanges in flight together (one LDS round trip)
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) asm volatile("" : "+v"(dv[k]));
-#pragma unroll
-        for (int k = 0; k < kSoftPre; ++k) {
-            c.acc += dv[k];
-            const float r = (float)c.acc;
-            col_store(c, y0 + k - kLMax, kScale ? r / cur.s[k] : r);
-        }
-    });
 }
 
 
@@ -936,20 +948,47 @@ __global__ __launch_bounds__(256) void k_soft_reduce2(const double* __restrict__
 
 // ---- launchers -------------------------------------------------------------
 
+// Row segments of the column passes.  A wavefront streams its segment's rows,
+// the 2 kLMax rows above and kSoftLag below that its outputs reach, and the
+// lead-in, in whole turns; a CU holds four of them.  The split that needs the
+// fewest turns one after the other is taken (the fewest segments on a tie):
+// one segment where the planes alone fill the device, several where they do
+// not.
+static int soft_segments(int W, int H, int planes) {
+    const long long wgs = (long long)((W + kSoftCols - 1) / kSoftCols) * planes;
+    int best = 1;
+    long long least = -1;
+    for (int s = 1; s <= 8; ++s) {
+        const int rows = (H + s - 1) / s;
+        const int head = s > 1 ? 2 * kLMax : 0;
+        const int turns = (kSoftLead * kSoftPre + head + rows + kSoftLag + kSoftRing - 1) / kSoftRing;
+        const long long cost = (wgs * s + kSoftSlots - 1) / kSoftSlots * turns;
+        if (least < 0 || cost < least) least = cost, best = s;
+    }
+    return best;
+}
+
+template <bool kAdj>
+static void launch_vv(const SoftGeom& g, const float* in, float* out, hipStream_t st) {
+    const int n = soft_segments(g.W, g.H, g.B * g.D), seg = (g.H + n - 1) / n;
+    hipLaunchKernelGGL(k_soft_vv<kAdj>,
+                       dim3((g.W + kSoftCols - 1) / kSoftCols, g.B * g.D, (g.H + seg - 1) / seg),
+                       dim3(kSoftCols), 0, st, g, in, out, seg);
+}
+
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, float* n1, float* n2, hipStream_t st) {
+                        int D, uint32_t* vrec, float* rn1, float* n2, hipStream_t st) {
     hipLaunchKernelGGL(k_soft_tables, dim3(4), dim3(256), 0, st, theta, tab);
-    SoftGeom g{arms, nullptr, nullptr, B, W, H, D};
+    SoftGeom g{arms, nullptr, nullptr, nullptr, B, W, H, D};
     hipLaunchKernelGGL(k_soft_counts, dim3((W + kCntTW - 1) / kCntTW, (H + kCntTH - 1) / kCntTH, B),
-                       dim3(256), 0, st, g, n1,
-                       n2);
+                       dim3(256), 0, st, g, vrec, rn1, n2);
     return hipGetLastError();
 }
 
 // Forward aggregation into A2 (B x D x H x W); t1, t2 are volume-sized scratch.
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, hipStream_t st) {
-    SoftGeom g{s.arms, s.n1, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const dim3 gr((nrows + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave));
@@ -961,18 +1000,15 @@ hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, floa
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_soft_hrow<true>, gr, dim3(64 * kRowWaves), kTabLds + kRowWaves * lc, st, g,
                        im, (const float*)nullptr, t1, lc);                                   // E1
-    const dim3 gv((W + kSoftCols - 1) / kSoftCols, B * D);
-    hipLaunchKernelGGL(k_soft_vs<true>, gv, dim3(kSoftCols), 0, st, g, t1, s.n1, t2);      // a1
-    hipLaunchKernelGGL(k_soft_vs<false>, gv, dim3(kSoftCols), 0, st, g, t2,
-                       (const float*)nullptr, t1);                                           // E2
-    hipLaunchKernelGGL(k_soft_hrow<false>, gr, dim3(64 * kRowWaves), kRowWaves * lf, st, g, im, t1,
+    launch_vv<false>(g, t1, t2, st);                                                         // E2
+    hipLaunchKernelGGL(k_soft_hrow<false>, gr, dim3(64 * kRowWaves), kRowWaves * lf, st, g, im, t2,
                        A2, lf);                                                              // A2
     return hipGetLastError();
 }
 
 hipError_t soft_argmin(const SoftBuffers& s, int B, int W, int H, int D, const float* A2,
                        const float* theta, float* dhat, float* lse, hipStream_t st) {
-    SoftGeom g{s.arms, s.n1, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
     const size_t P = (size_t)W * H;
     hipLaunchKernelGGL(k_soft_argmin, dim3((unsigned)((P + 255) / 256), B), dim3(256), 0, st, g,
                        A2, theta, dhat, lse);
@@ -984,7 +1020,7 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
                          const float* theta, const float* dhat, const float* lse,
                          const float* gdhat, float* t1, float* t2, double* partAC,
                          double* partT, float* grad, hipStream_t st) {
-    SoftGeom g{s.arms, s.n1, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const dim3 gr((nrows + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave));
@@ -995,12 +1031,9 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_soft_seed_adj, gr, dim3(64 * kRowWaves), kRowWaves * la, st, g, A2, theta,
                        dhat, lse, gdhat, t2, partT, la);                 // G_E2, T-gradient terms
-    const dim3 gv((W + kSoftCols - 1) / kSoftCols, B * D);
-    hipLaunchKernelGGL(k_soft_vsa<true>, gv, dim3(kSoftCols), 0, st, g, t2, s.n1, t1);  // G_a1/N1
-    hipLaunchKernelGGL(k_soft_vsa<false>, gv, dim3(kSoftCols), 0, st, g, t1,
-                       (const float*)nullptr, t2);                                    // G_E1
+    launch_vv<true>(g, t2, t1, st);                                   // G_E1
     hipLaunchKernelGGL(k_soft_hgrad, gr, dim3(64 * kRowWaves), kTabLds + kRowWaves * lg, st, g,
-                       im, t2, partAC, lg);                                // G_E1 . H dc/dlambda
+                       im, t1, partAC, lg);                                // G_E1 . H dc/dlambda
     double* blk = partT + (size_t)nrows;  // kRedBlocks x 3 after the row partials
     hipLaunchKernelGGL(k_soft_reduce1, dim3(kRedBlocks), dim3(256), 0, st, partAC,
                        (size_t)nrows, partT, (size_t)nrows, blk);
