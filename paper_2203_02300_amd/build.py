@@ -30,11 +30,15 @@ FLAGS = [
 # independent chains of its two slices: the 1280x720, D = 128 frame takes
 # 0.782 ms with it and 0.889 ms with the default one, with the same results
 # bit for bit.  The WTA and the other batched work-list kernels are a little
-# slower under it, so it is not global.
+# slower under it, so it is not global.  The soft path's matrix products read
+# their accumulators with vector instructions right away: kept in vector
+# registers instead of accumulation registers they save a move per output (the
+# gradient row pass of 8 640x480 pairs, D = 64: 0.47 instead of 0.49 ms).
 _MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 FILE_FLAGS = {
     "k_aggregate.hip": _MAX_ILP,
     "k_batch_agg.hip": _MAX_ILP,
+    "k_soft.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

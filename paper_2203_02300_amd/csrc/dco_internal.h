@@ -292,7 +292,7 @@ hipError_t launch_lrcheck(const int16_t* dL, const float* deltaL, const int16_t*
 
 // k_soft.hip
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, uint32_t* vrec, float* rn1, float* n2, hipStream_t st);
+                        int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2, hipStream_t st);
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, hipStream_t st);
 hipError_t soft_argmin(const SoftBuffers& s, int B, int W, int H, int D, const float* A2,

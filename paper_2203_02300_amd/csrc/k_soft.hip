@@ -6,9 +6,10 @@
 //   E1 = row range sum of c       a1 = (column range sum of E1) / N1     (Eq. 2, stage 1)
 //   E2 = column range sum of a1   A2 = (row range sum of E2) / N2         (Eq. 2, stage 2)
 //   dhat = sum_d d softmax_d(-A2 / T),  lse = log sum_d exp(-A2 / T)
-// Every range sum is a difference of two FP64 prefix sums (along the row, or
-// running down the column), so it is within one FP32 rounding of the exact
-// sum of its FP32 terms.  Every sum runs in a fixed order, so results are
+// The range sums of E1 are exact sums of fixed-point costs on the matrix cores,
+// the others differences of two FP64 prefix sums (along the row, or running
+// down the column), so each is within one FP32 rounding of the exact sum of its
+// FP32 terms.  Every sum runs in a fixed order, so results are
 // bit-reproducible.
 //
 // Backward, given g = dLoss/d dhat:
@@ -28,9 +29,12 @@
 // to its own column in program order.
 //
 // Layout: volumes are B x D x H x W float in handle scratch; arms and the
-// packed pixels (census, RGB, L_min) are per pair B x H x W.  Row passes run
-// one wavefront per image row with its FP64 prefix in LDS; column passes one
-// thread per column, streaming down the rows with a ring of FP64 sums in LDS.
+// packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost passes
+// run one wavefront per image row and 16 disparities (k_soft_mrow), the other
+// row passes one wavefront per image row with its FP64 prefix in LDS; the
+// column pass runs one thread per column, streaming down the rows with two
+// rings of FP64 sums in LDS (k_soft_vv).
+#include <algorithm>
 #include <type_traits>
 
 #include "dco_internal.h"
@@ -51,7 +55,22 @@ __device__ inline int arm(uint32_t a, int k) { return (a >> (8 * k)) & 0xff; }
 // Tables of Eq. 1 for the current theta, and their lambda derivatives:
 // tab[0..765] = 1 - exp(-(s/3)/lambda_AD),   tab[768..1533] = d/dlambda_AD
 // tab[1536..1600] = 1 - exp(-h/lambda_c),    tab[1664..1728] = d/dlambda_c
-__global__ void k_soft_tables(const float* __restrict__ theta, float* __restrict__ tab) {
+// tab[kTabScale + 0, 2, 4]  = fixed-point scales 2^k of c and of its two derivatives
+// (k_soft_mrow), + 1, 3, 5 = 2^-k.  c is alpha A + (1 - alpha) C and |A|, |C| grow
+// with x; |d/dlambda| grows with x up to lambda > 0 and falls beyond.  A scale
+// of no finite bound is 0 and its inverse NaN, so the results are NaN.
+constexpr int kTabScale = 1744;
+
+__device__ inline void put_scale(float bound, float* out) {
+    const bool ok = bound < 1e25f;  // false for NaN
+    // bound <= 1.001 * 2^(e + 1): the largest |q| stays far below 2^31 - 2^23
+    const int e = bound > 1e-25f ? ilogbf(0.999f * bound) : -84;
+    out[0] = ok ? ldexpf(1.0f, 29 - e) : 0.0f;
+    out[1] = ok ? ldexpf(1.0f, e - 29) : __builtin_nanf("");
+}
+
+__global__ void k_soft_tables(const float* __restrict__ theta, const float* __restrict__ alpha,
+                              float* __restrict__ tab) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const float la = theta[0], lc = theta[1];
     if (i < 766) {
@@ -64,6 +83,19 @@ __global__ void k_soft_tables(const float* __restrict__ theta, float* __restrict
         const float e = expf(-(float)h / lc);
         tab[1536 + h] = -expm1f(-(float)h / lc);
         tab[1664 + h] = -e * (float)h / (lc * lc);
+    } else if (i >= 896 && i < 899) {
+        const float A = fabsf(expm1f(-255.0f / la)), C = fabsf(expm1f(-64.0f / lc));
+        const float xa = la > 0.0f && la < 255.0f ? la : 255.0f;
+        const float xc = lc > 0.0f && lc < 64.0f ? lc : 64.0f;
+        float b = (0.0f / la + 0.0f / lc) * 0.0f;  // NaN where a table is (lambda = 0)
+        for (int L = 0; L <= kLMax; ++L) {
+            const float al = fabsf(alpha[L]), be = fabsf(1.0f - alpha[L]);
+            const float v = i == 896 ? al * A + be * C
+                          : i == 897 ? al * (expf(-xa / la) * xa / (la * la))
+                                     : be * (expf(-xc / lc) * xc / (lc * lc));
+            b = v > b || v != v ? v : b;  // keeps a NaN
+        }
+        put_scale(b, tab + kTabScale + 2 * (i - 896));
     }
 }
 
@@ -119,41 +151,12 @@ __global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, uint32_t* __res
     n2[i] = (float)s2;
 }
 
-// Eq. 1 tables of the current theta in LDS: the k_soft_tables layout, then
-// alpha_L for L = 0 .. kLMax.
-constexpr int kTabFloats = 1792;
-constexpr size_t kTabLds = (kTabFloats + 32) * sizeof(float);
-
 struct SoftImg {
     const uint4* pixL;   // B x H x W packed pixels: census lo, census hi,
     const uint4* pixR;   //   RGB, 8 L_min
     const float* alpha;  // alpha_L, L = 0..kLMax
     const float* tab;    // k_soft_tables output
 };
-
-__device__ inline void load_tables(const SoftImg& im, float* lds) {
-    for (int i = threadIdx.x; i < kTabFloats; i += blockDim.x) lds[i] = im.tab[i];
-    if (threadIdx.x <= kLMax) lds[kTabFloats + threadIdx.x] = im.alpha[threadIdx.x];
-    __syncthreads();
-}
-
-// Raw cost c of Eq. 1 for reference pixel a and partner pixel b (and, with
-// kDeriv, its lambda_AD and lambda_census derivatives); c = 1 and zero
-// derivatives when the partner lies outside the image.
-template <bool kDeriv>
-__device__ inline void cost_px(uint4 a, uint4 b, bool inside, const float* tab, float& c,
-                               float& dca, float& dcc) {
-    const uint32_t s = __builtin_amdgcn_sad_u8(a.z, b.z, 0u);
-    const int h = __popcll(((uint64_t)a.y << 32 | a.x) ^ ((uint64_t)b.y << 32 | b.x));
-    const float al = tab[kTabFloats + (a.w >> 3)];
-    const float v = al * tab[s] + (1.0f - al) * tab[1536 + h];
-    c = inside ? v : 1.0f;
-    if (kDeriv) {
-        const float va = al * tab[768 + s], vc = (1.0f - al) * tab[1664 + h];
-        dca = inside ? va : 0.0f;
-        dcc = inside ? vc : 0.0f;
-    }
-}
 
 // Row passes: one wavefront per image row, kRowWaves wavefronts per
 // workgroup, each with its own LDS slice (no workgroup barriers after the
@@ -275,60 +278,17 @@ __device__ inline double chunk_prefix(const float (&v)[4], int x, int W, double 
     return carry + readlane_f64(inc, 63);
 }
 
-// Moves the chunk's values c (lane `lane` holding columns x0 + 64 j + lane)
-// through the wavefront's LDS stage into the four-consecutive-columns layout.
-__device__ inline void restage(const float (&c)[4], float* stage, float (&v)[4]) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) stage[64 * j + lane] = c[j];
-    __builtin_amdgcn_wave_barrier();
-    const float4 q = *reinterpret_cast<const float4*>(stage + 4 * lane);
-    v[0] = q.x;
-    v[1] = q.y;
-    v[2] = q.z;
-    v[3] = q.w;
-    __builtin_amdgcn_wave_barrier();  // the stage is rewritten next
-}
-
 // FP64 prefixes of the wavefront's row (W <= 2048): P[0] = 0 and
-// P[x + 1] = v(0) + ... + v(x), where v is (kCost) the raw cost of Eq. 1 of
-// row y for disparity d, or (kDeriv) its lambda_AD derivative, with the
-// lambda_census derivative prefixed into P2, or else the row of `src`.  Raw
-// costs are computed with lane `lane` on columns x0 + 64 j + lane (coalesced
-// pixel loads) and restaged through `stage` (kPreChunk floats); `src` is read
-// directly in the four-column layout.  Fixed order, bit-reproducible.
-template <bool kCost, bool kDeriv>
-__device__ inline void prefix_row(const uint4* pl, const uint4* pr, const float* src, int W, int d,
-                                  const float* tab, float* stage, double* P, double* P2) {
+// P[x + 1] = src(0) + ... + src(x).  Fixed order, bit-reproducible.
+__device__ inline void prefix_row(const float* src, int W, double* P) {
     const int lane = threadIdx.x & 63;
-    double carry = 0.0, carry2 = 0.0;
-    if (lane == 0) {
-        P[0] = 0.0;
-        if (kDeriv) P2[0] = 0.0;
-    }
+    double carry = 0.0;
+    if (lane == 0) P[0] = 0.0;
     const bool vec = (W & 3) == 0;  // 16-byte aligned rows
     for (int x0 = 0; x0 < W; x0 += kPreChunk) {
         const int x = x0 + 4 * lane;
-        float v[4], v2[4];
-        if (kCost) {
-            uint4 a[4], b[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int xc = min(x0 + 64 * j + lane, W - 1);
-                a[j] = pl[xc];
-                b[j] = pr[max(xc - d, 0)];
-            }
-            float c[4], c2[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float cv, dca, dcc;
-                cost_px<kDeriv>(a[j], b[j], x0 + 64 * j + lane - d >= 0, tab, cv, dca, dcc);
-                c[j] = kDeriv ? dca : cv;
-                c2[j] = dcc;
-            }
-            restage(c, stage, v);
-            if (kDeriv) restage(c2, stage, v2);
-        } else if (vec) {
+        float v[4];
+        if (vec) {
             const float4 q = *reinterpret_cast<const float4*>(src + min(x, W - 4));
             v[0] = q.x;
             v[1] = q.y;
@@ -339,27 +299,19 @@ __device__ inline void prefix_row(const uint4* pl, const uint4* pr, const float*
             for (int k = 0; k < 4; ++k) v[k] = src[min(x + k, W - 1)];
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            v[k] = x + k < W ? v[k] : 0.0f;
-            if (kDeriv) v2[k] = x + k < W ? v2[k] : 0.0f;
-        }
+        for (int k = 0; k < 4; ++k) v[k] = x + k < W ? v[k] : 0.0f;
         carry = chunk_prefix(v, x, W, carry, P);
-        if (kDeriv) carry2 = chunk_prefix(v2, x, W, carry2, P2);
     }
     __builtin_amdgcn_wave_barrier();
 }
 
-// Bytes of dynamic LDS per wavefront: forward (one FP64 prefix, and the
-// stage when it computes raw costs), gradient (two and the stage) and
-// adjoint (64-bit difference array, the row, its arms).
+// Bytes of dynamic LDS per wavefront: forward (one FP64 prefix) and adjoint
+// (64-bit difference array, the row, its arms).
 __host__ __device__ inline size_t row_bytes(int W) { return ((size_t)W * 4 + 15) / 16 * 16; }
 __host__ __device__ inline size_t prefix_bytes(int W) {
     return ((size_t)(W + 1) * 8 + 15) / 16 * 16;
 }
-constexpr size_t kStageBytes = kPreChunk * sizeof(float);
 inline size_t row_lds_fwd(int W) { return prefix_bytes(W); }
-inline size_t row_lds_cost(int W) { return prefix_bytes(W) + kStageBytes; }
-inline size_t row_lds_grad(int W) { return 2 * prefix_bytes(W) + kStageBytes; }
 inline size_t row_lds_adj(int W) {
     return ((size_t)(W + 1) * 8 + 15) / 16 * 16 + row_bytes(W) + ((size_t)W * 2 + 15) / 16 * 16;
 }
@@ -373,35 +325,24 @@ inline hipError_t allow_lds(const void* kernel, size_t bytes) {
                              : hipSuccess;
 }
 
-// Forward row passes.  kCost: E1(x) = sum of the raw cost c over
-// [x - l, x + r] (Eq. 1 computed here); else A2(x) = (sum of E2 over the
-// range) / N2(x).
-template <bool kCost>
-__global__ __launch_bounds__(64 * kRowWaves) void k_soft_hrow(SoftGeom g, SoftImg im,
+// Second forward row pass: A2(x) = (sum of E2 over [x - l, x + r]) / N2(x).
+__global__ __launch_bounds__(64 * kRowWaves) void k_soft_hrow(SoftGeom g,
                                                               const float* __restrict__ in,
                                                               float* __restrict__ out,
                                                               size_t lds_wave) {
     extern __shared__ __align__(16) unsigned char dyn[];
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63,
               W = g.W;
-    float* tab = reinterpret_cast<float*>(dyn);
-    double* Pf = reinterpret_cast<double*>(dyn + (kCost ? kTabLds : 0) + w * lds_wave);
-    float* stage = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(Pf) + prefix_bytes(W));
-    if (kCost) load_tables(im, tab);
+    double* Pf = reinterpret_cast<double*>(dyn + w * lds_wave);
     const size_t P = (size_t)W * g.H;
     const int nrows = g.B * g.D * g.H;
-    // raw costs: the workgroups of one image row on one XCD (its pixels are
-    // the shared input); the other passes stream volumes and keep the
-    // round-robin order
-    const int blk = kCost ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-    const int r0 = (blk * kRowWaves + w) * kRowsPerWave;
+    const int r0 = ((int)blockIdx.x * kRowWaves + w) * kRowsPerWave;
     for (int rid = r0; rid < min(nrows, r0 + kRowsPerWave); ++rid) {
         int b, d, y;
         row_of(rid, g.D, g.H, b, d, y);
         const size_t base = ((size_t)b * g.D + d) * P + (size_t)y * W;
         const size_t pix = b * P + (size_t)y * W;
-        prefix_row<kCost, false>(im.pixL + pix, im.pixR + pix, in + base, W, d, tab, stage, Pf,
-                                 nullptr);
+        prefix_row(in + base, W, Pf);
         // the row's arrays through row pointers (uniform), indexed by column
         const uint32_t* __restrict__ ar = g.arms + pix;
         const float* __restrict__ nr = g.n2 + pix;
@@ -414,14 +355,14 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_soft_hrow(SoftGeom g, SoftIm
             for (int j = 0; j < NB; ++j) {
                 const int xc = min(x0 + 64 * j + lane, W - 1);
                 a[j] = ar[xc];
-                n[j] = kCost ? 1.0f : nr[xc];
+                n[j] = nr[xc];
             }
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 const int x = x0 + 64 * j + lane;
                 if (x < W) {
                     const float v = (float)(Pf[x + arm(a[j], 1) + 1] - Pf[x - arm(a[j], 0)]);
-                    orow[x] = kCost ? v : v * __builtin_amdgcn_rcpf(n[j]);
+                    orow[x] = v * __builtin_amdgcn_rcpf(n[j]);
                 }
             }
         });
@@ -429,65 +370,321 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_soft_hrow(SoftGeom g, SoftIm
     }
 }
 
-// Gradient row pass.  With G = dLoss/dE1 and E1 = H c (H the row range-sum
-// operator), dLoss/dlambda = sum_p (H^T G)(p) dc/dlambda(p)
-//                          = sum_x G(x) (H dc/dlambda)(x):
-// the range sums of the two cost derivatives, dotted with G, give one FP64
-// pair per row (no adjoint volume is formed).
-__global__ __launch_bounds__(64 * kRowWaves) void k_soft_hgrad(SoftGeom g, SoftImg im,
-                                                               const float* __restrict__ G,
-                                                               double* __restrict__ part,
-                                                               size_t lds_wave) {
-    extern __shared__ __align__(16) unsigned char dyn[];
-    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63,
-              W = g.W;
-    float* tab = reinterpret_cast<float*>(dyn);
-    unsigned char* mine = dyn + kTabLds + w * lds_wave;
-    double* Pa = reinterpret_cast<double*>(mine);
-    double* Pc = reinterpret_cast<double*>(mine + prefix_bytes(W));
-    float* stage = reinterpret_cast<float*>(mine + 2 * prefix_bytes(W));
-    load_tables(im, tab);
-    const size_t P = (size_t)W * g.H;
-    const int nrows = g.B * g.D * g.H;
-    const int r0 = (blockIdx.x * kRowWaves + w) * kRowsPerWave;
-    for (int rid = r0; rid < min(nrows, r0 + kRowsPerWave); ++rid) {
-        int b, d, y;
-        row_of(rid, g.D, g.H, b, d, y);
-        const size_t base = ((size_t)b * g.D + d) * P + (size_t)y * W;
-        const size_t pix = b * P + (size_t)y * W;
-        prefix_row<true, true>(im.pixL + pix, im.pixR + pix, nullptr, W, d, tab, stage, Pa, Pc);
+// Row sums of the costs (and of their lambda derivatives) on the matrix cores.
+// Along one image row E1(x, d) = sum_p [x - l <= p <= x + r] c(p, d): a product
+// of a banded 0/1 matrix, which the disparities share, with the costs.  The
+// costs go in as 32-bit fixed point q = c 2^k, split into four signed bytes
+// (balanced digits: q = sum_i 256^i b_i), so four i8 products with 32-bit
+// accumulation give the exact sum of the q, and the output is that sum rounded
+// once to FP32.  2^k puts the largest |c| that theta and alpha allow at 2^30
+// (k_soft_tables): a cost is exact down to 2^-6 of it and within 2^-30 of it
+// below, where the FP32 sum of a range is no finer.  Costs of partners outside
+// the image are 1 by definition: they enter as 0 and are counted.
+//
+// A workgroup takes one image row (or one of `segs` parts of it), a wavefront
+// 16 of its disparities (in rounds where there are more than 64), and they walk
+// the row together in blocks of 64 columns:
+//   - bands: the 0/1 operand of the block, which all the row's wavefronts use,
+//     each building its share: a lane's 16 columns are the bits of one
+//     interval, spread to bytes;
+//   - costs: lane = column, 16 disparities in turn, so a reference pixel is
+//     read once per block, and the partners are 80 consecutive pixels, in LDS;
+//   - the lanes' q go through LDS (16 x 68 words, conflict-free both ways) into
+//     the operand layout: lane = (disparity lane & 15, columns 16 (lane >> 4) ..
+//     + 15), a byte per column;
+//   - after block [X, X + 64) the 16-column outputs at X - 32, X - 16, X and
+//     X + 16 have all their columns (x - 17 .. x + 32) in this block and the one
+//     before, whose digits stay in registers: two products per digit and output;
+//   - E1 goes back through LDS to be stored as 256 contiguous bytes per
+//     disparity (64-byte pieces of 16 planes: 0.35 ms instead of 0.30 then).
+//
+// Measured at 8 pairs of 640 x 480, D = 64: E1 0.25 ms (writes 0.63 GB; vector
+// issue about 0.15 ms), the gradient 0.32 ms (reads 0.63 GB; issue bound, 64 %
+// vector busy).  As FP64 prefix sums per row and disparity, two table passes,
+// four LDS scans and eight gathers per 256 columns, they took 0.35 and 0.58 ms.
+// Steps: 32 or 64 disparities per wavefront 0.35 / 0.49 and 0.44 / 0.74 ms (too
+// few wavefronts), 16 with its own bands 0.32 / 0.40, shared bands 0.35 / 0.32,
+// rows stored whole 0.30, partners in LDS and a block ahead 0.25.  At one pair
+// of 320 x 240, D = 32 the split rows take 15 us, was 18.
+constexpr int kMxWaves = 4;          // most wavefronts per workgroup
+constexpr int kMxSlots = 16 * 256;   // wavefronts of it the device holds at once
+constexpr int kMxStride = 68;        // words per disparity of the stage
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4), may_alias));
+typedef uint32_t v4u __attribute__((ext_vector_type(4), may_alias));
+
+// Bytes 0 / 1 of the columns pb .. pb + 15 that lie in [lo, hi).
+__device__ inline v4i band_bytes(int lo, int hi, int pb) {
+    const int a = min(max(lo - pb, 0), 16), e = min(max(hi - pb, 0), 16);
+    const uint32_t bits = (1u << e) - (1u << a);
+    v4i r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        r[i] = (int)((bits >> (4 * i) & 15u) * 0x00204081u & 0x01010101u);
+    return r;
+}
+
+// The lane's 16 columns of disparity lane & 15, as digit planes.
+__device__ inline void digit_planes(const uint32_t* stage, v4i (&b)[4]) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t* s = stage + (lane & 15) * kMxStride + 16 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const v4u w = *reinterpret_cast<const v4u*>(s + 4 * i);
+        const uint32_t t0 = __builtin_amdgcn_perm(w.y, w.x, 0x05010400u);
+        const uint32_t t1 = __builtin_amdgcn_perm(w.w, w.z, 0x05010400u);
+        const uint32_t t2 = __builtin_amdgcn_perm(w.y, w.x, 0x07030602u);
+        const uint32_t t3 = __builtin_amdgcn_perm(w.w, w.z, 0x07030602u);
+        b[0][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x05040100u);
+        b[1][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x07060302u);
+        b[2][i] = (int)__builtin_amdgcn_perm(t3, t2, 0x05040100u);
+        b[3][i] = (int)__builtin_amdgcn_perm(t3, t2, 0x07060302u);
+    }
+}
+
+// q (|q| <= 2^30) with its bytes as balanced digits.
+__device__ inline uint32_t balanced(float v) {
+    return ((uint32_t)(int)v + 0x00808080u) ^ 0x00808080u;
+}
+
+// Stores the stage's 16 x 64 outputs: disparities d0 .. d0 + 15, columns x0 ..
+// x0 + 63, those inside the volume only; `out` is row y of disparity 0, P a
+// plane.  256 contiguous bytes per disparity, and four disparities per store.
+__device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, size_t P, int d0,
+                                int D, int x0, int W) {
+    const int lane = threadIdx.x & 63;
+    if ((W & 3) == 0) {  // a lane's four columns are inside together, 16-byte aligned
+        const int c = 4 * (lane & 15), x = x0 + c;
+        v4f o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            o[j] = *reinterpret_cast<const v4f*>(stage + (4 * j + (lane >> 4)) * kMxStride + c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int d = d0 + 4 * j + (lane >> 4);
+            if (x >= 0 && x < W && d < D) *reinterpret_cast<v4f*>(out + d * P + x) = o[j];
+        }
+    } else {
+        const int x = x0 + lane;
+#pragma unroll 1  // hoisted, its 16 row addresses would cost the other path its registers
+        for (int j = 0; j < 16; ++j) {
+            const float o = __builtin_bit_cast(float, stage[j * kMxStride + lane]);
+            if (x >= 0 && x < W && d0 + j < D) out[(d0 + j) * P + x] = o;
+        }
+    }
+}
+
+template <bool kDeriv>
+__global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, SoftImg im,
+                                                                const float* __restrict__ G,
+                                                                float* __restrict__ out,
+                                                                double* __restrict__ part,
+                                                                int seg_its) {
+    constexpr int NQ = kDeriv ? 2 : 1;
+    // 40 KB in all: four workgroups per CU
+    constexpr int kCenTab = 766;
+    __shared__ v4i bands[2][8][64];
+    __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
+    __shared__ uint2 cen[kMxWaves][80];
+    __shared__ uint32_t rgb[kMxWaves][80];
+    __shared__ float tab[kCenTab + 65];
+    const int nt = blockDim.x, nw = nt >> 6;
+    {
+        const float* t = im.tab + (kDeriv ? 768 : 0);
+        const float* c = im.tab + (kDeriv ? 1664 : 1536);
+        const float ka = im.tab[kTabScale + (kDeriv ? 2 : 0)];
+        const float kc = im.tab[kTabScale + (kDeriv ? 4 : 0)];
+        for (int i = threadIdx.x; i < 766; i += nt) tab[i] = t[i] * ka;
+        for (int i = threadIdx.x; i < 65; i += nt) tab[kCenTab + i] = c[i] * kc;
+        __syncthreads();
+    }
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = lane & 15, kg = lane >> 4;
+    const int W = g.W, D = g.D, ng = (D + 15) >> 4;
+    // the workgroups of one image row on one XCD: its pixels are the shared input
+    const int row = xcd_block(blockIdx.x, gridDim.x), y = row % g.H, b = row / g.H;
+    const int it0 = blockIdx.y * seg_its, it1 = min(it0 + seg_its, (W + 95) >> 6);
+    const size_t P = (size_t)W * g.H, pix = (size_t)b * P + (size_t)y * W;
+    const uint4* pl = im.pixL + pix;
+    const uint4* pr = im.pixR + pix;
+    const uint32_t* ar = g.arms + pix;
+    const size_t vol = ((size_t)b * D) * P + (size_t)y * W;
+    uint32_t* stage = stages[w];
+    const float inv0 = im.tab[kTabScale + (kDeriv ? 3 : 1)];
+    int par = 0;
+    for (int g0 = 0; g0 < ng; g0 += nw) {
+        const int grp = g0 + w, d0 = 16 * grp, d = d0 + n;
+        const bool active = grp < ng;
+        const size_t orow = vol + (size_t)min(d, D - 1) * P;
+        v4i bp[NQ][4];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bp[q][i] = v4i{0, 0, 0, 0};
         double sa = 0.0, sc = 0.0;
-        const uint32_t* __restrict__ ar = g.arms + pix;
-        const float* __restrict__ grow = G + base;
-        over_row(W, [&](auto nb, int x0) {
-            constexpr int NB = decltype(nb)::value;
-            uint32_t a[NB];
-            float gv[NB];
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int xc = min(x0 + 64 * j + lane, W - 1);
-                a[j] = ar[xc];
-                gv[j] = grow[xc];
+        // Partners of a block's 16 disparities: the 64 pixels from column X - d0 on
+        // and the last 16 of the 64 before, through LDS (entry 16 + lane - j holds
+        // column X + lane - (d0 + j)).  They and the reference pixels are loaded a
+        // block ahead.
+        const auto pixel = [&](int x) {
+            const uint4* q = pr + min(max(x - d0, 0), W - 1);
+            return uint3{q->x, q->y, q->z};
+        };
+        uint3 ro{}, rc{};
+        uint4 pn{};
+        if (active) {
+            const int X = 64 * max(it0 - 1, 0);
+            ro = pixel(X - 64 + lane);
+            rc = pixel(X + lane);
+            pn = pl[min(X + lane, W - 1)];
+        }
+        // the block before a segment's first only gives its digits
+        for (int it = max(it0 - 1, 0); it < it1; ++it, par ^= 1) {
+            const int X = it << 6;
+            // bands of the four 16-column outputs over the block before and this one
+            for (int c = w; c < 8; c += nw) {
+                const int x = X - 32 + 16 * (c >> 1) + n;
+                const uint32_t a = ar[min(max(x, 0), W - 1)];
+                bands[par][c][lane] = band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
+                                                 X - 64 + 64 * (c & 1) + 16 * kg);
             }
+            uint32_t q2[16];
+            if (active && X < W) {
+                cen[w][16 + lane] = uint2{rc.x, rc.y};
+                rgb[w][16 + lane] = rc.z;
+                if (lane >= 48) {
+                    cen[w][lane - 48] = uint2{ro.x, ro.y};
+                    rgb[w][lane - 48] = ro.z;
+                }
+                const uint4 pa = pn;
+                ro = rc;
+                rc = pixel(X + 64 + lane);
+                pn = pl[min(X + 64 + lane, W - 1)];
+                __builtin_amdgcn_wave_barrier();
+                const float al = im.alpha[pa.w >> 3], be = 1.0f - al;
+                const auto costs = [&](auto all_in) {
+                    constexpr bool kIn = decltype(all_in)::value;
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int x = x0 + 64 * j + lane;
-                if (x < W) {
-                    const int hi = x + arm(a[j], 1) + 1, lo = x - arm(a[j], 0);
-                    sa += (double)gv[j] * (Pa[hi] - Pa[lo]);
-                    sc += (double)gv[j] * (Pc[hi] - Pc[lo]);
+                    for (int j = 0; j < 16; ++j) {
+                        const uint2 cb = cen[w][16 + lane - j];
+                        const uint32_t s = __builtin_amdgcn_sad_u8(pa.z, rgb[w][16 + lane - j], 0u);
+                        const int hm = __popc(pa.x ^ cb.x) + __popc(pa.y ^ cb.y);
+                        const float ta = al * tab[s], tc = be * tab[kCenTab + hm];
+                        const bool in = kIn || X + lane - d0 - j >= 0;
+                        stage[j * kMxStride + lane] =
+                            balanced(in ? (kDeriv ? ta : ta + tc) : 0.0f);
+                        if (kDeriv) q2[j] = balanced(in ? tc : 0.0f);
+                    }
+                };
+                if (X >= d0 + 15)  // every partner of the block is in the image
+                    costs(std::true_type{});
+                else
+                    costs(std::false_type{});
+                __builtin_amdgcn_wave_barrier();
+            }
+            float gv[kDeriv ? 4 : 1][4];
+            if (kDeriv && active && it >= it0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int x4 = X - 32 + 16 * i + 4 * kg;
+                    const bool row_in = d < D && x4 >= 0;
+                    if (row_in && x4 + 4 <= W) {
+                        __builtin_memcpy(gv[i], G + orow + x4, 16);
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            gv[i][r] = row_in && x4 + r < W ? G[orow + min(x4 + r, W - 1)] : 0.0f;
+                    }
                 }
             }
-        });
-        for (int off = 32; off > 0; off >>= 1) {  // fixed-order wavefront reduction
-            sa += __shfl_down(sa, off, 64);
-            sc += __shfl_down(sc, off, 64);
+            __syncthreads();  // the bands; the buffer's next writers pass the next one first
+            if (!active) continue;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                v4i bc[4] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
+                if (X < W) {
+                    if (q > 0) {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) stage[j * kMxStride + lane] = q2[j];
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                    digit_planes(stage, bc);
+                    __builtin_amdgcn_wave_barrier();
+                }
+                if (it >= it0) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int xb = X - 32 + 16 * i, x4 = xb + 4 * kg;
+                        if (xb < 0 || xb >= W) continue;
+                        const v4i b0 = bands[par][2 * i][lane], b1 = bands[par][2 * i + 1][lane];
+                        v4i acc[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                                b0, bp[q][k], v4i{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b1, bc[k], acc[k], 0, 0,
+                                                                           0);
+                        // |lo|, |hi| < 2^21: the conversions are exact
+                        int lo[4], hi[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            lo[r] = acc[0][r] + (acc[1][r] << 8);
+                            hi[r] = acc[2][r] + (acc[3][r] << 8);
+                        }
+                        if constexpr (kDeriv) {
+                            double& t = q ? sc : sa;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                t = __builtin_fma(
+                                    (double)gv[i][r],
+                                    __builtin_fma((double)hi[r], 65536.0, (double)lo[r]), t);
+                        } else {
+                            float o[4];
+                            if (xb - kLMax >= d0 + 15) {
+#pragma unroll
+                                for (int r = 0; r < 4; ++r)
+                                    o[r] = __builtin_fmaf((float)hi[r], 65536.0f * inv0,
+                                                          (float)lo[r] * inv0);
+                            } else {  // ranges may hold columns left of d, where c = 1
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) {
+                                    const int x = x4 + r;
+                                    const uint32_t a = ar[min(x, W - 1)];
+                                    const int len = arm(a, 0) + arm(a, 1) + 1;
+                                    const int cnt = min(max(d - (x - arm(a, 0)), 0), len);
+                                    const double e =
+                                        __builtin_fma((double)hi[r], 65536.0, (double)lo[r]);
+                                    o[r] = (float)__builtin_fma(e, (double)inv0, (double)cnt);
+                                }
+                            }
+                            // to the stage (free since digit_planes), one row per d
+                            *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
+                                v4f{o[0], o[1], o[2], o[3]};
+                        }
+                    }
+                    if (!kDeriv) {
+                        __builtin_amdgcn_wave_barrier();
+                        put_rows(stage, out + vol, P, d0, D, X - 32, W);
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bp[q][i] = bc[i];
+            }
         }
-        if (lane == 0) {
-            part[2 * (size_t)rid] = sa;
-            part[2 * (size_t)rid + 1] = sc;
+        if (kDeriv && active) {
+            for (int off = 32; off > 0; off >>= 1) {  // fixed-order wavefront reduction
+                sa += __shfl_down(sa, off, 64);
+                sc += __shfl_down(sc, off, 64);
+            }
+            if (lane == 0) {
+                double* t = part + 2 * (((size_t)row * gridDim.y + blockIdx.y) * ng + grp);
+                t[0] = sa * (double)inv0;
+                t[1] = sc * (double)im.tab[kTabScale + 5];
+            }
         }
-        __builtin_amdgcn_wave_barrier();  // Pa, Pc are rewritten for the next row
     }
 }
 
@@ -976,9 +1173,26 @@ static void launch_vv(const SoftGeom& g, const float* in, float* out, hipStream_
                        dim3(kSoftCols), 0, st, g, in, out, seg);
 }
 
+// Row sums of the costs into `out`, or their gradient sums into `part`; returns
+// the number of pairs in `part`.
+template <bool kDeriv>
+static int launch_mrow(const SoftGeom& g, const SoftImg& im, const float* G, float* out,
+                       double* part, hipStream_t st) {
+    const int ng = (g.D + 15) / 16, nw = std::min(ng, kMxWaves), rows = g.B * g.H;
+    const int its = (g.W + 95) / 64;
+    // rows split (each part computes one more block) while they leave the
+    // device's slots empty; the partial sums have room for D pairs per row
+    const int most = std::max(1, std::min({its / 2, g.D / ng, kMxSlots / (rows * nw)}));
+    const int seg = (its + most - 1) / most, segs = (its + seg - 1) / seg;
+    hipLaunchKernelGGL(k_soft_mrow<kDeriv>, dim3(rows, segs), dim3(64 * nw), 0, st, g, im, G, out,
+                       part, seg);
+    return rows * segs * ng;
+}
+
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, uint32_t* vrec, float* rn1, float* n2, hipStream_t st) {
-    hipLaunchKernelGGL(k_soft_tables, dim3(4), dim3(256), 0, st, theta, tab);
+                        int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2,
+                        hipStream_t st) {
+    hipLaunchKernelGGL(k_soft_tables, dim3(4), dim3(256), 0, st, theta, alpha, tab);
     SoftGeom g{arms, nullptr, nullptr, nullptr, B, W, H, D};
     hipLaunchKernelGGL(k_soft_counts, dim3((W + kCntTW - 1) / kCntTW, (H + kCntTH - 1) / kCntTH, B),
                        dim3(256), 0, st, g, vrec, rn1, n2);
@@ -992,17 +1206,13 @@ hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, floa
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const dim3 gr((nrows + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave));
-    const size_t lf = row_lds_fwd(W), lc = row_lds_cost(W);
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_soft_hrow<true>),
-                             kTabLds + kRowWaves * lc);
-    if (e == hipSuccess)
-        e = allow_lds(reinterpret_cast<const void*>(&k_soft_hrow<false>), kRowWaves * lf);
+    const size_t lf = row_lds_fwd(W);
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_soft_hrow), kRowWaves * lf);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_soft_hrow<true>, gr, dim3(64 * kRowWaves), kTabLds + kRowWaves * lc, st, g,
-                       im, (const float*)nullptr, t1, lc);                                   // E1
+    launch_mrow<false>(g, im, nullptr, t1, nullptr, st);                                     // E1
     launch_vv<false>(g, t1, t2, st);                                                         // E2
-    hipLaunchKernelGGL(k_soft_hrow<false>, gr, dim3(64 * kRowWaves), kRowWaves * lf, st, g, im, t2,
-                       A2, lf);                                                              // A2
+    hipLaunchKernelGGL(k_soft_hrow, gr, dim3(64 * kRowWaves), kRowWaves * lf, st, g, t2, A2,
+                       lf);                                                                  // A2
     return hipGetLastError();
 }
 
@@ -1024,19 +1234,17 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const dim3 gr((nrows + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave));
-    const size_t la = row_lds_adj(W), lg = row_lds_grad(W);
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_soft_seed_adj), kRowWaves * la);
-    if (e == hipSuccess)
-        e = allow_lds(reinterpret_cast<const void*>(&k_soft_hgrad), kTabLds + kRowWaves * lg);
+    const size_t la = row_lds_adj(W);
+    const hipError_t e =
+        allow_lds(reinterpret_cast<const void*>(&k_soft_seed_adj), kRowWaves * la);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_soft_seed_adj, gr, dim3(64 * kRowWaves), kRowWaves * la, st, g, A2, theta,
                        dhat, lse, gdhat, t2, partT, la);                 // G_E2, T-gradient terms
     launch_vv<true>(g, t2, t1, st);                                   // G_E1
-    hipLaunchKernelGGL(k_soft_hgrad, gr, dim3(64 * kRowWaves), kTabLds + kRowWaves * lg, st, g,
-                       im, t1, partAC, lg);                                // G_E1 . H dc/dlambda
+    const int nac = launch_mrow<true>(g, im, t1, nullptr, partAC, st);   // G_E1 . H dc/dlambda
     double* blk = partT + (size_t)nrows;  // kRedBlocks x 3 after the row partials
     hipLaunchKernelGGL(k_soft_reduce1, dim3(kRedBlocks), dim3(256), 0, st, partAC,
-                       (size_t)nrows, partT, (size_t)nrows, blk);
+                       (size_t)nac, partT, (size_t)nrows, blk);
     hipLaunchKernelGGL(k_soft_reduce2, dim3(1), dim3(256), 0, st, blk, grad);
     return hipGetLastError();
 }
