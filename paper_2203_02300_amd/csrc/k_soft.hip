@@ -15,24 +15,22 @@
 // Backward, given g = dLoss/d dhat:
 //   G_A2  = g w (dhat - d) / T,   dLoss/dT = sum g w (d - dhat) A2 / T^2
 // then the adjoint of each range sum: an output that summed a range hands its
-// adjoint back to every pixel of that range.  The first row adjoint scatters
-// each G(x) into a 64-bit fixed-point difference array over the row (integer
-// adds, so their order does not matter); column adjoints are FP64 difference
-// arrays streamed down each column by one thread.  The last row adjoint is
-// never formed: with
+// adjoint back to every pixel of that range.  The first row adjoint is an exact
+// product of fixed-point G with the transposed band (k_soft_madj); column
+// adjoints are FP64 difference arrays streamed down each column by one thread.
+// The last row adjoint is never formed: with
 // E1 = H c,  sum_p (H^T G)(p) dc/dlambda(p) = sum_x G(x) (H dc/dlambda)(x),
 // so the row range sums of the two cost derivatives are dotted with G:
 //   dLoss/dlambda_AD     = sum G_E1 . H (alpha d(1 - exp(-(s/3)/lambda_AD))/dlambda_AD)
 //   dLoss/dlambda_census = sum G_E1 . H ((1 - alpha) d(1 - exp(-h/lambda_census))/dlambda_census)
-// with fixed-order two-level reductions.  The only atomics are LDS adds whose
-// result does not depend on their order (integers), or that one thread makes
-// to its own column in program order.
+// with fixed-order two-level reductions.  The only atomics are LDS adds that one
+// thread makes to its own column in program order.
 //
 // Layout: volumes are B x D x H x W float in handle scratch; arms and the
-// packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost passes
-// run one wavefront per image row and 16 disparities (k_soft_mrow), the other
-// row passes one wavefront per image row with its FP64 prefix in LDS; the
-// column pass runs one thread per column, streaming down the rows with two
+// packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost and
+// adjoint row passes run one wavefront per image row and 16 disparities
+// (k_soft_mrow, k_soft_madj), the A2 row pass one per image row and disparity
+// with its FP64 prefix in LDS; the column pass runs one thread per column, streaming down the rows with two
 // rings of FP64 sums in LDS (k_soft_vv).
 #include <algorithm>
 #include <type_traits>
@@ -227,34 +225,6 @@ __device__ inline double wave_scan_f64(double v) {
     return v;
 }
 
-// The same scan and lane read on exact 64-bit integers.
-template <unsigned Ctrl, unsigned RowMask>
-__device__ inline long long dpp_i64(long long v) {
-    const uint64_t u = (uint64_t)v;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, Ctrl, RowMask,
-                                                              0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), Ctrl,
-                                                              RowMask, 0xf, false);
-    return (long long)((uint64_t)hi << 32 | lo);
-}
-
-__device__ inline long long wave_scan_i64(long long v) {
-    v += dpp_i64<0x111, 0xf>(v);
-    v += dpp_i64<0x112, 0xf>(v);
-    v += dpp_i64<0x114, 0xf>(v);
-    v += dpp_i64<0x118, 0xf>(v);
-    v += dpp_i64<0x142, 0xa>(v);
-    v += dpp_i64<0x143, 0xc>(v);
-    return v;
-}
-
-__device__ inline long long readlane_i64(long long v, int l) {
-    const uint64_t u = (uint64_t)v;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-    return (long long)((uint64_t)hi << 32 | lo);
-}
-
 // The prefix phase of a row pass works on 256-column chunks in which lane
 // `lane` owns the four consecutive columns x0 + 4 lane .. x0 + 4 lane + 3:
 // a lane prefixes its four values in FP64, one wavefront scan over the lane
@@ -305,16 +275,11 @@ __device__ inline void prefix_row(const float* src, int W, double* P) {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Bytes of dynamic LDS per wavefront: forward (one FP64 prefix) and adjoint
-// (64-bit difference array, the row, its arms).
-__host__ __device__ inline size_t row_bytes(int W) { return ((size_t)W * 4 + 15) / 16 * 16; }
+// Bytes of dynamic LDS per wavefront: one FP64 prefix.
 __host__ __device__ inline size_t prefix_bytes(int W) {
     return ((size_t)(W + 1) * 8 + 15) / 16 * 16;
 }
 inline size_t row_lds_fwd(int W) { return prefix_bytes(W); }
-inline size_t row_lds_adj(int W) {
-    return ((size_t)(W + 1) * 8 + 15) / 16 * 16 + row_bytes(W) + ((size_t)W * 2 + 15) / 16 * 16;
-}
 
 // Lets a kernel take `bytes` of dynamic LDS (above the default limit for
 // wide rows).
@@ -455,6 +420,7 @@ __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, 
     const int lane = threadIdx.x & 63;
     if ((W & 3) == 0) {  // a lane's four columns are inside together, 16-byte aligned
         const int c = 4 * (lane & 15), x = x0 + c;
+        asm volatile("" : "+s"(P));  // the row addresses are made here, not kept over the row
         v4f o[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -694,136 +660,231 @@ __device__ inline float exp_e(float x) { return __builtin_amdgcn_exp2f(x * 1.442
 
 // Backward seed and adjoint row pass.  Per pixel and disparity, with
 // w = softmax weight and g = dLoss/d dhat:
-//   G_A2 / N2 = g w (dhat - d) / (T N2),   dLoss/dT term = g w (d - dhat) A2 / T^2;
-// out = the adjoint of A2's row range sums applied to G_A2 / N2 (G_E2), and
-// the temperature terms of the row summed into one FP64 value per row.
-// The adjoint scatters each G(x) as +G at x - l(x) and -G after x + r(x)
-// into a difference array and prefix-sums it.  The array holds 64-bit
-// integers: G(x) 2^k rounded, with 2^k chosen from the row's largest |G| so
-// that no sum can overflow, so the scatter's LDS atomic adds give the same
-// bits in any order; the result is converted back with 2^-k.
-__global__ __launch_bounds__(64 * kRowWaves) void k_soft_seed_adj(
+//   G(x, d) = G_A2 / N2 = g w (dhat - d) / (T N2),
+//   dLoss/dT term = g w (d - dhat) A2 / T^2;
+// out(p, d) = sum_x [x - l(x) <= p <= x + r(x)] G(x, d), the adjoint of A2's row
+// range sums (G_E2): the transposed band, as a product like k_soft_mrow's and on
+// the same blocks.  G spans many binades, so its fixed point is wider: q = G 2^k
+// in two 24-bit halves of three digits each, with 2^k set by the largest |G| the
+// wavefront has met in its row (2^-45 of it is kept).  Where a block raises that
+// bound, its outputs add the block before in the old scale: two products apart.
+// The bytes of a lane's 16 pixels x come four at a time: with e = x - p, l - e and
+// r + e are not negative, tested in bit 7 of biased bytes.
+//
+// The temperature terms of the wavefront's row and disparities are summed into
+// one FP64 value.  A G that is not finite makes the outputs from its block on NaN.
+__device__ inline v4i band_bytes_t(const uint32_t* lp, const uint32_t* r, int e) {
+    const v4u l4 = *reinterpret_cast<const v4u*>(lp), r4 = *reinterpret_cast<const v4u*>(r);
+    uint32_t e4 = (uint32_t)(e + 128) * 0x01010101u + 0x03020100u;  // e + 128 + byte
+    v4i o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i, e4 += 0x04040404u) {
+        const uint32_t a = l4[i] + ~e4;  // (l + 1) + 255 - (e + 128) = l - e + 128
+        const uint32_t b = r4[i] + e4;   // r + e + 128
+        o[i] = (int)((a & b & 0x80808080u) >> 7);
+    }
+    return o;
+}
+
+// As digit_planes, three planes.
+__device__ inline void digit_planes3(const uint32_t* stage, v4i (&b)[3]) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t* s = stage + (lane & 15) * kMxStride + 16 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const v4u w = *reinterpret_cast<const v4u*>(s + 4 * i);
+        const uint32_t t0 = __builtin_amdgcn_perm(w.y, w.x, 0x05010400u);
+        const uint32_t t1 = __builtin_amdgcn_perm(w.w, w.z, 0x05010400u);
+        const uint32_t t2 = __builtin_amdgcn_perm(w.y, w.x, 0x0c0c0602u);
+        const uint32_t t3 = __builtin_amdgcn_perm(w.w, w.z, 0x06020c0cu);
+        b[0][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x05040100u);
+        b[1][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x07060302u);
+        b[2][i] = (int)(t2 | t3);
+    }
+}
+
+__global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
     SoftGeom g, const float* __restrict__ A2, const float* __restrict__ theta,
     const float* __restrict__ dhat, const float* __restrict__ lse,
     const float* __restrict__ gdhat, float* __restrict__ out, double* __restrict__ partT,
-    size_t lds_wave) {
-    extern __shared__ __align__(16) unsigned char dyn[];
-    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63,
-              W = g.W;
-    unsigned char* mine = dyn + w * lds_wave;
-    long long* Dq = reinterpret_cast<long long*>(mine);  // W + 1 entries
-    float* row = reinterpret_cast<float*>(mine + ((size_t)(W + 1) * 8 + 15) / 16 * 16);
-    uchar2* lr = reinterpret_cast<uchar2*>(reinterpret_cast<unsigned char*>(row) + row_bytes(W));
+    int seg_its) {
+    __shared__ v4i bands[2][8][64];
+    __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
+    // l + 1 and r of the columns of this block and the one before, a byte each
+    __shared__ __align__(16) uint32_t arml[kMxWaves][2][16], armr[kMxWaves][2][16];
+    const int nt = blockDim.x, nw = nt >> 6;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = lane & 15, kg = lane >> 4;
+    const int W = g.W, D = g.D, ng = (D + 15) >> 4;
+    const int row = (int)blockIdx.x, y = row % g.H, b = row / g.H;
+    const int it0 = blockIdx.y * seg_its, it1 = min(it0 + seg_its, (W + 95) >> 6);
+    const size_t P = (size_t)W * g.H, pix = (size_t)b * P + (size_t)y * W;
+    const size_t vol = ((size_t)b * D) * P + (size_t)y * W;
     const float T = theta[2], invT = 1.0f / T;
-    const size_t P = (size_t)W * g.H;
-    const int nrows = g.B * g.D * g.H;
-    const int r0 = (blockIdx.x * kRowWaves + w) * kRowsPerWave;
-    const bool vec = (W & 3) == 0;  // 16-byte aligned rows
-    for (int rid = r0; rid < min(nrows, r0 + kRowsPerWave); ++rid) {
-        int b, d, y;
-        row_of(rid, g.D, g.H, b, d, y);
-        const size_t base = ((size_t)b * g.D + d) * P + (size_t)y * W;
-        const size_t pix = b * P + (size_t)y * W;
-        // the row's inputs through row pointers (uniform), indexed by column
-        const float* __restrict__ a2r = A2 + base;
-        const float* __restrict__ gr = gdhat + pix;
-        const float* __restrict__ dr = dhat + pix;
-        const float* __restrict__ lr0 = lse + pix;
-        const float* __restrict__ nr = g.n2 + pix;
-        const uint32_t* __restrict__ ar = g.arms + pix;
+    uint32_t* stage = stages[w];
+    int par = 0;
+    for (int g0 = 0; g0 < ng; g0 += nw) {
+        const int grp = g0 + w, d0 = 16 * grp;
+        const bool active = grp < ng;
+        v4i bp[2][3];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
         double acc = 0.0;
-        float gmax = 0.0f;
-        over_row<4>(W, [&](auto nb, int x0) {
-            constexpr int NB = decltype(nb)::value;
-            float a2[NB], gp[NB], dh[NB], l[NB], n2[NB];
-            uint32_t a[NB];
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int xc = min(x0 + 64 * j + lane, W - 1);
-                a2[j] = a2r[xc];
-                gp[j] = gr[xc];
-                dh[j] = dr[xc];
-                l[j] = lr0[xc];
-                n2[j] = nr[xc];
-                a[j] = ar[xc];
-            }
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int x = x0 + 64 * j + lane;
-                if (x < W) {
-                    const float wgt = exp_e(-a2[j] * invT - l[j]);
-                    const float G =
-                        gp[j] * wgt * (dh[j] - (float)d) * invT * __builtin_amdgcn_rcpf(n2[j]);
-                    acc += (double)(gp[j] * wgt * ((float)d - dh[j]) * a2[j]) *
-                           (double)(invT * invT);
-                    row[x] = G;
-                    lr[x] = make_uchar2((unsigned char)arm(a[j], 0), (unsigned char)arm(a[j], 1));
-                    gmax = fmaxf(gmax, fabsf(G));
+        int ex = -100;               // |G| <= 2^ex so far
+        bool bad = false;            // a G was not finite
+        // the block before a segment's first only gives its digits
+        for (int it = max(it0 - 1, 0), first = it; it < it1; ++it, par ^= 1) {
+            const int X = it << 6;
+            const int xc = min(X + lane, W - 1);
+            const bool in = X + lane < W;
+            {
+                const uint32_t a = X < W ? g.arms[pix + xc] : 0u;
+                reinterpret_cast<uint8_t*>(arml[w][it & 1])[lane] = (uint8_t)(arm(a, 0) + 1);
+                reinterpret_cast<uint8_t*>(armr[w][it & 1])[lane] = (uint8_t)arm(a, 1);
+                if (it == first) {  // no block before (its digits are zero)
+                    reinterpret_cast<uint8_t*>(arml[w][~it & 1])[lane] = 1;
+                    reinterpret_cast<uint8_t*>(armr[w][~it & 1])[lane] = 0;
+                }
+                __builtin_amdgcn_wave_barrier();
+                for (int c = w; c < 8; c += nw) {
+                    const int k = c & 1;  // 0: the block before, 1: this one
+                    const int p = X - 32 + 16 * (c >> 1) + n;
+                    bands[par][c][lane] =
+                        band_bytes_t(arml[w][(it + 1 + k) & 1] + 4 * kg,
+                                     armr[w][(it + 1 + k) & 1] + 4 * kg,
+                                     X - 64 + 64 * k + 16 * kg - p);
                 }
             }
-        });
-        for (int o = 32; o > 0; o >>= 1) gmax = fmaxf(gmax, __shfl_xor(gmax, o, 64));
-        for (int x = lane; x <= W; x += 64) Dq[x] = 0;
-        __builtin_amdgcn_wave_barrier();
-        // |G| < 2^(e+1) with e the exponent of the largest; 2^k G < 2^45, and
-        // a pixel sums at most 2 kLMax + 1 of them: far below 2^63
-        const int e = gmax > 0.0f ? ilogbf(gmax) : 0;
-        const double up = ldexp(1.0, 44 - e), down = ldexp(1.0, e - 44);
-        over_row(W, [&](auto nb, int x0) {
-            constexpr int NB = decltype(nb)::value;
-            float gx[NB];
-            uchar2 ax[NB];
+            uint32_t lo[16];
+            const int ex_old = ex;
+            if (active && X < W) {
+                const float gp = in ? gdhat[pix + xc] : 0.0f, dh = dhat[pix + xc];
+                const float ls = lse[pix + xc];
+                const float g1 = gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc]);
+                const float dh0 = dh - (float)d0;
+                float G[16];
+                uint32_t m = 0;  // bits of the largest |G| (a NaN's are larger still)
+                double t = 0.0;
+                size_t Pv = P;
+                asm volatile("" : "+s"(Pv));  // else 16 row addresses live in registers
+                const float* a2 = A2 + vol + (size_t)d0 * Pv + xc;
+                const auto seed = [&](auto full) {
+                    constexpr bool kFull = decltype(full)::value;
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {  // the batch's reads first, then its adds
-                const int xc = min(x0 + 64 * j + lane, W - 1);
-                gx[j] = row[xc];
-                ax[j] = lr[xc];
-            }
+                    for (int j = 0; j < 16; ++j) {
+                        G[j] = *a2;
+                        if (kFull || d0 + j + 1 < D) a2 += Pv;
+                    }
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int x = x0 + 64 * j + lane;
-                if (x < W) {
-                    const long long q = llrint((double)gx[j] * up);
-                    atomicAdd(reinterpret_cast<unsigned long long*>(&Dq[x - ax[j].x]),
-                              (unsigned long long)q);
-                    atomicAdd(reinterpret_cast<unsigned long long*>(&Dq[x + ax[j].y + 1]),
-                              (unsigned long long)(-q));
+                    for (int j = 0; j < 16; ++j) {
+                        const float u = exp_e(-G[j] * invT - ls) * (dh0 - (float)j);
+                        const bool on = kFull || d0 + j < D;
+                        t += (double)(on ? gp * u * G[j] : 0.0f);
+                        G[j] = on ? g1 * u : 0.0f;
+                        m = max(m, __float_as_uint(G[j]) & 0x7fffffffu);
+                    }
+                };
+                if (d0 + 16 <= D)
+                    seed(std::true_type{});
+                else
+                    seed(std::false_type{});
+                if (it >= it0) acc -= t;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+                m = __builtin_amdgcn_readfirstlane(m);
+                bad = bad || m >= 0x7f800000u;
+                ex = max(ex, (int)(m >> 23) - 126);
+                const float up = ldexpf(1.0f, 22 - ex);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const float q = G[j] * up, h = __builtin_rintf(q);
+                    stage[j * kMxStride + lane] = ((uint32_t)(int)h + 0x8080u) ^ 0x8080u;
+                    lo[j] = ((uint32_t)(int)((q - h) * 0x1p23f) + 0x8080u) ^ 0x8080u;
                 }
+                __builtin_amdgcn_wave_barrier();
             }
-        });
-        __builtin_amdgcn_wave_barrier();
-        // prefix of the difference array (exact integers) in 256-column
-        // chunks, a lane owning four consecutive columns: a local prefix, one
-        // wavefront scan of the lane totals, and the outputs stored straight
-        // from registers (16-byte stores when rows are 16-byte aligned)
-        long long carry = 0;
-        for (int x0 = 0; x0 < W; x0 += kPreChunk) {
-            const int x = x0 + 4 * lane;
-            long long sk[4];
+            __syncthreads();  // the bands; the buffer's next writers pass the next one first
+            if (!active) continue;
+            v4i bc[2][3];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) sk[k] = x + k < W ? Dq[min(x + k, W - 1)] : 0;
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int k = 1; k < 4; ++k) sk[k] += sk[k - 1];
-            const long long inc = wave_scan_i64(sk[3]);
-            const long long before = carry + (inc - sk[3]);
-            float o[4];
+                for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
+            if (X < W) {
+                digit_planes3(stage, bc[0]);
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int k = 0; k < 4; ++k) o[k] = (float)((double)(before + sk[k]) * down);
-            if (vec) {
-                if (x < W)
-                    *reinterpret_cast<float4*>(out + base + x) =
-                        make_float4(o[0], o[1], o[2], o[3]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (x + k < W) out[base + x + k] = o[k];
+                for (int j = 0; j < 16; ++j) stage[j * kMxStride + lane] = lo[j];
+                __builtin_amdgcn_wave_barrier();
+                digit_planes3(stage, bc[1]);
+                __builtin_amdgcn_wave_barrier();
             }
-            carry += readlane_i64(inc, 63);
+            if (it >= it0) {
+                const double inv = bad ? __builtin_nan("") : ldexp(1.0, ex - 45);
+                const auto value = [](const v4i (&s)[2][3], int r) {
+                    const int h = s[0][0][r] + ((s[0][1][r] + (s[0][2][r] << 8)) << 8);
+                    const int l = s[1][0][r] + ((s[1][1][r] + (s[1][2][r] << 8)) << 8);
+                    return __builtin_fma((double)h, 0x1p23, (double)l);
+                };
+                const auto outputs = [&](auto rescaled) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int xb = X - 32 + 16 * i;
+                        if (xb < 0 || xb >= W) continue;
+                        const v4i b0 = bands[par][2 * i][lane], b1 = bands[par][2 * i + 1][lane];
+                        v4i s[2][3];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+                                s[h][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                                    b0, bp[h][k], v4i{0, 0, 0, 0}, 0, 0, 0);
+                        double v[4];
+                        if (decltype(rescaled)::value) {
+                            const double inv_old = ldexp(1.0, ex_old - 45);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) v[r] = value(s, r) * inv_old;
+#pragma unroll
+                            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                                for (int k = 0; k < 3; ++k) s[h][k] = v4i{0, 0, 0, 0};
+                        }
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+                                s[h][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b1, bc[h][k],
+                                                                                s[h][k], 0, 0, 0);
+                        v4f o;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            o[r] = (float)(decltype(rescaled)::value
+                                               ? __builtin_fma(value(s, r), inv, v[r])
+                                               : value(s, r) * inv);
+                        *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) = o;
+                    }
+                };
+                if (ex == ex_old)
+                    outputs(std::false_type{});
+                else
+                    outputs(std::true_type{});
+                __builtin_amdgcn_wave_barrier();
+                put_rows(stage, out + vol, P, d0, D, X - 32, W);
+                __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
         }
-        __builtin_amdgcn_wave_barrier();
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-        if (lane == 0) partT[rid] = acc;
-        __builtin_amdgcn_wave_barrier();
+        if (active) {
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+            if (lane == 0)
+                partT[((size_t)row * gridDim.y + blockIdx.y) * ng + grp] =
+                    acc * (double)(invT * invT);
+        }
     }
 }
 
@@ -1173,20 +1234,21 @@ static void launch_vv(const SoftGeom& g, const float* in, float* out, hipStream_
                        dim3(kSoftCols), 0, st, g, in, out, seg);
 }
 
-// Row sums of the costs into `out`, or their gradient sums into `part`; returns
-// the number of pairs in `part`.
-template <bool kDeriv>
-static int launch_mrow(const SoftGeom& g, const SoftImg& im, const float* G, float* out,
-                       double* part, hipStream_t st) {
+// Launch shape of the matrix-core row passes: a workgroup per image row and
+// part of it, a wavefront per 16 disparities.  Rows are split (each part
+// computes one more block) while they leave the device's slots empty; the
+// partial sums have room for D values per row.
+struct RowGrid {
+    int seg, ng, parts;  // blocks per part, values per part, values in all
+    dim3 grid, block;
+};
+
+static RowGrid row_grid(const SoftGeom& g) {
     const int ng = (g.D + 15) / 16, nw = std::min(ng, kMxWaves), rows = g.B * g.H;
     const int its = (g.W + 95) / 64;
-    // rows split (each part computes one more block) while they leave the
-    // device's slots empty; the partial sums have room for D pairs per row
     const int most = std::max(1, std::min({its / 2, g.D / ng, kMxSlots / (rows * nw)}));
     const int seg = (its + most - 1) / most, segs = (its + seg - 1) / seg;
-    hipLaunchKernelGGL(k_soft_mrow<kDeriv>, dim3(rows, segs), dim3(64 * nw), 0, st, g, im, G, out,
-                       part, seg);
-    return rows * segs * ng;
+    return RowGrid{seg, ng, rows * segs * ng, dim3(rows, segs), dim3(64 * nw)};
 }
 
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
@@ -1209,7 +1271,9 @@ hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, floa
     const size_t lf = row_lds_fwd(W);
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_soft_hrow), kRowWaves * lf);
     if (e != hipSuccess) return e;
-    launch_mrow<false>(g, im, nullptr, t1, nullptr, st);                                     // E1
+    const RowGrid rg = row_grid(g);
+    hipLaunchKernelGGL(k_soft_mrow<false>, rg.grid, rg.block, 0, st, g, im, (const float*)nullptr,
+                       t1, (double*)nullptr, rg.seg);                                        // E1
     launch_vv<false>(g, t1, t2, st);                                                         // E2
     hipLaunchKernelGGL(k_soft_hrow, gr, dim3(64 * kRowWaves), kRowWaves * lf, st, g, t2, A2,
                        lf);                                                                  // A2
@@ -1233,18 +1297,15 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
     SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
-    const dim3 gr((nrows + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave));
-    const size_t la = row_lds_adj(W);
-    const hipError_t e =
-        allow_lds(reinterpret_cast<const void*>(&k_soft_seed_adj), kRowWaves * la);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_soft_seed_adj, gr, dim3(64 * kRowWaves), kRowWaves * la, st, g, A2, theta,
-                       dhat, lse, gdhat, t2, partT, la);                 // G_E2, T-gradient terms
+    const RowGrid rg = row_grid(g);
+    hipLaunchKernelGGL(k_soft_madj, rg.grid, rg.block, 0, st, g, A2, theta, dhat, lse, gdhat, t2,
+                       partT, rg.seg);                                // G_E2, T-gradient terms
     launch_vv<true>(g, t2, t1, st);                                   // G_E1
-    const int nac = launch_mrow<true>(g, im, t1, nullptr, partAC, st);   // G_E1 . H dc/dlambda
+    hipLaunchKernelGGL(k_soft_mrow<true>, rg.grid, rg.block, 0, st, g, im, t1, (float*)nullptr,
+                       partAC, rg.seg);                               // G_E1 . H dc/dlambda
     double* blk = partT + (size_t)nrows;  // kRedBlocks x 3 after the row partials
     hipLaunchKernelGGL(k_soft_reduce1, dim3(kRedBlocks), dim3(256), 0, st, partAC,
-                       (size_t)nac, partT, (size_t)nrows, blk);
+                       (size_t)rg.parts, partT, (size_t)rg.parts, blk);
     hipLaunchKernelGGL(k_soft_reduce2, dim3(1), dim3(256), 0, st, blk, grad);
     return hipGetLastError();
 }

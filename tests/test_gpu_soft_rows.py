@@ -70,3 +70,31 @@ def test_row_sums_keep_nan_of_theta():
             th = torch.tensor(theta, dtype=torch.float32, device="cuda")
             dh, _ = soft_forward(m, dev(p["left"][None]), dev(p["right"][None]), th)
             assert torch.isnan(dh).any()
+
+
+def test_row_adjoint_follows_growing_gradients():
+    """Gradients that grow by 2^9 per block of 64 columns (each block rescales the
+    fixed point), and shrink again: as close as ever to the largest component."""
+    import torch
+    from paper_2203_02300_amd import StereoMatcher
+    from paper_2203_02300_amd.soft import soft_backward, soft_forward
+    W, H, D = 300, 9, 20
+    p = synth.make_slanted_pair(W, H, D, 960, n_planes=2, dmin=2.0, dmax=D - 3.0,
+                                noise_sigma=2.0, occl_strip_frac=0.03)
+    Lb, Rb = p["left"], p["right"]
+    cL, cR, aL = oracle.census(oracle.grey(Lb)), oracle.census(oracle.grey(Rb)), oracle.arms(Lb)
+    base = np.random.default_rng(3).normal(0, 1e-3, (1, H, W))
+    th = torch.tensor((10.0, 30.0, 0.5), dtype=torch.float32, device="cuda")
+    with StereoMatcher(W, H, D) as m:
+        L, R = dev(Lb[None]), dev(Rb[None])
+        dh, lse = soft_forward(m, L, R, th)
+        for e in (np.arange(W) / 7.0, -np.arange(W) / 7.0, np.abs(np.arange(W) - 150) / -7.0):
+            gd = (base * 2.0 ** e).astype(np.float32)
+            g = host(soft_backward(m, L, R, th, dh, lse, dev(gd), reuse=True)).astype(np.float64)
+            ref = oracle.soft_grad(Lb, Rb, cL, cR, aL, D, gd[0], lam_ad=10.0, lam_c=30.0, T=0.5)
+            assert np.all(np.abs(g - ref) <= 1e-3 * np.abs(ref).max()), (g, ref)
+        gd = base.astype(np.float32)
+        for bad in (np.inf, np.nan):
+            gd[0, 4, 130] = bad
+            g = host(soft_backward(m, L, R, th, dh, lse, dev(gd), reuse=True))
+            assert not np.isfinite(g).any()
