@@ -157,7 +157,7 @@ static void free_handle_memory(dco_stereo* h) {
                     h->s.arms[1],    h->s.rec[0].b,   h->s.rec[0].c,
                     h->s.rec[1].b,   h->s.rec[1].c,
                     h->s.agg[0],     h->s.agg[1],     h->s.dint[0],
-                    h->s.dint[1],    h->s.delta,      h->s.vote[0],    h->s.vote[1],
+                    h->s.dint[1],    h->s.vote[0],    h->s.vote[1],
                     h->s.half[0],    h->s.half[1],
                     h->soft.pix[0],  h->soft.pix[1],
                     h->soft.arms,    h->soft.vrec,  h->soft.rn1,      h->soft.n2,
@@ -188,7 +188,6 @@ static dco_status alloc_scratch(dco_stereo* h) {
         DCO_TRY(dev_alloc(&s.agg[v], V));
         DCO_TRY(dev_alloc(&s.dint[v], P));
     }
-    DCO_TRY(dev_alloc(&s.delta, P));
     DCO_TRY(dev_alloc(&s.vote[0], P));
     DCO_TRY(dev_alloc(&s.vote[1], P));
     DCO_TRY(dev_alloc(&s.half[0], 3 * P));
@@ -402,10 +401,8 @@ extern "C" dco_status dco_wta_lrcheck(dco_stereo* h, const float* aggL, const fl
     DCO_TRY(need(valid, "valid"));
     int16_t* oL = dL ? dL : h->s.dint[0];
     int16_t* oR = dR ? dR : h->s.dint[1];
-    DCO_HIP_CHECK(launch_wta2(aggL, aggR, h->W, h->H, h->D, h->p.subpixel, oL, h->s.delta, oR,
-                              h->stream));
-    DCO_HIP_CHECK(launch_lrcheck(oL, h->s.delta, oR, h->W, h->H, h->p.lr_max_diff, disp, valid,
-                                 h->stream));
+    DCO_HIP_CHECK(launch_wta_lr(aggL, aggR, false, h->W, h->H, h->D, h->p.subpixel,
+                                h->p.lr_max_diff, oL, oR, disp, valid, h->stream));
     return DCO_OK;
 }
 
@@ -435,16 +432,11 @@ extern "C" dco_status dco_stereo_match(dco_stereo* h, const uint8_t* rgbL, const
     s.agg_paired = p.agg_iters == 2;
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
-    if (s.agg_paired)  // WTA from the even slices (each pair's minimum)
-        DCO_HIP_CHECK(launch_wta_pairs(s.agg[0], s.agg[1], h->W, h->H, h->D, p.subpixel,
-                                       s.dint[0], s.delta, s.dint[1], h->stream));
-    else
-        DCO_HIP_CHECK(launch_wta2(s.agg[0], s.agg[1], h->W, h->H, h->D, p.subpixel, s.dint[0],
-                                  s.delta, s.dint[1], h->stream));
+    // from the even slices (each pair's minimum) when the volumes are paired
+    DCO_HIP_CHECK(launch_wta_lr(s.agg[0], s.agg[1], s.agg_paired, h->W, h->H, h->D, p.subpixel,
+                                p.lr_max_diff, s.dint[0], s.dint[1], disp, valid, h->stream));
     DCO_TRY(prof_mark(h));
-    DCO_TRY(prof_mark(h));
-    DCO_HIP_CHECK(launch_lrcheck(s.dint[0], s.delta, s.dint[1], h->W, h->H, p.lr_max_diff, disp,
-                                 valid, h->stream));
+    DCO_TRY(prof_mark(h));  // the left-right check is part of the launch above
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
     if (p.vote_iters > 0) {

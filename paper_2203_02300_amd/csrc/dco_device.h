@@ -1304,46 +1304,44 @@ __device__ inline float subpixel_delta(float m, float c, float pl, int bd, int D
 }
 
 
-// Pixel i of a D-slice volume: smallest d minimising agg, with the values at
-// d - 1 and d + 1 tracked on the fly (ties keep the smallest d).
-__device__ inline void wta_pixel(const float* __restrict__ agg, int P, int D, int i,
-                                 int subpixel, int16_t* dout, float* delta_out) {
-    float best = agg[i], prev = best, m = 0.f, pl = 0.f;
-    int bd = 0;
-    constexpr int U = 8;
-    int d = 1;
-    for (; d + U <= D; d += U) {
-        float v[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = agg[(size_t)(d + k) * P + i];
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            if (d + k == bd + 1) pl = v[k];
-            if (v[k] < best) {
-                best = v[k];
-                bd = d + k;
-                m = prev;
-            }
-            prev = v[k];
-        }
-    }
-    for (; d < D; ++d) {
-        const float v = agg[(size_t)d * P + i];
-        if (d == bd + 1) pl = v;
-        if (v < best) {
-            best = v;
-            bd = d;
-            m = prev;
-        }
-        prev = v;
-    }
-    *dout = (int16_t)bd;
-    if (delta_out) *delta_out = subpixel ? subpixel_delta(m, best, pl, bd, D) : 0.f;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Four words at any 4-byte address, four int16 at any 2-byte address, four
+// bytes at any: the hardware's vector accesses need no more.
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int16_t i16x4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint8_t u8x4u __attribute__((ext_vector_type(4), aligned(1)));
+
+// WTA result of four consecutive pixels (del: the parabola's offset).
+struct WtaQuad {
+    int bd[4];
+    float del[4];
+};
+
+// Words of pixels i .. i + 3 of the slice at p.  kNarrow: of pixels i .. i + n - 1,
+// the last repeated (rows of n < 4 pixels).
+template <bool kNarrow>
+__device__ inline u32x4 wta_load(const uint32_t* p, int n) {
+    if constexpr (kNarrow)
+        return u32x4{p[0], p[min(1, n - 1)], p[min(2, n - 1)], p[n - 1]};
+    else
+        return __builtin_nontemporal_load(reinterpret_cast<const u32x4u*>(p));
 }
 
-// Four consecutive pixels i4 .. i4 + 3 of a D-slice volume (P % 4 == 0, so
-// every slice row of four is 16-byte aligned): the same rule as wta_pixel
-// per component, with one 16-byte load per slice and eight slices in flight.
+// Stores of a quad's values (kNarrow: the first n of them).
+template <bool kNarrow, typename V, typename T>
+__device__ inline void wta_store(T* p, T a, T b, T c, T d, int n) {
+    if constexpr (kNarrow) {
+        p[0] = a;
+        if (n > 1) p[1] = b;
+        if (n > 2) p[2] = c;
+    } else {
+        *reinterpret_cast<V*>(p) = V{a, b, c, d};
+    }
+}
+
+// Smallest d minimising agg, per pixel of the quad, with the values at d - 1 and
+// d + 1 tracked on the fly (ties keep the smallest d).
 __device__ inline void wta_quad_step(float v, int d, float& best, int& bd, float& m, float& pl,
                                      float& prev) {
     if (d == bd + 1) pl = v;
@@ -1355,60 +1353,49 @@ __device__ inline void wta_quad_step(float v, int d, float& best, int& bd, float
     prev = v;
 }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline void wta_quad(const float* __restrict__ agg, int P, int D, int i4, int subpixel,
-                                int16_t* __restrict__ dout, float* __restrict__ delta_out) {
+// Four consecutive pixels from i on of a D-slice volume, with one 16-byte load
+// per slice and eight slices in flight.
+template <bool kSub, bool kNarrow>
+__device__ inline WtaQuad wta_quad(const float* __restrict__ agg, int P, int D, int i, int n,
+                                   int subpixel) {
     // each volume is read once: non-temporal loads keep it from evicting
     // reused data from the caches
-    const f32x4* __restrict__ a4 = reinterpret_cast<const f32x4*>(agg + i4);
-    const size_t s4 = (size_t)P / 4;
-    const f32x4 v0 = __builtin_nontemporal_load(a4);
+    const uint32_t* __restrict__ a = reinterpret_cast<const uint32_t*>(agg) + i;
+    const auto load = [&](int d) {
+        return __builtin_bit_cast(f32x4, wta_load<kNarrow>(a + (size_t)d * P, n));
+    };
+    const f32x4 v0 = load(0);
     float best[4] = {v0.x, v0.y, v0.z, v0.w}, prev[4] = {v0.x, v0.y, v0.z, v0.w};
     float m[4] = {0.f, 0.f, 0.f, 0.f}, pl[4] = {0.f, 0.f, 0.f, 0.f};
-    int bd[4] = {0, 0, 0, 0};
+    WtaQuad r{};
+    const auto step = [&](const f32x4& v, int d) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            wta_quad_step(v[q], d, best[q], r.bd[q], m[q], pl[q], prev[q]);
+    };
     constexpr int U = 8;
     int d = 1;
     for (; d + U <= D; d += U) {
         f32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = __builtin_nontemporal_load(a4 + (size_t)(d + k) * s4);
+        for (int k = 0; k < U; ++k) v[k] = load(d + k);
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            wta_quad_step(v[k].x, d + k, best[0], bd[0], m[0], pl[0], prev[0]);
-            wta_quad_step(v[k].y, d + k, best[1], bd[1], m[1], pl[1], prev[1]);
-            wta_quad_step(v[k].z, d + k, best[2], bd[2], m[2], pl[2], prev[2]);
-            wta_quad_step(v[k].w, d + k, best[3], bd[3], m[3], pl[3], prev[3]);
-        }
+        for (int k = 0; k < U; ++k) step(v[k], d + k);
     }
-    for (; d < D; ++d) {
-        const f32x4 v = __builtin_nontemporal_load(a4 + (size_t)d * s4);
-        wta_quad_step(v.x, d, best[0], bd[0], m[0], pl[0], prev[0]);
-        wta_quad_step(v.y, d, best[1], bd[1], m[1], pl[1], prev[1]);
-        wta_quad_step(v.z, d, best[2], bd[2], m[2], pl[2], prev[2]);
-        wta_quad_step(v.w, d, best[3], bd[3], m[3], pl[3], prev[3]);
+    for (; d < D; ++d) step(load(d), d);
+    if (kSub && subpixel) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r.del[q] = subpixel_delta(m[q], best[q], pl[q], r.bd[q], D);
     }
-    const uint32_t lo = (uint32_t)(uint16_t)bd[0] | (uint32_t)(uint16_t)bd[1] << 16;
-    const uint32_t hi = (uint32_t)(uint16_t)bd[2] | (uint32_t)(uint16_t)bd[3] << 16;
-    *reinterpret_cast<uint2*>(dout + i4) = make_uint2(lo, hi);
-    if (delta_out) {
-        float4 del = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (subpixel) {
-            del.x = subpixel_delta(m[0], best[0], pl[0], bd[0], D);
-            del.y = subpixel_delta(m[1], best[1], pl[1], bd[1], D);
-            del.z = subpixel_delta(m[2], best[2], pl[2], bd[2], D);
-            del.w = subpixel_delta(m[3], best[3], pl[3], bd[3], D);
-        }
-        *reinterpret_cast<float4*>(delta_out + i4) = del;
-    }
+    return r;
 }
 
 // Winner-take-all on a volume in the paired layout: the same rule and the
-// same result as wta_pixel / wta_quad, since each even slice holds the
-// smaller cost of its pair (the first on a tie) and the pairs are visited in
-// order with a strict comparison; only the G = ceil(D / 2) even slices are
-// read.  The sub-pixel step gathers the costs at d - 1 and d + 1, which is
-// exactly where wta_pixel's m and pl come from when 0 < d < D - 1 (the only
+// same result as wta_quad, since each even slice holds the smaller cost of its
+// pair (the first on a tie) and the pairs are visited in order with a strict
+// comparison; only the G = ceil(D / 2) even slices are read.  The sub-pixel step
+// needs the costs at d - 1 and d + 1, which is exactly where wta_quad's m and pl
+// come from when 0 < d < D - 1 (the only
 // case in which subpixel_delta uses them).
 __device__ inline void wta_pair_step(uint32_t s, int g, float& best, int& bd) {
     const float v = __builtin_bit_cast(float, s & 0x7fffffffu);
@@ -1416,24 +1403,6 @@ __device__ inline void wta_pair_step(uint32_t s, int g, float& best, int& bd) {
         best = v;
         bd = 2 * g + (int)(s >> 31);
     }
-}
-
-__device__ inline float wta_pair_delta(const float* __restrict__ vol, int P, int D, int i,
-                                       float best, int bd) {
-    if (bd <= 0 || bd >= D - 1) return 0.f;
-    return subpixel_delta(paired_at(vol, P, D, bd - 1, i), best, paired_at(vol, P, D, bd + 1, i),
-                          bd, D);
-}
-
-__device__ inline void wta_pairs_pixel(const float* __restrict__ vol, int P, int D, int i,
-                                       int subpixel, int16_t* dout, float* delta_out) {
-    const uint32_t* __restrict__ u = reinterpret_cast<const uint32_t*>(vol);
-    const int G = (D + 1) / 2;
-    float best = __builtin_bit_cast(float, u[i] & 0x7fffffffu);
-    int bd = (int)(u[i] >> 31);
-    for (int g = 1; g < G; ++g) wta_pair_step(u[(size_t)2 * g * P + i], g, best, bd);
-    *dout = (int16_t)bd;
-    if (delta_out) *delta_out = subpixel ? wta_pair_delta(vol, P, D, i, best, bd) : 0.f;
 }
 
 // Pair step that also keeps, for the left view's parabola, the word of the
@@ -1456,7 +1425,7 @@ __device__ inline void wta_pair_step_tr(uint32_t s, int g, float& best, int& bd,
     lastw = s;
 }
 
-// wta_pair_delta with the adjacent pairs' words from the scan: the winner's
+// Parabola's offset, with the adjacent pairs' words from the scan: the winner's
 // pair partner is that pair's maximum (the odd slice), and the neighbour in
 // the adjacent pair is read only when it is not that pair's minimum.  The
 // values are the same ones paired_at decodes.
@@ -1478,36 +1447,32 @@ __device__ inline float wta_pair_delta_tr(const float* __restrict__ vol, int P, 
     return subpixel_delta(m, best, pl, bd, D);
 }
 
-// Four consecutive pixels (P % 4 == 0): one 16-byte load per even slice,
-// 21 slices in flight.  kSub: the left view, with the parabola's offset
-// into delta_out; else delta_out is null.
-template <bool kSub>
-__device__ inline void wta_pairs_quad(const float* __restrict__ vol, int P, int D, int i4,
-                                      int subpixel, int16_t* __restrict__ dout,
-                                      float* __restrict__ delta_out) {
+// Four consecutive pixels from i on: one 16-byte load per even slice, 21 slices
+// in flight.  kSub: the left view, with the parabola's offset.
+template <bool kSub, bool kNarrow>
+__device__ inline WtaQuad wta_pairs_quad(const float* __restrict__ vol, int P, int D, int i, int n,
+                                         int subpixel) {
     const int G = (D + 1) / 2;
-    const u32x4* __restrict__ s4 = reinterpret_cast<const u32x4*>(vol + i4);
-    const size_t st = (size_t)P / 2;  // two slices, in 16-byte words
-    const u32x4 w0 = __builtin_nontemporal_load(s4);
-    const uint32_t w0s[4] = {w0.x, w0.y, w0.z, w0.w};
+    const uint32_t* __restrict__ s = reinterpret_cast<const uint32_t*>(vol) + i;
+    const size_t st = (size_t)P * 2;  // two slices
+    const u32x4 w0 = wta_load<kNarrow>(s, n);
+    WtaQuad r{};
     float best[4];
-    int bd[4];
     uint32_t lastw[4], prevw[4] = {0u, 0u, 0u, 0u}, nextw[4] = {0u, 0u, 0u, 0u};
     bool pend[4] = {true, true, true, true};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        best[q] = __builtin_bit_cast(float, w0s[q] & 0x7fffffffu);
-        bd[q] = (int)(w0s[q] >> 31);
-        lastw[q] = w0s[q];
+        best[q] = __builtin_bit_cast(float, w0[q] & 0x7fffffffu);
+        r.bd[q] = (int)(w0[q] >> 31);
+        lastw[q] = w0[q];
     }
     const auto step = [&](const u32x4& v, int g) {
-        const uint32_t vs[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if constexpr (kSub)
-                wta_pair_step_tr(vs[q], g, best[q], bd[q], lastw[q], prevw[q], nextw[q], pend[q]);
+                wta_pair_step_tr(v[q], g, best[q], r.bd[q], lastw[q], prevw[q], nextw[q], pend[q]);
             else
-                wta_pair_step(vs[q], g, best[q], bd[q]);
+                wta_pair_step(v[q], g, best[q], r.bd[q]);
         }
     };
     constexpr int U = 21;  // 21 loads in flight per thread (three batches for D = 128)
@@ -1515,7 +1480,7 @@ __device__ inline void wta_pairs_quad(const float* __restrict__ vol, int P, int 
     for (; g + U <= G; g += U) {
         u32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = __builtin_nontemporal_load(s4 + (size_t)(g + k) * st);
+        for (int k = 0; k < U; ++k) v[k] = wta_load<kNarrow>(s + (size_t)(g + k) * st, n);
 #pragma unroll
         for (int k = 0; k < U; ++k) step(v[k], g + k);
     }
@@ -1523,23 +1488,56 @@ __device__ inline void wta_pairs_quad(const float* __restrict__ vol, int P, int 
         u32x4 v[U];
 #pragma unroll
         for (int k = 0; k < U; ++k)
-            v[k] = __builtin_nontemporal_load(s4 + (size_t)min(g + k, G - 1) * st);
+            v[k] = wta_load<kNarrow>(s + (size_t)min(g + k, G - 1) * st, n);
 #pragma unroll
         for (int k = 0; k < U; ++k)
             if (g + k < G) step(v[k], g + k);
     }
-    const uint32_t lo = (uint32_t)(uint16_t)bd[0] | (uint32_t)(uint16_t)bd[1] << 16;
-    const uint32_t hi = (uint32_t)(uint16_t)bd[2] | (uint32_t)(uint16_t)bd[3] << 16;
-    *reinterpret_cast<uint2*>(dout + i4) = make_uint2(lo, hi);
-    if constexpr (kSub) {
-        float del[4] = {0.f, 0.f, 0.f, 0.f};
-        if (subpixel) {
+    if (kSub && subpixel) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                del[q] = wta_pair_delta_tr(vol, P, D, i4 + q, best[q], bd[q], prevw[q], nextw[q]);
-        }
-        *reinterpret_cast<float4*>(delta_out + i4) = make_float4(del[0], del[1], del[2], del[3]);
+        for (int q = 0; q < 4; ++q)
+            r.del[q] = wta_pair_delta_tr(vol, P, D, i + (kNarrow ? min(q, n - 1) : q), best[q],
+                                         r.bd[q], prevw[q], nextw[q]);
     }
+    return r;
+}
+
+// Either layout.
+template <bool kPaired, bool kSub, bool kNarrow>
+__device__ inline WtaQuad wta_any(const float* __restrict__ vol, int P, int D, int i, int n,
+                                  int subpixel) {
+    if constexpr (kPaired)
+        return wta_pairs_quad<kSub, kNarrow>(vol, P, D, i, n, subpixel);
+    else
+        return wta_quad<kSub, kNarrow>(vol, P, D, i, n, subpixel);
+}
+
+template <bool kNarrow>
+__device__ inline void put_bd(int16_t* p, const WtaQuad& r, int n) {
+    wta_store<kNarrow, i16x4u>(p, (int16_t)r.bd[0], (int16_t)r.bd[1], (int16_t)r.bd[2],
+                               (int16_t)r.bd[3], n);
+}
+
+// WTA of both views for a list of pixels: quad i of an image of P pixels (the
+// last one moved back to end with the image; an image of less than four pixels
+// is one narrow quad).
+template <bool kPaired>
+__device__ inline void wta_quad_both(const float* __restrict__ aggL,
+                                     const float* __restrict__ aggR, int P, int D, int i4,
+                                     int subpixel, int16_t* __restrict__ dL,
+                                     float* __restrict__ deltaL, int16_t* __restrict__ dR) {
+    const auto both = [&](auto narrow) {
+        constexpr bool kN = decltype(narrow)::value;
+        const int i = kN ? 0 : min(i4, P - 4);
+        const WtaQuad l = wta_any<kPaired, true, kN>(aggL, P, D, i, P, subpixel);
+        put_bd<kN>(dL + i, l, P);
+        wta_store<kN, f32x4u>(deltaL + i, l.del[0], l.del[1], l.del[2], l.del[3], P);
+        put_bd<kN>(dR + i, wta_any<kPaired, false, kN>(aggR, P, D, i, P, subpixel), P);
+    };
+    if (P >= 4)
+        both(std::false_type{});
+    else
+        both(std::true_type{});
 }
 
 __device__ inline void lr_pixel(const int16_t* __restrict__ dL, const float* __restrict__ deltaL,

@@ -24,7 +24,6 @@ struct dco_scratch {
     float* agg[2];      // aggregated volumes of both views (D x H x W)
     bool agg_paired;    // ... written in the paired layout (two-stage aggregation)
     int16_t* dint[2];
-    float* delta;
     int16_t* vote[2];   // ping-pong maps of the Eq. 4 vote passes
     uint8_t* half[2];   // the reduced pair of dco_stereo_match_half (H x W x 3)
 };
@@ -278,21 +277,19 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
                                   const float* tabA, const float* tabC, const float* alpha,
                                   const float* beta, int L1, float* outL, float* outR,
                                   bool paired, hipStream_t st);
-hipError_t launch_wta2(const float* aggL, const float* aggR, int W, int H, int D, int subpixel,
-                       int16_t* dL, float* deltaL, int16_t* dR, hipStream_t st);
-// The same outputs from volumes in the paired layout (even slices only).
-hipError_t launch_wta_pairs(const float* aggL, const float* aggR, int W, int H, int D,
-                            int subpixel, int16_t* dL, float* deltaL, int16_t* dR,
-                            hipStream_t st);
+// WTA of both views and the left-right check in one launch; `paired`: from
+// volumes in the paired layout (even slices only).
+hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int W, int H, int D,
+                         int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
+                         uint8_t* valid, hipStream_t st);
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded into out (n x H x W).
 hipError_t launch_unpair(const float* vol, int W, int H, int D, int d0, int n, float* out,
                          hipStream_t st);
-hipError_t launch_lrcheck(const int16_t* dL, const float* deltaL, const int16_t* dR, int W,
-                          int H, int maxdiff, float* disp, uint8_t* valid, hipStream_t st);
 
 // k_soft.hip
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2, hipStream_t st);
+                        int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2,
+                        hipStream_t st);
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, hipStream_t st);
 hipError_t soft_argmin(const SoftBuffers& s, int B, int W, int H, int D, const float* A2,

@@ -109,36 +109,15 @@ __global__ __launch_bounds__(256, 2) void k_batch_stage(BatchArgs B, int first, 
             // layout (even slices hold each pair's minimum), else plain
             const int P = W * H;
             const bool paired = ITERS == 2 && pr.dchunk % 2 == 0;
-            if (P % 4 == 0) {  // 16-byte loads (the pair's buffers are 256-byte aligned)
-                for (int r = 0; r < kWtaPx / 1024; ++r) {
-                    const int i4 = I.a + (r * 256 + t) * 4;
-                    if (i4 >= P) break;
-                    if (paired) {
-                        dco::wta_pairs_quad<true>(pr.agg[0], P, pr.D, i4, B.subpixel,
-                                                  pr.dint[0], pr.delta);
-                        dco::wta_pairs_quad<false>(pr.agg[1], P, pr.D, i4, B.subpixel,
-                                                   pr.dint[1], nullptr);
-                    } else {
-                        dco::wta_quad(pr.agg[0], P, pr.D, i4, B.subpixel, pr.dint[0], pr.delta);
-                        dco::wta_quad(pr.agg[1], P, pr.D, i4, B.subpixel, pr.dint[1], nullptr);
-                    }
-                }
-            } else {
-                for (int r = 0; r < kWtaPx / 256; ++r) {
-                    const int i = I.a + r * 256 + t;
-                    if (i >= P) break;
-                    if (paired) {
-                        dco::wta_pairs_pixel(pr.agg[0], P, pr.D, i, B.subpixel, pr.dint[0] + i,
-                                             pr.delta + i);
-                        dco::wta_pairs_pixel(pr.agg[1], P, pr.D, i, B.subpixel, pr.dint[1] + i,
-                                             nullptr);
-                    } else {
-                        dco::wta_pixel(pr.agg[0], P, pr.D, i, B.subpixel, pr.dint[0] + i,
-                                       pr.delta + i);
-                        dco::wta_pixel(pr.agg[1], P, pr.D, i, B.subpixel, pr.dint[1] + i,
-                                       nullptr);
-                    }
-                }
+            for (int r = 0; r < kWtaPx / 1024; ++r) {
+                const int i4 = I.a + (r * 256 + t) * 4;
+                if (i4 >= P) break;
+                if (paired)
+                    dco::wta_quad_both<true>(pr.agg[0], pr.agg[1], P, pr.D, i4, B.subpixel,
+                                             pr.dint[0], pr.delta, pr.dint[1]);
+                else
+                    dco::wta_quad_both<false>(pr.agg[0], pr.agg[1], P, pr.D, i4, B.subpixel,
+                                              pr.dint[0], pr.delta, pr.dint[1]);
             }
         } else {  // LR check of rows [a, a + kLrRows)
             for (int y = I.a; y < min(H, I.a + kLrRows); ++y)

@@ -92,7 +92,6 @@ struct StaticBufs {
     size_t rec_words[2];  // words of b and c
     float* agg[2];
     int16_t* dint[2];
-    float* delta;
     int16_t* vote[2];
 };
 
@@ -118,7 +117,6 @@ size_t layout(unsigned char* base, int W, int H, int D, StaticBufs& b) {
         b.dint[v] = c.take<int16_t>(P);
         b.vote[v] = c.take<int16_t>(P);
     }
-    b.delta = c.take<float>(P);
     return (c.used + 255) & ~size_t(255);
 }
 
@@ -225,14 +223,8 @@ extern "C" dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_pa
                                          p.agg_iters, b.tabA, b.tabC, b.alpha, b.beta, p.arm_L1,
                                          b.agg[0], b.agg[1], true, st));
     const bool paired = p.agg_iters == 2;
-    if (paired)
-        DCO_HIP_CHECK(launch_wta_pairs(b.agg[0], b.agg[1], W, H, D, p.subpixel, b.dint[0],
-                                       b.delta, b.dint[1], st));
-    else
-        DCO_HIP_CHECK(launch_wta2(b.agg[0], b.agg[1], W, H, D, p.subpixel, b.dint[0], b.delta,
-                                  b.dint[1], st));
-    DCO_HIP_CHECK(launch_lrcheck(b.dint[0], b.delta, b.dint[1], W, H, p.lr_max_diff, disp, valid,
-                                 st));
+    DCO_HIP_CHECK(launch_wta_lr(b.agg[0], b.agg[1], paired, W, H, D, p.subpixel, p.lr_max_diff,
+                                b.dint[0], b.dint[1], disp, valid, st));
     if (p.vote_iters > 0) {
         const int16_t* dv = nullptr;
         DCO_HIP_CHECK(launch_vote(b.dint[0], valid, b.arms[0], W, H, D, p.vote_iters, b.vote[0],

@@ -1,67 +1,77 @@
 // k_wta.hip -- winner-take-all over the aggregated volumes (Eq. 3) with
-// parabola sub-pixel refinement, and the left-right consistency check.
-// k_wta_pairs* take the same decision on volumes in the paired layout
-// (dco::paired_at): they read only the even slices; for the sub-pixel step
-// they gather the winner's pair partner and, when it is not the adjacent
-// pair's minimum kept from the scan, its other neighbour.
-// One thread per pixel (or per four pixels, with 16-byte loads, when W * H is
-// a multiple of four) walks d = 0 .. D-1; loads of one slice are coalesced
-// across the block, so each volume is read exactly once.  The stage bodies
-// live in dco_device.h.
+// parabola sub-pixel refinement, and the left-right consistency check, in one
+// launch.  On volumes in the paired layout (dco::paired_at) only the even slices
+// are read; for the sub-pixel step the winner's pair partner is gathered and,
+// when it is not the adjacent pair's minimum kept from the scan, its other
+// neighbour.  A thread takes four consecutive pixels with 16-byte loads and
+// walks d = 0 .. D-1; loads of one slice are coalesced across the row, so each
+// volume is read exactly once.  The stage bodies live in dco_device.h.
+#include <algorithm>
+
 #include "dco_device.h"
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_wta(const float* __restrict__ aggL,
-                                             const float* __restrict__ aggR, int P, int D,
-                                             int subpixel, int16_t* __restrict__ dL,
-                                             float* __restrict__ deltaL,
-                                             int16_t* __restrict__ dR) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= P) return;
-    if (blockIdx.y == 0)
-        dco::wta_pixel(aggL, P, D, i, subpixel, dL + i, deltaL + i);
-    else
-        dco::wta_pixel(aggR, P, D, i, subpixel, dR + i, nullptr);
-}
+constexpr int kWtaThreads = 512;  // most threads of a row
 
-__global__ __launch_bounds__(256) void k_wta4(const float* __restrict__ aggL,
-                                              const float* __restrict__ aggR, int P, int D,
-                                              int subpixel, int16_t* __restrict__ dL,
-                                              float* __restrict__ deltaL,
-                                              int16_t* __restrict__ dR) {
-    const int i4 = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i4 >= P) return;
-    if (blockIdx.y == 0)
-        dco::wta_quad(aggL, P, D, i4, subpixel, dL, deltaL);
-    else
-        dco::wta_quad(aggR, P, D, i4, subpixel, dR, nullptr);
-}
-
-__global__ __launch_bounds__(256) void k_wta_pairs(const float* __restrict__ aggL,
-                                                   const float* __restrict__ aggR, int P, int D,
-                                                   int subpixel, int16_t* __restrict__ dL,
-                                                   float* __restrict__ deltaL,
-                                                   int16_t* __restrict__ dR) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= P) return;
-    if (blockIdx.y == 0)
-        dco::wta_pairs_pixel(aggL, P, D, i, subpixel, dL + i, deltaL + i);
-    else
-        dco::wta_pairs_pixel(aggR, P, D, i, subpixel, dR + i, nullptr);
-}
-
-__global__ __launch_bounds__(256) void k_wta_pairs4(const float* __restrict__ aggL,
-                                                    const float* __restrict__ aggR, int P, int D,
-                                                    int subpixel, int16_t* __restrict__ dL,
-                                                    float* __restrict__ deltaL,
-                                                    int16_t* __restrict__ dR) {
-    const int i4 = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i4 >= P) return;
-    if (blockIdx.y == 0)
-        dco::wta_pairs_quad<true>(aggL, P, D, i4, subpixel, dL, deltaL);
-    else
-        dco::wta_pairs_quad<false>(aggR, P, D, i4, subpixel, dR, nullptr);
+// One workgroup per image row: its second half takes the right view's quads of
+// four pixels, the first half the left view's; the right disparities go to LDS
+// for the left-right check, which the left view's threads make on their own
+// quads.  A row of more quads than half a workgroup has threads: the right
+// view's in turns, the left view's rest by all threads after the barrier.  The
+// last quad of a row is moved back to end with it (rows of less than four
+// pixels: kNarrow), so quads may start at any pixel.
+//
+// Bound by the volumes' bytes at large frames (1280 x 720, D = 128: 472 MB read
+// in 0.09 ms) and by the latency of about D / 42 batches of loads at small ones.
+// As a launch per step, with quads only where W H was a multiple of four (else
+// one pixel and one load in flight per thread): frames of 437 x 93, D = 40 took
+// 61.4 us, now 57.0; 64 x 48, D = 16 43.2, now 40.0; 640 x 480, D = 64 168.8,
+// now 167.2; 1280 x 720 the same.  Workgroups of at most 128, 256, 512 and 640
+// threads: 437 x 93 63.0, 57.0, 57.0, 57.2; staged 640 x 480 256, 254, 239, 239
+// (243 before).
+template <bool kPaired, bool kNarrow>
+__global__ __launch_bounds__(kWtaThreads) void k_wta_row(
+    const float* __restrict__ aggL, const float* __restrict__ aggR, int P, int W, int D,
+    int subpixel, int maxdiff, int16_t* __restrict__ dL, int16_t* __restrict__ dR,
+    float* __restrict__ disp, uint8_t* __restrict__ valid) {
+    extern __shared__ int16_t right[];  // W entries
+    const int t = threadIdx.x, half = blockDim.x / 2, nq = (W + 3) / 4;
+    const int row = blockIdx.x * W;
+    const auto start = [&](int q) { return kNarrow ? 0 : min(4 * q, W - 4); };
+    const auto left = [&](int q) {
+        return dco::wta_any<kPaired, true, kNarrow>(aggL, P, D, row + start(q), W, subpixel);
+    };
+    const auto check = [&](int q, const dco::WtaQuad& l) {
+        const int x = start(q), i = row + x;
+        float dv[4];
+        uint8_t ok[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int xr = x + k - l.bd[k];
+            const bool in = xr >= 0 && xr < W && abs(l.bd[k] - (int)right[xr]) <= maxdiff;
+            ok[k] = in ? 1 : 0;
+            dv[k] = in ? (float)l.bd[k] + l.del[k] : 0.0f;
+        }
+        dco::put_bd<kNarrow>(dL + i, l, W);
+        dco::wta_store<kNarrow, dco::f32x4u>(disp + i, dv[0], dv[1], dv[2], dv[3], W);
+        dco::wta_store<kNarrow, dco::u8x4u>(valid + i, ok[0], ok[1], ok[2], ok[3], W);
+    };
+    dco::WtaQuad l{};
+    if (t >= half) {
+        for (int q = t - half; q < nq; q += half) {
+            const int x = start(q);
+            const dco::WtaQuad r =
+                dco::wta_any<kPaired, false, kNarrow>(aggR, P, D, row + x, W, subpixel);
+            dco::put_bd<kNarrow>(right + x, r, W);
+            dco::put_bd<kNarrow>(dR + row + x, r, W);
+        }
+    } else if (t < nq) {
+        l = left(t);
+    }
+    __syncthreads();
+    if (t < half && t < nq) check(t, l);
+    for (int q = half + t; q < nq; q += blockDim.x) check(q, left(q));
 }
 
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded to n x P.
@@ -73,49 +83,20 @@ __global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, i
     out[k] = dco::paired_at(vol, P, D, d0 + s, i);
 }
 
-__global__ __launch_bounds__(256) void k_lrcheck(const int16_t* __restrict__ dL,
-                                                 const float* __restrict__ deltaL,
-                                                 const int16_t* __restrict__ dR, int W, int H,
-                                                 int maxdiff, float* __restrict__ disp,
-                                                 uint8_t* __restrict__ valid) {
-    const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
-    if (x < W) dco::lr_pixel(dL, deltaL, dR, W, x, y, maxdiff, disp, valid);
-}
-
 }  // namespace
 
-hipError_t launch_wta2(const float* aggL, const float* aggR, int W, int H, int D, int subpixel,
-                       int16_t* dL, float* deltaL, int16_t* dR, hipStream_t st) {
-    const int P = W * H;
-    const bool aligned = ((uintptr_t)aggL | (uintptr_t)aggR | (uintptr_t)deltaL) % 16 == 0 &&
-                         ((uintptr_t)dL | (uintptr_t)dR) % 8 == 0;
-    if (P % 4 == 0 && aligned) {
-        dim3 grid((P / 4 + 255) / 256, 2);
-        hipLaunchKernelGGL(k_wta4, grid, dim3(256), 0, st, aggL, aggR, P, D, subpixel, dL, deltaL,
-                           dR);
-    } else {
-        dim3 grid((P + 255) / 256, 2);
-        hipLaunchKernelGGL(k_wta, grid, dim3(256), 0, st, aggL, aggR, P, D, subpixel, dL, deltaL,
-                           dR);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_wta_pairs(const float* aggL, const float* aggR, int W, int H, int D,
-                            int subpixel, int16_t* dL, float* deltaL, int16_t* dR,
-                            hipStream_t st) {
-    const int P = W * H;
-    const bool aligned = ((uintptr_t)aggL | (uintptr_t)aggR | (uintptr_t)deltaL) % 16 == 0 &&
-                         ((uintptr_t)dL | (uintptr_t)dR) % 8 == 0;
-    if (P % 4 == 0 && aligned) {
-        dim3 grid((P / 4 + 255) / 256, 2);
-        hipLaunchKernelGGL(k_wta_pairs4, grid, dim3(256), 0, st, aggL, aggR, P, D, subpixel, dL,
-                           deltaL, dR);
-    } else {
-        dim3 grid((P + 255) / 256, 2);
-        hipLaunchKernelGGL(k_wta_pairs, grid, dim3(256), 0, st, aggL, aggR, P, D, subpixel, dL,
-                           deltaL, dR);
-    }
+hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int W, int H, int D,
+                         int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
+                         uint8_t* valid, hipStream_t st) {
+    const int half = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(H), dim3(2 * half), (size_t)W * sizeof(int16_t), st, aggL,
+                           aggR, W * H, W, D, subpixel, maxdiff, dL, dR, disp, valid);
+    };
+    if (W < 4)
+        paired ? go(k_wta_row<true, true>) : go(k_wta_row<false, true>);
+    else
+        paired ? go(k_wta_row<true, false>) : go(k_wta_row<false, false>);
     return hipGetLastError();
 }
 
@@ -124,13 +105,5 @@ hipError_t launch_unpair(const float* vol, int W, int H, int D, int d0, int n, f
     const size_t total = (size_t)n * W * H;
     hipLaunchKernelGGL(k_unpair, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, vol,
                        W * H, D, d0, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_lrcheck(const int16_t* dL, const float* deltaL, const int16_t* dR, int W,
-                          int H, int maxdiff, float* disp, uint8_t* valid, hipStream_t st) {
-    dim3 grid((W + 255) / 256, H);
-    hipLaunchKernelGGL(k_lrcheck, grid, dim3(256), 0, st, dL, deltaL, dR, W, H, maxdiff, disp,
-                       valid);
     return hipGetLastError();
 }
