@@ -10,7 +10,6 @@ struct dco_contour {
     dco_contour_params p{};
     hipStream_t stream = nullptr;
     ContourBufs b{};
-    float* Mn = nullptr;        // the normalised fused amplitude when the caller wants none
     int* changed_host = nullptr;
     int launches = 0;
 };
@@ -29,8 +28,8 @@ extern "C" dco_status dco_contour_default_params(dco_contour_params* out) {
 
 static void free_contour(dco_contour* h) {
     ContourBufs& b = h->b;
-    void* ptrs[] = {b.fused, b.box_max, b.g2_max, b.g, b.G2, b.state[0], b.state[1], b.changed,
-                    h->Mn};
+    void* ptrs[] = {b.fused, b.box_max, b.g2_max,  b.box,    b.g,
+                    b.strong[0], b.strong[1], b.weak, b.changed};
     for (void* q : ptrs) dev_free(q);
     pinned_free(h->changed_host);
 }
@@ -84,13 +83,14 @@ extern "C" dco_status dco_contour_create(dco_contour** out, int W, int H,
     };
     dco_status st;
     if ((st = dev_alloc(&b.fused, q)) != DCO_OK) return fail(st);
-    if ((st = dev_alloc(&h->Mn, q)) != DCO_OK) return fail(st);
+    if ((st = dev_alloc(&b.box, q)) != DCO_OK) return fail(st);
     if ((st = dev_alloc(&b.box_max, kContourMaxSlots)) != DCO_OK) return fail(st);
     if ((st = dev_alloc(&b.g2_max, kContourMaxSlots)) != DCO_OK) return fail(st);
     if ((st = dev_alloc(&b.g, P)) != DCO_OK) return fail(st);
-    if ((st = dev_alloc(&b.G2, P)) != DCO_OK) return fail(st);
-    if ((st = dev_alloc(&b.state[0], P)) != DCO_OK) return fail(st);
-    if ((st = dev_alloc(&b.state[1], P)) != DCO_OK) return fail(st);
+    const size_t pw = contour_plane_words(W, H);
+    if ((st = dev_alloc(&b.strong[0], pw)) != DCO_OK) return fail(st);
+    if ((st = dev_alloc(&b.strong[1], pw)) != DCO_OK) return fail(st);
+    if ((st = dev_alloc(&b.weak, pw)) != DCO_OK) return fail(st);
     if ((st = dev_alloc(&b.changed, kHystGroup)) != DCO_OK) return fail(st);
     if ((st = pinned_alloc((void**)&h->changed_host, kHystGroup * sizeof(int))) != DCO_OK)
         return fail(st);
@@ -107,18 +107,18 @@ extern "C" dco_status dco_contour_run(dco_contour* h, const uint8_t* rgb, const 
     DCO_TRY(need(B, "B"));
     DCO_TRY(need_align(past, 8, "past"));
     DCO_TRY(need_align(future, 8, "future"));
-    float* mn = Mn ? Mn : h->Mn;
     const dco_contour_params& p = h->p;
     DCO_HIP_CHECK(launch_contour_maps(past, future, h->w, h->h, p.box_radius, rgb, h->W, h->H,
-                                      p.T_high, p.T_low, p.T_depth, h->b, mn, MI, h->stream));
+                                      p.T_high, p.T_low, p.T_depth, h->b, Mn, MI, h->stream));
     // Groups of kHystGroup launches, one host check per group; each launch
     // that changes a pixel turns a weak pixel strong, so at most W H launches
     // change anything.  The first launch that changed nothing read the final
-    // state; it and the launches before it are counted.
+    // state; it and the launches before it are counted, and the launch after
+    // it wrote the contour (one of its own where the group ended first).
     int parity = 0;
     h->launches = 0;
-    for (;;) {
-        DCO_HIP_CHECK(launch_contour_hyst_group(h->b, h->W, h->H, parity, h->stream));
+    for (bool first = true;; first = false) {
+        DCO_HIP_CHECK(launch_contour_hyst_group(h->b, h->W, h->H, parity, first, B, h->stream));
         DCO_HIP_CHECK(hipMemcpyAsync(h->changed_host, h->b.changed, kHystGroup * sizeof(int),
                                      hipMemcpyDeviceToHost, h->stream));
         DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
@@ -127,12 +127,12 @@ extern "C" dco_status dco_contour_run(dco_contour* h, const uint8_t* rgb, const 
         if (k < kHystGroup) {
             h->launches += k + 1;
             parity ^= k & 1;  // the input of launch k
-            break;
+            if (k == kHystGroup - 1)
+                DCO_HIP_CHECK(launch_contour_edges(h->b, h->W, h->H, parity, B, h->stream));
+            return DCO_OK;
         }
-        h->launches += kHystGroup;  // the group's last output is state[parity] again
+        h->launches += kHystGroup;  // the group's last output is strong[parity] again
     }
-    DCO_HIP_CHECK(launch_contour_edges(h->b, h->W, h->H, parity, B, h->stream));
-    return DCO_OK;
 }
 
 extern "C" dco_status dco_contour_launches(dco_contour* h, int* launches) {

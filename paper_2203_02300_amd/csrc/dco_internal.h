@@ -233,9 +233,10 @@ struct ContourBufs {
     float* fused;        // w x h: Eq. 12 before the box filter
     unsigned* box_max;   // largest box mean (float bits), kContourMaxSlots partial maxima
     int* g2_max;         // largest G2, kContourMaxSlots partial maxima
+    float* box;          // w x h: box means before the normalisation
     short2* g;           // W x H Sobel gradients
-    int* G2;             // W x H squared magnitudes
-    uint8_t* state[2];   // W x H: 0 none, 1 weak, 2 strong (hysteresis ping-pong)
+    unsigned long long* strong[2];  // bit planes of 64-pixel words: strong pixels (hysteresis
+    unsigned long long* weak;       //   ping-pong), weak ones
     int* changed;        // kHystGroup flags: set by a hysteresis launch that changed a pixel
 };
 hipError_t launch_contour_maps(const float* past, const float* future, int w, int h, int R,
@@ -243,10 +244,13 @@ hipError_t launch_contour_maps(const float* past, const float* future, int w, in
                                float Tdepth, const ContourBufs& b, float* Mn, float* MI,
                                hipStream_t st);
 // Hysteresis launches go in groups of kHystGroup with one host check per
-// group: launch k of a group does nothing once launch k - 1 changed nothing.
-constexpr int kHystGroup = 4;
-hipError_t launch_contour_hyst_group(const ContourBufs& b, int W, int H, int parity,
-                                     hipStream_t st);
+// group: the launch after the first that changed nothing writes the contour B,
+// the group's others do nothing.  A launch that does nothing takes 1 us, a
+// check 30: eight cover the frames measured.
+constexpr int kHystGroup = 8;
+size_t contour_plane_words(int W, int H);
+hipError_t launch_contour_hyst_group(const ContourBufs& b, int W, int H, int parity, bool first,
+                                     uint8_t* B, hipStream_t st);
 hipError_t launch_contour_edges(const ContourBufs& b, int W, int H, int parity, uint8_t* B,
                                 hipStream_t st);
 // Arms and packed pixels of both views of B pairs (HWC images of 3 W H

@@ -7,11 +7,21 @@
 // gate) is formed with the same IEEE operations, in the same order, as the
 // definition; square roots are correctly rounded (sqrt_rn), so the maps are
 // exact functions of the inputs.  The Sobel gradients are exact integers.
-// Hysteresis grows strong pixels into 8-connected weak ones: each launch
-// iterates inside 64 x 16 tiles in LDS until nothing changes, from one state
-// buffer into the other, and the host repeats launches until a launch
-// changes nothing.  The fixed point is the set of weak pixels connected to a
-// strong one, whatever the order of the growth.
+// Hysteresis grows strong pixels into 8-connected weak ones on bit planes (one
+// 64-bit word per 64 pixels of a row): each launch iterates inside 64 x 16 tiles
+// in registers until nothing changes, from one plane into the other, and the
+// host repeats launches until a launch changes nothing.  The fixed point is the
+// set of weak pixels connected to a strong one, whatever the order of the
+// growth.
+//
+// A frame is a chain of short launches: three for the maps, then a group of
+// kHystGroup hysteresis launches, of which the one after the first that changed
+// nothing writes the contour and the rest do nothing, and one host check.
+// 1280 x 720: the maps 27 us (49 as six launches, the Sobel tiles 64 x 4 with a
+// load per byte: 21 us of them), a hysteresis launch 4 us (9.5 on bytes in
+// LDS), the whole call 81 us (180 with groups of four launches, a check after
+// each, and the contour as a launch after the last).  It is bound by its
+// eleven launches and the check, not by its 30 MB.
 #include "dco_device.h"
 
 namespace {
@@ -100,9 +110,18 @@ __device__ inline T slots_max(const T* slots) {
 }
 
 // Eq. 12 per pixel of the flow grid (equal scores keep the larger amplitude).
+// The first block clears the frame's maxima and the first group's flags.
 __global__ __launch_bounds__(256) void k_fuse(const float2* __restrict__ past,
                                               const float2* __restrict__ future, int w, int h,
-                                              float* __restrict__ fused) {
+                                              float* __restrict__ fused,
+                                              unsigned* __restrict__ box_max,
+                                              int* __restrict__ g2_max,
+                                              int* __restrict__ changed) {
+    if (blockIdx.x == 0 && threadIdx.x < kContourMaxSlots) {
+        box_max[threadIdx.x] = 0u;
+        g2_max[threadIdx.x] = 0;
+        if (threadIdx.x < kHystGroup) changed[threadIdx.x] = 0;
+    }
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= w * h) return;
     const int y = i / w, x = i - y * w;
@@ -113,176 +132,291 @@ __global__ __launch_bounds__(256) void k_fuse(const float2* __restrict__ past,
 
 // Mean over the (2R + 1)^2 window clipped to the grid, summed row by row,
 // left to right; the largest mean goes to *mx (non-negative floats order
-// like their bit patterns, so an integer maximum is exact).
-__global__ __launch_bounds__(256) void k_box(const float* __restrict__ fused, int w, int h, int R,
-                                             float* __restrict__ box, unsigned* __restrict__ mx) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    unsigned bits = 0u;  // the bits of a non-negative float order like the float
-    if (i < w * h) {
-        const int y = i / w, x = i - y * w;
-        float s = 0.0f;
-        int n = 0;
-        for (int yy = max(y - R, 0); yy <= min(y + R, h - 1); ++yy)
-            for (int xx = max(x - R, 0); xx <= min(x + R, w - 1); ++xx) {
-                s += fused[yy * w + xx];
-                ++n;
+// like their bit patterns, so an integer maximum is exact).  kR >= 0: the
+// window size at compile time, so its loads are issued together; a place
+// outside the grid adds zero, which changes no bit of the sum.
+template <int kR>
+__device__ inline unsigned box_pixel(const float* __restrict__ fused, int w, int h, int R, int i,
+                                     float* __restrict__ box) {
+    const int y = i / w, x = i - y * w;
+    float s = 0.0f;
+    if constexpr (kR >= 0) {
+        float v[(2 * kR + 1) * (2 * kR + 1)];
+        int k = 0;
+#pragma unroll
+        for (int dy = -kR; dy <= kR; ++dy)
+#pragma unroll
+            for (int dx = -kR; dx <= kR; ++dx)
+                v[k++] = fused[dco::clampi(y + dy, 0, h - 1) * w + dco::clampi(x + dx, 0, w - 1)];
+        k = 0;
+#pragma unroll
+        for (int dy = -kR; dy <= kR; ++dy)
+#pragma unroll
+            for (int dx = -kR; dx <= kR; ++dx) {
+                const bool in = y + dy >= 0 && y + dy < h && x + dx >= 0 && x + dx < w;
+                s += in ? v[k] : 0.0f;
+                ++k;
             }
-        const float v = s / (float)n;
-        box[i] = v;
-        bits = __float_as_uint(v);
+    } else {
+        for (int yy = max(y - R, 0); yy <= min(y + R, h - 1); ++yy)
+            for (int xx = max(x - R, 0); xx <= min(x + R, w - 1); ++xx) s += fused[yy * w + xx];
     }
-    block_max_to(bits, mx);
+    const int n = (min(y + R, h - 1) - max(y - R, 0) + 1) * (min(x + R, w - 1) - max(x - R, 0) + 1);
+    const float v = s / (float)n;
+    box[i] = v;
+    return __float_as_uint(v);
 }
 
-__global__ __launch_bounds__(256) void k_norm(float* __restrict__ box, int n,
-                                              const unsigned* __restrict__ mx) {
-    const float m = __uint_as_float(slots_max(mx));
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    box[i] = m > 0.0f ? box[i] / m : 0.0f;
-}
+// Sobel of the census grey (replicated borders): gx and gy, exact integers; the
+// largest G2 = gx^2 + gy^2 of the block is returned to each thread's share.
+// One block per 64 x 16 tile: the grey of the tile and a one-pixel ring is
+// computed once into LDS, four pixels (12 bytes) per load where the tile lies
+// inside the image (else pixel by pixel, clamped, which replicates the
+// borders); a thread then takes four rows of one column.
+constexpr int kSobTW = 64, kSobTH = 16;
+constexpr int kSobRW = kSobTW + 4, kSobRH = kSobTH + 2;  // columns x0 - 2 .. x0 + 65
+struct SobelLds {
+    int Y[kSobRH][kSobRW];
+};
 
-// Sobel of the census grey (replicated borders): gx, gy and G2 = gx^2 + gy^2
-// (exact integers); the largest G2 goes to *mx.  One block per 64 x 4 tile:
-// the grey of the tile and a one-pixel ring is computed once into LDS (the
-// ring clamped to the image, which replicates the borders), then each
-// thread reads its 3 x 3 neighbourhood from there.
-constexpr int kSobTW = 64, kSobTH = 4;
-__global__ __launch_bounds__(256) void k_sobel(const uint8_t* __restrict__ rgb, int W, int H,
-                                               short2* __restrict__ g, int* __restrict__ G2,
-                                               int* __restrict__ mx) {
-    constexpr int RW = kSobTW + 2, RH = kSobTH + 2, N = RW * RH;
-    __shared__ int Yt[RH][RW];
-    const int x0 = blockIdx.x * kSobTW, y0 = blockIdx.y * kSobTH, t = threadIdx.x;
-    for (int k = t; k < N; k += 256) {
-        const int ry = k / RW, rx = k - ry * RW;
-        const int xx = dco::clampi(x0 + rx - 1, 0, W - 1), yy = dco::clampi(y0 + ry - 1, 0, H - 1);
-        const size_t q = 3 * ((size_t)yy * W + xx);
-        Yt[ry][rx] = (int)dco::grey_of((uint32_t)rgb[q] | (uint32_t)rgb[q + 1] << 8 |
-                                       (uint32_t)rgb[q + 2] << 16);
+__device__ inline int sobel_tile(const uint8_t* __restrict__ rgb, int W, int H, int x0, int y0,
+                                 short2* __restrict__ g, SobelLds& S) {
+    typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+    typedef u32x3 u32x3u __attribute__((aligned(1)));
+    const int t = threadIdx.x;
+    if (x0 >= 2 && y0 >= 1 && x0 + kSobTW + 2 <= W && y0 + kSobTH + 1 <= H) {
+        for (int k = t; k < kSobRH * (kSobRW / 4); k += 256) {
+            const int ry = k / (kSobRW / 4), c = 4 * (k - ry * (kSobRW / 4));
+            const u32x3 v = *reinterpret_cast<const u32x3u*>(
+                rgb + 3 * ((size_t)(y0 + ry - 1) * W + (x0 + c - 2)));
+            S.Y[ry][c] = (int)dco::grey_of(v.x);
+            S.Y[ry][c + 1] = (int)dco::grey_of(__builtin_amdgcn_alignbyte(v.y, v.x, 3));
+            S.Y[ry][c + 2] = (int)dco::grey_of(__builtin_amdgcn_alignbyte(v.z, v.y, 2));
+            S.Y[ry][c + 3] = (int)dco::grey_of(v.z >> 8);
+        }
+    } else {
+        for (int k = t; k < kSobRH * kSobRW; k += 256) {
+            const int ry = k / kSobRW, c = k - ry * kSobRW;
+            const int xx = dco::clampi(x0 + c - 2, 0, W - 1), yy = dco::clampi(y0 + ry - 1, 0, H - 1);
+            const size_t q = 3 * ((size_t)yy * W + xx);
+            S.Y[ry][c] = (int)dco::grey_of((uint32_t)rgb[q] | (uint32_t)rgb[q + 1] << 8 |
+                                           (uint32_t)rgb[q + 2] << 16);
+        }
     }
     __syncthreads();
-    const int tx = t & (kSobTW - 1), ty = t / kSobTW;
-    const int x = x0 + tx, y = y0 + ty;
-    int v = 0;
-    if (x < W && y < H) {
-        // Yt[ty + 1 + dy][tx + 1 + dx] is the grey at (x + dx, y + dy), clamped
-        const int a = Yt[ty][tx + 2] + 2 * Yt[ty + 1][tx + 2] + Yt[ty + 2][tx + 2] - Yt[ty][tx] -
-                      2 * Yt[ty + 1][tx] - Yt[ty + 2][tx];
-        const int b = Yt[ty + 2][tx] + 2 * Yt[ty + 2][tx + 1] + Yt[ty + 2][tx + 2] - Yt[ty][tx] -
-                      2 * Yt[ty][tx + 1] - Yt[ty][tx + 2];
-        const size_t i = (size_t)y * W + x;
-        g[i] = make_short2((short)a, (short)b);
-        v = a * a + b * b;
-        G2[i] = v;
+    const int tx = t & (kSobTW - 1), ty = t / kSobTW * 4, x = x0 + tx;
+    int best = 0;
+    int l[3], m[3], r[3];  // S.Y[row][tx + 2 + dx] is the grey at x + dx
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        l[k] = S.Y[ty + k][tx + 1];
+        m[k] = S.Y[ty + k][tx + 2];
+        r[k] = S.Y[ty + k][tx + 3];
     }
-    block_max_to(v, mx);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i0 = k % 3, i1 = (k + 1) % 3, i2 = (k + 2) % 3;  // rows above, of, below
+        l[i2] = S.Y[ty + k + 2][tx + 1];
+        m[i2] = S.Y[ty + k + 2][tx + 2];
+        r[i2] = S.Y[ty + k + 2][tx + 3];
+        const int y = y0 + ty + k;
+        if (x < W && y < H) {
+            const int a = r[i0] + 2 * r[i1] + r[i2] - l[i0] - 2 * l[i1] - l[i2];
+            const int b = l[i2] + 2 * m[i2] + r[i2] - l[i0] - 2 * m[i0] - r[i0];
+            g[(size_t)y * W + x] = make_short2((short)a, (short)b);
+            best = max(best, a * a + b * b);
+        }
+    }
+    return best;
 }
 
-// Suppression along the gradient's sector, the depth gate on the flow grid,
-// and the double threshold: state 2 strong, 1 weak, 0 none.  MI = the
-// normalised magnitude sqrt(G2 / max G2).
-__global__ __launch_bounds__(256) void k_nms(const short2* __restrict__ g,
-                                             const int* __restrict__ G2, int W, int H,
-                                             const float* __restrict__ Mn, int w, int h,
-                                             const int* __restrict__ mxp, float Thigh, float Tlow,
-                                             float Tdepth, uint8_t* __restrict__ st,
-                                             float* __restrict__ MI) {
-    const int mx = slots_max(mxp);
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= W * H) return;
-    const int y = i / W, x = i - y * W;
-    const int v = G2[i];
-    if (MI) MI[i] = mx > 0 ? sqrt_rn((float)((double)v / (double)mx)) : 0.0f;
-    const short2 gi = g[i];
-    const int ax = abs((int)gi.x), ay = abs((int)gi.y);
-    int dx, dy;
-    if (128 * ay < 53 * ax) {
-        dx = 1;
-        dy = 0;
-    } else if (128 * ax < 53 * ay) {
-        dx = 0;
-        dy = 1;
-    } else if ((gi.x > 0) == (gi.y > 0)) {
-        dx = 1;
-        dy = 1;
+// The Sobel tiles of the frame (blocks 0 .. nsob - 1) and the box means of the
+// flow grid (the others) in one launch.
+__global__ __launch_bounds__(256) void k_sobel_box(const uint8_t* __restrict__ rgb, int W, int H,
+                                                   short2* __restrict__ g,
+                                                   int* __restrict__ g2_max, int nsob,
+                                                   const float* __restrict__ fused, int w, int h,
+                                                   int R, float* __restrict__ box,
+                                                   unsigned* __restrict__ box_max) {
+    __shared__ SobelLds S;
+    if ((int)blockIdx.x < nsob) {
+        const int nx = (W + kSobTW - 1) / kSobTW;
+        const int by = blockIdx.x / nx, bx = blockIdx.x - by * nx;
+        block_max_to(sobel_tile(rgb, W, H, bx * kSobTW, by * kSobTH, g, S), g2_max);
     } else {
-        dx = 1;
-        dy = -1;
+        const int i = (blockIdx.x - nsob) * 256 + threadIdx.x;
+        unsigned bits = 0u;
+        if (i < w * h)
+            bits = R == 2 ? box_pixel<2>(fused, w, h, R, i, box)
+                          : box_pixel<-1>(fused, w, h, R, i, box);
+        block_max_to(bits, box_max);
     }
-    const int xa = x - dx, ya = y - dy, xb = x + dx, yb = y + dy;
-    const int ga = xa >= 0 && xa < W && ya >= 0 && ya < H ? G2[ya * W + xa] : 0;
-    const int gb = xb >= 0 && xb < W && yb >= 0 && yb < H ? G2[yb * W + xb] : 0;
-    uint8_t s = 0;
-    if (v > ga && v >= gb) {
-        const float gate = Mn[min(y / 2, h - 1) * w + min(x / 2, w - 1)];
-        if (!(gate < Tdepth)) {
+}
+
+__device__ inline int mag2(short2 v) { return (int)v.x * (int)v.x + (int)v.y * (int)v.y; }
+
+// Words of a bit plane's row.
+__host__ __device__ inline int plane_words(int W) { return (W + 63) / 64; }
+
+// Suppression along the gradient's sector, the depth gate on the flow grid,
+// and the double threshold, as bit planes: strong, and weak (above the low
+// threshold only).  MI = the normalised magnitude sqrt(G2 / max G2), Mn = the
+// box means over their maximum (pixel (2 x, 2 y) writes that of (x, y)).  A
+// wavefront takes 64 pixels of a row, a block four rows.
+__global__ __launch_bounds__(256) void k_nms(const short2* __restrict__ g, int W, int H,
+                                             const float* __restrict__ box, int w, int h,
+                                             const unsigned* __restrict__ box_max,
+                                             const int* __restrict__ g2_max, float Thigh,
+                                             float Tlow, float Tdepth,
+                                             unsigned long long* __restrict__ strong,
+                                             unsigned long long* __restrict__ weak,
+                                             float* __restrict__ MI, float* __restrict__ Mn) {
+    const int mx = slots_max(g2_max);
+    const float bm = __uint_as_float(slots_max(box_max));
+    const int x = blockIdx.x * 64 + (threadIdx.x & 63), y = blockIdx.y * 4 + (threadIdx.x >> 6);
+    if (y >= H) return;  // whole wavefronts
+    int s = 0;
+    if (x < W) {
+        const int i = y * W + x;
+        const short2 gi = g[i];
+        const int v = mag2(gi);
+        if (MI) MI[i] = mx > 0 ? sqrt_rn((float)((double)v / (double)mx)) : 0.0f;
+        const int fx = min(x / 2, w - 1), fy = min(y / 2, h - 1);
+        const float bv = box[fy * w + fx];
+        const float gate = bm > 0.0f ? bv / bm : 0.0f;
+        if (Mn && x == 2 * fx && y == 2 * fy) Mn[fy * w + fx] = gate;
+        const int ax = abs((int)gi.x), ay = abs((int)gi.y);
+        int dx, dy;
+        if (128 * ay < 53 * ax) {
+            dx = 1;
+            dy = 0;
+        } else if (128 * ax < 53 * ay) {
+            dx = 0;
+            dy = 1;
+        } else if ((gi.x > 0) == (gi.y > 0)) {
+            dx = 1;
+            dy = 1;
+        } else {
+            dx = 1;
+            dy = -1;
+        }
+        const int xa = x - dx, ya = y - dy, xb = x + dx, yb = y + dy;
+        const int ga = xa >= 0 && xa < W && ya >= 0 && ya < H ? mag2(g[ya * W + xa]) : 0;
+        const int gb = xb >= 0 && xb < W && yb >= 0 && yb < H ? mag2(g[yb * W + xb]) : 0;
+        if (v > ga && v >= gb && !(gate < Tdepth)) {
             const double th = (double)Thigh * (double)Thigh * (double)mx;
             const double tl = (double)Tlow * (double)Tlow * (double)mx;
             const double dv = (double)v;
             s = dv > th ? 2 : (dv > tl ? 1 : 0);
         }
     }
-    st[i] = s;
+    const unsigned long long ms = __ballot(s == 2), mw = __ballot(s == 1);
+    if ((threadIdx.x & 63) == 0) {
+        const size_t q = (size_t)y * plane_words(W) + blockIdx.x;
+        strong[q] = ms;
+        weak[q] = mw;
+    }
 }
 
-// One hysteresis launch: tile + 1-pixel halo from `in` to LDS, grow strong
-// pixels into 8-neighbouring weak ones inside the tile until it is stable,
-// write the tile to `out`; *changed is set if any pixel changed.
-constexpr int kHTW = 64, kHTH = 16;
-
-__global__ __launch_bounds__(256) void k_hyst(const uint8_t* __restrict__ in, int W, int H,
-                                              uint8_t* __restrict__ out,
-                                              const int* __restrict__ prev,
-                                              int* __restrict__ changed) {
-    __shared__ uint8_t T[kHTH + 2][kHTW + 2];
-    // the previous launch of the group changed nothing: the state is final
-    // (the same value for every thread of every block)
-    if (prev && *prev == 0) return;
-    const int x0 = blockIdx.x * kHTW, y0 = blockIdx.y * kHTH;
-    for (int k = threadIdx.x; k < (kHTH + 2) * (kHTW + 2); k += 256) {
-        const int ty = k / (kHTW + 2), tx = k - ty * (kHTW + 2);
-        const int x = x0 + tx - 1, y = y0 + ty - 1;
-        T[ty][tx] = x >= 0 && x < W && y >= 0 && y < H ? in[(size_t)y * W + x] : 0;
-    }
-    __syncthreads();
-    bool any = false;
-    for (;;) {
-        bool grew = false;
-        for (int k = threadIdx.x; k < kHTH * kHTW; k += 256) {
-            const int ty = k / kHTW + 1, tx = k % kHTW + 1;
-            if (T[ty][tx] != 1) continue;
-            const bool hit = T[ty - 1][tx - 1] == 2 || T[ty - 1][tx] == 2 ||
-                             T[ty - 1][tx + 1] == 2 || T[ty][tx - 1] == 2 ||
-                             T[ty][tx + 1] == 2 || T[ty + 1][tx - 1] == 2 ||
-                             T[ty + 1][tx] == 2 || T[ty + 1][tx + 1] == 2;
-            if (hit) {
-                T[ty][tx] = 2;
-                grew = true;
-            }
+// 64 pixels of the contour from their word.
+__device__ inline void put_edges(unsigned long long m, int W, int x0, uint8_t* __restrict__ row) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef u32x4 u32x4u __attribute__((aligned(1)));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t b = (uint32_t)(m >> (16 * k)) & 0xffffu;
+        const int x = x0 + 16 * k;
+        if (x + 16 <= W) {
+            u32x4 o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] = (b >> (4 * j) & 15u) * 0x00204081u & 0x01010101u;
+            *reinterpret_cast<u32x4u*>(row + x) = o;
+        } else {
+            for (int j = 0; j < 16 && x + j < W; ++j) row[x + j] = (uint8_t)(b >> j & 1u);
         }
-        any = any || grew;
-        if (!__syncthreads_or(grew)) break;
     }
-    for (int k = threadIdx.x; k < kHTH * kHTW; k += 256) {
-        const int ty = k / kHTW, tx = k % kHTW;
-        const int x = x0 + tx, y = y0 + ty;
-        if (x < W && y < H) out[(size_t)y * W + x] = T[ty + 1][tx + 1];
-    }
-    if (__syncthreads_or(any) && threadIdx.x == 0) *changed = 1;
 }
 
-__global__ __launch_bounds__(256) void k_edges(const uint8_t* __restrict__ st, int n,
-                                               uint8_t* __restrict__ B) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) B[i] = st[i] == 2;
+// v of the lane before / after in its 16 lanes (a tile's rows); 0 past its ends.
+template <unsigned Ctrl>
+__device__ inline unsigned long long row_shift(unsigned long long v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, Ctrl, 0xf, 0xf,
+                                                              true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), Ctrl,
+                                                              0xf, 0xf, true);
+    return (unsigned long long)hi << 32 | lo;
 }
 
-__global__ void k_zero2(unsigned* a, int* b) {
-    if (threadIdx.x < kContourMaxSlots) {
-        a[threadIdx.x] = 0u;
-        b[threadIdx.x] = 0;
+// The bits of `s` and everything that candidates `c` connect to them along the
+// word, both ways (s within s | c).
+__device__ inline unsigned long long fill_row(unsigned long long s, unsigned long long c) {
+    unsigned long long u = c, d = c, a = s, b = s;
+#pragma unroll
+    for (int k = 1; k < 64; k *= 2) {
+        a |= u & (a << k);
+        u &= u << k;
+        b |= d & (b >> k);
+        d &= d >> k;
     }
+    return a | b;
+}
+
+// One hysteresis launch.  A lane holds one row of a 64 x 16 tile (a wavefront
+// four tiles, one above the other) and grows its strong bits into the weak ones
+// around them until its tiles are stable; strong bits outside the tile count as
+// `in` has them.  *changed is set if any pixel changed.  prev: the flag of the
+// launch before (none for a group's first): if it changed nothing, the state is
+// final, and the first launch to see that writes the contour.
+constexpr int kHystRows = 64;  // rows of a block's four wavefronts, one word each
+
+__global__ __launch_bounds__(256) void k_hyst(const unsigned long long* __restrict__ in,
+                                              const unsigned long long* __restrict__ weak, int W,
+                                              int H, unsigned long long* __restrict__ out,
+                                              const int* __restrict__ prev,
+                                              const int* __restrict__ prev2,
+                                              int* __restrict__ changed,
+                                              uint8_t* __restrict__ B) {
+    const int nw = plane_words(W);
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), y = blockIdx.y * kHystRows + (threadIdx.x & 63);
+    // the same values for every thread of every block
+    const bool final_state = prev && *prev == 0;
+    if (final_state) {
+        if (!(prev2 && *prev2 == 0) && q < nw && y < H)
+            put_edges(in[(size_t)y * nw + q], W, 64 * q, B + (size_t)y * W);
+        return;
+    }
+    if (q >= nw) return;  // whole wavefronts
+    const auto word = [&](int yy, int qq) {
+        return yy >= 0 && yy < H && qq >= 0 && qq < nw ? in[(size_t)yy * nw + qq] : 0ull;
+    };
+    // a row's strong bits and their neighbours along the row, as `in` has them
+    const auto halo = [&](int yy) { return word(yy, q - 1) >> 63 | word(yy, q + 1) << 63; };
+    const auto spread = [](unsigned long long s) { return s | s << 1 | s >> 1; };
+    const unsigned long long c = y < H ? weak[(size_t)y * nw + q] : 0ull;
+    const unsigned long long s0 = word(y, q), side = halo(y);
+    unsigned long long fixed = side;  // neighbours outside the tile
+    if ((y & 15) == 0) fixed |= spread(word(y - 1, q)) | halo(y - 1);
+    if ((y & 15) == 15) fixed |= spread(word(y + 1, q)) | halo(y + 1);
+    unsigned long long s = s0;
+    for (;;) {
+        const unsigned long long n = spread(s) | side;
+        const unsigned long long around = n | row_shift<0x111>(n) | row_shift<0x101>(n) | fixed;
+        const unsigned long long grown = fill_row(s | (c & around), c);
+        const bool grew = grown != s;
+        s = grown;
+        if (!__any(grew)) break;
+    }
+    if (y < H) out[(size_t)y * nw + q] = s;
+    if (__any(s != s0) && (threadIdx.x & 63) == 0) *changed = 1;
+}
+
+__global__ __launch_bounds__(256) void k_edges(const unsigned long long* __restrict__ st, int W,
+                                               int H, uint8_t* __restrict__ B) {
+    const int nw = plane_words(W);
+    const size_t k = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= (size_t)nw * H) return;
+    const int y = (int)(k / nw), q = (int)(k - (size_t)y * nw);
+    put_edges(st[k], W, 64 * q, B + (size_t)y * W);
 }
 
 __global__ void k_zero1(int* a, int n) {
@@ -297,37 +431,43 @@ hipError_t launch_contour_maps(const float* past, const float* future, int w, in
                                const uint8_t* rgb, int W, int H, float Thigh, float Tlow,
                                float Tdepth, const ContourBufs& b, float* Mn, float* MI,
                                hipStream_t st) {
-    hipLaunchKernelGGL(k_zero2, dim3(1), dim3(kContourMaxSlots), 0, st, b.box_max, b.g2_max);
+    static_assert(kHystGroup <= kContourMaxSlots, "the clearing block covers the flags");
     hipLaunchKernelGGL(k_fuse, grid1(w * h), dim3(256), 0, st,
                        reinterpret_cast<const float2*>(past),
-                       reinterpret_cast<const float2*>(future), w, h, b.fused);
-    hipLaunchKernelGGL(k_box, grid1(w * h), dim3(256), 0, st, b.fused, w, h, R, Mn, b.box_max);
-    hipLaunchKernelGGL(k_norm, grid1(w * h), dim3(256), 0, st, Mn, w * h, b.box_max);
-    hipLaunchKernelGGL(k_sobel, dim3((W + kSobTW - 1) / kSobTW, (H + kSobTH - 1) / kSobTH),
-                       dim3(256), 0, st, rgb, W, H, b.g, b.G2, b.g2_max);
-    hipLaunchKernelGGL(k_nms, grid1(W * H), dim3(256), 0, st, b.g, b.G2, W, H, Mn, w, h, b.g2_max,
-                       Thigh, Tlow, Tdepth, b.state[0], MI);
+                       reinterpret_cast<const float2*>(future), w, h, b.fused, b.box_max, b.g2_max,
+                       b.changed);
+    const int nsob = (W + kSobTW - 1) / kSobTW * ((H + kSobTH - 1) / kSobTH);
+    hipLaunchKernelGGL(k_sobel_box, dim3(nsob + (w * h + 255) / 256), dim3(256), 0, st, rgb, W, H,
+                       b.g, b.g2_max, nsob, b.fused, w, h, R, b.box, b.box_max);
+    hipLaunchKernelGGL(k_nms, dim3(plane_words(W), (H + 3) / 4), dim3(256), 0, st, b.g, W, H,
+                       b.box, w, h, b.box_max, b.g2_max, Thigh, Tlow, Tdepth, b.strong[0], b.weak,
+                       MI, Mn);
     return hipGetLastError();
 }
 
-// Launch k of the group reads state[parity ^ (k & 1)] and writes the other
-// buffer; kHystGroup is even, so the group's last output is state[parity].
-hipError_t launch_contour_hyst_group(const ContourBufs& b, int W, int H, int parity,
-                                     hipStream_t st) {
+size_t contour_plane_words(int W, int H) { return (size_t)plane_words(W) * H; }
+
+// Launch k of the group reads strong[parity ^ (k & 1)] and writes the other
+// plane; kHystGroup is even, so the group's last output is strong[parity].
+hipError_t launch_contour_hyst_group(const ContourBufs& b, int W, int H, int parity, bool first,
+                                     uint8_t* B, hipStream_t st) {
     static_assert(kHystGroup % 2 == 0 && kHystGroup <= 64, "even group, one flag per lane");
-    hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, st, b.changed, kHystGroup);
-    const dim3 grid((W + kHTW - 1) / kHTW, (H + kHTH - 1) / kHTH);
+    if (!first)  // the first group's flags are cleared with the maps
+        hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, st, b.changed, kHystGroup);
+    const dim3 grid((plane_words(W) + 3) / 4, (H + kHystRows - 1) / kHystRows);
     for (int k = 0; k < kHystGroup; ++k) {
         const int p = parity ^ (k & 1);
-        hipLaunchKernelGGL(k_hyst, grid, dim3(256), 0, st, b.state[p], W, H, b.state[1 - p],
-                           k ? (const int*)(b.changed + k - 1) : (const int*)nullptr,
-                           b.changed + k);
+        const int* none = nullptr;
+        hipLaunchKernelGGL(k_hyst, grid, dim3(256), 0, st, b.strong[p], b.weak, W, H,
+                           b.strong[1 - p], k > 0 ? (const int*)(b.changed + k - 1) : none,
+                           k > 1 ? (const int*)(b.changed + k - 2) : none, b.changed + k, B);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_contour_edges(const ContourBufs& b, int W, int H, int parity, uint8_t* B,
                                 hipStream_t st) {
-    hipLaunchKernelGGL(k_edges, grid1(W * H), dim3(256), 0, st, b.state[parity], W * H, B);
+    hipLaunchKernelGGL(k_edges, dim3((unsigned)((contour_plane_words(W, H) + 255) / 256)),
+                       dim3(256), 0, st, b.strong[parity], W, H, B);
     return hipGetLastError();
 }
