@@ -574,9 +574,10 @@ static dco_status soft_reserve(dco_stereo* h, int B) {
 }
 
 // Arms and packed pixels of every pair, the Eq. 1 tables for theta,
-// region counts, and the aggregated volume A2 (vol[0]).
+// region counts, the aggregated volume A2 (vol[0]), and dhat and lse where
+// given.
 static dco_status soft_front(dco_stereo* h, int B, const uint8_t* L, const uint8_t* R,
-                             const float* theta, SoftBuffers* sb) {
+                             const float* theta, float* dhat, float* lse, SoftBuffers* sb) {
     SoftScratch& f = h->soft;
     const dco_params& p = h->p;
     f.held = false;
@@ -587,7 +588,8 @@ static dco_status soft_front(dco_stereo* h, int B, const uint8_t* L, const uint8
                                f.vrec, f.rn1, f.n2, h->stream));
     *sb = SoftBuffers{f.arms, f.vrec, f.rn1, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
     DCO_HIP_CHECK(
-        soft_aggregate(*sb, B, h->W, h->H, h->D, f.vol[0], f.vol[1], f.vol[2], h->stream));
+        soft_aggregate(*sb, B, h->W, h->H, h->D, f.vol[0], f.vol[1], f.vol[2], theta, dhat, lse,
+                       h->stream));
     f.held = true;
     f.held_B = B;
     f.held_L = L;
@@ -625,9 +627,7 @@ extern "C" dco_status dco_soft_forward(dco_stereo* h, int B, const uint8_t* L, c
     DCO_TRY(need(lse, "lse"));
     DCO_TRY(soft_reserve(h, B));
     SoftBuffers sb;
-    DCO_TRY(soft_front(h, B, L, R, theta, &sb));
-    DCO_HIP_CHECK(soft_argmin(sb, B, h->W, h->H, h->D, h->soft.vol[0], theta, dhat, lse,
-                              h->stream));
+    DCO_TRY(soft_front(h, B, L, R, theta, dhat, lse, &sb));
     return DCO_OK;
 }
 
@@ -644,7 +644,7 @@ extern "C" dco_status dco_soft_backward(dco_stereo* h, int B, const uint8_t* L, 
     DCO_TRY(need(grad_theta, "grad_theta"));
     DCO_TRY(soft_reserve(h, B));
     SoftBuffers sb;
-    DCO_TRY(soft_front(h, B, L, R, theta, &sb));  // recompute the aggregation
+    DCO_TRY(soft_front(h, B, L, R, theta, nullptr, nullptr, &sb));  // recompute the aggregation
     SoftScratch& f = h->soft;
     DCO_HIP_CHECK(soft_backward(sb, B, h->W, h->H, h->D, f.vol[0], theta, dhat, lse, grad_dhat,
                                 f.vol[1], f.vol[2], f.partAC, f.partT, grad_theta, h->stream));
@@ -672,7 +672,7 @@ extern "C" dco_status dco_soft_backward_reuse(dco_stereo* h, int B, const uint8_
         f.held_stream == h->stream)
         sb = SoftBuffers{f.arms, f.vrec, f.rn1, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
     else
-        DCO_TRY(soft_front(h, B, L, R, theta, &sb));
+        DCO_TRY(soft_front(h, B, L, R, theta, nullptr, nullptr, &sb));
     DCO_HIP_CHECK(soft_backward(sb, B, h->W, h->H, h->D, f.vol[0], theta, dhat, lse, grad_dhat,
                                 f.vol[1], f.vol[2], f.partAC, f.partT, grad_theta, h->stream));
     return DCO_OK;

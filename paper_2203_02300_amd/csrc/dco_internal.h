@@ -295,9 +295,8 @@ hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, in
                         int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2,
                         hipStream_t st);
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
-                          float* t2, hipStream_t st);
-hipError_t soft_argmin(const SoftBuffers& s, int B, int W, int H, int D, const float* A2,
-                       const float* theta, float* dhat, float* lse, hipStream_t st);
+                          float* t2, const float* theta, float* dhat, float* lse,
+                          hipStream_t st);
 hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const float* A2,
                          const float* theta, const float* dhat, const float* lse,
                          const float* gdhat, float* t1, float* t2, double* partAC,

@@ -6,17 +6,16 @@
 //   E1 = row range sum of c       a1 = (column range sum of E1) / N1     (Eq. 2, stage 1)
 //   E2 = column range sum of a1   A2 = (row range sum of E2) / N2         (Eq. 2, stage 2)
 //   dhat = sum_d d softmax_d(-A2 / T),  lse = log sum_d exp(-A2 / T)
-// The range sums of E1 are exact sums of fixed-point costs on the matrix cores,
-// the others differences of two FP64 prefix sums (along the row, or running
-// down the column), so each is within one FP32 rounding of the exact sum of its
-// FP32 terms.  Every sum runs in a fixed order, so results are
-// bit-reproducible.
+// The row sums are exact sums of fixed-point values on the matrix cores, the
+// column sums differences of two FP64 prefix sums running down the column, so
+// each is within one FP32 rounding of the exact sum of its FP32 terms.  Every
+// sum runs in a fixed order, so results are bit-reproducible.
 //
 // Backward, given g = dLoss/d dhat:
 //   G_A2  = g w (dhat - d) / T,   dLoss/dT = sum g w (d - dhat) A2 / T^2
 // then the adjoint of each range sum: an output that summed a range hands its
 // adjoint back to every pixel of that range.  The first row adjoint is an exact
-// product of fixed-point G with the transposed band (k_soft_madj); column
+// product of fixed-point G with the transposed band (k_soft_wide); column
 // adjoints are FP64 difference arrays streamed down each column by one thread.
 // The last row adjoint is never formed: with
 // E1 = H c,  sum_p (H^T G)(p) dc/dlambda(p) = sum_x G(x) (H dc/dlambda)(x),
@@ -27,18 +26,16 @@
 // thread makes to its own column in program order.
 //
 // Layout: volumes are B x D x H x W float in handle scratch; arms and the
-// packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost and
-// adjoint row passes run one wavefront per image row and 16 disparities
-// (k_soft_mrow, k_soft_madj), the A2 row pass one per image row and disparity
-// with its FP64 prefix in LDS; the column pass runs one thread per column, streaming down the rows with two
-// rings of FP64 sums in LDS (k_soft_vv).
+// packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost and row
+// passes run one wavefront per image row and 16 disparities (k_soft_mrow,
+// k_soft_wide); the column pass runs one thread per column, streaming down the
+// rows with two rings of FP64 sums in LDS (k_soft_vv).
 #include <algorithm>
 #include <type_traits>
 
 #include "dco_internal.h"
 
 namespace {
-
 
 struct SoftGeom {
     const uint32_t* arms;  // B x H x W packed arms of the left view
@@ -156,30 +153,6 @@ struct SoftImg {
     const float* tab;    // k_soft_tables output
 };
 
-// Row passes: one wavefront per image row, kRowWaves wavefronts per
-// workgroup, each with its own LDS slice (no workgroup barriers after the
-// table load) and kRowsPerWave rows in turn.  Row ids run over (b, y, d)
-// with d fastest, so the rows that run together share one image row (its
-// pixels, arms and counts stay in cache across the disparities).  Outside
-// the prefix phase (which has its own layout, see prefix_row) lane `lane`
-// handles columns lane + 64 k; loads are issued
-// kRowBatch columns at a time with clamped (always valid) addresses.
-constexpr int kRowWaves = 4;
-constexpr int kRowsPerWave = 4;
-constexpr int kRowBatch = 8;
-
-// Runs body(nb, x0) over a row of W columns in batches of 64 NB columns
-// (NB = decltype(nb)::value): batches of kMax while they fit, then of 2, then
-// of 1 (the last may run past W; the body masks those lanes).  A row of 640
-// columns takes one batch of 8 and one of 2, not two of 8.
-template <int kMax = kRowBatch, typename Body>
-__device__ inline void over_row(int W, Body body) {
-    int x0 = 0;
-    for (; x0 + 64 * kMax <= W; x0 += 64 * kMax) body(std::integral_constant<int, kMax>{}, x0);
-    for (; x0 + 64 * 2 <= W; x0 += 64 * 2) body(std::integral_constant<int, 2>{}, x0);
-    for (; x0 < W; x0 += 64) body(std::integral_constant<int, 1>{}, x0);
-}
-
 // Workgroup index in the row order of workgroup b of n: the workgroups one
 // XCD runs (round-robin dispatch, b mod 8) take a contiguous run, so the
 // workgroups that share an image row share that XCD's L2.
@@ -187,152 +160,6 @@ __device__ inline int xcd_block(int b, int n) {
     const int xcd = b & 7, i = b >> 3;
     const int per = n >> 3, rem = n & 7;
     return xcd < rem ? xcd * (per + 1) + i : rem * (per + 1) + (xcd - rem) * per + i;
-}
-
-__device__ inline void row_of(int rid, int D, int H, int& b, int& d, int& y) {
-    d = rid % D;
-    const int by = rid / D;
-    y = by % H;
-    b = by / H;
-}
-
-template <unsigned Ctrl, unsigned RowMask>
-__device__ inline double dpp_f64(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, Ctrl, RowMask,
-                                                              0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), Ctrl,
-                                                              RowMask, 0xf, false);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-
-__device__ inline double readlane_f64(double v, int l) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-
-// FP64 inclusive scan across the wavefront (lane L gets v(0) + ... + v(L)):
-// DPP row shifts 1, 2, 4, 8, then the row broadcasts of lanes 15 and 31.
-__device__ inline double wave_scan_f64(double v) {
-    v += dpp_f64<0x111, 0xf>(v);
-    v += dpp_f64<0x112, 0xf>(v);
-    v += dpp_f64<0x114, 0xf>(v);
-    v += dpp_f64<0x118, 0xf>(v);
-    v += dpp_f64<0x142, 0xa>(v);
-    v += dpp_f64<0x143, 0xc>(v);
-    return v;
-}
-
-// The prefix phase of a row pass works on 256-column chunks in which lane
-// `lane` owns the four consecutive columns x0 + 4 lane .. x0 + 4 lane + 3:
-// a lane prefixes its four values in FP64, one wavefront scan over the lane
-// totals places them, so a chunk costs one FP64 scan per four columns instead
-// of one per column.
-constexpr int kPreChunk = 256;
-
-// Writes P[x + k + 1] (x = the lane's first column, k < 4, x + k < W) for one
-// chunk from the lane's four values (zero past the row's end), given the
-// row's sum before the chunk; returns the row's sum up to the chunk's end.
-__device__ inline double chunk_prefix(const float (&v)[4], int x, int W, double carry, double* P) {
-    double s[4];
-    s[0] = (double)v[0];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) s[k] = s[k - 1] + (double)v[k];
-    const double inc = wave_scan_f64(s[3]);
-    const double base = carry + (inc - s[3]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (x + k < W) P[x + k + 1] = base + s[k];
-    return carry + readlane_f64(inc, 63);
-}
-
-// FP64 prefixes of the wavefront's row (W <= 2048): P[0] = 0 and
-// P[x + 1] = src(0) + ... + src(x).  Fixed order, bit-reproducible.
-__device__ inline void prefix_row(const float* src, int W, double* P) {
-    const int lane = threadIdx.x & 63;
-    double carry = 0.0;
-    if (lane == 0) P[0] = 0.0;
-    const bool vec = (W & 3) == 0;  // 16-byte aligned rows
-    for (int x0 = 0; x0 < W; x0 += kPreChunk) {
-        const int x = x0 + 4 * lane;
-        float v[4];
-        if (vec) {
-            const float4 q = *reinterpret_cast<const float4*>(src + min(x, W - 4));
-            v[0] = q.x;
-            v[1] = q.y;
-            v[2] = q.z;
-            v[3] = q.w;
-        } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = src[min(x + k, W - 1)];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = x + k < W ? v[k] : 0.0f;
-        carry = chunk_prefix(v, x, W, carry, P);
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Bytes of dynamic LDS per wavefront: one FP64 prefix.
-__host__ __device__ inline size_t prefix_bytes(int W) {
-    return ((size_t)(W + 1) * 8 + 15) / 16 * 16;
-}
-inline size_t row_lds_fwd(int W) { return prefix_bytes(W); }
-
-// Lets a kernel take `bytes` of dynamic LDS (above the default limit for
-// wide rows).
-inline hipError_t allow_lds(const void* kernel, size_t bytes) {
-    return bytes > 48 * 1024 ? hipFuncSetAttribute(kernel,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   (int)bytes)
-                             : hipSuccess;
-}
-
-// Second forward row pass: A2(x) = (sum of E2 over [x - l, x + r]) / N2(x).
-__global__ __launch_bounds__(64 * kRowWaves) void k_soft_hrow(SoftGeom g,
-                                                              const float* __restrict__ in,
-                                                              float* __restrict__ out,
-                                                              size_t lds_wave) {
-    extern __shared__ __align__(16) unsigned char dyn[];
-    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63,
-              W = g.W;
-    double* Pf = reinterpret_cast<double*>(dyn + w * lds_wave);
-    const size_t P = (size_t)W * g.H;
-    const int nrows = g.B * g.D * g.H;
-    const int r0 = ((int)blockIdx.x * kRowWaves + w) * kRowsPerWave;
-    for (int rid = r0; rid < min(nrows, r0 + kRowsPerWave); ++rid) {
-        int b, d, y;
-        row_of(rid, g.D, g.H, b, d, y);
-        const size_t base = ((size_t)b * g.D + d) * P + (size_t)y * W;
-        const size_t pix = b * P + (size_t)y * W;
-        prefix_row(in + base, W, Pf);
-        // the row's arrays through row pointers (uniform), indexed by column
-        const uint32_t* __restrict__ ar = g.arms + pix;
-        const float* __restrict__ nr = g.n2 + pix;
-        float* __restrict__ orow = out + base;
-        over_row(W, [&](auto nb, int x0) {
-            constexpr int NB = decltype(nb)::value;
-            uint32_t a[NB];
-            float n[NB];
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int xc = min(x0 + 64 * j + lane, W - 1);
-                a[j] = ar[xc];
-                n[j] = nr[xc];
-            }
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int x = x0 + 64 * j + lane;
-                if (x < W) {
-                    const float v = (float)(Pf[x + arm(a[j], 1) + 1] - Pf[x - arm(a[j], 0)]);
-                    orow[x] = v * __builtin_amdgcn_rcpf(n[j]);
-                }
-            }
-        });
-        __builtin_amdgcn_wave_barrier();
-    }
 }
 
 // Row sums of the costs (and of their lambda derivatives) on the matrix cores.
@@ -658,17 +485,26 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
 // rounding of the product adds a relative error of about |x| 2^-24.
 __device__ inline float exp_e(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
-// Backward seed and adjoint row pass.  Per pixel and disparity, with
+// Row sums of values that span many binades, as wider fixed-point products.
+//
+// Forward: A2(x, d) = (sum of E2 over [x - l, x + r]) / N2(x), and, where the
+// workgroup's wavefronts hold all disparities (dhat given, D <= 64), the soft
+// argmin: each wavefront's 16 disparities give a maximum and two sums per column,
+// merged one block later.
+//
+// Adjoint: the seed and the transposed sums.  Per pixel and disparity, with
 // w = softmax weight and g = dLoss/d dhat:
 //   G(x, d) = G_A2 / N2 = g w (dhat - d) / (T N2),
 //   dLoss/dT term = g w (d - dhat) A2 / T^2;
 // out(p, d) = sum_x [x - l(x) <= p <= x + r(x)] G(x, d), the adjoint of A2's row
-// range sums (G_E2): the transposed band, as a product like k_soft_mrow's and on
-// the same blocks.  G spans many binades, so its fixed point is wider: q = G 2^k
-// in two 24-bit halves of three digits each, with 2^k set by the largest |G| the
-// wavefront has met in its row (2^-45 of it is kept).  Where a block raises that
+// range sums (G_E2): the transposed band.
+//
+// Both run as k_soft_mrow, on the same blocks, with a wider fixed point of the
+// value G (E2 in the forward): q = G 2^k in two 24-bit halves of three digits
+// each, with 2^k set by the largest |G| the wavefront has met in its row (2^-45
+// of it is kept).  Where a block raises that
 // bound, its outputs add the block before in the old scale: two products apart.
-// The bytes of a lane's 16 pixels x come four at a time: with e = x - p, l - e and
+// The adjoint's bytes of a lane's 16 pixels x come four at a time: with e = x - p, l - e and
 // r + e are not negative, tested in bit 7 of biased bytes.
 //
 // The temperature terms of the wavefront's row and disparities are summed into
@@ -703,15 +539,18 @@ __device__ inline void digit_planes3(const uint32_t* stage, v4i (&b)[3]) {
     }
 }
 
-__global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
-    SoftGeom g, const float* __restrict__ A2, const float* __restrict__ theta,
-    const float* __restrict__ dhat, const float* __restrict__ lse,
-    const float* __restrict__ gdhat, float* __restrict__ out, double* __restrict__ partT,
-    int seg_its) {
+template <bool kAdj>
+__global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
+    SoftGeom g, const float* __restrict__ in, const float* __restrict__ theta,
+    float* __restrict__ dhat, float* __restrict__ lse, const float* __restrict__ gdhat,
+    float* __restrict__ out, double* __restrict__ partT, int seg_its) {
     __shared__ v4i bands[2][8][64];
     __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
-    // l + 1 and r of the columns of this block and the one before, a byte each
-    __shared__ __align__(16) uint32_t arml[kMxWaves][2][16], armr[kMxWaves][2][16];
+    // adjoint: l + 1 and r of the columns of this block and the one before, a byte each
+    __shared__ __align__(16) uint32_t arml[kAdj ? kMxWaves : 1][2][16],
+        armr[kAdj ? kMxWaves : 1][2][16];
+    // forward: the wavefronts' softmax sums of a block's columns
+    __shared__ float soft[2][kAdj ? 1 : kMxWaves][3][64];
     const int nt = blockDim.x, nw = nt >> 6;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 15, kg = lane >> 4;
@@ -735,11 +574,33 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
         int ex = -100;               // |G| <= 2^ex so far
         bool bad = false;            // a G was not finite
         // the block before a segment's first only gives its digits
+        const auto merge = [&](int it, int buf) {
+            // dhat and lse of block it's columns from the wavefronts' sums
+            const int x = (it << 6) - 32 + lane;
+            float m = -INFINITY, z = 0.0f, zd = 0.0f;
+            for (int k = 0; k < nw; ++k) m = fmaxf(m, soft[buf][k][0][lane]);
+            for (int k = 0; k < nw; ++k) {
+                const float sc = exp_e(soft[buf][k][0][lane] - m);
+                z += sc * soft[buf][k][1][lane];
+                zd += sc * soft[buf][k][2][lane];
+            }
+            if (x >= 0 && x < W) {
+                dhat[pix + x] = zd / z;
+                lse[pix + x] = m + logf(z);
+            }
+        };
         for (int it = max(it0 - 1, 0), first = it; it < it1; ++it, par ^= 1) {
             const int X = it << 6;
             const int xc = min(X + lane, W - 1);
-            const bool in = X + lane < W;
-            {
+            const bool in_row = X + lane < W;
+            if constexpr (!kAdj) {
+                for (int c = w; c < 8; c += nw) {
+                    const int x = X - 32 + 16 * (c >> 1) + n;
+                    const uint32_t a = g.arms[pix + min(max(x, 0), W - 1)];
+                    bands[par][c][lane] = band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
+                                                     X - 64 + 64 * (c & 1) + 16 * kg);
+                }
+            } else {
                 const uint32_t a = X < W ? g.arms[pix + xc] : 0u;
                 reinterpret_cast<uint8_t*>(arml[w][it & 1])[lane] = (uint8_t)(arm(a, 0) + 1);
                 reinterpret_cast<uint8_t*>(armr[w][it & 1])[lane] = (uint8_t)arm(a, 1);
@@ -760,16 +621,18 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
             uint32_t lo[16];
             const int ex_old = ex;
             if (active && X < W) {
-                const float gp = in ? gdhat[pix + xc] : 0.0f, dh = dhat[pix + xc];
-                const float ls = lse[pix + xc];
-                const float g1 = gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc]);
+                const float gp = kAdj && in_row ? gdhat[pix + xc] : 0.0f;
+                const float dh = kAdj ? dhat[pix + xc] : 0.0f;
+                const float ls = kAdj ? lse[pix + xc] : 0.0f;
+                const float g1 = kAdj ? gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc])
+                                      : (in_row ? 1.0f : 0.0f);
                 const float dh0 = dh - (float)d0;
                 float G[16];
                 uint32_t m = 0;  // bits of the largest |G| (a NaN's are larger still)
                 double t = 0.0;
                 size_t Pv = P;
                 asm volatile("" : "+s"(Pv));  // else 16 row addresses live in registers
-                const float* a2 = A2 + vol + (size_t)d0 * Pv + xc;
+                const float* a2 = in + vol + (size_t)d0 * Pv + xc;
                 const auto seed = [&](auto full) {
                     constexpr bool kFull = decltype(full)::value;
 #pragma unroll
@@ -779,10 +642,14 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
                     }
 #pragma unroll
                     for (int j = 0; j < 16; ++j) {
-                        const float u = exp_e(-G[j] * invT - ls) * (dh0 - (float)j);
                         const bool on = kFull || d0 + j < D;
-                        t += (double)(on ? gp * u * G[j] : 0.0f);
-                        G[j] = on ? g1 * u : 0.0f;
+                        if constexpr (kAdj) {
+                            const float u = exp_e(-G[j] * invT - ls) * (dh0 - (float)j);
+                            t += (double)(on ? gp * u * G[j] : 0.0f);
+                            G[j] = on ? g1 * u : 0.0f;
+                        } else {
+                            G[j] = in_row && on ? G[j] : 0.0f;
+                        }
                         m = max(m, __float_as_uint(G[j]) & 0x7fffffffu);
                     }
                 };
@@ -790,7 +657,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
                     seed(std::true_type{});
                 else
                     seed(std::false_type{});
-                if (it >= it0) acc -= t;
+                if (kAdj && it >= it0) acc -= t;
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
                 m = __builtin_amdgcn_readfirstlane(m);
@@ -806,7 +673,14 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
                 __builtin_amdgcn_wave_barrier();
             }
             __syncthreads();  // the bands; the buffer's next writers pass the next one first
-            if (!active) continue;
+            if (!kAdj && dhat && it > it0 && w == it % nw) merge(it - 1, par ^ 1);
+            if (!active) {
+                if (!kAdj && dhat) {
+                    soft[par][w][0][lane] = -INFINITY;
+                    soft[par][w][1][lane] = soft[par][w][2][lane] = 0.0f;
+                }
+                continue;
+            }
             v4i bc[2][3];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -871,6 +745,34 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
                 else
                     outputs(std::true_type{});
                 __builtin_amdgcn_wave_barrier();
+                if constexpr (!kAdj) {
+                    // A2 = sum / N2, and the softmax sums of the wavefront's 16
+                    // disparities for each column
+                    const float rn = __builtin_amdgcn_rcpf(
+                        g.n2[pix + min(max(X - 32 + lane, 0), W - 1)]);
+                    float v[16], m = -INFINITY, z = 0.0f, zd = 0.0f;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        uint32_t* q = stage + j * kMxStride + lane;
+                        const float a = __builtin_bit_cast(float, *q) * rn;
+                        *q = __builtin_bit_cast(uint32_t, a);
+                        v[j] = -a * invT;
+                    }
+                    if (dhat) {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) m = d0 + j < D ? fmaxf(m, v[j]) : m;
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) {
+                            const float e = d0 + j < D ? exp_e(v[j] - m) : 0.0f;
+                            z += e;
+                            zd += (float)j * e;
+                        }
+                        soft[par][w][0][lane] = m;
+                        soft[par][w][1][lane] = z;
+                        soft[par][w][2][lane] = zd + (float)d0 * z;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
                 put_rows(stage, out + vol, P, d0, D, X - 32, W);
                 __builtin_amdgcn_wave_barrier();
             }
@@ -879,7 +781,11 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_madj(
 #pragma unroll
                 for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
         }
-        if (active) {
+        if (!kAdj && dhat) {
+            __syncthreads();
+            if (w == 0) merge(it1 - 1, par ^ 1);
+        }
+        if (kAdj && active) {
             for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
             if (lane == 0)
                 partT[((size_t)row * gridDim.y + blockIdx.y) * ng + grp] =
@@ -1261,31 +1167,26 @@ hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, in
     return hipGetLastError();
 }
 
-// Forward aggregation into A2 (B x D x H x W); t1, t2 are volume-sized scratch.
+// Forward aggregation into A2 (B x D x H x W), and the soft argmin where dhat
+// (and lse) are given; t1, t2 are volume-sized scratch.
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
-                          float* t2, hipStream_t st) {
+                          float* t2, const float* theta, float* dhat, float* lse,
+                          hipStream_t st) {
     SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
-    const int nrows = B * D * H;
-    const dim3 gr((nrows + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave));
-    const size_t lf = row_lds_fwd(W);
-    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_soft_hrow), kRowWaves * lf);
-    if (e != hipSuccess) return e;
     const RowGrid rg = row_grid(g);
     hipLaunchKernelGGL(k_soft_mrow<false>, rg.grid, rg.block, 0, st, g, im, (const float*)nullptr,
                        t1, (double*)nullptr, rg.seg);                                        // E1
     launch_vv<false>(g, t1, t2, st);                                                         // E2
-    hipLaunchKernelGGL(k_soft_hrow, gr, dim3(64 * kRowWaves), kRowWaves * lf, st, g, t2, A2,
-                       lf);                                                                  // A2
-    return hipGetLastError();
-}
-
-hipError_t soft_argmin(const SoftBuffers& s, int B, int W, int H, int D, const float* A2,
-                       const float* theta, float* dhat, float* lse, hipStream_t st) {
-    SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
-    const size_t P = (size_t)W * H;
-    hipLaunchKernelGGL(k_soft_argmin, dim3((unsigned)((P + 255) / 256), B), dim3(256), 0, st, g,
-                       A2, theta, dhat, lse);
+    const bool soft = dhat && D <= 16 * kMxWaves;
+    hipLaunchKernelGGL(k_soft_wide<false>, rg.grid, rg.block, 0, st, g, t2, theta,
+                       soft ? dhat : nullptr, lse, (const float*)nullptr, A2, (double*)nullptr,
+                       rg.seg);                                                              // A2
+    if (dhat && !soft) {
+        const size_t P = (size_t)W * H;
+        hipLaunchKernelGGL(k_soft_argmin, dim3((unsigned)((P + 255) / 256), B), dim3(256), 0, st,
+                           g, A2, theta, dhat, lse);
+    }
     return hipGetLastError();
 }
 
@@ -1298,8 +1199,9 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const RowGrid rg = row_grid(g);
-    hipLaunchKernelGGL(k_soft_madj, rg.grid, rg.block, 0, st, g, A2, theta, dhat, lse, gdhat, t2,
-                       partT, rg.seg);                                // G_E2, T-gradient terms
+    hipLaunchKernelGGL(k_soft_wide<true>, rg.grid, rg.block, 0, st, g, A2, theta,
+                       const_cast<float*>(dhat), const_cast<float*>(lse), gdhat, t2, partT,
+                       rg.seg);                                // G_E2, T-gradient terms
     launch_vv<true>(g, t2, t1, st);                                   // G_E1
     hipLaunchKernelGGL(k_soft_mrow<true>, rg.grid, rg.block, 0, st, g, im, t1, (float*)nullptr,
                        partAC, rg.seg);                               // G_E1 . H dc/dlambda
