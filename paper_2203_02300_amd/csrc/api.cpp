@@ -160,7 +160,7 @@ static void free_handle_memory(dco_stereo* h) {
                     h->s.dint[1],    h->s.vote[0],    h->s.vote[1],
                     h->s.half[0],    h->s.half[1],
                     h->soft.pix[0],  h->soft.pix[1],
-                    h->soft.arms,    h->soft.vrec,  h->soft.rn1,      h->soft.n2,
+                    h->soft.arms,    h->soft.vrec,    h->soft.n2,
                     h->soft.tab,     h->soft.vol[0],  h->soft.vol[1],  h->soft.vol[2],
                     h->soft.partAC,  h->soft.partT};
     for (void* p : ptrs) dev_free(p);
@@ -547,7 +547,7 @@ extern "C" dco_status dco_stereo_last_disparities(dco_stereo* h, int16_t* dL, in
 // ---- differentiable soft-argmin form ----
 
 static void free_soft(SoftScratch& f) {
-    void* ptrs[] = {f.pix[0], f.pix[1], f.arms,   f.vrec, f.rn1,     f.n2,
+    void* ptrs[] = {f.pix[0], f.pix[1], f.arms,   f.vrec, f.n2,
                     f.tab,    f.vol[0], f.vol[1], f.vol[2], f.partAC, f.partT};
     for (void* p : ptrs) dev_free(p);
     f = SoftScratch{};
@@ -563,7 +563,6 @@ static dco_status soft_reserve(dco_stereo* h, int B) {
     DCO_TRY(dev_alloc(&f.pix[1], P * B));
     DCO_TRY(dev_alloc(&f.arms, P * B));
     DCO_TRY(dev_alloc(&f.vrec, P * B));
-    DCO_TRY(dev_alloc(&f.rn1, P * B));
     DCO_TRY(dev_alloc(&f.n2, P * B));
     DCO_TRY(dev_alloc(&f.tab, 1792));
     for (int k = 0; k < 3; ++k) DCO_TRY(dev_alloc(&f.vol[k], V));
@@ -582,11 +581,11 @@ static dco_status soft_front(dco_stereo* h, int B, const uint8_t* L, const uint8
     const dco_params& p = h->p;
     f.held = false;
     DCO_HIP_CHECK(launch_census_pairs(L, R, B, h->W, h->H, p.census_w, p.census_h, p.arm_L1,
-                                      p.arm_tau1, f.arms, f.vrec, f.pix[0], f.pix[1],
+                                      p.arm_tau1, f.arms, (uint32_t*)f.vrec, f.pix[0], f.pix[1],
                                       h->stream));
     DCO_HIP_CHECK(soft_prepare(theta, f.tab, f.arms, B, h->W, h->H, h->D, h->alpha,
-                               f.vrec, f.rn1, f.n2, h->stream));
-    *sb = SoftBuffers{f.arms, f.vrec, f.rn1, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
+                               f.vrec, f.n2, h->stream));
+    *sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
     DCO_HIP_CHECK(
         soft_aggregate(*sb, B, h->W, h->H, h->D, f.vol[0], f.vol[1], f.vol[2], theta, dhat, lse,
                        h->stream));
@@ -670,7 +669,7 @@ extern "C" dco_status dco_soft_backward_reuse(dco_stereo* h, int B, const uint8_
     // and pixels as they are, so any number of backward calls can reuse them
     if (f.held && f.held_B == B && f.held_L == L && f.held_R == R && f.held_theta == theta &&
         f.held_stream == h->stream)
-        sb = SoftBuffers{f.arms, f.vrec, f.rn1, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
+        sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
     else
         DCO_TRY(soft_front(h, B, L, R, theta, nullptr, nullptr, &sb));
     DCO_HIP_CHECK(soft_backward(sb, B, h->W, h->H, h->D, f.vol[0], theta, dhat, lse, grad_dhat,

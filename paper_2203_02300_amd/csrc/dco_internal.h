@@ -35,9 +35,8 @@ struct SoftScratch {
     uint4* pix[2];         // packed pixels of left / right views (census lo, census
                            // hi, RGB, 8 L_min)
     uint32_t* arms;        // arms of the left views
-    uint32_t* vrec;        // column records of the left views (the census pass puts the
+    uint2* vrec;           // column records of the left views (the census pass puts the
                            // right views' arms here first, which nothing reads)
-    float* rn1;            // 1 / stage-1 region counts
     float* n2;             // stage-2 region counts
     float* tab;            // Eq. 1 tables and derivatives for the current theta
     float* vol[3];
@@ -58,8 +57,7 @@ struct SoftScratch {
 // Read-only view of the soft-path inputs handed to the kernels.
 struct SoftBuffers {
     const uint32_t* arms;
-    const uint32_t* vrec;
-    const float* rn1;
+    const uint2* vrec;
     const float* n2;
     const uint4* pixL;
     const uint4* pixR;
@@ -292,8 +290,7 @@ hipError_t launch_unpair(const float* vol, int W, int H, int D, int d0, int n, f
 
 // k_soft.hip
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2,
-                        hipStream_t st);
+                        int D, const float* alpha, uint2* vrec, float* n2, hipStream_t st);
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, const float* theta, float* dhat, float* lse,
                           hipStream_t st);

@@ -39,8 +39,7 @@ namespace {
 
 struct SoftGeom {
     const uint32_t* arms;  // B x H x W packed arms of the left view
-    const uint32_t* vrec;  // B x H x W column records (col_record)
-    const float* rn1;      // B x H x W 1 / stage-1 region counts
+    const uint2* vrec;     // B x H x W column records (col_record, 1 / stage-1 region count)
     const float* n2;       // B x H x W stage-2 region counts
     int B, W, H, D;
 };
@@ -64,9 +63,10 @@ __device__ inline void put_scale(float bound, float* out) {
     out[1] = ok ? ldexpf(1.0f, e - 29) : __builtin_nanf("");
 }
 
-__global__ void k_soft_tables(const float* __restrict__ theta, const float* __restrict__ alpha,
-                              float* __restrict__ tab) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+constexpr int kTabThreads = 1024;  // entry i of them, 0 <= i < kTabThreads
+
+__device__ inline void table_entry(int i, const float* __restrict__ theta,
+                                   const float* __restrict__ alpha, float* __restrict__ tab) {
     const float la = theta[0], lc = theta[1];
     if (i < 766) {
         const float x = (float)i / 3.0f;
@@ -104,19 +104,27 @@ __device__ inline uint32_t col_record(uint32_t a, int n1) {
 }
 
 // Region pixel counts of the left view (as floats) for every pair: one
-// block per 64 x 4 tile.  The row lengths l + r + 1 of the tile's columns
-// over kLMax rows above and below, and the column lengths u + dn + 1 of the
-// tile's rows over kLMax columns left and right, go to LDS (0 outside the
-// image, where no arm reaches); each count is then a sum of LDS entries.
+// block per 64 x 4 tile; the first blocks also make the tables (as a launch of
+// its own 3 us of a 320 x 240 forward of 74).  The row lengths l + r + 1 of the
+// tile's columns over kLMax rows above and below, and the column lengths u + dn
+// + 1 of the tile's rows over kLMax columns left and right, go to LDS (0 outside
+// the image, where no arm reaches); each count is then a sum of LDS entries.
 constexpr int kCntTW = 64, kCntTH = 4;
-__global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, uint32_t* __restrict__ vrec,
-                                                     float* __restrict__ rn1,
+__global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, const float* __restrict__ theta,
+                                                     const float* __restrict__ alpha,
+                                                     float* __restrict__ tab,
+                                                     uint2* __restrict__ vrec,
                                                      float* __restrict__ n2) {
     constexpr int CH = kCntTH + 2 * kLMax, RW = kCntTW + 2 * kLMax;
     __shared__ uint8_t hl[CH][kCntTW];  // l + r + 1 down each tile column
     __shared__ uint8_t vl[kCntTH][RW];  // u + dn + 1 along each tile row
     const int t = threadIdx.x, b = blockIdx.z;
     const int x0 = blockIdx.x * kCntTW, y0 = blockIdx.y * kCntTH;
+    {   // the tables, which only the later passes need: the first blocks' threads
+        const unsigned n = gridDim.x * gridDim.y * gridDim.z;
+        unsigned i = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        for (; i < kTabThreads / 256; i += n) table_entry((int)i * 256 + t, theta, alpha, tab);
+    }
     const uint32_t* A = g.arms + (size_t)b * g.W * g.H;
     for (int k = t; k < CH * kCntTW; k += 256) {
         const int r = k / kCntTW, c = k - r * kCntTW;
@@ -141,8 +149,7 @@ __global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, uint32_t* __res
     for (int k = -arm(a, 2); k <= arm(a, 3); ++k) s1 += hl[ty + kLMax + k][tx];
     for (int k = -arm(a, 0); k <= arm(a, 1); ++k) s2 += vl[ty][tx + kLMax + k];
     const size_t i = (size_t)b * g.W * g.H + (size_t)y * g.W + x;
-    vrec[i] = col_record(a, s1);
-    rn1[i] = 1.0f / (float)s1;
+    vrec[i] = make_uint2(col_record(a, s1), __float_as_uint(1.0f / (float)s1));
     n2[i] = (float)s2;
 }
 
@@ -150,7 +157,7 @@ struct SoftImg {
     const uint4* pixL;   // B x H x W packed pixels: census lo, census hi,
     const uint4* pixR;   //   RGB, 8 L_min
     const float* alpha;  // alpha_L, L = 0..kLMax
-    const float* tab;    // k_soft_tables output
+    const float* tab;    // table_entry's
 };
 
 // Workgroup index in the row order of workgroup b of n: the workgroups one
@@ -169,7 +176,7 @@ __device__ inline int xcd_block(int b, int n) {
 // (balanced digits: q = sum_i 256^i b_i), so four i8 products with 32-bit
 // accumulation give the exact sum of the q, and the output is that sum rounded
 // once to FP32.  2^k puts the largest |c| that theta and alpha allow at 2^30
-// (k_soft_tables): a cost is exact down to 2^-6 of it and within 2^-30 of it
+// (table_entry): a cost is exact down to 2^-6 of it and within 2^-30 of it
 // below, where the FP32 sum of a range is no finer.  Costs of partners outside
 // the image are 1 by definition: they enter as 0 and are counted.
 //
@@ -821,9 +828,11 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
 // 1/N = 0: they add zero to both sums.
 //
 // Measured at 8 x 64 planes of 640 x 480 (1.26 GB in and out; a copy of that
-// size takes about 0.25 ms): 0.35 ms forward and 0.36 ms adjoint, bound by the
-// issue of the four wavefronts (33 instructions per row); as two passes over
-// the volume, each at the copy's rate, 0.58 ms each.  Loading 2, 5 or 7
+// size takes about 0.25 ms): 0.34 ms forward and 0.38 ms adjoint, bound by the
+// issue of the four wavefronts (33 instructions per row) and, in the adjoint,
+// the LDS adds; as two passes over the volume, each near the copy's rate, 0.58
+// ms each.  Record and 1 / N in one 8-byte load instead of two loads: forward
+// 0.36 -> 0.34, adjoint 0.37 -> 0.38, 320 x 240 forward 74.0 -> 72.7 us.  Loading 2, 5 or 7
 // batches ahead instead of 3: 0.37, 0.35, 0.35 ms.  At 32 planes of 320 x 240
 // (160 wavefronts, six segments each) 19 us, was 53 us.
 constexpr int kSoftCols = 64;
@@ -876,9 +885,7 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
     const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + (size_t)bd * P),
                                                        (short)0, plane, 0x00020000);
     const auto rec = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint32_t*>(g.vrec + (size_t)b * P), (short)0, plane, 0x00020000);
-    const auto rni = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.rn1 + (size_t)b * P),
-                                                       (short)0, plane, 0x00020000);
+        const_cast<uint2*>(g.vrec + (size_t)b * P), (short)0, 2 * plane, 0x00020000);
     const auto dst = __builtin_amdgcn_make_buffer_rsrc(
         out + (size_t)bd * P + (size_t)r0 * g.W, (short)0, (int)((uint32_t)(r1 - r0) * W4),
         0x00020000);
@@ -892,17 +899,19 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
     const int first = max(r0 - 2 * kLMax, 0);
     const int last = r1 + kSoftLag;
     uint32_t v_off = x4 + (uint32_t)first * W4;                     // row y + lead
-    uint32_t n_off = v_off - (uint32_t)kLMax * W4;                  // row y - kLMax + lead
+    // records of row y + lead (adjoint) or y - kLMax + lead (forward)
+    uint32_t n_off = x < g.W ? 2 * (v_off - (kAdj ? 0u : (uint32_t)kLMax * W4)) : kSoftDrop;
     uint32_t d_off = x4 + (uint32_t)(first - r0 - kSoftLead * kSoftPre - kSoftLag) * W4;
-    float v[kSoftBufs][kSoftPre], rn[kSoftBufs][kSoftPre];
+    float v[kSoftBufs][kSoftPre], rn[kSoftTurn][kSoftPre];
     uint32_t p[kSoftBufs][kSoftPre], p2[kSoftTurn][kSoftPre];
+    float rl[kSoftBufs][kSoftPre];
     double h1[kSoftPre], l1[kSoftPre], h2[kSoftPre], l2[kSoftPre];
 #pragma unroll
     for (int k = 0; k < kSoftPre; ++k) {
 #pragma unroll
-        for (int j = 0; j < kSoftBufs; ++j) v[j][k] = rn[j][k] = 0.0f, p[j][k] = 0u;
+        for (int j = 0; j < kSoftBufs; ++j) v[j][k] = rl[j][k] = 0.0f, p[j][k] = 0u;
 #pragma unroll
-        for (int j = 0; j < kSoftTurn; ++j) p2[j][k] = 0u;
+        for (int j = 0; j < kSoftTurn; ++j) p2[j][k] = 0u, rn[j][k] = 0.0f;
         h1[k] = l1[k] = h2[k] = l2[k] = 0.0;
     }
     double acc1 = 0.0, acc2 = 0.0;
@@ -916,7 +925,7 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
             const int s2 = ring_mod((j - kSoftLead - 1) * kSoftPre);   // and of the batch before
             float (&cv)[kSoftPre] = v[j % kSoftBufs];
             uint32_t (&cp)[kSoftPre] = p[j % kSoftBufs];
-            float (&crn)[kSoftPre] = rn[(j + kSoftBufs - 1) % kSoftBufs];  // of the batch before
+            float (&crn)[kSoftPre] = rl[j % kSoftBufs];
             // The batch's values are used from here on: without this pin the
             // compiler starts converting a later batch early, which waits for
             // loads that should still be in flight.
@@ -952,7 +961,10 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
                 } else {
                     r = (float)(h1[k] - l1[k]);
                 }
-                a1[k] = col_div(r, q, crn[k]);
+                const float rq = kAdj ? (k < 2 ? rn[(j + 3) % kSoftTurn][k + 3]
+                                               : rn[(j + 4) % kSoftTurn][k - 2])
+                                      : rn[(j + kSoftTurn - 1) % kSoftTurn][k];
+                a1[k] = col_div(r, q, rq);
             }
             // first sum, batch j
 #pragma unroll
@@ -1005,18 +1017,21 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
                 }
             }
 #pragma unroll
-            for (int k = 0; k < kSoftPre; ++k) p2[j][k] = cp[k];
+            for (int k = 0; k < kSoftPre; ++k) {
+                p2[j][k] = cp[k];
+                rn[j][k] = crn[k];
+            }
             // the batch kSoftLead ahead
 #pragma unroll
             for (int k = 0; k < kSoftPre; ++k) {
                 const int f = (j + kSoftLead) % kSoftBufs;
                 v[f][k] = __builtin_bit_cast(
                     float, __builtin_amdgcn_raw_buffer_load_b32(src, v_off, 0, 0));
-                p[f][k] = __builtin_amdgcn_raw_buffer_load_b32(rec, kAdj ? v_off : n_off, 0, 0);
-                rn[f][k] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(rni, n_off, 0, 0));
+                const auto r = __builtin_amdgcn_raw_buffer_load_b64(rec, n_off, 0, 0);
+                p[f][k] = r[0];
+                rl[f][k] = __builtin_bit_cast(float, (uint32_t)r[1]);
                 v_off += W4;
-                n_off += W4;
+                n_off += 2 * W4;
             }
         }
     }
@@ -1158,12 +1173,10 @@ static RowGrid row_grid(const SoftGeom& g) {
 }
 
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, const float* alpha, uint32_t* vrec, float* rn1, float* n2,
-                        hipStream_t st) {
-    hipLaunchKernelGGL(k_soft_tables, dim3(4), dim3(256), 0, st, theta, alpha, tab);
-    SoftGeom g{arms, nullptr, nullptr, nullptr, B, W, H, D};
+                        int D, const float* alpha, uint2* vrec, float* n2, hipStream_t st) {
+    SoftGeom g{arms, nullptr, nullptr, B, W, H, D};
     hipLaunchKernelGGL(k_soft_counts, dim3((W + kCntTW - 1) / kCntTW, (H + kCntTH - 1) / kCntTH, B),
-                       dim3(256), 0, st, g, vrec, rn1, n2);
+                       dim3(256), 0, st, g, theta, alpha, tab, vrec, n2);
     return hipGetLastError();
 }
 
@@ -1172,7 +1185,7 @@ hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, in
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, const float* theta, float* dhat, float* lse,
                           hipStream_t st) {
-    SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const RowGrid rg = row_grid(g);
     hipLaunchKernelGGL(k_soft_mrow<false>, rg.grid, rg.block, 0, st, g, im, (const float*)nullptr,
@@ -1195,7 +1208,7 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
                          const float* theta, const float* dhat, const float* lse,
                          const float* gdhat, float* t1, float* t2, double* partAC,
                          double* partT, float* grad, hipStream_t st) {
-    SoftGeom g{s.arms, s.vrec, s.rn1, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const RowGrid rg = row_grid(g);
