@@ -83,12 +83,13 @@ std::vector<BatchItem> make_items(std::vector<BatchPair>& pairs, int* xsplit) {
     for (int i = 0; i < (int)pairs.size(); ++i) {
         BatchPair& pr = pairs[i];
         const int bx = (pr.W + 63) / 64, by = (pr.H + 63) / 64;
+        const int gy = (pr.H + kWsRecRows + 63) / 64;  // blocks of record rows
         const int nb = (pr.H + pr.band - 1) / pr.band;
         const int nd = (pr.D + pr.dchunk - 1) / pr.dchunk;
         for (int v = 0; v < 2; ++v)
-            for (int y = 0; y < by; ++y)
+            for (int y = 0; y < gy; ++y)
                 for (int x = 0; x < bx; ++x) {
-                    st[0].push_back(BatchItem{i, 0, v, x, y, 0});
+                    if (y < by) st[0].push_back(BatchItem{i, 0, v, x, y, 0});
                     st[1].push_back(BatchItem{i, 1, v, x, y, 0});
                 }
         // neighbouring disparities of one strip and band next to each other:
@@ -101,7 +102,8 @@ std::vector<BatchItem> make_items(std::vector<BatchPair>& pairs, int* xsplit) {
         const int P = pr.W * pr.H;
         for (int a = 0; a < P; a += kWtaPx) st[3].push_back(BatchItem{i, 3, 0, a, 0, 0});
         for (int a = 0; a < pr.H; a += kLrRows) st[4].push_back(BatchItem{i, 4, 0, a, 0, 0});
-        pr.nitems[0] = pr.nitems[1] = 2 * bx * by;
+        pr.nitems[0] = 2 * bx * by;
+        pr.nitems[1] = 2 * bx * gy;
         pr.nitems[2] = 2 * nb * nd * pr.nstrips;
         pr.nitems[3] = (P + kWtaPx - 1) / kWtaPx;
         pr.nitems[4] = (pr.H + kLrRows - 1) / kLrRows;

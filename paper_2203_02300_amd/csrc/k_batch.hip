@@ -48,8 +48,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         } else {
             for (int r = 0; r < 64 / dco::kGeoTH; ++r) {
                 const int y0 = I.b * 64 + r * dco::kGeoTH;
-                if (y0 >= H) break;
-                dco::geometry_tile<1024>(pr.arms[I.view], W, H, ITERS, pr.rec[I.view],
+                if (y0 >= dco::geo_rows(H)) break;
+                dco::geometry_tile(pr.arms[I.view], W, H, ITERS, pr.rec[I.view],
                                          I.a * dco::kGeoTW, y0, S);
                 __syncthreads();
             }

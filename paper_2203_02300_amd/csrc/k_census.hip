@@ -22,7 +22,7 @@ __global__ __launch_bounds__(64 * TH) __attribute__((amdgpu_waves_per_eu(8))) vo
 __global__ __launch_bounds__(1024) void k_geometry(const uint32_t* __restrict__ arms, int W, int H,
                                                    int iters, AggRecords rec) {
     __shared__ dco::GeomLds S;
-    dco::geometry_tile<1024>(arms, W, H, iters, rec, blockIdx.x * dco::kGeoTW,
+    dco::geometry_tile(arms, W, H, iters, rec, blockIdx.x * dco::kGeoTW,
                              blockIdx.y * dco::kGeoTH, S);
 }
 
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(1024) void k_geometry2(const uint32_t* __restrict__
                                                    AggRecords recR) {
     __shared__ dco::GeomLds S;
     const bool r = blockIdx.z != 0;
-    dco::geometry_tile<1024>(r ? armsR : armsL, W, H, iters, r ? recR : recL,
+    dco::geometry_tile(r ? armsR : armsL, W, H, iters, r ? recR : recL,
                              blockIdx.x * dco::kGeoTW, blockIdx.y * dco::kGeoTH, S);
 }
 
@@ -111,7 +111,8 @@ hipError_t launch_front2(const uint8_t* rgbL, const uint8_t* rgbR, int W, int H,
         hipLaunchKernelGGL(k_census_arms2<TH>, g, dim3(64 * TH), 0, st, rgbL, rgbR, W, H, cw, ch,
                            L1, tau1, armsL, armsR, pixL, pixR, iters == 2);
     });
-    dim3 g2((W + dco::kGeoTW - 1) / dco::kGeoTW, (H + dco::kGeoTH - 1) / dco::kGeoTH, 2);
+    dim3 g2((W + dco::kGeoTW - 1) / dco::kGeoTW,
+            (dco::geo_rows(H) + dco::kGeoTH - 1) / dco::kGeoTH, 2);
     hipLaunchKernelGGL(k_geometry2, g2, dim3(1024), 0, st, armsL, armsR, W, H, iters, recL, recR);
     return hipGetLastError();
 }
@@ -130,7 +131,8 @@ hipError_t launch_census_arms(const uint8_t* rgb, int W, int H, int cw, int ch, 
 
 hipError_t launch_geometry(const uint32_t* arms, int W, int H, int iters, const AggRecords& rec,
                            hipStream_t st) {
-    dim3 grid((W + dco::kGeoTW - 1) / dco::kGeoTW, (H + dco::kGeoTH - 1) / dco::kGeoTH);
+    dim3 grid((W + dco::kGeoTW - 1) / dco::kGeoTW,
+              (dco::geo_rows(H) + dco::kGeoTH - 1) / dco::kGeoTH);
     hipLaunchKernelGGL(k_geometry, grid, dim3(1024), 0, st, arms, W, H, iters, rec);
     return hipGetLastError();
 }
