@@ -402,12 +402,13 @@ extern "C" dco_status dco_wta_lrcheck(dco_stereo* h, const float* aggL, const fl
     int16_t* oL = dL ? dL : h->s.dint[0];
     int16_t* oR = dR ? dR : h->s.dint[1];
     DCO_HIP_CHECK(launch_wta_lr(aggL, aggR, false, h->W, h->H, h->D, h->p.subpixel,
-                                h->p.lr_max_diff, oL, oR, disp, valid, h->stream));
+                                h->p.lr_max_diff, oL, oR, disp, valid, HalfOut{}, h->stream));
     return DCO_OK;
 }
 
-extern "C" dco_status dco_stereo_match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
-                                       float* disp, uint8_t* valid) {
+// dco_stereo_match; the launch that ends it makes the outputs `half` asks for.
+static dco_status match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR, float* disp,
+                        uint8_t* valid, const HalfOut& half) {
     DCO_TRY(need(h, "handle"));
     DCO_TRY(need(rgbL, "rgbL"));
     DCO_TRY(need(rgbR, "rgbR"));
@@ -434,20 +435,23 @@ extern "C" dco_status dco_stereo_match(dco_stereo* h, const uint8_t* rgbL, const
     DCO_TRY(prof_mark(h));
     // from the even slices (each pair's minimum) when the volumes are paired
     DCO_HIP_CHECK(launch_wta_lr(s.agg[0], s.agg[1], s.agg_paired, h->W, h->H, h->D, p.subpixel,
-                                p.lr_max_diff, s.dint[0], s.dint[1], disp, valid, h->stream));
+                                p.lr_max_diff, s.dint[0], s.dint[1], disp, valid,
+                                p.vote_iters > 0 ? HalfOut{} : half, h->stream));
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));  // the left-right check is part of the launch above
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
-    if (p.vote_iters > 0) {
-        const int16_t* dv = nullptr;
-        DCO_HIP_CHECK(launch_vote(s.dint[0], valid, s.arms[0], h->W, h->H, h->D, p.vote_iters,
-                                  s.vote[0], s.vote[1], &dv, h->stream));
-        DCO_HIP_CHECK(launch_vote_finish(dv, nullptr, s.agg[0], s.agg_paired, h->W, h->H, h->D,
-                                         p.subpixel, disp, valid, nullptr, h->stream));
-    }
+    if (p.vote_iters > 0)
+        DCO_HIP_CHECK(launch_vote(s.dint[0], valid, s.arms[0], s.agg[0], s.agg_paired, h->W, h->H,
+                                  h->D, p.vote_iters, p.subpixel, s.vote[0], s.vote[1], disp,
+                                  valid, nullptr, half, h->stream));
     DCO_TRY(prof_mark(h));
     return DCO_OK;
+}
+
+extern "C" dco_status dco_stereo_match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
+                                       float* disp, uint8_t* valid) {
+    return match(h, rgbL, rgbR, disp, valid, HalfOut{});
 }
 
 extern "C" dco_status dco_stereo_match_half(dco_stereo* h, const uint8_t* rgbL2,
@@ -473,9 +477,7 @@ extern "C" dco_status dco_stereo_match_half(dco_stereo* h, const uint8_t* rgbL2,
     }
     DCO_HIP_CHECK(launch_downscale2(rgbL2, rgbR2, W2, h->W, h->H, h->s.half[0], h->s.half[1],
                                     h->stream));
-    DCO_TRY(dco_stereo_match(h, h->s.half[0], h->s.half[1], disp2, valid));
-    DCO_HIP_CHECK(launch_depth_half(disp2, valid, h->W, h->H, fB, depth, h->stream));
-    return DCO_OK;
+    return match(h, h->s.half[0], h->s.half[1], disp2, valid, HalfOut{true, fB, depth});
 }
 
 extern "C" dco_status dco_vote_refine(dco_stereo* h, const uint8_t* armsL, const float* aggL,
@@ -497,15 +499,9 @@ extern "C" dco_status dco_vote_refine(dco_stereo* h, const uint8_t* armsL, const
         dco_set_error("handle has no scratch");
         return DCO_ERR_STATE;
     }
-    const int16_t* dv = dL;
-    const uint8_t* mask = valid;
-    if (iters > 0) {
-        DCO_HIP_CHECK(launch_vote(dL, valid, reinterpret_cast<const uint32_t*>(armsL), h->W, h->H,
-                                  h->D, iters, h->s.vote[0], h->s.vote[1], &dv, h->stream));
-        mask = nullptr;
-    }
-    DCO_HIP_CHECK(launch_vote_finish(dv, mask, aggL, false, h->W, h->H, h->D, h->p.subpixel, disp,
-                                     valid_out, dvote, h->stream));
+    DCO_HIP_CHECK(launch_vote(dL, valid, reinterpret_cast<const uint32_t*>(armsL), aggL, false,
+                              h->W, h->H, h->D, iters, h->p.subpixel, h->s.vote[0], h->s.vote[1],
+                              disp, valid_out, dvote, HalfOut{}, h->stream));
     return DCO_OK;
 }
 

@@ -178,24 +178,27 @@ dco_status alloc_records(AggRecords* r, int W, int H);
 hipError_t launch_census_arms(const uint8_t* rgb, int W, int H, int cw, int ch, int L1, int tau1,
                               uint64_t* census, uint32_t* arms, uint32_t* rgb_packed, uint4* pix,
                               hipStream_t st);
-// Eq. 4 vote: `iters` passes (>= 1) over the left integer map dL (pixels
-// with valid = 0 or a value outside [0, D) do not vote), ping-ponging between
-// buf0 and buf1 (H x W int16 each); *result points at the final map (-1 where
-// invalid).  Then the output step: disp / valid from a voted map (valid_in
-// null) or from dL and its mask (no pass).
-hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* arms, int W, int H,
-                       int D, int iters, int16_t* buf0, int16_t* buf1, const int16_t** result,
-                       hipStream_t st);
-hipError_t launch_vote_finish(const int16_t* dv, const uint8_t* valid_in, const float* agg,
-                              bool paired, int W, int H, int D, int subpixel, float* disp,
-                              uint8_t* valid, int16_t* dv_out, hipStream_t st);
+// Output of the quarter-size front end: with `on`, a launch that ends a match
+// stores 2 disp instead of disp, and fB / (2 disp) where that is > 0 (else 0) to
+// depth (optional).
+struct HalfOut {
+    bool on;
+    float fB;
+    float* depth;
+};
+// Eq. 4 vote: `iters` passes (0: none) over the left integer map dL (pixels with
+// valid = 0 or a value outside [0, D) do not vote), ping-ponging between buf0 and
+// buf1 (H x W int16 each), then the output step: disp and valid_out (which may be
+// valid) from the voted map and the aggregated costs, dv_out (optional) the map
+// itself, -1 where invalid.
+hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* arms,
+                       const float* agg, bool paired, int W, int H, int D, int iters, int subpixel,
+                       int16_t* buf0, int16_t* buf1, float* disp, uint8_t* valid_out,
+                       int16_t* dv_out, const HalfOut& half, hipStream_t st);
 // Quarter-size front end: 2 x 2 block means of both full images (row length
-// W2 pixels) into W x H x 3 outputs; then disp = 2 disp where valid (else 0)
-// in place, and depth = fB / disp where > 0 (depth optional).
+// W2 pixels) into W x H x 3 outputs.
 hipError_t launch_downscale2(const uint8_t* rgbL, const uint8_t* rgbR, int W2, int W, int H,
                              uint8_t* outL, uint8_t* outR, hipStream_t st);
-hipError_t launch_depth_half(float* disp, const uint8_t* valid, int W, int H, float fB,
-                             float* depth, hipStream_t st);
 // Depth densification (Eq. 13-20): device buffers of one grid (FP64 state,
 // nblk = densify_blocks(W, H) block partials per sum) and its launches.
 struct DensifyBufs {
@@ -283,7 +286,7 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
 // volumes in the paired layout (even slices only).
 hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int W, int H, int D,
                          int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
-                         uint8_t* valid, hipStream_t st);
+                         uint8_t* valid, const HalfOut& half, hipStream_t st);
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded into out (n x H x W).
 hipError_t launch_unpair(const float* vol, int W, int H, int D, int d0, int n, float* out,
                          hipStream_t st);

@@ -1,6 +1,7 @@
 // k_half.hip -- the quarter-size front end (Sec. 4.4): the pair is reduced
 // to half width and half height before matching, and the disparity found
-// there is doubled and turned into depth.
+// there is doubled and turned into depth by the launch that ends the match
+// (HalfOut).
 #include "dco_internal.h"
 
 namespace {
@@ -24,18 +25,6 @@ __global__ __launch_bounds__(256) void k_downscale2(const uint8_t* __restrict__ 
     (r ? outR : outL)[i] = (uint8_t)((s + 2) >> 2);
 }
 
-// disp (in place) = 2 disp where valid, else 0; depth = fB / disp where that
-// is > 0, else 0 (optional).
-__global__ __launch_bounds__(256) void k_depth_half(float* __restrict__ disp,
-                                                    const uint8_t* __restrict__ valid, int P,
-                                                    float fB, float* __restrict__ depth) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= P) return;
-    const float d2 = valid[i] ? 2.0f * disp[i] : 0.0f;
-    disp[i] = d2;
-    if (depth) depth[i] = d2 > 0.0f ? fB / d2 : 0.0f;
-}
-
 }  // namespace
 
 hipError_t launch_downscale2(const uint8_t* rgbL, const uint8_t* rgbR, int W2, int W, int H,
@@ -43,13 +32,5 @@ hipError_t launch_downscale2(const uint8_t* rgbL, const uint8_t* rgbR, int W2, i
     const int n = 3 * W * H;
     hipLaunchKernelGGL(k_downscale2, dim3((n + 255) / 256, 2), dim3(256), 0, st, rgbL, rgbR, W2, W,
                        H, outL, outR);
-    return hipGetLastError();
-}
-
-hipError_t launch_depth_half(float* disp, const uint8_t* valid, int W, int H, float fB,
-                             float* depth, hipStream_t st) {
-    const int P = W * H;
-    hipLaunchKernelGGL(k_depth_half, dim3((P + 255) / 256), dim3(256), 0, st, disp, valid, P, fB,
-                       depth);
     return hipGetLastError();
 }

@@ -224,13 +224,10 @@ extern "C" dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_pa
                                          b.agg[0], b.agg[1], true, st));
     const bool paired = p.agg_iters == 2;
     DCO_HIP_CHECK(launch_wta_lr(b.agg[0], b.agg[1], paired, W, H, D, p.subpixel, p.lr_max_diff,
-                                b.dint[0], b.dint[1], disp, valid, st));
-    if (p.vote_iters > 0) {
-        const int16_t* dv = nullptr;
-        DCO_HIP_CHECK(launch_vote(b.dint[0], valid, b.arms[0], W, H, D, p.vote_iters, b.vote[0],
-                                  b.vote[1], &dv, st));
-        DCO_HIP_CHECK(launch_vote_finish(dv, nullptr, b.agg[0], paired, W, H, D, p.subpixel, disp,
-                                         valid, nullptr, st));
-    }
+                                b.dint[0], b.dint[1], disp, valid, HalfOut{}, st));
+    if (p.vote_iters > 0)
+        DCO_HIP_CHECK(launch_vote(b.dint[0], valid, b.arms[0], b.agg[0], paired, W, H, D,
+                                  p.vote_iters, p.subpixel, b.vote[0], b.vote[1], disp, valid,
+                                  nullptr, HalfOut{}, st));
     return DCO_OK;
 }

@@ -34,9 +34,9 @@ template <bool kPaired, bool kNarrow>
 __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
     const float* __restrict__ aggL, const float* __restrict__ aggR, int P, int W, int D,
     int subpixel, int maxdiff, int16_t* __restrict__ dL, int16_t* __restrict__ dR,
-    float* __restrict__ disp, uint8_t* __restrict__ valid) {
+    float* __restrict__ disp, uint8_t* __restrict__ valid, HalfOut half) {
     extern __shared__ int16_t right[];  // W entries
-    const int t = threadIdx.x, half = blockDim.x / 2, nq = (W + 3) / 4;
+    const int t = threadIdx.x, nt = blockDim.x / 2, nq = (W + 3) / 4;
     const int row = blockIdx.x * W;
     const auto start = [&](int q) { return kNarrow ? 0 : min(4 * q, W - 4); };
     const auto left = [&](int q) {
@@ -52,14 +52,21 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
             const bool in = xr >= 0 && xr < W && abs(l.bd[k] - (int)right[xr]) <= maxdiff;
             ok[k] = in ? 1 : 0;
             dv[k] = in ? (float)l.bd[k] + l.del[k] : 0.0f;
+            if (half.on) dv[k] *= 2.0f;
+        }
+        if (half.depth) {
+            float z[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) z[k] = dv[k] > 0.0f ? half.fB / dv[k] : 0.0f;
+            dco::wta_store<kNarrow, dco::f32x4u>(half.depth + i, z[0], z[1], z[2], z[3], W);
         }
         dco::put_bd<kNarrow>(dL + i, l, W);
         dco::wta_store<kNarrow, dco::f32x4u>(disp + i, dv[0], dv[1], dv[2], dv[3], W);
         dco::wta_store<kNarrow, dco::u8x4u>(valid + i, ok[0], ok[1], ok[2], ok[3], W);
     };
     dco::WtaQuad l{};
-    if (t >= half) {
-        for (int q = t - half; q < nq; q += half) {
+    if (t >= nt) {
+        for (int q = t - nt; q < nq; q += nt) {
             const int x = start(q);
             const dco::WtaQuad r =
                 dco::wta_any<kPaired, false, kNarrow>(aggR, P, D, row + x, W, subpixel);
@@ -70,8 +77,8 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
         l = left(t);
     }
     __syncthreads();
-    if (t < half && t < nq) check(t, l);
-    for (int q = half + t; q < nq; q += blockDim.x) check(q, left(q));
+    if (t < nt && t < nq) check(t, l);
+    for (int q = nt + t; q < nq; q += blockDim.x) check(q, left(q));
 }
 
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded to n x P.
@@ -87,11 +94,11 @@ __global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, i
 
 hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int W, int H, int D,
                          int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
-                         uint8_t* valid, hipStream_t st) {
-    const int half = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
+                         uint8_t* valid, const HalfOut& half, hipStream_t st) {
+    const int nt = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(H), dim3(2 * half), (size_t)W * sizeof(int16_t), st, aggL,
-                           aggR, W * H, W, D, subpixel, maxdiff, dL, dR, disp, valid);
+        hipLaunchKernelGGL(kernel, dim3(H), dim3(2 * nt), (size_t)W * sizeof(int16_t), st, aggL,
+                           aggR, W * H, W, D, subpixel, maxdiff, dL, dR, disp, valid, half);
     };
     if (W < 4)
         paired ? go(k_wta_row<true, true>) : go(k_wta_row<false, true>);
