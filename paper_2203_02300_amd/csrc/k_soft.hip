@@ -246,6 +246,24 @@ __device__ inline uint32_t balanced(float v) {
     return ((uint32_t)(int)v + 0x00808080u) ^ 0x00808080u;
 }
 
+// What a wavefront of a row pass works on.  kShare: the workgroup's wavefronts take
+// one row and its groups of 16 disparities in turns, and share the bands.  Else
+// (one or two groups, where the shared buffers would leave a CU few wavefronts):
+// the workgroup takes as many rows as it has wavefronts for, and each builds its
+// own.  A forward and backward of two pairs of 600 x 400, D = 16 takes 259 us so
+// and 404 shared, of eight of 400 x 300, D = 17 538 and 680; at three groups
+// shared is as fast (five pairs of 90 x 300, D = 40: 264).
+struct RowTask {
+    int row, grp;
+    bool on;
+};
+template <bool kShare>
+__device__ inline RowTask row_task(int block, int rows, int ng, int w, int nw) {
+    if constexpr (kShare) return RowTask{block, w, true};
+    const int row = block * (nw / ng) + w / ng;
+    return RowTask{min(row, rows - 1), w % ng, row < rows};
+}
+
 // Stores the stage's 16 x 64 outputs: disparities d0 .. d0 + 15, columns x0 ..
 // x0 + 63, those inside the volume only; `out` is row y of disparity 0, P a
 // plane.  256 contiguous bytes per disparity, and four disparities per store.
@@ -274,7 +292,7 @@ __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, 
     }
 }
 
-template <bool kDeriv>
+template <bool kDeriv, bool kShare>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, SoftImg im,
                                                                 const float* __restrict__ G,
                                                                 float* __restrict__ out,
@@ -283,7 +301,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     constexpr int NQ = kDeriv ? 2 : 1;
     // 40 KB in all: four workgroups per CU
     constexpr int kCenTab = 766;
-    __shared__ v4i bands[2][8][64];
+    __shared__ v4i bands[kShare ? 2 : 1][kShare ? 8 : 1][64];
     __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
     __shared__ uint2 cen[kMxWaves][80];
     __shared__ uint32_t rgb[kMxWaves][80];
@@ -302,7 +320,8 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     const int n = lane & 15, kg = lane >> 4;
     const int W = g.W, D = g.D, ng = (D + 15) >> 4;
     // the workgroups of one image row on one XCD: its pixels are the shared input
-    const int row = xcd_block(blockIdx.x, gridDim.x), y = row % g.H, b = row / g.H;
+    const RowTask rt = row_task<kShare>(xcd_block(blockIdx.x, gridDim.x), g.B * g.H, ng, w, nw);
+    const int row = rt.row, y = row % g.H, b = row / g.H;
     const int it0 = blockIdx.y * seg_its, it1 = min(it0 + seg_its, (W + 95) >> 6);
     const size_t P = (size_t)W * g.H, pix = (size_t)b * P + (size_t)y * W;
     const uint4* pl = im.pixL + pix;
@@ -312,9 +331,9 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     uint32_t* stage = stages[w];
     const float inv0 = im.tab[kTabScale + (kDeriv ? 3 : 1)];
     int par = 0;
-    for (int g0 = 0; g0 < ng; g0 += nw) {
-        const int grp = g0 + w, d0 = 16 * grp, d = d0 + n;
-        const bool active = grp < ng;
+    for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
+        const int grp = g0 + rt.grp, d0 = 16 * grp, d = d0 + n;
+        const bool active = rt.on && grp < ng;
         const size_t orow = vol + (size_t)min(d, D - 1) * P;
         v4i bp[NQ][4];
 #pragma unroll
@@ -342,12 +361,13 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
         for (int it = max(it0 - 1, 0); it < it1; ++it, par ^= 1) {
             const int X = it << 6;
             // bands of the four 16-column outputs over the block before and this one
-            for (int c = w; c < 8; c += nw) {
+            const auto band = [&](int c) {
                 const int x = X - 32 + 16 * (c >> 1) + n;
                 const uint32_t a = ar[min(max(x, 0), W - 1)];
-                bands[par][c][lane] = band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
-                                                 X - 64 + 64 * (c & 1) + 16 * kg);
-            }
+                return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1, X - 64 + 64 * (c & 1) + 16 * kg);
+            };
+            if constexpr (kShare)
+                for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
             uint32_t q2[16];
             if (active && X < W) {
                 cen[w][16 + lane] = uint2{rc.x, rc.y};
@@ -397,7 +417,8 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
                     }
                 }
             }
-            __syncthreads();  // the bands; the buffer's next writers pass the next one first
+            // the bands; the buffer's next writers pass the next one first
+            if (kShare) __syncthreads();
             if (!active) continue;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
@@ -416,7 +437,8 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
                     for (int i = 0; i < 4; ++i) {
                         const int xb = X - 32 + 16 * i, x4 = xb + 4 * kg;
                         if (xb < 0 || xb >= W) continue;
-                        const v4i b0 = bands[par][2 * i][lane], b1 = bands[par][2 * i + 1][lane];
+                        const v4i b0 = kShare ? bands[par][2 * i][lane] : band(2 * i);
+                        const v4i b1 = kShare ? bands[par][2 * i + 1][lane] : band(2 * i + 1);
                         v4i acc[4];
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
@@ -546,12 +568,12 @@ __device__ inline void digit_planes3(const uint32_t* stage, v4i (&b)[3]) {
     }
 }
 
-template <bool kAdj>
+template <bool kAdj, bool kShare>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     SoftGeom g, const float* __restrict__ in, const float* __restrict__ theta,
     float* __restrict__ dhat, float* __restrict__ lse, const float* __restrict__ gdhat,
     float* __restrict__ out, double* __restrict__ partT, int seg_its) {
-    __shared__ v4i bands[2][8][64];
+    __shared__ v4i bands[kShare ? 2 : 1][kShare ? 8 : 1][64];
     __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
     // adjoint: l + 1 and r of the columns of this block and the one before, a byte each
     __shared__ __align__(16) uint32_t arml[kAdj ? kMxWaves : 1][2][16],
@@ -562,16 +584,17 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 15, kg = lane >> 4;
     const int W = g.W, D = g.D, ng = (D + 15) >> 4;
-    const int row = (int)blockIdx.x, y = row % g.H, b = row / g.H;
+    const RowTask rt = row_task<kShare>(blockIdx.x, g.B * g.H, ng, w, nw);
+    const int row = rt.row, y = row % g.H, b = row / g.H;
     const int it0 = blockIdx.y * seg_its, it1 = min(it0 + seg_its, (W + 95) >> 6);
     const size_t P = (size_t)W * g.H, pix = (size_t)b * P + (size_t)y * W;
     const size_t vol = ((size_t)b * D) * P + (size_t)y * W;
     const float T = theta[2], invT = 1.0f / T;
     uint32_t* stage = stages[w];
     int par = 0;
-    for (int g0 = 0; g0 < ng; g0 += nw) {
-        const int grp = g0 + w, d0 = 16 * grp;
-        const bool active = grp < ng;
+    for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
+        const int grp = g0 + rt.grp, d0 = 16 * grp;
+        const bool active = rt.on && grp < ng;
         v4i bp[2][3];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -585,13 +608,14 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
             // dhat and lse of block it's columns from the wavefronts' sums
             const int x = (it << 6) - 32 + lane;
             float m = -INFINITY, z = 0.0f, zd = 0.0f;
-            for (int k = 0; k < nw; ++k) m = fmaxf(m, soft[buf][k][0][lane]);
-            for (int k = 0; k < nw; ++k) {
-                const float sc = exp_e(soft[buf][k][0][lane] - m);
-                z += sc * soft[buf][k][1][lane];
-                zd += sc * soft[buf][k][2][lane];
+            const auto* r = soft[buf] + (w - rt.grp);  // the row's wavefronts
+            for (int k = 0; k < ng; ++k) m = fmaxf(m, r[k][0][lane]);
+            for (int k = 0; k < ng; ++k) {
+                const float sc = exp_e(r[k][0][lane] - m);
+                z += sc * r[k][1][lane];
+                zd += sc * r[k][2][lane];
             }
-            if (x >= 0 && x < W) {
+            if (rt.on && x >= 0 && x < W) {
                 dhat[pix + x] = zd / z;
                 lse[pix + x] = m + logf(z);
             }
@@ -600,14 +624,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
             const int X = it << 6;
             const int xc = min(X + lane, W - 1);
             const bool in_row = X + lane < W;
-            if constexpr (!kAdj) {
-                for (int c = w; c < 8; c += nw) {
-                    const int x = X - 32 + 16 * (c >> 1) + n;
-                    const uint32_t a = g.arms[pix + min(max(x, 0), W - 1)];
-                    bands[par][c][lane] = band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
-                                                     X - 64 + 64 * (c & 1) + 16 * kg);
-                }
-            } else {
+            if constexpr (kAdj) {
                 const uint32_t a = X < W ? g.arms[pix + xc] : 0u;
                 reinterpret_cast<uint8_t*>(arml[w][it & 1])[lane] = (uint8_t)(arm(a, 0) + 1);
                 reinterpret_cast<uint8_t*>(armr[w][it & 1])[lane] = (uint8_t)arm(a, 1);
@@ -616,15 +633,21 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                     reinterpret_cast<uint8_t*>(armr[w][~it & 1])[lane] = 0;
                 }
                 __builtin_amdgcn_wave_barrier();
-                for (int c = w; c < 8; c += nw) {
-                    const int k = c & 1;  // 0: the block before, 1: this one
-                    const int p = X - 32 + 16 * (c >> 1) + n;
-                    bands[par][c][lane] =
-                        band_bytes_t(arml[w][(it + 1 + k) & 1] + 4 * kg,
-                                     armr[w][(it + 1 + k) & 1] + 4 * kg,
-                                     X - 64 + 64 * k + 16 * kg - p);
-                }
             }
+            const auto band = [&](int c) {
+                const int k = c & 1;  // 0: the block before, 1: this one
+                const int x = X - 32 + 16 * (c >> 1) + n;
+                if constexpr (kAdj) {
+                    return band_bytes_t(arml[w][(it + 1 + k) & 1] + 4 * kg,
+                                        armr[w][(it + 1 + k) & 1] + 4 * kg,
+                                        X - 64 + 64 * k + 16 * kg - x);
+                } else {
+                    const uint32_t a = g.arms[pix + min(max(x, 0), W - 1)];
+                    return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1, X - 64 + 64 * k + 16 * kg);
+                }
+            };
+            if constexpr (kShare)
+                for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
             uint32_t lo[16];
             const int ex_old = ex;
             if (active && X < W) {
@@ -679,15 +702,11 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-            __syncthreads();  // the bands; the buffer's next writers pass the next one first
-            if (!kAdj && dhat && it > it0 && w == it % nw) merge(it - 1, par ^ 1);
-            if (!active) {
-                if (!kAdj && dhat) {
-                    soft[par][w][0][lane] = -INFINITY;
-                    soft[par][w][1][lane] = soft[par][w][2][lane] = 0.0f;
-                }
-                continue;
-            }
+            // the bands and the softmax sums; the buffers' next writers pass the next
+            // one first
+            if (kShare || (!kAdj && dhat)) __syncthreads();
+            if (!kAdj && dhat && it > it0 && rt.grp == it % ng) merge(it - 1, par ^ 1);
+            if (!active) continue;
             v4i bc[2][3];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -714,7 +733,8 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                     for (int i = 0; i < 4; ++i) {
                         const int xb = X - 32 + 16 * i;
                         if (xb < 0 || xb >= W) continue;
-                        const v4i b0 = bands[par][2 * i][lane], b1 = bands[par][2 * i + 1][lane];
+                        const v4i b0 = kShare ? bands[par][2 * i][lane] : band(2 * i);
+                        const v4i b1 = kShare ? bands[par][2 * i + 1][lane] : band(2 * i + 1);
                         v4i s[2][3];
 #pragma unroll
                         for (int h = 0; h < 2; ++h)
@@ -790,7 +810,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
         }
         if (!kAdj && dhat) {
             __syncthreads();
-            if (w == 0) merge(it1 - 1, par ^ 1);
+            if (rt.grp == 0) merge(it1 - 1, par ^ 1);
         }
         if (kAdj && active) {
             for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
@@ -1155,21 +1175,48 @@ static void launch_vv(const SoftGeom& g, const float* in, float* out, hipStream_
                        dim3(kSoftCols), 0, st, g, in, out, seg);
 }
 
-// Launch shape of the matrix-core row passes: a workgroup per image row and
-// part of it, a wavefront per 16 disparities.  Rows are split (each part
-// computes one more block) while they leave the device's slots empty; the
+// Launch shape of the matrix-core row passes (RowTask).  Rows are split in parts
+// (each computes one more block) while they leave the device's slots empty; the
 // partial sums have room for D values per row.
 struct RowGrid {
-    int seg, ng, parts;  // blocks per part, values per part, values in all
+    bool share;
+    int seg, parts;  // blocks per part of a row, values in all
     dim3 grid, block;
 };
 
 static RowGrid row_grid(const SoftGeom& g) {
-    const int ng = (g.D + 15) / 16, nw = std::min(ng, kMxWaves), rows = g.B * g.H;
-    const int its = (g.W + 95) / 64;
-    const int most = std::max(1, std::min({its / 2, g.D / ng, kMxSlots / (rows * nw)}));
+    const int ng = (g.D + 15) / 16, rows = g.B * g.H, its = (g.W + 95) / 64;
+    const bool share = ng > 2;
+    // shared: wavefronts for the groups in as few turns as possible, evenly
+    const int turns = (ng + kMxWaves - 1) / kMxWaves;
+    const int nw = share ? (ng + turns - 1) / turns : kMxWaves;
+    const int blocks = share ? rows : (rows + kMxWaves / ng - 1) / (kMxWaves / ng);
+    const int most = std::max(1, std::min({its / 2, g.D / ng, kMxSlots / (blocks * nw)}));
     const int seg = (its + most - 1) / most, segs = (its + seg - 1) / seg;
-    return RowGrid{seg, ng, rows * segs * ng, dim3(rows, segs), dim3(64 * nw)};
+    return RowGrid{share, seg, rows * segs * ng, dim3(blocks, segs), dim3(64 * nw)};
+}
+
+template <bool kDeriv>
+static void launch_mrow(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, const float* G,
+                        float* out, double* part, hipStream_t st) {
+    if (rg.share)
+        hipLaunchKernelGGL((k_soft_mrow<kDeriv, true>), rg.grid, rg.block, 0, st, g, im, G, out,
+                           part, rg.seg);
+    else
+        hipLaunchKernelGGL((k_soft_mrow<kDeriv, false>), rg.grid, rg.block, 0, st, g, im, G, out,
+                           part, rg.seg);
+}
+
+template <bool kAdj>
+static void launch_wide(const RowGrid& rg, const SoftGeom& g, const float* in, const float* theta,
+                        float* dhat, float* lse, const float* gdhat, float* out, double* partT,
+                        hipStream_t st) {
+    if (rg.share)
+        hipLaunchKernelGGL((k_soft_wide<kAdj, true>), rg.grid, rg.block, 0, st, g, in, theta, dhat,
+                           lse, gdhat, out, partT, rg.seg);
+    else
+        hipLaunchKernelGGL((k_soft_wide<kAdj, false>), rg.grid, rg.block, 0, st, g, in, theta,
+                           dhat, lse, gdhat, out, partT, rg.seg);
 }
 
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
@@ -1188,13 +1235,11 @@ hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, floa
     SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const RowGrid rg = row_grid(g);
-    hipLaunchKernelGGL(k_soft_mrow<false>, rg.grid, rg.block, 0, st, g, im, (const float*)nullptr,
-                       t1, (double*)nullptr, rg.seg);                                        // E1
+    launch_mrow<false>(rg, g, im, nullptr, t1, nullptr, st);                                 // E1
     launch_vv<false>(g, t1, t2, st);                                                         // E2
     const bool soft = dhat && D <= 16 * kMxWaves;
-    hipLaunchKernelGGL(k_soft_wide<false>, rg.grid, rg.block, 0, st, g, t2, theta,
-                       soft ? dhat : nullptr, lse, (const float*)nullptr, A2, (double*)nullptr,
-                       rg.seg);                                                              // A2
+    launch_wide<false>(rg, g, t2, theta, soft ? dhat : nullptr, lse, nullptr, A2, nullptr,
+                       st);                                                                  // A2
     if (dhat && !soft) {
         const size_t P = (size_t)W * H;
         hipLaunchKernelGGL(k_soft_argmin, dim3((unsigned)((P + 255) / 256), B), dim3(256), 0, st,
@@ -1212,12 +1257,10 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const RowGrid rg = row_grid(g);
-    hipLaunchKernelGGL(k_soft_wide<true>, rg.grid, rg.block, 0, st, g, A2, theta,
-                       const_cast<float*>(dhat), const_cast<float*>(lse), gdhat, t2, partT,
-                       rg.seg);                                // G_E2, T-gradient terms
+    launch_wide<true>(rg, g, A2, theta, const_cast<float*>(dhat), const_cast<float*>(lse), gdhat,
+                      t2, partT, st);                                 // G_E2, T-gradient terms
     launch_vv<true>(g, t2, t1, st);                                   // G_E1
-    hipLaunchKernelGGL(k_soft_mrow<true>, rg.grid, rg.block, 0, st, g, im, t1, (float*)nullptr,
-                       partAC, rg.seg);                               // G_E1 . H dc/dlambda
+    launch_mrow<true>(rg, g, im, t1, nullptr, partAC, st);            // G_E1 . H dc/dlambda
     double* blk = partT + (size_t)nrows;  // kRedBlocks x 3 after the row partials
     hipLaunchKernelGGL(k_soft_reduce1, dim3(kRedBlocks), dim3(256), 0, st, partAC,
                        (size_t)rg.parts, partT, (size_t)rg.parts, blk);
