@@ -790,7 +790,10 @@ __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, in
 // columns.  A cost or output lane owns four consecutive columns, so a row
 // prefix is three adds per lane and one wavefront scan of the lane totals,
 // every per-pixel input is a 16-byte load of four columns from a plane, and a
-// store is one 16-byte word.  The apron is 36 rather than 2 kLMax = 34, and
+// store is one 16-byte word; in a row of any length only the quad that the
+// border cuts is stored as what is left of it (stored and, in the staged call,
+// read as single words wherever W % 4 != 0, a frame of 1279 x 720, D = 128 took
+// 0.865 ms, now 0.764, a staged one of 295 x 717, D = 41 0.312 and 0.255).  The apron is 36 rather than 2 kLMax = 34, and
 // the strip 184 rather than 188, so that those quads are aligned to the
 // image's.  The first and last strip have no apron at the image's border and
 // take 20 columns more, so that narrower strips do not mean more of them (960
@@ -826,6 +829,8 @@ struct AggLdsWs {
 };
 static_assert(sizeof(AggLdsWs) <= 160 * 1024, "one workgroup per CU");
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline uint2 lds_ld2(const void* base, uint32_t byte_off) {
@@ -845,6 +850,16 @@ __device__ inline void st128(u32x4 v, rsrc_t r, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+__device__ inline void st96(u32x3 v, rsrc_t r, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b96(v, r, voff, soff, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 0" : : "v"(v));
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ inline void st64(u32x2 v, rsrc_t r, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, 2);
+}
+
 // What the wavefronts of a workgroup share: the item and its buffers.
 struct WsItem {
     rsrc_t rB, rC, rRef, rPar, rCost, rOut;
@@ -853,7 +868,10 @@ struct WsItem {
     uint32_t in_slice_bytes;       // ... and the cost volume's (0 when one slice is left)
     int nout;                      // slices that exist (the others are not stored)
     bool paired;                   // paired layout (see paired_at)
-    bool quads;                    // W % 4 == 0: rows of the volumes keep quads aligned
+    bool quads;                    // W >= 4: a row of the volumes holds a quad
+    bool cut;                      // W % 4 != 0, and the image's right border cuts a quad of
+                                   // the strip's columns
+    int tail;                      // columns of the cut quad that the strip stores
     int base, o0, o1;              // image columns of the strip's first, of its output range
     int ys, y0, y1, nch;           // first stream row (a multiple of 4), band, chunks
 };
@@ -875,6 +893,7 @@ struct WsOutIn {
 struct WsCostLane {
     uint32_t vref, vlm, vpar;      // byte offsets of the lane's columns in a plane row
     uint32_t vq[4];                // staged: byte offsets in a cost row, or kOOB
+    int shift;                     // staged: columns the lane's quad is read further left
     bool ok[kWsSlices][4];         // fused: partner inside the image
 };
 
@@ -941,7 +960,7 @@ __device__ inline void ws_scan(uint32_t (&v)[kWsSlices][4]) {
 // prefixes are modular and every range of a stored output ends inside the
 // image (arms stop at the border), so neither reaches a stored output.
 template <bool kFused>
-__device__ inline void ws_cost_phase(const WsCostLane& ln, const WsCostIn& in, uint2* row,
+__device__ inline void ws_cost_phase(const WsItem& I, const WsCostLane& ln, const WsCostIn& in, uint2* row,
                                      AggLdsWs& S) {
     uint32_t q[kWsSlices][4];
     if constexpr (kFused) {
@@ -975,7 +994,15 @@ __device__ inline void ws_cost_phase(const WsCostLane& ln, const WsCostIn& in, u
         // the volume holds q 2^-20 exactly (1.0 where the partner is outside)
 #pragma unroll
         for (int s = 0; s < kWsSlices; ++s) {
-            const uint32_t c[4] = {in.ref[s].x, in.ref[s].y, in.ref[s].z, in.ref[s].w};
+            uint32_t c[4] = {in.ref[s].x, in.ref[s].y, in.ref[s].z, in.ref[s].w};
+            if (I.cut && I.quads) {  // uniform
+                const bool one = ln.shift & 1, two = ln.shift & 2;
+                c[0] = one ? c[1] : c[0];
+                c[1] = one ? c[2] : c[1];
+                c[2] = one ? c[3] : c[2];
+                c[0] = two ? c[2] : c[0];
+                c[1] = two ? c[3] : c[1];
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 q[s][j] = (uint32_t)(__builtin_bit_cast(float, c[j]) * 0x1p20f);
@@ -1070,9 +1097,9 @@ __device__ inline void ws_out_load(const WsItem& I, int H, uint32_t Wp4, uint32_
 // issues the same number of stores (the hardware drops those out of range):
 // loads and stores complete in order, so with a fixed count the next chunk's
 // records are waited for without waiting for this chunk's stores.
-template <int kRef, bool kQuads>
+template <int kRef, bool kTail>
 __device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
-                                    const uint32_t (&vout)[4], const WsOutIn& in) {
+                                    const uint32_t (&vout)[2], const WsOutIn& in) {
     const int lane = threadIdx.x & 63;
     uint32_t v[kWsSlices][4];
     {
@@ -1121,27 +1148,31 @@ __device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
         const uint32_t(&o)[4] = out[k ? kHi : kLo];
         const bool keep = live && k < I.nout;
         const uint32_t so = keep ? row4 + k * I.slice_bytes : 0u;
-        if constexpr (kQuads) {
-            st128(u32x4{o[0], o[1], o[2], o[3]}, I.rOut, keep ? vout[0] : kOOB, so);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                st32(__builtin_bit_cast(float, o[j]), I.rOut, keep ? vout[j] : kOOB, so);
+        st128(u32x4{o[0], o[1], o[2], o[3]}, I.rOut, keep ? vout[0] : kOOB, so);
+        if constexpr (kTail) {
+            if (I.tail == 1)  // uniform
+                st32(__builtin_bit_cast(float, o[0]), I.rOut, keep ? vout[1] : kOOB, so);
+            else if (I.tail == 2)
+                st64(u32x2{o[0], o[1]}, I.rOut, keep ? vout[1] : kOOB, so);
+            else
+                st96(u32x3{o[0], o[1], o[2]}, I.rOut, keep ? vout[1] : kOOB, so);
         }
     }
 }
 
-// kQuads: rows of the output volume keep the lanes' quads 16-byte aligned.
-template <int kRef, bool kQuads>
+// kTail: the image's right border cuts the strip's last quad.
+template <int kRef, bool kTail>
 __device__ inline void ws_out_loop(const AggArgs& A, const WsItem& I, int w, AggLdsWs& S) {
     const int lane = threadIdx.x & 63, W = A.W, H = A.H;
     const uint32_t Wp4 = (uint32_t)A.rec.Wp * 4, cplane4 = Wp4 * (uint32_t)H;
     const int c = I.base + kWsI0 + 4 * lane;  // image column of the lane's first
     const uint32_t vcol = (uint32_t)(c + kRecApronL) * 4;
-    uint32_t vout[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        vout[j] = c >= I.o0 && c + j < I.o1 && lane < kWsLanes ? (uint32_t)(c + j) * 4 : kOOB;
+    // whole quads are stored as 16 bytes (rows of the volumes keep words aligned,
+    // which is all a buffer store needs); the one that the image's right border
+    // cuts, as its columns inside
+    const bool out = c >= I.o0 && c < I.o1 && lane < kWsLanes, whole = c + 3 < I.o1;
+    const uint32_t vout[2] = {out && whole ? (uint32_t)c * 4 : kOOB,
+                              out && !whole ? (uint32_t)c * 4 : kOOB};
     // the first chunk, even, with an output row of the band: before it there
     // is nothing to do but keep the phases
     const int q0 = max(0, I.y0 + 2 * kLMax - I.ys) / kAggK & ~1;
@@ -1150,11 +1181,11 @@ __device__ inline void ws_out_loop(const AggArgs& A, const WsItem& I, int w, Agg
     for (int p = 0; p < q0 + 2; ++p) __syncthreads();  // phases without a chunk to finish
     for (int q = q0;; q += 2) {
         ws_out_load(I, H, Wp4, cplane4, q + 1, w, vcol, ib);
-        ws_out_phase<kRef, kQuads>(I, W, ws_out_row(I, q, w), S.e2[0][w], vout, ia);
+        ws_out_phase<kRef, kTail>(I, W, ws_out_row(I, q, w), S.e2[0][w], vout, ia);
         __syncthreads();
         if (q + 1 >= I.nch) break;
         ws_out_load(I, H, Wp4, cplane4, q + 2, w, vcol, ia);
-        ws_out_phase<kRef, kQuads>(I, W, ws_out_row(I, q + 1, w), S.e2[1][w], vout, ib);
+        ws_out_phase<kRef, kTail>(I, W, ws_out_row(I, q + 1, w), S.e2[1][w], vout, ib);
         __syncthreads();
         if (q + 2 >= I.nch) break;
     }
@@ -1184,8 +1215,9 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
     I.nch = (y1 + 2 * kLMax - I.ys + kAggK - 1) / kAggK;
     I.nout = min(kWsSlices, min(A.D, dend) - d);
     I.paired = A.paired;
-    I.quads = W % 4 == 0 && (reinterpret_cast<uintptr_t>(A.out) & 15) == 0 &&
-              (kFused || (reinterpret_cast<uintptr_t>(A.cost) & 15) == 0);
+    I.quads = W >= 4;
+    I.cut = W % 4 != 0 && I.base + kStripThreads > W;
+    I.tail = strip == A.nstrips - 1 ? W % 4 : 0;
     const PixPlanes px(W, H);
     const uint32_t pixbytes = px.bytes();
     I.Wq4 = px.Wq * 4;
@@ -1233,8 +1265,13 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
                 for (int s = 0; s < kWsSlices; ++s)
                     ln.ok[s][j] = b + j + s >= 0 && b + j + s < W;
         } else {
+            // the quad that the border cuts is read as the row's last four
+            // columns and shifted (columns outside the image may hold anything:
+            // they only shift prefixes whose differences nothing takes)
+            ln.shift = I.cut && c < W && c + 4 > W ? c + 4 - W : 0;
+            ln.vq[0] = c >= 0 && c < W ? (uint32_t)(I.quads ? c - ln.shift : c) * 4 : kOOB;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 1; j < 4; ++j)
                 ln.vq[j] = c + j >= 0 && c + j < W ? (uint32_t)(c + j) * 4 : kOOB;
         }
         const int last = I.nch + 1;  // phases 0 .. nch + 1
@@ -1242,11 +1279,11 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
         ws_cost_load<kFused>(I, H, W, 0, w, ln, ia);
         for (int p = 0;; p += 2) {
             ws_cost_load<kFused>(I, H, W, p + 1, w, ln, ib);
-            ws_cost_phase<kFused>(ln, ia, S.x1[0][w], S);
+            ws_cost_phase<kFused>(I, ln, ia, S.x1[0][w], S);
             __syncthreads();
             if (p + 1 > last) break;
             ws_cost_load<kFused>(I, H, W, p + 2, w, ln, ia);
-            ws_cost_phase<kFused>(ln, ib, S.x1[1][w], S);
+            ws_cost_phase<kFused>(I, ln, ib, S.x1[1][w], S);
             __syncthreads();
             if (p + 2 > last) break;
         }
@@ -1280,14 +1317,14 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
         __syncthreads();  // the last phase: output wavefronts only
     } else {
         const bool right = !kFused || A.ref != 0;
-        if (right && I.quads)
-            ws_out_loop<1, true>(A, I, w, S);
-        else if (right)
+        if (right && I.tail == 0)
             ws_out_loop<1, false>(A, I, w, S);
-        else if (I.quads)
-            ws_out_loop<0, true>(A, I, w, S);
-        else
+        else if (right)
+            ws_out_loop<1, true>(A, I, w, S);
+        else if (I.tail == 0)
             ws_out_loop<0, false>(A, I, w, S);
+        else
+            ws_out_loop<0, true>(A, I, w, S);
     }
 }
 

@@ -25,6 +25,10 @@ SHAPES = [
     (409, 38, 3),     # three strips
     (592, 70, 16),    # three strips exactly
     (593, 39, 2),
+    (410, 37, 3),     # the border cuts a quad of the second strip's apron too
+    (411, 21, 5),
+    (10, 9, 4),
+    (11, 8, 5),
 ]
 
 
@@ -55,17 +59,20 @@ def test_one_call_volumes_and_maps(W, H, D):
 
 
 @pytest.mark.parametrize("offset", [0, 1])
-@pytest.mark.parametrize("W,H,D", [(184, 37, 5), (225, 34, 7), (408, 71, 6)])
+@pytest.mark.parametrize("W,H,D", [(184, 37, 5), (225, 34, 7), (408, 71, 6), (226, 20, 3),
+                                   (227, 19, 4), (411, 21, 5), (3, 5, 2), (2, 4, 1)])
 def test_staged_aggregation_any_alignment(W, H, D, offset):
-    """Volumes that start `offset` floats into their buffers: only 4-byte
-    aligned, so the rows are read and written word by word."""
+    """Volumes that start `offset` floats into their buffers, rows of any length:
+    only 4-byte aligned, with a last quad of one to four columns (words where a
+    row has less than four)."""
     import torch
     from paper_2203_02300_amd import StereoMatcher
     L, R = scene(W, H, D)
-    st = oracle.stages(L, R, D)
+    cw = 9 if W >= 9 and H >= 7 else 1
+    st = oracle.stages(L, R, D, cw=cw, ch=min(cw, 7))
     n = D * H * W
     print(f"staged {W}x{H} D={D} offset {offset}", flush=True)
-    with StereoMatcher(W, H, D) as m:
+    with StereoMatcher(W, H, D, census_w=cw, census_h=min(cw, 7)) as m:
         for tag in ("L", "R"):
             q = (st["q" + tag].astype(np.float64) * 2.0 ** -20).astype(np.float32)
             cost = torch.zeros(n + offset, device="cuda")
