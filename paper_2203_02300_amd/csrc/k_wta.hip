@@ -12,7 +12,7 @@
 
 namespace {
 
-constexpr int kWtaThreads = 512;  // most threads of a row
+constexpr int kWtaThreads = 1024;  // most threads of a row
 
 // One workgroup per image row: its second half takes the right view's quads of
 // four pixels, the first half the left view's; the right disparities go to LDS
@@ -29,7 +29,10 @@ constexpr int kWtaThreads = 512;  // most threads of a row
 // 61.4 us, now 57.0; 64 x 48, D = 16 43.2, now 40.0; 640 x 480, D = 64 168.8,
 // now 167.2; 1280 x 720 the same.  Workgroups of at most 128, 256, 512 and 640
 // threads: 437 x 93 63.0, 57.0, 57.0, 57.2; staged 640 x 480 256, 254, 239, 239
-// (243 before).
+// (243 before).  Rows of more than 1024 columns want more than 512: with them a
+// row's last quads went in a second turn, staged 1280 x 720, D = 128 192 us
+// instead of 153 with up to 1024 threads (157 as two launches), the one-call
+// launch 87.2 instead of 85.0.
 template <bool kPaired, bool kNarrow>
 __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
     const float* __restrict__ aggL, const float* __restrict__ aggR, int P, int W, int D,
