@@ -267,10 +267,13 @@ __device__ inline RowTask row_task(int block, int rows, int ng, int w, int nw) {
 // Stores the stage's 16 x 64 outputs: disparities d0 .. d0 + 15, columns x0 ..
 // x0 + 63, those inside the volume only; `out` is row y of disparity 0, P a
 // plane.  256 contiguous bytes per disparity, and four disparities per store.
+// kStream (W a multiple of eight): past the caches, which a large volume only
+// passes through; see soft_stream.
+template <bool kStream>
 __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, size_t P, int d0,
                                 int D, int x0, int W) {
     const int lane = threadIdx.x & 63;
-    if ((W & 3) == 0) {  // a lane's four columns are inside together, 16-byte aligned
+    if (kStream || (W & 3) == 0) {  // a lane's four columns are inside together, 16-byte aligned
         const int c = 4 * (lane & 15), x = x0 + c;
         asm volatile("" : "+s"(P));  // the row addresses are made here, not kept over the row
         v4f o[4];
@@ -280,7 +283,12 @@ __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, 
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int d = d0 + 4 * j + (lane >> 4);
-            if (x >= 0 && x < W && d < D) *reinterpret_cast<v4f*>(out + d * P + x) = o[j];
+            v4f* p = reinterpret_cast<v4f*>(out + d * P + x);
+            if (x < 0 || x >= W || d >= D) continue;
+            if (kStream)
+                __builtin_nontemporal_store(o[j], p);
+            else
+                *p = o[j];
         }
     } else {
         const int x = x0 + lane;
@@ -292,7 +300,7 @@ __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, 
     }
 }
 
-template <bool kDeriv, bool kShare>
+template <bool kDeriv, bool kShare, bool kStream>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, SoftImg im,
                                                                 const float* __restrict__ G,
                                                                 float* __restrict__ out,
@@ -488,7 +496,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
                     }
                     if (!kDeriv) {
                         __builtin_amdgcn_wave_barrier();
-                        put_rows(stage, out + vol, P, d0, D, X - 32, W);
+                        put_rows<kStream>(stage, out + vol, P, d0, D, X - 32, W);
                         __builtin_amdgcn_wave_barrier();
                     }
                 }
@@ -568,7 +576,7 @@ __device__ inline void digit_planes3(const uint32_t* stage, v4i (&b)[3]) {
     }
 }
 
-template <bool kAdj, bool kShare>
+template <bool kAdj, bool kShare, bool kStream>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     SoftGeom g, const float* __restrict__ in, const float* __restrict__ theta,
     float* __restrict__ dhat, float* __restrict__ lse, const float* __restrict__ gdhat,
@@ -800,7 +808,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                     }
                     __builtin_amdgcn_wave_barrier();
                 }
-                put_rows(stage, out + vol, P, d0, D, X - 32, W);
+                put_rows<kStream>(stage, out + vol, P, d0, D, X - 32, W);
                 __builtin_amdgcn_wave_barrier();
             }
 #pragma unroll
@@ -1196,27 +1204,51 @@ static RowGrid row_grid(const SoftGeom& g) {
     return RowGrid{share, seg, rows * segs * ng, dim3(blocks, segs), dim3(64 * nw)};
 }
 
+// Volumes are written past the caches where they are large and their rows are
+// whole sectors (a part of one has to be read first).  8 pairs of 640 x 480, D = 64:
+// forward and backward 2147 us, 2050 so, the forward alone 1063 and 984; 8 of
+// 400 x 300, D = 32 (31 M entries) 677 and 661; 1 of 640 x 480, D = 63 (19 M) 391 and
+// 389; but 4 of 328 x 240, D = 40 (13 M) 333 and 342, and 8 of 636 x 480, D = 63 2560
+// and 2693.
+static bool soft_stream(const SoftGeom& g) {
+    return g.W % 8 == 0 && (long long)g.B * g.D * g.H * g.W > 16LL << 20;
+}
+
+// go(share, stream): the bools as types
+template <typename Go>
+static void with_row_kind(const RowGrid& rg, const SoftGeom& g, Go go) {
+    const auto second = [&](auto share) {
+        if (soft_stream(g))
+            go(share, std::true_type{});
+        else
+            go(share, std::false_type{});
+    };
+    if (rg.share)
+        second(std::true_type{});
+    else
+        second(std::false_type{});
+}
+
 template <bool kDeriv>
 static void launch_mrow(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, const float* G,
                         float* out, double* part, hipStream_t st) {
-    if (rg.share)
-        hipLaunchKernelGGL((k_soft_mrow<kDeriv, true>), rg.grid, rg.block, 0, st, g, im, G, out,
-                           part, rg.seg);
-    else
-        hipLaunchKernelGGL((k_soft_mrow<kDeriv, false>), rg.grid, rg.block, 0, st, g, im, G, out,
-                           part, rg.seg);
+    with_row_kind(rg, g, [&](auto share, auto stream) {
+        // the derivative's pass writes no volume
+        constexpr bool kStream = !kDeriv && decltype(stream)::value;
+        hipLaunchKernelGGL((k_soft_mrow<kDeriv, decltype(share)::value, kStream>), rg.grid,
+                           rg.block, 0, st, g, im, G, out, part, rg.seg);
+    });
 }
 
 template <bool kAdj>
 static void launch_wide(const RowGrid& rg, const SoftGeom& g, const float* in, const float* theta,
                         float* dhat, float* lse, const float* gdhat, float* out, double* partT,
                         hipStream_t st) {
-    if (rg.share)
-        hipLaunchKernelGGL((k_soft_wide<kAdj, true>), rg.grid, rg.block, 0, st, g, in, theta, dhat,
-                           lse, gdhat, out, partT, rg.seg);
-    else
-        hipLaunchKernelGGL((k_soft_wide<kAdj, false>), rg.grid, rg.block, 0, st, g, in, theta,
-                           dhat, lse, gdhat, out, partT, rg.seg);
+    with_row_kind(rg, g, [&](auto share, auto stream) {
+        hipLaunchKernelGGL((k_soft_wide<kAdj, decltype(share)::value, decltype(stream)::value>),
+                           rg.grid, rg.block, 0, st, g, in, theta, dhat, lse, gdhat, out, partT,
+                           rg.seg);
+    });
 }
 
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
