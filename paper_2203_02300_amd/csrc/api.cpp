@@ -554,7 +554,8 @@ static dco_status soft_reserve(dco_stereo* h, int B) {
     if (f.cap >= B) return DCO_OK;
     (void)hipStreamSynchronize(h->stream);
     free_soft(f);
-    const size_t P = (size_t)h->W * h->H, V = P * h->D * B;
+    const size_t P = (size_t)h->W * h->H;
+    const size_t V = (size_t)soft_pitch(h->W) * h->H * h->D * B;
     DCO_TRY(dev_alloc(&f.pix[0], P * B));
     DCO_TRY(dev_alloc(&f.pix[1], P * B));
     DCO_TRY(dev_alloc(&f.arms, P * B));

@@ -42,6 +42,8 @@ struct SoftGeom {
     const uint2* vrec;     // B x H x W column records (col_record, 1 / stage-1 region count)
     const float* n2;       // B x H x W stage-2 region counts
     int B, W, H, D;
+    __host__ __device__ int pitch() const { return soft_pitch(W); }  // of a volume's row
+    __host__ __device__ size_t plane() const { return (size_t)pitch() * H; }
 };
 
 __device__ inline int arm(uint32_t a, int k) { return (a >> (8 * k)) & 0xff; }
@@ -267,36 +269,28 @@ __device__ inline RowTask row_task(int block, int rows, int ng, int w, int nw) {
 // Stores the stage's 16 x 64 outputs: disparities d0 .. d0 + 15, columns x0 ..
 // x0 + 63, those inside the volume only; `out` is row y of disparity 0, P a
 // plane.  256 contiguous bytes per disparity, and four disparities per store.
-// kStream (W a multiple of eight): past the caches, which a large volume only
-// passes through; see soft_stream.
+// Rows are whole 64-byte pieces (soft_pitch): the columns past the image's hold
+// nothing.  kStream: past the caches, which a large volume only passes through;
+// see soft_stream.
 template <bool kStream>
 __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, size_t P, int d0,
                                 int D, int x0, int W) {
     const int lane = threadIdx.x & 63;
-    if (kStream || (W & 3) == 0) {  // a lane's four columns are inside together, 16-byte aligned
-        const int c = 4 * (lane & 15), x = x0 + c;
-        asm volatile("" : "+s"(P));  // the row addresses are made here, not kept over the row
-        v4f o[4];
+    const int c = 4 * (lane & 15), x = x0 + c;
+    asm volatile("" : "+s"(P));  // the row addresses are made here, not kept over the row
+    v4f o[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            o[j] = *reinterpret_cast<const v4f*>(stage + (4 * j + (lane >> 4)) * kMxStride + c);
+    for (int j = 0; j < 4; ++j)
+        o[j] = *reinterpret_cast<const v4f*>(stage + (4 * j + (lane >> 4)) * kMxStride + c);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int d = d0 + 4 * j + (lane >> 4);
-            v4f* p = reinterpret_cast<v4f*>(out + d * P + x);
-            if (x < 0 || x >= W || d >= D) continue;
-            if (kStream)
-                __builtin_nontemporal_store(o[j], p);
-            else
-                *p = o[j];
-        }
-    } else {
-        const int x = x0 + lane;
-#pragma unroll 1  // hoisted, its 16 row addresses would cost the other path its registers
-        for (int j = 0; j < 16; ++j) {
-            const float o = __builtin_bit_cast(float, stage[j * kMxStride + lane]);
-            if (x >= 0 && x < W && d0 + j < D) out[(d0 + j) * P + x] = o;
-        }
+    for (int j = 0; j < 4; ++j) {
+        const int d = d0 + 4 * j + (lane >> 4);
+        if (x < 0 || x >= W || d >= D) continue;
+        v4f* p = reinterpret_cast<v4f*>(out + d * P + x);
+        if (kStream)
+            __builtin_nontemporal_store(o[j], p);
+        else
+            *p = o[j];
     }
 }
 
@@ -335,14 +329,14 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     const uint4* pl = im.pixL + pix;
     const uint4* pr = im.pixR + pix;
     const uint32_t* ar = g.arms + pix;
-    const size_t vol = ((size_t)b * D) * P + (size_t)y * W;
+    const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch();
     uint32_t* stage = stages[w];
     const float inv0 = im.tab[kTabScale + (kDeriv ? 3 : 1)];
     int par = 0;
     for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
         const int grp = g0 + rt.grp, d0 = 16 * grp, d = d0 + n;
         const bool active = rt.on && grp < ng;
-        const size_t orow = vol + (size_t)min(d, D - 1) * P;
+        const size_t orow = vol + (size_t)min(d, D - 1) * Q;
         v4i bp[NQ][4];
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
@@ -496,7 +490,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
                     }
                     if (!kDeriv) {
                         __builtin_amdgcn_wave_barrier();
-                        put_rows<kStream>(stage, out + vol, P, d0, D, X - 32, W);
+                        put_rows<kStream>(stage, out + vol, Q, d0, D, X - 32, g.pitch());
                         __builtin_amdgcn_wave_barrier();
                     }
                 }
@@ -596,7 +590,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     const int row = rt.row, y = row % g.H, b = row / g.H;
     const int it0 = blockIdx.y * seg_its, it1 = min(it0 + seg_its, (W + 95) >> 6);
     const size_t P = (size_t)W * g.H, pix = (size_t)b * P + (size_t)y * W;
-    const size_t vol = ((size_t)b * D) * P + (size_t)y * W;
+    const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch();
     const float T = theta[2], invT = 1.0f / T;
     uint32_t* stage = stages[w];
     int par = 0;
@@ -668,7 +662,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                 float G[16];
                 uint32_t m = 0;  // bits of the largest |G| (a NaN's are larger still)
                 double t = 0.0;
-                size_t Pv = P;
+                size_t Pv = Q;
                 asm volatile("" : "+s"(Pv));  // else 16 row addresses live in registers
                 const float* a2 = in + vol + (size_t)d0 * Pv + xc;
                 const auto seed = [&](auto full) {
@@ -808,7 +802,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                     }
                     __builtin_amdgcn_wave_barrier();
                 }
-                put_rows<kStream>(stage, out + vol, P, d0, D, X - 32, W);
+                put_rows<kStream>(stage, out + vol, Q, d0, D, X - 32, g.pitch());
                 __builtin_amdgcn_wave_barrier();
             }
 #pragma unroll
@@ -906,17 +900,16 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
     __shared__ __align__(16) double rings[2][kSoftRing][kSoftCols];
     const int t = threadIdx.x, x = blockIdx.x * kSoftCols + t;
     const int bd = blockIdx.y, b = bd / g.D;
-    const size_t P = (size_t)g.W * g.H;
+    const size_t P = (size_t)g.W * g.H, Q = g.plane();
     const int r0 = blockIdx.z * seg_rows, r1 = min(r0 + seg_rows, g.H);
-    const int plane = (int)(P * 4);
-    const uint32_t W4 = 4u * (uint32_t)g.W;
-    const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + (size_t)bd * P),
-                                                       (short)0, plane, 0x00020000);
+    const uint32_t W4 = 4u * (uint32_t)g.pitch(), W8 = 8u * (uint32_t)g.W;
+    const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + (size_t)bd * Q),
+                                                       (short)0, (int)(Q * 4), 0x00020000);
     const auto rec = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint2*>(g.vrec + (size_t)b * P), (short)0, 2 * plane, 0x00020000);
+        const_cast<uint2*>(g.vrec + (size_t)b * P), (short)0, (int)(P * 8), 0x00020000);
     const auto dst = __builtin_amdgcn_make_buffer_rsrc(
-        out + (size_t)bd * P + (size_t)r0 * g.W, (short)0, (int)((uint32_t)(r1 - r0) * W4),
-        0x00020000);
+        out + (size_t)bd * Q + (size_t)r0 * g.pitch(), (short)0,
+        (int)((uint32_t)(r1 - r0) * W4), 0x00020000);
     const uint32_t x4 = x < g.W ? 4u * (uint32_t)x : kSoftDrop;
     const uint32_t t8 = 8u * t;
     char* const R1 = reinterpret_cast<char*>(&rings[0][0][0]);
@@ -928,7 +921,7 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
     const int last = r1 + kSoftLag;
     uint32_t v_off = x4 + (uint32_t)first * W4;                     // row y + lead
     // records of row y + lead (adjoint) or y - kLMax + lead (forward)
-    uint32_t n_off = x < g.W ? 2 * (v_off - (kAdj ? 0u : (uint32_t)kLMax * W4)) : kSoftDrop;
+    uint32_t n_off = x < g.W ? 2 * x4 + (uint32_t)(first - (kAdj ? 0 : kLMax)) * W8 : kSoftDrop;
     uint32_t d_off = x4 + (uint32_t)(first - r0 - kSoftLead * kSoftPre - kSoftLag) * W4;
     float v[kSoftBufs][kSoftPre], rn[kSoftTurn][kSoftPre];
     uint32_t p[kSoftBufs][kSoftPre], p2[kSoftTurn][kSoftPre];
@@ -1059,7 +1052,7 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
                 p[f][k] = r[0];
                 rl[f][k] = __builtin_bit_cast(float, (uint32_t)r[1]);
                 v_off += W4;
-                n_off += 2 * W4;
+                n_off += W8;
             }
         }
     }
@@ -1080,12 +1073,14 @@ __global__ __launch_bounds__(256) void k_soft_argmin(SoftGeom g, const float* __
     const int b = blockIdx.y;
     if (i >= P) return;
     const float invT = 1.0f / theta[2];
-    const float* a = A2 + (size_t)b * g.D * P + i;
+    const size_t Q = g.plane();
+    const float* a = A2 + (size_t)b * g.D * Q + i +
+                     (uint32_t)i / (uint32_t)g.W * (uint32_t)(g.pitch() - g.W);
     float m = -INFINITY, z = 0.0f, zd = 0.0f;
     for (int d0 = 0; d0 < g.D; d0 += kArgBatch) {
         float v[kArgBatch];
 #pragma unroll
-        for (int j = 0; j < kArgBatch; ++j) v[j] = -a[(size_t)min(d0 + j, g.D - 1) * P] * invT;
+        for (int j = 0; j < kArgBatch; ++j) v[j] = -a[(size_t)min(d0 + j, g.D - 1) * Q] * invT;
         float mb = m;
 #pragma unroll
         for (int j = 0; j < kArgBatch; ++j) mb = d0 + j < g.D ? fmaxf(mb, v[j]) : mb;
@@ -1204,14 +1199,12 @@ static RowGrid row_grid(const SoftGeom& g) {
     return RowGrid{share, seg, rows * segs * ng, dim3(blocks, segs), dim3(64 * nw)};
 }
 
-// Volumes are written past the caches where they are large and their rows are
-// whole sectors (a part of one has to be read first).  8 pairs of 640 x 480, D = 64:
-// forward and backward 2147 us, 2050 so, the forward alone 1063 and 984; 8 of
-// 400 x 300, D = 32 (31 M entries) 677 and 661; 1 of 640 x 480, D = 63 (19 M) 391 and
-// 389; but 4 of 328 x 240, D = 40 (13 M) 333 and 342, and 8 of 636 x 480, D = 63 2560
-// and 2693.
+// Large volumes are written past the caches.  8 pairs of 640 x 480, D = 64: forward
+// and backward 2147 us, 2050 so, the forward alone 1063 and 977; 8 of 400 x 300,
+// D = 32 (31 M entries) 677 and 658; 1 of 640 x 480, D = 63 (19 M) 393 and 385; but 4
+// of 328 x 240, D = 40 (13 M) 333 and 342.
 static bool soft_stream(const SoftGeom& g) {
-    return g.W % 8 == 0 && (long long)g.B * g.D * g.H * g.W > 16LL << 20;
+    return (long long)g.B * g.D * g.H * g.W > 16LL << 20;
 }
 
 // go(share, stream): the bools as types
