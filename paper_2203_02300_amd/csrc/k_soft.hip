@@ -25,7 +25,7 @@
 // with fixed-order two-level reductions.  The only atomics are LDS adds that one
 // thread makes to its own column in program order.
 //
-// Layout: volumes are B x D x H x W float in handle scratch; arms and the
+// Layout: volumes are B x D x H x soft_pitch(W) float in handle scratch; arms and the
 // packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost and row
 // passes run one wavefront per image row and 16 disparities (k_soft_mrow,
 // k_soft_wide); the column pass runs one thread per column, streaming down the
@@ -199,8 +199,8 @@ __device__ inline int xcd_block(int b, int n) {
 //   - E1 goes back through LDS to be stored as 256 contiguous bytes per
 //     disparity (64-byte pieces of 16 planes: 0.35 ms instead of 0.30 then).
 //
-// Measured at 8 pairs of 640 x 480, D = 64: E1 0.25 ms (writes 0.63 GB; vector
-// issue about 0.15 ms), the gradient 0.32 ms (reads 0.63 GB; issue bound, 64 %
+// Measured at 8 pairs of 640 x 480, D = 64: E1 0.22 ms (writes 0.63 GB, past the
+// caches, 0.25 through them; vector issue about 0.15 ms), the gradient 0.32 ms (reads 0.63 GB; issue bound, 64 %
 // vector busy).  As FP64 prefix sums per row and disparity, two table passes,
 // four LDS scans and eight gathers per 256 columns, they took 0.35 and 0.58 ms.
 // Steps: 32 or 64 disparities per wavefront 0.35 / 0.49 and 0.44 / 0.74 ms (too
@@ -850,7 +850,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
 // 1/N = 0: they add zero to both sums.
 //
 // Measured at 8 x 64 planes of 640 x 480 (1.26 GB in and out; a copy of that
-// size takes about 0.25 ms): 0.34 ms forward and 0.38 ms adjoint, bound by the
+// size takes about 0.25 ms): 0.33 ms forward and 0.38 to 0.41 ms adjoint, bound by the
 // issue of the four wavefronts (33 instructions per row) and, in the adjoint,
 // the LDS adds; as two passes over the volume, each near the copy's rate, 0.58
 // ms each.  Record and 1 / N in one 8-byte load instead of two loads: forward
