@@ -179,7 +179,8 @@ dco_status alloc_records(AggRecords* r, int W, int H) {
 }
 
 static dco_status alloc_scratch(dco_stereo* h) {
-    const size_t P = (size_t)h->W * h->H, V = P * h->D;
+    const size_t P = (size_t)h->W * h->H;
+    const size_t V = (size_t)agg_pitch(h->W, h->p.agg_iters) * h->H * h->D;
     dco_scratch& s = h->s;
     for (int v = 0; v < 2; ++v) {
         DCO_TRY(dev_alloc(&s.arms[v], P));
@@ -401,7 +402,7 @@ extern "C" dco_status dco_wta_lrcheck(dco_stereo* h, const float* aggL, const fl
     DCO_TRY(need(valid, "valid"));
     int16_t* oL = dL ? dL : h->s.dint[0];
     int16_t* oR = dR ? dR : h->s.dint[1];
-    DCO_HIP_CHECK(launch_wta_lr(aggL, aggR, false, h->W, h->H, h->D, h->p.subpixel,
+    DCO_HIP_CHECK(launch_wta_lr(aggL, aggR, false, h->W, h->W, h->H, h->D, h->p.subpixel,
                                 h->p.lr_max_diff, oL, oR, disp, valid, HalfOut{}, h->stream));
     return DCO_OK;
 }
@@ -420,6 +421,7 @@ static dco_status match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
     }
     dco_scratch& s = h->s;
     const dco_params& p = h->p;
+    const int pitch = agg_pitch(h->W, p.agg_iters);
     const uint8_t* img[2] = {rgbL, rgbR};
     DCO_TRY(prof_mark(h));
     DCO_HIP_CHECK(launch_front2(img[0], img[1], h->W, h->H, p.census_w, p.census_h, p.arm_L1,
@@ -429,12 +431,12 @@ static dco_status match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
     DCO_TRY(prof_mark(h));
     DCO_HIP_CHECK(launch_cost_aggregate2(s.pix[0], s.pix[1], s.rec[0], s.rec[1], h->W, h->H, h->D,
                                          p.agg_iters, h->tabA, h->tabC, h->alpha, h->beta,
-                                         p.arm_L1, s.agg[0], s.agg[1], true, h->stream));
+                                         p.arm_L1, s.agg[0], s.agg[1], true, pitch, h->stream));
     s.agg_paired = p.agg_iters == 2;
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
     // from the even slices (each pair's minimum) when the volumes are paired
-    DCO_HIP_CHECK(launch_wta_lr(s.agg[0], s.agg[1], s.agg_paired, h->W, h->H, h->D, p.subpixel,
+    DCO_HIP_CHECK(launch_wta_lr(s.agg[0], s.agg[1], s.agg_paired, pitch, h->W, h->H, h->D, p.subpixel,
                                 p.lr_max_diff, s.dint[0], s.dint[1], disp, valid,
                                 p.vote_iters > 0 ? HalfOut{} : half, h->stream));
     DCO_TRY(prof_mark(h));
@@ -442,8 +444,8 @@ static dco_status match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
     if (p.vote_iters > 0)
-        DCO_HIP_CHECK(launch_vote(s.dint[0], valid, s.arms[0], s.agg[0], s.agg_paired, h->W, h->H,
-                                  h->D, p.vote_iters, p.subpixel, s.vote[0], s.vote[1], disp,
+        DCO_HIP_CHECK(launch_vote(s.dint[0], valid, s.arms[0], s.agg[0], s.agg_paired, pitch, h->W,
+                                  h->H, h->D, p.vote_iters, p.subpixel, s.vote[0], s.vote[1], disp,
                                   valid, nullptr, half, h->stream));
     DCO_TRY(prof_mark(h));
     return DCO_OK;
@@ -499,7 +501,7 @@ extern "C" dco_status dco_vote_refine(dco_stereo* h, const uint8_t* armsL, const
         dco_set_error("handle has no scratch");
         return DCO_ERR_STATE;
     }
-    DCO_HIP_CHECK(launch_vote(dL, valid, reinterpret_cast<const uint32_t*>(armsL), aggL, false,
+    DCO_HIP_CHECK(launch_vote(dL, valid, reinterpret_cast<const uint32_t*>(armsL), aggL, false, h->W,
                               h->W, h->H, h->D, iters, h->p.subpixel, h->s.vote[0], h->s.vote[1],
                               disp, valid_out, dvote, HalfOut{}, h->stream));
     return DCO_OK;
@@ -522,7 +524,7 @@ extern "C" dco_status dco_stereo_agg_slices(dco_stereo* h, int view, int d0, int
     }
     const size_t P = (size_t)h->W * h->H;
     if (h->s.agg_paired)
-        DCO_HIP_CHECK(launch_unpair(h->s.agg[view], h->W, h->H, h->D, d0, n, out, h->stream));
+        DCO_HIP_CHECK(launch_unpair(h->s.agg[view], agg_pitch(h->W, 2), h->W, h->H, h->D, d0, n, out, h->stream));
     else
         DCO_HIP_CHECK(hipMemcpyAsync(out, h->s.agg[view] + (size_t)d0 * P,
                                      (size_t)n * P * sizeof(float), hipMemcpyDeviceToDevice,

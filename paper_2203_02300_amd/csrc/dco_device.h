@@ -550,10 +550,11 @@ struct AggArgs {
     const float* alpha;
     const float* beta;
     AggRecords rec;            // padded per-pixel records of the reference view
-    float* out;                // D x H x W
+    float* out;                // D x H rows of `pitch` columns (one stage: W)
     // two-slice kernel: store `out` in the paired layout (see paired_at)
     bool paired;
     int W, H, D, nstrips, ref, L1;
+    int pitch;  // two-slice kernel: columns past W may hold anything
 };
 
 // Paired layout of a D-slice cost volume: for each pixel and pair of slices
@@ -871,7 +872,7 @@ struct WsItem {
     bool quads;                    // W >= 4: a row of the volumes holds a quad
     bool cut;                      // W % 4 != 0, and the image's right border cuts a quad of
                                    // the strip's columns
-    int tail;                      // columns of the cut quad that the strip stores
+    int tail;                      // columns that the strip stores of a quad the rows' end cuts
     int base, o0, o1;              // image columns of the strip's first, of its output range
     int ys, y0, y1, nch;           // first stream row (a multiple of 4), band, chunks
 };
@@ -1098,7 +1099,7 @@ __device__ inline void ws_out_load(const WsItem& I, int H, uint32_t Wp4, uint32_
 // loads and stores complete in order, so with a fixed count the next chunk's
 // records are waited for without waiting for this chunk's stores.
 template <int kRef, bool kTail>
-__device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
+__device__ inline void ws_out_phase(const WsItem& I, int pitch, int y2, uint2* row,
                                     const uint32_t (&vout)[2], const WsOutIn& in) {
     const int lane = threadIdx.x & 63;
     uint32_t v[kWsSlices][4];
@@ -1142,7 +1143,7 @@ __device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
         }
     }
     const bool live = y2 >= I.y0 && y2 < I.y1;  // uniform
-    const uint32_t row4 = live ? (uint32_t)(y2 * W) * 4 : 0u;
+    const uint32_t row4 = live ? (uint32_t)(y2 * pitch) * 4 : 0u;
 #pragma unroll
     for (int k = 0; k < kWsSlices; ++k) {
         const uint32_t(&o)[4] = out[k ? kHi : kLo];
@@ -1160,16 +1161,16 @@ __device__ inline void ws_out_phase(const WsItem& I, int W, int y2, uint2* row,
     }
 }
 
-// kTail: the image's right border cuts the strip's last quad.
+// kTail: the output rows' end cuts the strip's last quad.
 template <int kRef, bool kTail>
 __device__ inline void ws_out_loop(const AggArgs& A, const WsItem& I, int w, AggLdsWs& S) {
-    const int lane = threadIdx.x & 63, W = A.W, H = A.H;
+    const int lane = threadIdx.x & 63, H = A.H;
     const uint32_t Wp4 = (uint32_t)A.rec.Wp * 4, cplane4 = Wp4 * (uint32_t)H;
     const int c = I.base + kWsI0 + 4 * lane;  // image column of the lane's first
     const uint32_t vcol = (uint32_t)(c + kRecApronL) * 4;
     // whole quads are stored as 16 bytes (rows of the volumes keep words aligned,
-    // which is all a buffer store needs); the one that the image's right border
-    // cuts, as its columns inside
+    // which is all a buffer store needs); the one that the rows' end cuts, as its
+    // columns inside
     const bool out = c >= I.o0 && c < I.o1 && lane < kWsLanes, whole = c + 3 < I.o1;
     const uint32_t vout[2] = {out && whole ? (uint32_t)c * 4 : kOOB,
                               out && !whole ? (uint32_t)c * 4 : kOOB};
@@ -1181,11 +1182,11 @@ __device__ inline void ws_out_loop(const AggArgs& A, const WsItem& I, int w, Agg
     for (int p = 0; p < q0 + 2; ++p) __syncthreads();  // phases without a chunk to finish
     for (int q = q0;; q += 2) {
         ws_out_load(I, H, Wp4, cplane4, q + 1, w, vcol, ib);
-        ws_out_phase<kRef, kTail>(I, W, ws_out_row(I, q, w), S.e2[0][w], vout, ia);
+        ws_out_phase<kRef, kTail>(I, A.pitch, ws_out_row(I, q, w), S.e2[0][w], vout, ia);
         __syncthreads();
         if (q + 1 >= I.nch) break;
         ws_out_load(I, H, Wp4, cplane4, q + 2, w, vcol, ia);
-        ws_out_phase<kRef, kTail>(I, W, ws_out_row(I, q + 1, w), S.e2[1][w], vout, ib);
+        ws_out_phase<kRef, kTail>(I, A.pitch, ws_out_row(I, q + 1, w), S.e2[1][w], vout, ib);
         __syncthreads();
         if (q + 2 >= I.nch) break;
     }
@@ -1208,7 +1209,7 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
     WsItem I;
     I.base = strip * kWsOut - kWsI0;
     I.o0 = strip == 0 ? 0 : I.base + kWsApron;
-    I.o1 = strip == A.nstrips - 1 ? W : I.base + kWsApron + kWsOut;
+    I.o1 = strip == A.nstrips - 1 ? A.pitch : I.base + kWsApron + kWsOut;
     I.y0 = y0;
     I.y1 = y1;
     I.ys = max(0, y0 - 2 * kLMax) & ~3;  // warm-up rows so that every range is complete
@@ -1217,7 +1218,7 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
     I.paired = A.paired;
     I.quads = W >= 4;
     I.cut = W % 4 != 0 && I.base + kStripThreads > W;
-    I.tail = strip == A.nstrips - 1 ? W % 4 : 0;
+    I.tail = strip == A.nstrips - 1 ? A.pitch % 4 : 0;
     const PixPlanes px(W, H);
     const uint32_t pixbytes = px.bytes();
     I.Wq4 = px.Wq * 4;
@@ -1232,8 +1233,8 @@ __device__ inline void agg_stream_ws(const AggArgs& A, int d, int dend, int stri
                      : make_rsrc(A.cost + (size_t)d * slice,
                                  (uint32_t)min(kWsSlices, A.D - d) * P4);
     I.in_slice_bytes = A.D - d >= 2 ? P4 : 0u;
-    I.rOut = make_rsrc(A.out + (size_t)d * slice, (uint32_t)I.nout * P4);
-    I.slice_bytes = P4;
+    I.slice_bytes = (uint32_t)A.pitch * H * 4;
+    I.rOut = make_rsrc(A.out + (size_t)d * A.pitch * H, (uint32_t)I.nout * I.slice_bytes);
 
     if constexpr (kFused) {
         for (int i = t; i < 766; i += kWsThreads) S.tabA[i] = A.tabA[i];

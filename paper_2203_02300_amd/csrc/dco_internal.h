@@ -28,6 +28,12 @@ struct dco_scratch {
     uint8_t* half[2];   // the reduced pair of dco_stereo_match_half (H x W x 3)
 };
 
+// Columns of a row of a handle's own aggregated volumes with two stages: rows that
+// end within a quad cost the aggregation a second kind of store, and quads that
+// start anywhere cost the loads (one call at 1279 x 720, D = 128 760 us, 719 so;
+// 399 x 300, D = 40 87.8 and 83.9; multiples of four within 1 %).
+constexpr int agg_pitch(int W, int iters) { return iters == 2 ? (W + 15) & ~15 : W; }
+
 // Columns of a row of the soft path's volumes: whole 64-byte pieces, so that no
 // store ends within one and every row's 16-byte words are aligned.  A training
 // step on 8 pairs of 639 x 480, D = 63 took 2670 us with rows of W columns, 2154
@@ -199,7 +205,7 @@ struct HalfOut {
 // valid) from the voted map and the aggregated costs, dv_out (optional) the map
 // itself, -1 where invalid.
 hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* arms,
-                       const float* agg, bool paired, int W, int H, int D, int iters, int subpixel,
+                       const float* agg, bool paired, int pitch, int W, int H, int D, int iters, int subpixel,
                        int16_t* buf0, int16_t* buf1, float* disp, uint8_t* valid_out,
                        int16_t* dv_out, const HalfOut& half, hipStream_t st);
 // Quarter-size front end: 2 x 2 block means of both full images (row length
@@ -282,20 +288,21 @@ hipError_t launch_cost(int ref, const uint8_t* rgbL, const uint8_t* rgbR, const 
 hipError_t launch_aggregate(const float* cost, const AggRecords& rec, int W, int H, int D,
                             int iters, float* out, hipStream_t st);
 // Both views in one launch (the one-call path).  With two stages and
-// `paired`, the volumes are written in the paired layout (dco::paired_at);
-// with one stage they are always plain.
+// `paired`, the volumes are written in the paired layout (dco::paired_at), in rows
+// of `pitch` columns; with one stage they are always plain, in rows of W.
 hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const AggRecords& recL,
                                   const AggRecords& recR, int W, int H, int D, int iters,
                                   const float* tabA, const float* tabC, const float* alpha,
                                   const float* beta, int L1, float* outL, float* outR,
-                                  bool paired, hipStream_t st);
-// WTA of both views and the left-right check in one launch; `paired`: from
-// volumes in the paired layout (even slices only).
-hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int W, int H, int D,
+                                  bool paired, int pitch, hipStream_t st);
+// WTA of both views and the left-right check in one launch, from volumes in rows of
+// `pitch` columns; `paired`: in the paired layout (even slices only).
+hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int pitch, int W,
+                         int H, int D,
                          int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
                          uint8_t* valid, const HalfOut& half, hipStream_t st);
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded into out (n x H x W).
-hipError_t launch_unpair(const float* vol, int W, int H, int D, int d0, int n, float* out,
+hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d0, int n, float* out,
                          hipStream_t st);
 
 // k_soft.hip

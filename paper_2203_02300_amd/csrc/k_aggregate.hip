@@ -187,6 +187,7 @@ hipError_t launch_aggregate(const float* cost, const AggRecords& rec, int W, int
     a.rec = rec;
     a.out = out;
     a.W = W;
+    a.pitch = W;
     a.H = H;
     a.D = D;
     a.nstrips = agg_strips(W, iters);
@@ -198,7 +199,7 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
                                   const AggRecords& recR, int W, int H, int D, int iters,
                                   const float* tabA, const float* tabC, const float* alpha,
                                   const float* beta, int L1, float* outL, float* outR,
-                                  bool paired, hipStream_t st) {
+                                  bool paired, int pitch, hipStream_t st) {
     dco::AggArgs a{};
     a.pixL = pixL;
     a.pixR = pixR;
@@ -207,6 +208,7 @@ hipError_t launch_cost_aggregate2(const uint4* pixL, const uint4* pixR, const Ag
     a.alpha = alpha;
     a.beta = beta;
     a.W = W;
+    a.pitch = pitch;
     a.H = H;
     a.D = D;
     a.L1 = L1;

@@ -29,6 +29,7 @@ __global__ __launch_bounds__(dco::kWsThreads, 1) void k_batch_agg_ws(BatchArgs B
     A.rec = pr.rec[I.view];
     A.out = pr.agg[I.view];
     A.W = pr.W;
+    A.pitch = pr.W;
     A.H = pr.H;
     A.D = pr.D;
     A.nstrips = pr.nstrips;

@@ -221,12 +221,12 @@ extern "C" dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_pa
                                 b.rec[1], st));
     DCO_HIP_CHECK(launch_cost_aggregate2(b.pix[0], b.pix[1], b.rec[0], b.rec[1], W, H, D,
                                          p.agg_iters, b.tabA, b.tabC, b.alpha, b.beta, p.arm_L1,
-                                         b.agg[0], b.agg[1], true, st));
+                                         b.agg[0], b.agg[1], true, W, st));
     const bool paired = p.agg_iters == 2;
-    DCO_HIP_CHECK(launch_wta_lr(b.agg[0], b.agg[1], paired, W, H, D, p.subpixel, p.lr_max_diff,
+    DCO_HIP_CHECK(launch_wta_lr(b.agg[0], b.agg[1], paired, W, W, H, D, p.subpixel, p.lr_max_diff,
                                 b.dint[0], b.dint[1], disp, valid, HalfOut{}, st));
     if (p.vote_iters > 0)
-        DCO_HIP_CHECK(launch_vote(b.dint[0], valid, b.arms[0], b.agg[0], paired, W, H, D,
+        DCO_HIP_CHECK(launch_vote(b.dint[0], valid, b.arms[0], b.agg[0], paired, W, W, H, D,
                                   p.vote_iters, p.subpixel, b.vote[0], b.vote[1], disp, valid,
                                   nullptr, HalfOut{}, st));
     return DCO_OK;

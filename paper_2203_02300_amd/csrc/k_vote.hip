@@ -81,23 +81,24 @@ struct VoteOut {
     uint8_t* valid;
     int16_t* dv;
     HalfOut half;
-    int P, D, subpixel, paired;
+    int pitch, W, H, D, subpixel, paired;  // volume rows of `pitch` columns
 };
 
-__device__ inline void vote_output(const VoteOut& o, int d, size_t i) {
+__device__ inline void vote_output(const VoteOut& o, int d, int x, int y) {
+    const size_t i = (size_t)y * o.W + x;
+    const int v = y * o.pitch + x, P = o.pitch * o.H;  // in the volume
     const bool ok = d >= 0 && d < o.D;
     float out = 0.0f;
     if (ok) {
         float del = 0.0f;
         if (o.subpixel && d > 0 && d < o.D - 1) {
             if (o.paired)
-                del = dco::subpixel_delta(dco::paired_at(o.agg, o.P, o.D, d - 1, (int)i),
-                                          dco::paired_at(o.agg, o.P, o.D, d, (int)i),
-                                          dco::paired_at(o.agg, o.P, o.D, d + 1, (int)i), d, o.D);
+                del = dco::subpixel_delta(dco::paired_at(o.agg, P, o.D, d - 1, v),
+                                          dco::paired_at(o.agg, P, o.D, d, v),
+                                          dco::paired_at(o.agg, P, o.D, d + 1, v), d, o.D);
             else
-                del = dco::subpixel_delta(o.agg[(size_t)(d - 1) * o.P + i],
-                                          o.agg[(size_t)d * o.P + i],
-                                          o.agg[(size_t)(d + 1) * o.P + i], d, o.D);
+                del = dco::subpixel_delta(o.agg[(size_t)(d - 1) * P + v], o.agg[(size_t)d * P + v],
+                                          o.agg[(size_t)(d + 1) * P + v], d, o.D);
         }
         out = (float)d + del;
     }
@@ -317,7 +318,7 @@ __global__ __launch_bounds__(kVThreads) void k_vote(const int16_t* __restrict__ 
             d = 32 * q + __builtin_ctz(m);
         }
         if constexpr (kOut)
-            vote_output(o, d, (size_t)y * W + x);
+            vote_output(o, d, x, y);
         else
             dout[(size_t)y * W + x] = (int16_t)d;
     }
@@ -327,17 +328,18 @@ __global__ __launch_bounds__(kVThreads) void k_vote(const int16_t* __restrict__ 
 __global__ __launch_bounds__(256) void k_vote_finish(const int16_t* dv, const uint8_t* valid_in,
                                                      VoteOut o) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= o.P) return;
-    vote_output(o, valid_in && !valid_in[i] ? -1 : dv[i], i);
+    if (i >= o.W * o.H) return;
+    const int y = i / o.W;
+    vote_output(o, valid_in && !valid_in[i] ? -1 : dv[i], i - y * o.W, y);
 }
 
 }  // namespace
 
 hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* arms,
-                       const float* agg, bool paired, int W, int H, int D, int iters, int subpixel,
-                       int16_t* buf0, int16_t* buf1, float* disp, uint8_t* valid_out,
+                       const float* agg, bool paired, int pitch, int W, int H, int D, int iters,
+                       int subpixel, int16_t* buf0, int16_t* buf1, float* disp, uint8_t* valid_out,
                        int16_t* dv_out, const HalfOut& half, hipStream_t st) {
-    const VoteOut o{agg, disp, valid_out, dv_out, half, W * H, D, subpixel, (int)paired};
+    const VoteOut o{agg, disp, valid_out, dv_out, half, pitch, W, H, D, subpixel, (int)paired};
     const dim3 grid((W + kVTW - 1) / kVTW, (H + kVTH - 1) / kVTH);
     // the last pass makes the outputs, unless it is also the first: other tiles
     // then still read the mask that valid_out may be
@@ -356,6 +358,6 @@ hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* 
         hipLaunchKernelGGL(k_vote<true>, grid, dim3(kVThreads), 0, st, src, mask, arms, W, H, D,
                            (int16_t*)nullptr, o);
     else
-        hipLaunchKernelGGL(k_vote_finish, dim3((o.P + 255) / 256), dim3(256), 0, st, src, mask, o);
+        hipLaunchKernelGGL(k_vote_finish, dim3((W * H + 255) / 256), dim3(256), 0, st, src, mask, o);
     return hipGetLastError();
 }

@@ -35,15 +35,15 @@ constexpr int kWtaThreads = 1024;  // most threads of a row
 // launch 87.2 instead of 85.0.
 template <bool kPaired, bool kNarrow>
 __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
-    const float* __restrict__ aggL, const float* __restrict__ aggR, int P, int W, int D,
+    const float* __restrict__ aggL, const float* __restrict__ aggR, int pitch, int P, int W, int D,
     int subpixel, int maxdiff, int16_t* __restrict__ dL, int16_t* __restrict__ dR,
     float* __restrict__ disp, uint8_t* __restrict__ valid, HalfOut half) {
     extern __shared__ int16_t right[];  // W entries
     const int t = threadIdx.x, nt = blockDim.x / 2, nq = (W + 3) / 4;
-    const int row = blockIdx.x * W;
+    const int row = blockIdx.x * W, vrow = blockIdx.x * pitch;  // P: a plane of the volumes
     const auto start = [&](int q) { return kNarrow ? 0 : min(4 * q, W - 4); };
     const auto left = [&](int q) {
-        return dco::wta_any<kPaired, true, kNarrow>(aggL, P, D, row + start(q), W, subpixel);
+        return dco::wta_any<kPaired, true, kNarrow>(aggL, P, D, vrow + start(q), W, subpixel);
     };
     const auto check = [&](int q, const dco::WtaQuad& l) {
         const int x = start(q), i = row + x;
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
         for (int q = t - nt; q < nq; q += nt) {
             const int x = start(q);
             const dco::WtaQuad r =
-                dco::wta_any<kPaired, false, kNarrow>(aggR, P, D, row + x, W, subpixel);
+                dco::wta_any<kPaired, false, kNarrow>(aggR, P, D, vrow + x, W, subpixel);
             dco::put_bd<kNarrow>(right + x, r, W);
             dco::put_bd<kNarrow>(dR + row + x, r, W);
         }
@@ -85,23 +85,25 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
 }
 
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded to n x P.
-__global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, int P, int D,
-                                                int d0, int n, float* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, int pitch, int W,
+                                                int H, int D, int d0, int n,
+                                                float* __restrict__ out) {
     const size_t k = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const int P = W * H;
     if (k >= (size_t)n * P) return;
-    const int s = (int)(k / P), i = (int)(k - (size_t)s * P);
-    out[k] = dco::paired_at(vol, P, D, d0 + s, i);
+    const int s = (int)(k / P), i = (int)(k - (size_t)s * P), y = i / W;
+    out[k] = dco::paired_at(vol, pitch * H, D, d0 + s, i + y * (pitch - W));
 }
 
 }  // namespace
 
-hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int W, int H, int D,
-                         int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
+hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int pitch, int W,
+                         int H, int D, int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
                          uint8_t* valid, const HalfOut& half, hipStream_t st) {
     const int nt = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(H), dim3(2 * nt), (size_t)W * sizeof(int16_t), st, aggL,
-                           aggR, W * H, W, D, subpixel, maxdiff, dL, dR, disp, valid, half);
+                           aggR, pitch, pitch * H, W, D, subpixel, maxdiff, dL, dR, disp, valid, half);
     };
     if (W < 4)
         paired ? go(k_wta_row<true, true>) : go(k_wta_row<false, true>);
@@ -110,10 +112,10 @@ hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int 
     return hipGetLastError();
 }
 
-hipError_t launch_unpair(const float* vol, int W, int H, int D, int d0, int n, float* out,
+hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d0, int n, float* out,
                          hipStream_t st) {
     const size_t total = (size_t)n * W * H;
     hipLaunchKernelGGL(k_unpair, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, vol,
-                       W * H, D, d0, n, out);
+                       pitch, W, H, D, d0, n, out);
     return hipGetLastError();
 }
