@@ -582,8 +582,8 @@ static dco_status soft_front(dco_stereo* h, int B, const uint8_t* L, const uint8
     DCO_HIP_CHECK(launch_census_pairs(L, R, B, h->W, h->H, p.census_w, p.census_h, p.arm_L1,
                                       p.arm_tau1, f.arms, (uint32_t*)f.vrec, f.pix[0], f.pix[1],
                                       h->stream));
-    DCO_HIP_CHECK(soft_prepare(theta, f.tab, f.arms, B, h->W, h->H, h->D, h->alpha,
-                               f.vrec, f.n2, h->stream));
+    DCO_HIP_CHECK(soft_prepare(theta, f.tab, f.arms, B, h->W, h->H, h->D, f.vrec, f.n2,
+                               h->stream));
     *sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
     DCO_HIP_CHECK(
         soft_aggregate(*sb, B, h->W, h->H, h->D, f.vol[0], f.vol[1], f.vol[2], theta, dhat, lse,

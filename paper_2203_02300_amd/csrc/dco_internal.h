@@ -307,7 +307,7 @@ hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d
 
 // k_soft.hip
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, const float* alpha, uint2* vrec, float* n2, hipStream_t st);
+                        int D, uint2* vrec, float* n2, hipStream_t st);
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, const float* theta, float* dhat, float* lse,
                           hipStream_t st);

@@ -6,22 +6,21 @@
 //   E1 = row range sum of c       a1 = (column range sum of E1) / N1     (Eq. 2, stage 1)
 //   E2 = column range sum of a1   A2 = (row range sum of E2) / N2         (Eq. 2, stage 2)
 //   dhat = sum_d d softmax_d(-A2 / T),  lse = log sum_d exp(-A2 / T)
-// The row sums are exact sums of fixed-point values on the matrix cores, the
-// column sums differences of two FP64 prefix sums running down the column, so
-// each is within one FP32 rounding of the exact sum of its FP32 terms.  Every
-// sum runs in a fixed order, so results are bit-reproducible.
+// The row sums are exact sums of fixed-point values on the matrix cores (a term is
+// held to 2^-46 of the largest one that its wavefront has met in the row), the
+// column sums differences of two FP64 prefix sums running down the column; each
+// sum is then rounded once to FP32.  Every sum runs in a fixed order, so results
+// are bit-reproducible.
 //
 // Backward, given g = dLoss/d dhat:
 //   G_A2  = g w (dhat - d) / T,   dLoss/dT = sum g w (d - dhat) A2 / T^2
 // then the adjoint of each range sum: an output that summed a range hands its
-// adjoint back to every pixel of that range.  The first row adjoint is an exact
-// product of fixed-point G with the transposed band (k_soft_wide); column
-// adjoints are FP64 difference arrays streamed down each column by one thread.
-// The last row adjoint is never formed: with
-// E1 = H c,  sum_p (H^T G)(p) dc/dlambda(p) = sum_x G(x) (H dc/dlambda)(x),
-// so the row range sums of the two cost derivatives are dotted with G:
-//   dLoss/dlambda_AD     = sum G_E1 . H (alpha d(1 - exp(-(s/3)/lambda_AD))/dlambda_AD)
-//   dLoss/dlambda_census = sum G_E1 . H ((1 - alpha) d(1 - exp(-h/lambda_census))/dlambda_census)
+// adjoint back to every pixel of that range.  The row adjoints are exact products of
+// fixed-point G with the transposed band (k_soft_wide); column adjoints are FP64
+// difference arrays streamed down each column by one thread.  The last row adjoint is
+// not stored: with E1 = H c, its values go in FP64 into
+//   dLoss/dlambda_AD     = sum H^T G_E1 . alpha d(1 - exp(-(s/3)/lambda_AD))/dlambda_AD
+//   dLoss/dlambda_census = sum H^T G_E1 . (1 - alpha) d(1 - exp(-h/lambda_census))/dlambda_census
 // with fixed-order two-level reductions.  The only atomics are LDS adds that one
 // thread makes to its own column in program order.
 //
@@ -51,24 +50,10 @@ __device__ inline int arm(uint32_t a, int k) { return (a >> (8 * k)) & 0xff; }
 // Tables of Eq. 1 for the current theta, and their lambda derivatives:
 // tab[0..765] = 1 - exp(-(s/3)/lambda_AD),   tab[768..1533] = d/dlambda_AD
 // tab[1536..1600] = 1 - exp(-h/lambda_c),    tab[1664..1728] = d/dlambda_c
-// tab[kTabScale + 0, 2, 4]  = fixed-point scales 2^k of c and of its two derivatives
-// (k_soft_mrow), + 1, 3, 5 = 2^-k.  c is alpha A + (1 - alpha) C and |A|, |C| grow
-// with x; |d/dlambda| grows with x up to lambda > 0 and falls beyond.  A scale
-// of no finite bound is 0 and its inverse NaN, so the results are NaN.
-constexpr int kTabScale = 1744;
-
-__device__ inline void put_scale(float bound, float* out) {
-    const bool ok = bound < 1e25f;  // false for NaN
-    // bound <= 1.001 * 2^(e + 1): the largest |q| stays far below 2^31 - 2^23
-    const int e = bound > 1e-25f ? ilogbf(0.999f * bound) : -84;
-    out[0] = ok ? ldexpf(1.0f, 29 - e) : 0.0f;
-    out[1] = ok ? ldexpf(1.0f, e - 29) : __builtin_nanf("");
-}
-
 constexpr int kTabThreads = 1024;  // entry i of them, 0 <= i < kTabThreads
 
 __device__ inline void table_entry(int i, const float* __restrict__ theta,
-                                   const float* __restrict__ alpha, float* __restrict__ tab) {
+                                   float* __restrict__ tab) {
     const float la = theta[0], lc = theta[1];
     if (i < 766) {
         const float x = (float)i / 3.0f;
@@ -80,19 +65,6 @@ __device__ inline void table_entry(int i, const float* __restrict__ theta,
         const float e = expf(-(float)h / lc);
         tab[1536 + h] = -expm1f(-(float)h / lc);
         tab[1664 + h] = -e * (float)h / (lc * lc);
-    } else if (i >= 896 && i < 899) {
-        const float A = fabsf(expm1f(-255.0f / la)), C = fabsf(expm1f(-64.0f / lc));
-        const float xa = la > 0.0f && la < 255.0f ? la : 255.0f;
-        const float xc = lc > 0.0f && lc < 64.0f ? lc : 64.0f;
-        float b = (0.0f / la + 0.0f / lc) * 0.0f;  // NaN where a table is (lambda = 0)
-        for (int L = 0; L <= kLMax; ++L) {
-            const float al = fabsf(alpha[L]), be = fabsf(1.0f - alpha[L]);
-            const float v = i == 896 ? al * A + be * C
-                          : i == 897 ? al * (expf(-xa / la) * xa / (la * la))
-                                     : be * (expf(-xc / lc) * xc / (lc * lc));
-            b = v > b || v != v ? v : b;  // keeps a NaN
-        }
-        put_scale(b, tab + kTabScale + 2 * (i - 896));
     }
 }
 
@@ -113,7 +85,6 @@ __device__ inline uint32_t col_record(uint32_t a, int n1) {
 // the image, where no arm reaches); each count is then a sum of LDS entries.
 constexpr int kCntTW = 64, kCntTH = 4;
 __global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, const float* __restrict__ theta,
-                                                     const float* __restrict__ alpha,
                                                      float* __restrict__ tab,
                                                      uint2* __restrict__ vrec,
                                                      float* __restrict__ n2) {
@@ -125,7 +96,7 @@ __global__ __launch_bounds__(256) void k_soft_counts(SoftGeom g, const float* __
     {   // the tables, which only the later passes need: the first blocks' threads
         const unsigned n = gridDim.x * gridDim.y * gridDim.z;
         unsigned i = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        for (; i < kTabThreads / 256; i += n) table_entry((int)i * 256 + t, theta, alpha, tab);
+        for (; i < kTabThreads / 256; i += n) table_entry((int)i * 256 + t, theta, tab);
     }
     const uint32_t* A = g.arms + (size_t)b * g.W * g.H;
     for (int k = t; k < CH * kCntTW; k += 256) {
@@ -171,16 +142,19 @@ __device__ inline int xcd_block(int b, int n) {
     return xcd < rem ? xcd * (per + 1) + i : rem * (per + 1) + (xcd - rem) * per + i;
 }
 
-// Row sums of the costs (and of their lambda derivatives) on the matrix cores.
+// Row sums of the costs on the matrix cores.
 // Along one image row E1(x, d) = sum_p [x - l <= p <= x + r] c(p, d): a product
 // of a banded 0/1 matrix, which the disparities share, with the costs.  The
-// costs go in as 32-bit fixed point q = c 2^k, split into four signed bytes
-// (balanced digits: q = sum_i 256^i b_i), so four i8 products with 32-bit
-// accumulation give the exact sum of the q, and the output is that sum rounded
-// once to FP32.  2^k puts the largest |c| that theta and alpha allow at 2^30
-// (table_entry): a cost is exact down to 2^-6 of it and within 2^-30 of it
-// below, where the FP32 sum of a range is no finer.  Costs of partners outside
-// the image are 1 by definition: they enter as 0 and are counted.
+// costs go in as fixed point q = c 2^k in two 24-bit halves, each of three signed
+// bytes (balanced digits: q = sum_i 256^i b_i), so six i8 products with 32-bit
+// accumulation give the exact sum of the q.  2^k puts the largest |c| that the
+// wavefront has met in its row at 2^45: a cost is exact down to 2^-21 of that and
+// within 2^-46 of it below.  (FP64 prefix sums along the row, 2^-53 of a sum of
+// hundreds of them, keep as much; 30 bits of the largest cost that theta allows
+// lost up to 5e-3 of costs far below it.)  Where a block raises the scale, its
+// outputs add the block before in the old one: two products apart.  Costs of
+// partners outside the image are 1 by definition: they enter as 0 and are counted.
+// A cost that is not finite makes the outputs from its block on NaN.
 //
 // A workgroup takes one image row (or one of `segs` parts of it), a wavefront
 // 16 of its disparities (in rounds where there are more than 64), and they walk
@@ -190,23 +164,23 @@ __device__ inline int xcd_block(int b, int n) {
 //     interval, spread to bytes;
 //   - costs: lane = column, 16 disparities in turn, so a reference pixel is
 //     read once per block, and the partners are 80 consecutive pixels, in LDS;
-//   - the lanes' q go through LDS (16 x 68 words, conflict-free both ways) into
-//     the operand layout: lane = (disparity lane & 15, columns 16 (lane >> 4) ..
-//     + 15), a byte per column;
+//   - the lanes' q go through LDS (16 x 68 words, conflict-free both ways), a half
+//     at a time, into the operand layout: lane = (disparity lane & 15, columns 16
+//     (lane >> 4) .. + 15), a byte per column;
 //   - after block [X, X + 64) the 16-column outputs at X - 32, X - 16, X and
 //     X + 16 have all their columns (x - 17 .. x + 32) in this block and the one
 //     before, whose digits stay in registers: two products per digit and output;
 //   - E1 goes back through LDS to be stored as 256 contiguous bytes per
 //     disparity (64-byte pieces of 16 planes: 0.35 ms instead of 0.30 then).
 //
-// Measured at 8 pairs of 640 x 480, D = 64: E1 0.22 ms (writes 0.63 GB, past the
-// caches, 0.25 through them; vector issue about 0.15 ms), the gradient 0.32 ms (reads 0.63 GB; issue bound, 64 %
-// vector busy).  As FP64 prefix sums per row and disparity, two table passes,
-// four LDS scans and eight gathers per 256 columns, they took 0.35 and 0.58 ms.
-// Steps: 32 or 64 disparities per wavefront 0.35 / 0.49 and 0.44 / 0.74 ms (too
-// few wavefronts), 16 with its own bands 0.32 / 0.40, shared bands 0.35 / 0.32,
-// rows stored whole 0.30, partners in LDS and a block ahead 0.25.  At one pair
-// of 320 x 240, D = 32 the split rows take 15 us, was 18.
+// Measured at 8 pairs of 640 x 480, D = 64: 0.28 ms (writes 0.63 GB, past the caches;
+// bound by vector issue).  As FP64 prefix sums per row and disparity, two table
+// passes, four LDS scans and eight gathers per 256 columns, 0.35.  In 32-bit fixed
+// point (four digits) 0.22.  Steps there: 32 or 64 disparities per wavefront 0.35 and
+// 0.44 ms (too few wavefronts), 16 with its own bands 0.32, rows stored whole 0.30,
+// partners in LDS and a block ahead 0.25.  The lower half taken to digits before the
+// barrier, the halves' products one after the other and the last partners of a block
+// kept in LDS: 124 registers; without, 0.30 and more to spilling.
 constexpr int kMxWaves = 4;          // most wavefronts per workgroup
 constexpr int kMxSlots = 16 * 256;   // wavefronts of it the device holds at once
 constexpr int kMxStride = 68;        // words per disparity of the stage
@@ -225,8 +199,16 @@ __device__ inline v4i band_bytes(int lo, int hi, int pb) {
     return r;
 }
 
+// Tables of the colour and census terms in LDS.
+constexpr int kCenTab = 766;
+__device__ inline void put_tables(const float* colour, const float* census, float* tab) {
+    for (int i = threadIdx.x; i < kCenTab; i += blockDim.x) tab[i] = colour[i];
+    for (int i = threadIdx.x; i < 65; i += blockDim.x) tab[kCenTab + i] = census[i];
+    __syncthreads();
+}
+
 // The lane's 16 columns of disparity lane & 15, as digit planes.
-__device__ inline void digit_planes(const uint32_t* stage, v4i (&b)[4]) {
+__device__ inline void digit_planes3(const uint32_t* stage, v4i (&b)[3]) {
     const int lane = threadIdx.x & 63;
     const uint32_t* s = stage + (lane & 15) * kMxStride + 16 * (lane >> 4);
 #pragma unroll
@@ -234,18 +216,129 @@ __device__ inline void digit_planes(const uint32_t* stage, v4i (&b)[4]) {
         const v4u w = *reinterpret_cast<const v4u*>(s + 4 * i);
         const uint32_t t0 = __builtin_amdgcn_perm(w.y, w.x, 0x05010400u);
         const uint32_t t1 = __builtin_amdgcn_perm(w.w, w.z, 0x05010400u);
-        const uint32_t t2 = __builtin_amdgcn_perm(w.y, w.x, 0x07030602u);
-        const uint32_t t3 = __builtin_amdgcn_perm(w.w, w.z, 0x07030602u);
+        const uint32_t t2 = __builtin_amdgcn_perm(w.y, w.x, 0x0c0c0602u);
+        const uint32_t t3 = __builtin_amdgcn_perm(w.w, w.z, 0x06020c0cu);
         b[0][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x05040100u);
         b[1][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x07060302u);
-        b[2][i] = (int)__builtin_amdgcn_perm(t3, t2, 0x05040100u);
-        b[3][i] = (int)__builtin_amdgcn_perm(t3, t2, 0x07060302u);
+        b[2][i] = (int)(t2 | t3);
     }
 }
 
-// q (|q| <= 2^30) with its bytes as balanced digits.
-__device__ inline uint32_t balanced(float v) {
-    return ((uint32_t)(int)v + 0x00808080u) ^ 0x00808080u;
+// A wavefront's fixed point: |v| <= 2^ex for every value it has met in its row.
+struct WideScale {
+    int ex = -100;
+    bool bad = false;  // a value was not finite
+};
+
+// Largest of the wavefront's values (DPP row shifts, then the row broadcasts).
+template <unsigned Ctrl, unsigned RowMask>
+__device__ inline uint32_t dpp_max(uint32_t m) {
+    return max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, Ctrl, RowMask, 0xf, false));
+}
+__device__ inline uint32_t wave_max(uint32_t m) {
+    m = dpp_max<0x111, 0xf>(m);
+    m = dpp_max<0x112, 0xf>(m);
+    m = dpp_max<0x114, 0xf>(m);
+    m = dpp_max<0x118, 0xf>(m);
+    m = dpp_max<0x142, 0xa>(m);
+    m = dpp_max<0x143, 0xc>(m);
+    return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+}
+
+// A lane's values of 16 disparities as q = v 2^(45 - ex) in two halves of three
+// balanced digits, with ex raised to the largest of the wavefront's values: the
+// upper halves go to the stage, the lower ones to `lo`.
+__device__ inline void put_wide(const float (&v)[16], uint32_t* stage, uint32_t (&lo)[16],
+                                WideScale& s) {
+    const int lane = threadIdx.x & 63;
+    uint32_t m = 0;  // bits of the largest |v| (a NaN's are larger still)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) m = max(m, __float_as_uint(v[j]) & 0x7fffffffu);
+    m = wave_max(m);
+    s.bad = s.bad || m >= 0x7f800000u;
+    s.ex = max(s.ex, (int)(m >> 23) - 126);
+    const float up = ldexpf(1.0f, 22 - s.ex);
+    // x + kMagic rounds |x| <= 2^22 to a whole number, the sum's low bits
+    constexpr float kMagic = 0x1.8p23f;
+    constexpr uint32_t kDigits = 0x8080u - 0x4b400000u;  // kMagic's bits, and balanced digits
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const float h = __builtin_fmaf(v[j], up, kMagic);
+        const float r = __builtin_fmaf(v[j], up, kMagic - h);  // exact
+        stage[j * kMxStride + lane] = (__float_as_uint(h) + kDigits) ^ 0x8080u;
+        lo[j] = (__float_as_uint(__builtin_fmaf(r, 0x1p23f, kMagic)) + kDigits) ^ 0x8080u;
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The digits of both halves as operands.
+__device__ inline void wide_planes(uint32_t* stage, const uint32_t (&lo)[16], v4i (&b)[2][3]) {
+    const int lane = threadIdx.x & 63;
+    digit_planes3(stage, b[0]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) stage[j * kMxStride + lane] = lo[j];
+    __builtin_amdgcn_wave_barrier();
+    digit_planes3(stage, b[1]);
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The four 16-column outputs of block X over the block before (digits bp, scale
+// 2^ex_old) and this one (bc): sink(i, xb, v) gets the lane's four sums of output
+// i, columns xb + 4 (lane >> 4) .. + 3 of disparity lane & 15.  band(c): operand c
+// of the block's eight.  Where the block raised the scale, the two products are
+// taken apart.
+template <typename Band, typename Sink>
+__device__ inline void wide_outputs(int X, int W, const v4i (&bp)[2][3], const v4i (&bc)[2][3],
+                                    int ex_old, const WideScale& sc, Band band, Sink sink) {
+    const double inv = sc.bad ? __builtin_nan("") : ldexp(1.0, sc.ex - 45);
+    // a half's sums from its digits'
+    const auto whole = [](const v4i (&s)[3], int r) {
+        return s[0][r] + ((s[1][r] + (s[2][r] << 8)) << 8);
+    };
+    const auto outputs = [&](auto rescaled) {
+        constexpr bool kTwo = decltype(rescaled)::value;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int xb = X - 32 + 16 * i;
+            if (xb < 0 || xb >= W) continue;
+            const v4i b0 = band(2 * i), b1 = band(2 * i + 1);
+            int q[2][4], old[2][4];  // of both blocks together, or of each
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                v4i s[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    s[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b0, bp[h][k], v4i{0, 0, 0, 0}, 0,
+                                                                 0, 0);
+                if (kTwo) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) old[h][r] = whole(s, r);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) s[k] = v4i{0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    s[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b1, bc[h][k], s[k], 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) q[h][r] = whole(s, r);
+            }
+            double v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = __builtin_fma((double)q[0][r], 0x1p23, (double)q[1][r]) * inv;
+                if (kTwo)
+                    v[r] = __builtin_fma(
+                        __builtin_fma((double)old[0][r], 0x1p23, (double)old[1][r]),
+                        ldexp(1.0, ex_old - 45), v[r]);
+            }
+            sink(i, xb, v);
+        }
+    };
+    if (sc.ex == ex_old)
+        outputs(std::false_type{});
+    else
+        outputs(std::true_type{});
 }
 
 // What a wavefront of a row pass works on.  kShare: the workgroup's wavefronts take
@@ -294,30 +387,17 @@ __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, 
     }
 }
 
-template <bool kDeriv, bool kShare, bool kStream>
+template <bool kShare, bool kStream>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, SoftImg im,
-                                                                const float* __restrict__ G,
                                                                 float* __restrict__ out,
-                                                                double* __restrict__ part,
                                                                 int seg_its) {
-    constexpr int NQ = kDeriv ? 2 : 1;
-    // 40 KB in all: four workgroups per CU
-    constexpr int kCenTab = 766;
     __shared__ v4i bands[kShare ? 2 : 1][kShare ? 8 : 1][64];
     __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
     __shared__ uint2 cen[kMxWaves][80];
     __shared__ uint32_t rgb[kMxWaves][80];
     __shared__ float tab[kCenTab + 65];
     const int nt = blockDim.x, nw = nt >> 6;
-    {
-        const float* t = im.tab + (kDeriv ? 768 : 0);
-        const float* c = im.tab + (kDeriv ? 1664 : 1536);
-        const float ka = im.tab[kTabScale + (kDeriv ? 2 : 0)];
-        const float kc = im.tab[kTabScale + (kDeriv ? 4 : 0)];
-        for (int i = threadIdx.x; i < 766; i += nt) tab[i] = t[i] * ka;
-        for (int i = threadIdx.x; i < 65; i += nt) tab[kCenTab + i] = c[i] * kc;
-        __syncthreads();
-    }
+    put_tables(im.tab, im.tab + 1536, tab);
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 15, kg = lane >> 4;
     const int W = g.W, D = g.D, ng = (D + 15) >> 4;
@@ -331,18 +411,16 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     const uint32_t* ar = g.arms + pix;
     const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch();
     uint32_t* stage = stages[w];
-    const float inv0 = im.tab[kTabScale + (kDeriv ? 3 : 1)];
     int par = 0;
     for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
         const int grp = g0 + rt.grp, d0 = 16 * grp, d = d0 + n;
         const bool active = rt.on && grp < ng;
-        const size_t orow = vol + (size_t)min(d, D - 1) * Q;
-        v4i bp[NQ][4];
+        v4i bp[2][3];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) bp[q][i] = v4i{0, 0, 0, 0};
-        double sa = 0.0, sc = 0.0;
+            for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
+        WideScale sc;
         // Partners of a block's 16 disparities: the 64 pixels from column X - d0 on
         // and the last 16 of the 64 before, through LDS (entry 16 + lane - j holds
         // column X + lane - (d0 + j)).  They and the reference pixels are loaded a
@@ -351,11 +429,15 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
             const uint4* q = pr + min(max(x - d0, 0), W - 1);
             return uint3{q->x, q->y, q->z};
         };
-        uint3 ro{}, rc{};
+        uint3 rc{};
         uint4 pn{};
         if (active) {
             const int X = 64 * max(it0 - 1, 0);
-            ro = pixel(X - 64 + lane);
+            if (lane < 16) {
+                const uint3 r = pixel(X - 16 + lane);
+                cen[w][64 + lane] = uint2{r.x, r.y};
+                rgb[w][64 + lane] = r.z;
+            }
             rc = pixel(X + lane);
             pn = pl[min(X + lane, W - 1)];
         }
@@ -366,24 +448,32 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
             const auto band = [&](int c) {
                 const int x = X - 32 + 16 * (c >> 1) + n;
                 const uint32_t a = ar[min(max(x, 0), W - 1)];
-                return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1, X - 64 + 64 * (c & 1) + 16 * kg);
+                return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
+                                  X - 64 + 64 * (c & 1) + 16 * kg);
             };
             if constexpr (kShare)
                 for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
-            uint32_t q2[16];
+            v4i bc[2][3];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
+            const int ex_old = sc.ex;
             if (active && X < W) {
+                if (lane < 16) {  // the last 16 of the block before
+                    cen[w][lane] = cen[w][64 + lane];
+                    rgb[w][lane] = rgb[w][64 + lane];
+                }
+                __builtin_amdgcn_wave_barrier();
                 cen[w][16 + lane] = uint2{rc.x, rc.y};
                 rgb[w][16 + lane] = rc.z;
-                if (lane >= 48) {
-                    cen[w][lane - 48] = uint2{ro.x, ro.y};
-                    rgb[w][lane - 48] = ro.z;
-                }
                 const uint4 pa = pn;
-                ro = rc;
                 rc = pixel(X + 64 + lane);
                 pn = pl[min(X + 64 + lane, W - 1)];
                 __builtin_amdgcn_wave_barrier();
                 const float al = im.alpha[pa.w >> 3], be = 1.0f - al;
+                const bool in_row = X + lane < W;
+                float v[16];
                 const auto costs = [&](auto all_in) {
                     constexpr bool kIn = decltype(all_in)::value;
 #pragma unroll
@@ -391,123 +481,45 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
                         const uint2 cb = cen[w][16 + lane - j];
                         const uint32_t s = __builtin_amdgcn_sad_u8(pa.z, rgb[w][16 + lane - j], 0u);
                         const int hm = __popc(pa.x ^ cb.x) + __popc(pa.y ^ cb.y);
-                        const float ta = al * tab[s], tc = be * tab[kCenTab + hm];
-                        const bool in = kIn || X + lane - d0 - j >= 0;
-                        stage[j * kMxStride + lane] =
-                            balanced(in ? (kDeriv ? ta : ta + tc) : 0.0f);
-                        if (kDeriv) q2[j] = balanced(in ? tc : 0.0f);
+                        const float c = al * tab[s] + be * tab[kCenTab + hm];
+                        v[j] = kIn || (in_row && X + lane - d0 - j >= 0) ? c : 0.0f;
                     }
                 };
-                if (X >= d0 + 15)  // every partner of the block is in the image
+                if (X >= d0 + 15 && X + 64 <= W)  // every column and partner is in the image
                     costs(std::true_type{});
                 else
                     costs(std::false_type{});
-                __builtin_amdgcn_wave_barrier();
-            }
-            float gv[kDeriv ? 4 : 1][4];
-            if (kDeriv && active && it >= it0) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int x4 = X - 32 + 16 * i + 4 * kg;
-                    const bool row_in = d < D && x4 >= 0;
-                    if (row_in && x4 + 4 <= W) {
-                        __builtin_memcpy(gv[i], G + orow + x4, 16);
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            gv[i][r] = row_in && x4 + r < W ? G[orow + min(x4 + r, W - 1)] : 0.0f;
-                    }
-                }
+                uint32_t lo[16];
+                put_wide(v, stage, lo, sc);
+                wide_planes(stage, lo, bc);
             }
             // the bands; the buffer's next writers pass the next one first
             if (kShare) __syncthreads();
             if (!active) continue;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                v4i bc[4] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
-                if (X < W) {
-                    if (q > 0) {
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) stage[j * kMxStride + lane] = q2[j];
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                    digit_planes(stage, bc);
-                    __builtin_amdgcn_wave_barrier();
-                }
-                if (it >= it0) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int xb = X - 32 + 16 * i, x4 = xb + 4 * kg;
-                        if (xb < 0 || xb >= W) continue;
-                        const v4i b0 = kShare ? bands[par][2 * i][lane] : band(2 * i);
-                        const v4i b1 = kShare ? bands[par][2 * i + 1][lane] : band(2 * i + 1);
-                        v4i acc[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
-                                b0, bp[q][k], v4i{0, 0, 0, 0}, 0, 0, 0);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b1, bc[k], acc[k], 0, 0,
-                                                                           0);
-                        // |lo|, |hi| < 2^21: the conversions are exact
-                        int lo[4], hi[4];
+            if (it >= it0) {
+                const auto bands_of = [&](int c) { return kShare ? bands[par][c][lane] : band(c); };
+                wide_outputs(X, W, bp, bc, ex_old, sc, bands_of, [&](int i, int xb, double(&v)[4]) {
+                    if (xb - kLMax < d0 + 15) {  // ranges may hold columns left of d: c = 1
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            lo[r] = acc[0][r] + (acc[1][r] << 8);
-                            hi[r] = acc[2][r] + (acc[3][r] << 8);
-                        }
-                        if constexpr (kDeriv) {
-                            double& t = q ? sc : sa;
-#pragma unroll
-                            for (int r = 0; r < 4; ++r)
-                                t = __builtin_fma(
-                                    (double)gv[i][r],
-                                    __builtin_fma((double)hi[r], 65536.0, (double)lo[r]), t);
-                        } else {
-                            float o[4];
-                            if (xb - kLMax >= d0 + 15) {
-#pragma unroll
-                                for (int r = 0; r < 4; ++r)
-                                    o[r] = __builtin_fmaf((float)hi[r], 65536.0f * inv0,
-                                                          (float)lo[r] * inv0);
-                            } else {  // ranges may hold columns left of d, where c = 1
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) {
-                                    const int x = x4 + r;
-                                    const uint32_t a = ar[min(x, W - 1)];
-                                    const int len = arm(a, 0) + arm(a, 1) + 1;
-                                    const int cnt = min(max(d - (x - arm(a, 0)), 0), len);
-                                    const double e =
-                                        __builtin_fma((double)hi[r], 65536.0, (double)lo[r]);
-                                    o[r] = (float)__builtin_fma(e, (double)inv0, (double)cnt);
-                                }
-                            }
-                            // to the stage (free since digit_planes), one row per d
-                            *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
-                                v4f{o[0], o[1], o[2], o[3]};
+                            const int x = xb + 4 * kg + r;
+                            const uint32_t a = ar[min(x, W - 1)];
+                            const int len = arm(a, 0) + arm(a, 1) + 1;
+                            v[r] += (double)min(max(d - (x - arm(a, 0)), 0), len);
                         }
                     }
-                    if (!kDeriv) {
-                        __builtin_amdgcn_wave_barrier();
-                        put_rows<kStream>(stage, out + vol, Q, d0, D, X - 32, g.pitch());
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
+                    // to the stage (free since the digits), one row per d
+                    *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
+                        v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+                });
+                __builtin_amdgcn_wave_barrier();
+                put_rows<kStream>(stage, out + vol, Q, d0, D, X - 32, g.pitch());
+                __builtin_amdgcn_wave_barrier();
+            }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) bp[q][i] = bc[i];
-            }
-        }
-        if (kDeriv && active) {
-            for (int off = 32; off > 0; off >>= 1) {  // fixed-order wavefront reduction
-                sa += __shfl_down(sa, off, 64);
-                sc += __shfl_down(sc, off, 64);
-            }
-            if (lane == 0) {
-                double* t = part + 2 * (((size_t)row * gridDim.y + blockIdx.y) * ng + grp);
-                t[0] = sa * (double)inv0;
-                t[1] = sc * (double)im.tab[kTabScale + 5];
-            }
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
         }
     }
 }
@@ -516,30 +528,35 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
 // rounding of the product adds a relative error of about |x| 2^-24.
 __device__ inline float exp_e(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
-// Row sums of values that span many binades, as wider fixed-point products.
+// Row sums of a volume, as k_soft_mrow makes those of the costs: on the same blocks,
+// in the same fixed point of the value G.
 //
-// Forward: A2(x, d) = (sum of E2 over [x - l, x + r]) / N2(x), and, where the
+// kMean: A2(x, d) = (sum of E2 over [x - l, x + r]) / N2(x), and, where the
 // workgroup's wavefronts hold all disparities (dhat given, D <= 64), the soft
 // argmin: each wavefront's 16 disparities give a maximum and two sums per column,
 // merged one block later.
 //
-// Adjoint: the seed and the transposed sums.  Per pixel and disparity, with
+// kSeed: the seed and the transposed sums.  Per pixel and disparity, with
 // w = softmax weight and g = dLoss/d dhat:
 //   G(x, d) = G_A2 / N2 = g w (dhat - d) / (T N2),
 //   dLoss/dT term = g w (d - dhat) A2 / T^2;
 // out(p, d) = sum_x [x - l(x) <= p <= x + r(x)] G(x, d), the adjoint of A2's row
-// range sums (G_E2): the transposed band.
+// range sums (G_E2): the transposed band.  The band's bytes of a lane's 16 pixels x
+// come four at a time: with e = x - p, l - e and r + e are not negative, tested in
+// bit 7 of biased bytes.  The temperature terms of the wavefront's row and
+// disparities are summed into one FP64 value.
 //
-// Both run as k_soft_mrow, on the same blocks, with a wider fixed point of the
-// value G (E2 in the forward): q = G 2^k in two 24-bit halves of three digits
-// each, with 2^k set by the largest |G| the wavefront has met in its row (2^-45
-// of it is kept).  Where a block raises that
-// bound, its outputs add the block before in the old scale: two products apart.
-// The adjoint's bytes of a lane's 16 pixels x come four at a time: with e = x - p, l - e and
-// r + e are not negative, tested in bit 7 of biased bytes.
+// kDot: the same adjoint of E1's row range sums, of G = G_E1, whose outputs are not
+// stored: each goes in FP64 into the sums of its product with the two FP32
+// derivatives of Eq. 1, looked up for the output's pixels and partners, which lie on
+// the stage once the digits have left it.  (The other way round, row sums of the two
+// derivatives dotted with G, takes two fixed points instead of one: 0.63 ms with
+// these digits, 0.35 with 30 bits of the derivatives' bound, which left nothing of
+// those far below it; 0.58 as FP64 prefix sums.)
 //
-// The temperature terms of the wavefront's row and disparities are summed into
-// one FP64 value.  A G that is not finite makes the outputs from its block on NaN.
+// 8 pairs of 640 x 480, D = 64: 0.35, 0.33 and 0.37 ms, bound by vector issue (0.63
+// GB read by each, and written by the first two).
+// A G that is not finite makes the outputs from its block on NaN.
 __device__ inline v4i band_bytes_t(const uint32_t* lp, const uint32_t* r, int e) {
     const v4u l4 = *reinterpret_cast<const v4u*>(lp), r4 = *reinterpret_cast<const v4u*>(r);
     uint32_t e4 = (uint32_t)(e + 128) * 0x01010101u + 0x03020100u;  // e + 128 + byte
@@ -553,35 +570,24 @@ __device__ inline v4i band_bytes_t(const uint32_t* lp, const uint32_t* r, int e)
     return o;
 }
 
-// As digit_planes, three planes.
-__device__ inline void digit_planes3(const uint32_t* stage, v4i (&b)[3]) {
-    const int lane = threadIdx.x & 63;
-    const uint32_t* s = stage + (lane & 15) * kMxStride + 16 * (lane >> 4);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const v4u w = *reinterpret_cast<const v4u*>(s + 4 * i);
-        const uint32_t t0 = __builtin_amdgcn_perm(w.y, w.x, 0x05010400u);
-        const uint32_t t1 = __builtin_amdgcn_perm(w.w, w.z, 0x05010400u);
-        const uint32_t t2 = __builtin_amdgcn_perm(w.y, w.x, 0x0c0c0602u);
-        const uint32_t t3 = __builtin_amdgcn_perm(w.w, w.z, 0x06020c0cu);
-        b[0][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x05040100u);
-        b[1][i] = (int)__builtin_amdgcn_perm(t1, t0, 0x07060302u);
-        b[2][i] = (int)(t2 | t3);
-    }
-}
+enum WideKind { kMean, kSeed, kDot };
 
-template <bool kAdj, bool kShare, bool kStream>
+template <WideKind kKind, bool kShare, bool kStream>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
-    SoftGeom g, const float* __restrict__ in, const float* __restrict__ theta,
+    SoftGeom g, SoftImg im, const float* __restrict__ in, const float* __restrict__ theta,
     float* __restrict__ dhat, float* __restrict__ lse, const float* __restrict__ gdhat,
-    float* __restrict__ out, double* __restrict__ partT, int seg_its) {
+    float* __restrict__ out, double* __restrict__ part, int seg_its) {
+    constexpr bool kAdj = kKind != kMean;  // transposed bands
     __shared__ v4i bands[kShare ? 2 : 1][kShare ? 8 : 1][64];
     __shared__ __align__(16) uint32_t stages[kMxWaves][16 * kMxStride];
     // adjoint: l + 1 and r of the columns of this block and the one before, a byte each
     __shared__ __align__(16) uint32_t arml[kAdj ? kMxWaves : 1][2][16],
         armr[kAdj ? kMxWaves : 1][2][16];
-    // forward: the wavefronts' softmax sums of a block's columns
+    // kMean: the wavefronts' softmax sums of a block's columns
     __shared__ float soft[2][kAdj ? 1 : kMxWaves][3][64];
+    // kDot: the derivatives' tables
+    __shared__ float tab[kKind == kDot ? kCenTab + 65 : 1];
+    if constexpr (kKind == kDot) put_tables(im.tab + 768, im.tab + 1664, tab);
     const int nt = blockDim.x, nw = nt >> 6;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 15, kg = lane >> 4;
@@ -602,9 +608,8 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
-        double acc = 0.0;
-        int ex = -100;               // |G| <= 2^ex so far
-        bool bad = false;            // a G was not finite
+        double acc = 0.0, acc2 = 0.0;
+        WideScale sc;
         // the block before a segment's first only gives its digits
         const auto merge = [&](int it, int buf) {
             // dhat and lse of block it's columns from the wavefronts' sums
@@ -650,17 +655,20 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
             };
             if constexpr (kShare)
                 for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
-            uint32_t lo[16];
-            const int ex_old = ex;
+            v4i bc[2][3];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
+            const int ex_old = sc.ex;
             if (active && X < W) {
-                const float gp = kAdj && in_row ? gdhat[pix + xc] : 0.0f;
-                const float dh = kAdj ? dhat[pix + xc] : 0.0f;
-                const float ls = kAdj ? lse[pix + xc] : 0.0f;
-                const float g1 = kAdj ? gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc])
-                                      : (in_row ? 1.0f : 0.0f);
+                const float gp = kKind == kSeed && in_row ? gdhat[pix + xc] : 0.0f;
+                const float dh = kKind == kSeed ? dhat[pix + xc] : 0.0f;
+                const float ls = kKind == kSeed ? lse[pix + xc] : 0.0f;
+                const float g1 =
+                    kKind == kSeed ? gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc]) : 0.0f;
                 const float dh0 = dh - (float)d0;
                 float G[16];
-                uint32_t m = 0;  // bits of the largest |G| (a NaN's are larger still)
                 double t = 0.0;
                 size_t Pv = Q;
                 asm volatile("" : "+s"(Pv));  // else 16 row addresses live in registers
@@ -675,104 +683,85 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
 #pragma unroll
                     for (int j = 0; j < 16; ++j) {
                         const bool on = kFull || d0 + j < D;
-                        if constexpr (kAdj) {
+                        if constexpr (kKind == kSeed) {
                             const float u = exp_e(-G[j] * invT - ls) * (dh0 - (float)j);
                             t += (double)(on ? gp * u * G[j] : 0.0f);
                             G[j] = on ? g1 * u : 0.0f;
                         } else {
                             G[j] = in_row && on ? G[j] : 0.0f;
                         }
-                        m = max(m, __float_as_uint(G[j]) & 0x7fffffffu);
                     }
                 };
                 if (d0 + 16 <= D)
                     seed(std::true_type{});
                 else
                     seed(std::false_type{});
-                if (kAdj && it >= it0) acc -= t;
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
-                m = __builtin_amdgcn_readfirstlane(m);
-                bad = bad || m >= 0x7f800000u;
-                ex = max(ex, (int)(m >> 23) - 126);
-                const float up = ldexpf(1.0f, 22 - ex);
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const float q = G[j] * up, h = __builtin_rintf(q);
-                    stage[j * kMxStride + lane] = ((uint32_t)(int)h + 0x8080u) ^ 0x8080u;
-                    lo[j] = ((uint32_t)(int)((q - h) * 0x1p23f) + 0x8080u) ^ 0x8080u;
-                }
-                __builtin_amdgcn_wave_barrier();
+                if (kKind == kSeed && it >= it0) acc -= t;
+                uint32_t lo[16];
+                put_wide(G, stage, lo, sc);
+                wide_planes(stage, lo, bc);
             }
             // the bands and the softmax sums; the buffers' next writers pass the next
             // one first
             if (kShare || (!kAdj && dhat)) __syncthreads();
             if (!kAdj && dhat && it > it0 && rt.grp == it % ng) merge(it - 1, par ^ 1);
             if (!active) continue;
-            v4i bc[2][3];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
-            if (X < W) {
-                digit_planes3(stage, bc[0]);
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int j = 0; j < 16; ++j) stage[j * kMxStride + lane] = lo[j];
-                __builtin_amdgcn_wave_barrier();
-                digit_planes3(stage, bc[1]);
-                __builtin_amdgcn_wave_barrier();
-            }
-            if (it >= it0) {
-                const double inv = bad ? __builtin_nan("") : ldexp(1.0, ex - 45);
-                const auto value = [](const v4i (&s)[2][3], int r) {
-                    const int h = s[0][0][r] + ((s[0][1][r] + (s[0][2][r] << 8)) << 8);
-                    const int l = s[1][0][r] + ((s[1][1][r] + (s[1][2][r] << 8)) << 8);
-                    return __builtin_fma((double)h, 0x1p23, (double)l);
+            const auto bands_of = [&](int c) { return kShare ? bands[par][c][lane] : band(c); };
+            if (kKind == kDot && it >= it0) {
+                // the outputs' pixels and their partners, on the stage: reference
+                // columns X - 32 .. X + 31, partner columns X - 47 - d0 .. X + 31 - d0
+                uint32_t* const rx = stage;            // census of the reference pixels
+                uint32_t* const ry = stage + 64;
+                uint32_t* const rz = stage + 128;      // their colours
+                float* const ra = reinterpret_cast<float*>(stage + 192);  // their alphas
+                uint2* const px = reinterpret_cast<uint2*>(stage + 256);  // partners: census
+                uint32_t* const pz = stage + 416;                         // colours
+                // 0 <= x - d < span: the disparity is one, column and partner in the image
+                const int xd = X - 32 - (d0 + n);
+                const uint32_t span = d0 + n < D ? (uint32_t)(W - (d0 + n)) : 0u;
+                const auto at = [&](const uint4* p, int x) {
+                    return p[pix + min(max(x, 0), W - 1)];
                 };
-                const auto outputs = [&](auto rescaled) {
+                const uint4 r = at(im.pixL, X - 32 + lane);
+                const uint4 q0 = at(im.pixR, X - 47 - d0 + lane);
+                const uint4 q1 = at(im.pixR, X + 17 - d0 + (lane & 15));
+                rx[lane] = r.x;
+                ry[lane] = r.y;
+                rz[lane] = r.z;
+                ra[lane] = im.alpha[r.w >> 3];
+                px[lane] = uint2{q0.x, q0.y};
+                pz[lane] = q0.z;
+                if (lane < 16) {
+                    px[64 + lane] = uint2{q1.x, q1.y};
+                    pz[64 + lane] = q1.z;
+                }
+                __builtin_amdgcn_wave_barrier();
+                wide_outputs(X, W, bp, bc, ex_old, sc, bands_of, [&](int i, int, double(&v)[4]) {
+                    int c = 16 * i + 4 * kg;
+                    asm volatile("" : "+v"(c));  // the addresses are made here, not kept
+                    const v4u cx = *reinterpret_cast<const v4u*>(rx + c);
+                    const v4u cy = *reinterpret_cast<const v4u*>(ry + c);
+                    const v4u cz = *reinterpret_cast<const v4u*>(rz + c);
+                    const v4f al = *reinterpret_cast<const v4f*>(ra + c);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int xb = X - 32 + 16 * i;
-                        if (xb < 0 || xb >= W) continue;
-                        const v4i b0 = kShare ? bands[par][2 * i][lane] : band(2 * i);
-                        const v4i b1 = kShare ? bands[par][2 * i + 1][lane] : band(2 * i + 1);
-                        v4i s[2][3];
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-#pragma unroll
-                            for (int k = 0; k < 3; ++k)
-                                s[h][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
-                                    b0, bp[h][k], v4i{0, 0, 0, 0}, 0, 0, 0);
-                        double v[4];
-                        if (decltype(rescaled)::value) {
-                            const double inv_old = ldexp(1.0, ex_old - 45);
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) v[r] = value(s, r) * inv_old;
-#pragma unroll
-                            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                                for (int k = 0; k < 3; ++k) s[h][k] = v4i{0, 0, 0, 0};
-                        }
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-#pragma unroll
-                            for (int k = 0; k < 3; ++k)
-                                s[h][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b1, bc[h][k],
-                                                                                s[h][k], 0, 0, 0);
-                        v4f o;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            o[r] = (float)(decltype(rescaled)::value
-                                               ? __builtin_fma(value(s, r), inv, v[r])
-                                               : value(s, r) * inv);
-                        *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) = o;
+                    for (int k = 0; k < 4; ++k) {
+                        const int e = c + k + 15 - n;
+                        const uint2 q = px[e];
+                        const uint32_t s = __builtin_amdgcn_sad_u8(cz[k], pz[e], 0u);
+                        const int hm = __popc(cx[k] ^ q.x) + __popc(cy[k] ^ q.y);
+                        const float da = al[k] * tab[s], dc = (1.0f - al[k]) * tab[kCenTab + hm];
+                        const bool on = (uint32_t)(xd + c + k) < span;
+                        acc = __builtin_fma(v[k], (double)(on ? da : 0.0f), acc);
+                        acc2 = __builtin_fma(v[k], (double)(on ? dc : 0.0f), acc2);
                     }
-                };
-                if (ex == ex_old)
-                    outputs(std::false_type{});
-                else
-                    outputs(std::true_type{});
+                });
+                __builtin_amdgcn_wave_barrier();
+            } else if (it >= it0) {
+                wide_outputs(X, W, bp, bc, ex_old, sc, bands_of,
+                             [&](int i, int, double(&v)[4]) {
+                                 *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
+                                     v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+                             });
                 __builtin_amdgcn_wave_barrier();
                 if constexpr (!kAdj) {
                     // A2 = sum / N2, and the softmax sums of the wavefront's 16
@@ -815,10 +804,16 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
             if (rt.grp == 0) merge(it1 - 1, par ^ 1);
         }
         if (kAdj && active) {
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-            if (lane == 0)
-                partT[((size_t)row * gridDim.y + blockIdx.y) * ng + grp] =
-                    acc * (double)(invT * invT);
+            for (int off = 32; off > 0; off >>= 1) {  // fixed-order wavefront reduction
+                acc += __shfl_down(acc, off, 64);
+                if (kKind == kDot) acc2 += __shfl_down(acc2, off, 64);
+            }
+            const size_t k = ((size_t)row * gridDim.y + blockIdx.y) * ng + grp;
+            if (lane == 0 && kKind == kSeed) part[k] = acc * (double)(invT * invT);
+            if (lane == 0 && kKind == kDot) {
+                part[2 * k] = acc;
+                part[2 * k + 1] = acc2;
+            }
         }
     }
 }
@@ -1222,33 +1217,31 @@ static void with_row_kind(const RowGrid& rg, const SoftGeom& g, Go go) {
         second(std::false_type{});
 }
 
-template <bool kDeriv>
-static void launch_mrow(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, const float* G,
-                        float* out, double* part, hipStream_t st) {
+static void launch_mrow(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, float* out,
+                        hipStream_t st) {
     with_row_kind(rg, g, [&](auto share, auto stream) {
-        // the derivative's pass writes no volume
-        constexpr bool kStream = !kDeriv && decltype(stream)::value;
-        hipLaunchKernelGGL((k_soft_mrow<kDeriv, decltype(share)::value, kStream>), rg.grid,
-                           rg.block, 0, st, g, im, G, out, part, rg.seg);
+        hipLaunchKernelGGL((k_soft_mrow<decltype(share)::value, decltype(stream)::value>), rg.grid,
+                           rg.block, 0, st, g, im, out, rg.seg);
     });
 }
 
-template <bool kAdj>
-static void launch_wide(const RowGrid& rg, const SoftGeom& g, const float* in, const float* theta,
-                        float* dhat, float* lse, const float* gdhat, float* out, double* partT,
-                        hipStream_t st) {
+template <WideKind kKind>
+static void launch_wide(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, const float* in,
+                        const float* theta, float* dhat, float* lse, const float* gdhat, float* out,
+                        double* part, hipStream_t st) {
     with_row_kind(rg, g, [&](auto share, auto stream) {
-        hipLaunchKernelGGL((k_soft_wide<kAdj, decltype(share)::value, decltype(stream)::value>),
-                           rg.grid, rg.block, 0, st, g, in, theta, dhat, lse, gdhat, out, partT,
-                           rg.seg);
+        // the dot products write no volume
+        constexpr bool kStream = kKind != kDot && decltype(stream)::value;
+        hipLaunchKernelGGL((k_soft_wide<kKind, decltype(share)::value, kStream>), rg.grid, rg.block,
+                           0, st, g, im, in, theta, dhat, lse, gdhat, out, part, rg.seg);
     });
 }
 
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
-                        int D, const float* alpha, uint2* vrec, float* n2, hipStream_t st) {
+                        int D, uint2* vrec, float* n2, hipStream_t st) {
     SoftGeom g{arms, nullptr, nullptr, B, W, H, D};
     hipLaunchKernelGGL(k_soft_counts, dim3((W + kCntTW - 1) / kCntTW, (H + kCntTH - 1) / kCntTH, B),
-                       dim3(256), 0, st, g, theta, alpha, tab, vrec, n2);
+                       dim3(256), 0, st, g, theta, tab, vrec, n2);
     return hipGetLastError();
 }
 
@@ -1260,10 +1253,10 @@ hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, floa
     SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const RowGrid rg = row_grid(g);
-    launch_mrow<false>(rg, g, im, nullptr, t1, nullptr, st);                                 // E1
+    launch_mrow(rg, g, im, t1, st);                                 // E1
     launch_vv<false>(g, t1, t2, st);                                                         // E2
     const bool soft = dhat && D <= 16 * kMxWaves;
-    launch_wide<false>(rg, g, t2, theta, soft ? dhat : nullptr, lse, nullptr, A2, nullptr,
+    launch_wide<kMean>(rg, g, im, t2, theta, soft ? dhat : nullptr, lse, nullptr, A2, nullptr,
                        st);                                                                  // A2
     if (dhat && !soft) {
         const size_t P = (size_t)W * H;
@@ -1282,10 +1275,11 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const RowGrid rg = row_grid(g);
-    launch_wide<true>(rg, g, A2, theta, const_cast<float*>(dhat), const_cast<float*>(lse), gdhat,
-                      t2, partT, st);                                 // G_E2, T-gradient terms
+    launch_wide<kSeed>(rg, g, im, A2, theta, const_cast<float*>(dhat), const_cast<float*>(lse),
+                       gdhat, t2, partT, st);                         // G_E2, T-gradient terms
     launch_vv<true>(g, t2, t1, st);                                   // G_E1
-    launch_mrow<true>(rg, g, im, t1, nullptr, partAC, st);            // G_E1 . H dc/dlambda
+    launch_wide<kDot>(rg, g, im, t1, theta, nullptr, nullptr, nullptr, nullptr, partAC,
+                      st);                                            // H^T G_E1 . dc/dlambda
     double* blk = partT + (size_t)nrows;  // kRedBlocks x 3 after the row partials
     hipLaunchKernelGGL(k_soft_reduce1, dim3(kRedBlocks), dim3(256), 0, st, partAC,
                        (size_t)rg.parts, partT, (size_t)rg.parts, blk);
