@@ -262,6 +262,9 @@ dco_status dco_densify_run(dco_densify* h, const float* Ds, const float* Dpre, c
 /* Iterations used by the last solve and its final |r| / |b| (host outputs,
  * either may be NULL).  Synchronises the stream. */
 dco_status dco_densify_stats(dco_densify* h, int* iters, double* rel_residual);
+/* Launches of a group of iterations in the last solve, 0 if it ran as one launch
+ * (diagnostics).  The two give the same bits. */
+dco_status dco_densify_launches(dco_densify* h, int* launches);
 
 /* ---- Depth contour extraction given the optical flows (Sec. 5) ---- */
 

@@ -213,13 +213,13 @@ hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* 
 hipError_t launch_downscale2(const uint8_t* rgbL, const uint8_t* rgbR, int W2, int W, int H,
                              uint8_t* outL, uint8_t* outR, hipStream_t st);
 // Depth densification (Eq. 13-20): device buffers of one grid (FP64 state,
-// nblk = densify_blocks(W, H) block partials per sum) and its launches.
+// densify_parts(W, H, k) block partials per sum) and its launches.
 struct DensifyBufs {
     double *cr, *cd, *diag, *invdiag;  // edge coefficients (p, p + x), (p, p + y); diagonal
     double *x, *r, *q, *p[2];          // solution, residual, A p, search directions
     double *rz[2], *rr[2], *pq, *bb;   // block partial sums
     int* flags;                        // [0] converged, [1] iterations done, [2] abort
-    // one-launch solve
+    // grids that can be solved in one launch
     uint64_t* words;                   // what its workgroups exchange
     double* res;                       // [0] r.r, [1] b.b
 };
@@ -228,17 +228,22 @@ constexpr int kDensifyMaxK = 4;
 int densify_solve_k(int W, int H, int cus);
 size_t densify_solve_words(int W, int H, int k);
 // The whole solve in one launch (k = densify_solve_k; `ticks` of the 100 MHz
-// clock bound each of its waits): D, flags and res are its results; with flags[2] set it was given up and D holds nothing.
+// clock bound each of its waits): D, flags and res are its results; with flags[2]
+// set it was given up and D holds nothing.
 hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
                                 const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
                                 int H, double lam_d, double lam_s, double lam_s2, double tol,
                                 int limit, uint64_t ticks, float* D, hipStream_t st);
-hipError_t launch_densify_setup(const DensifyBufs& b, const float* Ds, const float* Dpre,
+// The solve as a sequence of launches, k as above (0: one that cannot run as one
+// launch); the block sums of a solve have densify_parts entries.
+size_t densify_parts(int W, int H, int k);
+hipError_t launch_densify_setup(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
                                 const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
                                 int H, double lam_d, double lam_s, double lam_s2, hipStream_t st);
-hipError_t launch_densify_iters(const DensifyBufs& b, int W, int H, double tol, int n,
+hipError_t launch_densify_iters(const DensifyBufs& b, int k, int W, int H, double tol, int n,
                                 hipStream_t st);
-hipError_t launch_densify_out(const DensifyBufs& b, int W, int H, float* D, hipStream_t st);
+hipError_t launch_densify_out(const DensifyBufs& b, int k, int W, int H, float* D,
+                              hipStream_t st);
 
 // Depth contour extraction given the flows (Sec. 5): scratch of one frame
 // (full size W x H, flow grid w x h) and its launches.

@@ -16,10 +16,9 @@ struct dco_densify {
     DensifyBufs b{};
     hipGraphExec_t exec = nullptr;
     int* flags_host = nullptr;  // pinned copy of b.flags
-    int launches = 0;           // graph launches of the last run
+    int launches = 0;           // graph launches of the last run (0: one launch)
     int device = 0;
     int solve_k = 0;            // pixels per thread of the one-launch solve (0: not possible)
-    bool one_launch = false;    // the last run was one
     // longest wait of its workgroups for each other, in 10 ns (0.2 s); the
     // environment variable DCO_DENSIFY_WAIT, read at create, lets a test
     // force a solve to be given up
@@ -97,8 +96,7 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
     h->H = H;
     h->p = prm;
     h->stream = (hipStream_t)stream;
-    h->nblk = densify_blocks(W, H);
-    const size_t P = (size_t)W * H, nb = (size_t)h->nblk;
+    const size_t P = (size_t)W * H;
     DensifyBufs& b = h->b;
     auto fail = [&](dco_status s) {
         free_densify(h);
@@ -106,14 +104,6 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
         return s;
     };
     dco_status st;
-    double** vecs[] = {&b.cr, &b.cd, &b.diag, &b.invdiag, &b.x, &b.r, &b.q, &b.p[0], &b.p[1]};
-    for (double** v : vecs)
-        if ((st = dev_alloc(v, P)) != DCO_OK) return fail(st);
-    double** parts[] = {&b.rz[0], &b.rz[1], &b.rr[0], &b.rr[1], &b.pq, &b.bb};
-    for (double** v : parts)
-        if ((st = dev_alloc(v, nb)) != DCO_OK) return fail(st);
-    if ((st = dev_alloc(&b.flags, 3)) != DCO_OK) return fail(st);
-    if ((st = pinned_alloc((void**)&h->flags_host, 3 * sizeof(int))) != DCO_OK) return fail(st);
     int cus = 0;
     if (hipGetDevice(&h->device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) !=
@@ -124,6 +114,16 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
     }
     if (const char* w = getenv("DCO_DENSIFY_WAIT")) h->ticks = strtoull(w, nullptr, 10);
     h->solve_k = h->device < 64 ? densify_solve_k(W, H, cus) : 0;
+    const size_t nb = densify_parts(W, H, h->solve_k);
+    h->nblk = (int)nb;
+    double** vecs[] = {&b.cr, &b.cd, &b.diag, &b.invdiag, &b.x, &b.r, &b.q, &b.p[0], &b.p[1]};
+    for (double** v : vecs)
+        if ((st = dev_alloc(v, P)) != DCO_OK) return fail(st);
+    double** parts[] = {&b.rz[0], &b.rz[1], &b.rr[0], &b.rr[1], &b.pq, &b.bb};
+    for (double** v : parts)
+        if ((st = dev_alloc(v, nb)) != DCO_OK) return fail(st);
+    if ((st = dev_alloc(&b.flags, 3)) != DCO_OK) return fail(st);
+    if ((st = pinned_alloc((void**)&h->flags_host, 3 * sizeof(int))) != DCO_OK) return fail(st);
     if (h->solve_k) {
         if ((st = dev_alloc(&b.words, densify_solve_words(W, H, h->solve_k))) != DCO_OK)
             return fail(st);
@@ -140,7 +140,8 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        const hipError_t e1 = launch_densify_iters(b, W, H, prm.tol, prm.iters_per_launch, cap);
+        const hipError_t e1 = launch_densify_iters(b, h->solve_k, W, H, prm.tol,
+                                                   prm.iters_per_launch, cap);
         e = hipStreamEndCapture(cap, &g);
         if (e == hipSuccess) e = e1;
     }
@@ -166,7 +167,7 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
     DCO_TRY(need(MI, "MI"));
     DCO_TRY(need(D, "D"));
     const dco_densify_params& p = h->p;
-    h->one_launch = false;
+    h->launches = 0;
     if (h->solve_k) {
         // whole groups of iters_per_launch iterations, as the launches below run
         const long long groups = ((long long)p.max_iters + p.iters_per_launch - 1) /
@@ -180,14 +181,13 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
         DCO_HIP_CHECK(hipMemcpyAsync(h->flags_host, h->b.flags, 3 * sizeof(int),
                                      hipMemcpyDeviceToHost, h->stream));
         DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
-        h->one_launch = h->flags_host[2] == 0;
-        if (h->one_launch) return DCO_OK;
+        if (h->flags_host[2] == 0) return DCO_OK;
         // given up: its workgroups could not all run (another process held the
-        // CUs); the launches below need nothing to run at the same time
+        // CUs); the launches below need nothing to run at the same time, and give
+        // the same bits
     }
-    DCO_HIP_CHECK(launch_densify_setup(h->b, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H, p.lambda_d,
-                                       p.lambda_s, p.lambda_s2, h->stream));
-    h->launches = 0;
+    DCO_HIP_CHECK(launch_densify_setup(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
+                                       p.lambda_d, p.lambda_s, p.lambda_s2, h->stream));
     for (int done = 0; done < p.max_iters; done += p.iters_per_launch) {
         DCO_HIP_CHECK(hipGraphLaunch(h->exec, h->stream));
         ++h->launches;
@@ -196,7 +196,7 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
         DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
         if (h->flags_host[0]) break;
     }
-    DCO_HIP_CHECK(launch_densify_out(h->b, h->W, h->H, D, h->stream));
+    DCO_HIP_CHECK(launch_densify_out(h->b, h->solve_k, h->W, h->H, D, h->stream));
     return DCO_OK;
 }
 
@@ -206,7 +206,7 @@ extern "C" dco_status dco_densify_stats(dco_densify* h, int* iters, double* rel_
     int f[2];
     DCO_HIP_CHECK(hipMemcpy(f, h->b.flags, sizeof(f), hipMemcpyDeviceToHost));
     if (iters) *iters = f[1];
-    if (rel_residual && h->one_launch) {
+    if (rel_residual && h->solve_k) {
         double res[2];
         DCO_HIP_CHECK(hipMemcpy(res, h->b.res, sizeof(res), hipMemcpyDeviceToHost));
         *rel_residual = res[1] > 0.0 ? std::sqrt(res[0] / res[1]) : 0.0;
@@ -224,5 +224,12 @@ extern "C" dco_status dco_densify_stats(dco_densify* h, int* iters, double* rel_
         }
         *rel_residual = sb > 0.0 ? std::sqrt(sr / sb) : 0.0;
     }
+    return DCO_OK;
+}
+
+extern "C" dco_status dco_densify_launches(dco_densify* h, int* launches) {
+    DCO_TRY(need(h, "handle"));
+    DCO_TRY(need(launches, "launches"));
+    *launches = h->launches;
     return DCO_OK;
 }

@@ -20,9 +20,10 @@
 // returns at once (no pixel is touched).
 //
 // Grids of up to about a million pixels run the whole solve in one launch
-// instead (k_dz_solve, below); the launches above serve larger grids, and a
-// solve whose workgroups could not all run at once.
+// instead (k_dz_solve, below), and as launches on that kernel's tiles when its
+// workgroups could not all run at once; the launches above serve larger grids.
 #include <climits>
+#include <type_traits>
 
 #include "dco_internal.h"
 
@@ -71,62 +72,83 @@ __device__ inline void partial_sums(const double* const (&part)[N], int n, doubl
     block_sums<N>(out, red);
 }
 
-// Coefficients, right-hand side and the initial state x = 0, r = b, p = 0,
-// block sums of r.z, r.r and b.b.  Eq. 16: w_pq = 0 when exactly one of p, q
-// is on the depth contour, else max(1 - min(s_p, s_q), 0) with s = Mfuse MI.
-__global__ __launch_bounds__(kDzThreads) void k_dz_setup(
-    const float* __restrict__ Ds, const float* __restrict__ Dpre,
-    const uint8_t* __restrict__ Bdp, const float* __restrict__ Mfuse,
-    const float* __restrict__ MI, int W, int H, double lam_d, double lam_s, double lam_s2,
-    double* __restrict__ cr, double* __restrict__ cd, double* __restrict__ diag_out,
-    double* __restrict__ invdiag, double* __restrict__ x, double* __restrict__ r,
-    double* __restrict__ p0, double* __restrict__ p1, double* __restrict__ rz_part,
-    double* __restrict__ rr_part, double* __restrict__ bb_part, double* __restrict__ rz_init,
-    int* __restrict__ flags) {
+// The inputs of a solve, and the edge coefficients, diagonal and right-hand side of
+// a pixel.  Eq. 16: w_pq = 0 when exactly one of p, q is on the depth contour, else
+// max(1 - min(s_p, s_q), 0) with s = Mfuse MI.
+struct DzIn {
+    const float *Ds, *Dpre;
+    const uint8_t* Bdp;
+    const float *Mfuse, *MI;
+    int W, H;
+    double lam_d, lam_s, lam_s2;
+};
+struct DzPixel {
+    double cr, cd, cl, cu, diag, b, id;  // id = 1 / diag (0 where diag is 0)
+};
+__device__ inline DzPixel dz_pixel(const DzIn& A, int x, int y) {
+    const int W = A.W, i = y * W + x;
+    const double s = (double)A.Mfuse[i] * (double)A.MI[i];
+    const int b = A.Bdp[i] != 0;
+    const auto w = [&](int j) {
+        const int bj = A.Bdp[j] != 0;
+        if (b + bj == 1) return 0.0;
+        const double sj = (double)A.Mfuse[j] * (double)A.MI[j];
+        return fmax(1.0 - fmin(s, sj), 0.0);
+    };
+    DzPixel c;
+    c.cr = x + 1 < W ? 2.0 * A.lam_s * w(i + 1) : 0.0;
+    c.cd = y + 1 < A.H ? 2.0 * A.lam_s * w(i + W) : 0.0;
+    c.cl = x > 0 ? 2.0 * A.lam_s * w(i - 1) : 0.0;
+    c.cu = y > 0 ? 2.0 * A.lam_s * w(i - W) : 0.0;
+    const double ds = A.Ds[i], dp = A.Dpre ? (double)A.Dpre[i] : 0.0;
+    const double wsp = ds > 0.0 ? 1.0 : 0.0, wst = dp > 0.0 ? 1.0 : 0.0;
+    c.diag = A.lam_d * wsp + A.lam_s2 * wst + c.cr + c.cd + c.cl + c.cu;
+    c.b = A.lam_d * wsp * ds + A.lam_s2 * wst * dp;
+    c.id = c.diag > 0.0 ? 1.0 / c.diag : 0.0;
+    return c;
+}
+
+// Where a solve keeps its state between launches.
+struct DzMem {
+    double *cr, *cd, *diag, *invdiag, *x, *r, *p0, *p1;
+    double *rz, *rr, *bb, *rz_init;  // block sums
+    int* flags;                      // [0] converged, [1] iterations done
+    __device__ void put(int i, const DzPixel& c) const {
+        cr[i] = c.cr;
+        cd[i] = c.cd;
+        diag[i] = c.diag;
+        invdiag[i] = c.id;
+        x[i] = 0.0;
+        r[i] = c.b;
+        p0[i] = 0.0;
+        p1[i] = 0.0;
+    }
+    __device__ void put_sums(int k, double rz_k, double rr_k) const {
+        rz[k] = rz_k;
+        rr[k] = rr_k;
+        bb[k] = rr_k;
+        rz_init[k] = 1.0;  // any nonzero "old" r.z: p starts at 0
+    }
+};
+
+// The initial state x = 0, r = b, p = 0, block sums of r.z, r.r and b.b.
+__global__ __launch_bounds__(kDzThreads) void k_dz_setup(DzIn A, DzMem m) {
     __shared__ double red[2 * kDzWaves];
-    const int P = W * H;
+    const int P = A.W * A.H;
     double rz = 0.0, rr = 0.0;
     for (int k = 0; k < kDzPix; ++k) {
         const int i = (blockIdx.x * kDzPix + k) * kDzThreads + threadIdx.x;
         if (i >= P) break;
-        const int y = i / W, xx = i - y * W;
-        const double s = (double)Mfuse[i] * (double)MI[i];
-        const int b = Bdp[i] != 0;
-        auto w = [&](int j) {
-            const int bj = Bdp[j] != 0;
-            if (b + bj == 1) return 0.0;
-            const double sj = (double)Mfuse[j] * (double)MI[j];
-            return fmax(1.0 - fmin(s, sj), 0.0);
-        };
-        const double c_r = xx + 1 < W ? 2.0 * lam_s * w(i + 1) : 0.0;
-        const double c_d = y + 1 < H ? 2.0 * lam_s * w(i + W) : 0.0;
-        const double c_l = xx > 0 ? 2.0 * lam_s * w(i - 1) : 0.0;
-        const double c_u = y > 0 ? 2.0 * lam_s * w(i - W) : 0.0;
-        const double ds = Ds[i], dp = Dpre ? (double)Dpre[i] : 0.0;
-        const double wsp = ds > 0.0 ? 1.0 : 0.0, wst = dp > 0.0 ? 1.0 : 0.0;
-        const double diag = lam_d * wsp + lam_s2 * wst + c_r + c_d + c_l + c_u;
-        const double bi = lam_d * wsp * ds + lam_s2 * wst * dp;
-        const double id = diag > 0.0 ? 1.0 / diag : 0.0;
-        cr[i] = c_r;
-        cd[i] = c_d;
-        diag_out[i] = diag;
-        invdiag[i] = id;
-        x[i] = 0.0;
-        r[i] = bi;
-        p0[i] = 0.0;
-        p1[i] = 0.0;
-        rz += bi * bi * id;
-        rr += bi * bi;
+        const int y = i / A.W;
+        const DzPixel c = dz_pixel(A, i - y * A.W, y);
+        m.put(i, c);
+        rz += c.b * c.b * c.id;
+        rr += c.b * c.b;
     }
     double sums[2] = {rz, rr};
     block_sums<2>(sums, red);
-    if (threadIdx.x == 0) {
-        rz_part[blockIdx.x] = sums[0];
-        rr_part[blockIdx.x] = sums[1];
-        bb_part[blockIdx.x] = sums[1];
-        rz_init[blockIdx.x] = 1.0;  // any nonzero "old" r.z: p starts at 0
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 2) flags[threadIdx.x] = 0;
+    if (threadIdx.x == 0) m.put_sums(blockIdx.x, sums[0], sums[1]);
+    if (blockIdx.x == 0 && threadIdx.x < 2) m.flags[threadIdx.x] = 0;
 }
 
 struct DzState {
@@ -259,8 +281,9 @@ __global__ __launch_bounds__(kDzThreads) void k_dz_out(const double* __restrict_
 //
 // A wait ends after `ticks` (0.2 s) without the awaited word (workgroups that do
 // not run: another process holds the CUs): the workgroup raises an abort flag
-// that every wait looks at, all leave, and the host repeats the solve with
-// the launches above.
+// that every wait looks at, all leave, and the host repeats the solve as a
+// sequence of launches on the same tiles (k_dz_tile_*), which form every value and
+// every sum as this kernel does: the same bits either way.
 //
 // What bounds it: the two exchanges of an iteration (a store to memory and
 // loads from it across the XCDs, 1.3 us each, more with the tiles polled) and
@@ -273,12 +296,10 @@ constexpr int kLineWords = 32;                       // a tile's sums, 256 bytes
                                                      // workgroup polls them
 
 struct SolveArgs {
-    const float *Ds, *Dpre;
-    const uint8_t* Bdp;
-    const float *Mfuse, *MI;
+    DzIn in;
     float* D;
-    int W, H, tx, ntiles, limit;  // tiles per row, tiles, iterations at most
-    double lam_d, lam_s, lam_s2, tol2;
+    int tx, ntiles, limit;  // tiles per row, tiles, iterations at most
+    double tol2;
     uint64_t ticks;  // longest wait, in ticks of the 100 MHz clock
     uint64_t* pq;    // ntiles lines: p.q (two words)
     uint64_t* rzr;   // ntiles lines: r.z, r.r (two words each)
@@ -353,6 +374,44 @@ __device__ inline double lane_sum(double v) {
     return v;
 }
 
+// The sum of N values per thread of a tile's workgroup, in a fixed order: across each
+// wavefront, then over the wavefronts' totals.  put(j, total) in one thread.
+template <int N, typename Put>
+__device__ inline void tile_sums(double (&v)[N], double (*red)[kSolveWaves], Put put) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        v[j] = lane_sum<true>(v[j]);
+        if ((t & 63) == 63) red[j][t >> 6] = v[j];
+    }
+    __syncthreads();
+    static_assert(kSolveWaves == 16, "one wavefront total per lane of a DPP row");
+    if (t < kSolveWaves) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const double u = lane_sum<false>(red[j][t]);
+            if (t == kSolveWaves - 1) put(j, u);
+        }
+    }
+}
+
+// The sum over the tiles, in a fixed order, of what threads 0 .. 255 hold of tiles t,
+// t + 256, ...; in every thread.
+template <int N>
+__device__ inline void over_tiles(double (&v)[N], double (*all)[4]) {
+    const int t = threadIdx.x;
+    if (t < 256) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            v[j] = lane_sum<true>(v[j]);
+            if ((t & 63) == 63) all[j][t >> 6] = v[j];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = (all[j][0] + all[j][1]) + (all[j][2] + all[j][3]);
+}
+
 // Clears what k_dz_solve waits on (words of an earlier solve bear the same
 // iteration numbers) and the flags.
 __global__ __launch_bounds__(256) void k_dz_clear(uint64_t* __restrict__ words, size_t n,
@@ -371,7 +430,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
     __shared__ int gave_up;
     const int t = threadIdx.x, lx = t & 31, ly = t >> 5;
     const int tile = blockIdx.x, ty0 = tile / A.tx, tx0 = tile - ty0 * A.tx;
-    const int x0 = tx0 * kTileW, y0 = ty0 * TH, W = A.W, H = A.H;
+    const int x0 = tx0 * kTileW, y0 = ty0 * TH, W = A.in.W, H = A.in.H;
     if (t == 0) gave_up = 0;
 
     // own pixels: rows ly + 32 k of the tile; outside the image all is zero
@@ -382,24 +441,14 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
         const int xx = x0 + lx, y = y0 + ly + kTileRows * k;
         x[k] = r[k] = p[k] = id[k] = dg[k] = cr[k] = cd[k] = cl[k] = cu[k] = 0.0;
         if (xx >= W || y >= H) continue;
-        const int i = y * W + xx;
-        const double s = (double)A.Mfuse[i] * (double)A.MI[i];
-        const int b = A.Bdp[i] != 0;
-        auto w = [&](int j) {
-            const int bj = A.Bdp[j] != 0;
-            if (b + bj == 1) return 0.0;
-            const double sj = (double)A.Mfuse[j] * (double)A.MI[j];
-            return fmax(1.0 - fmin(s, sj), 0.0);
-        };
-        cr[k] = xx + 1 < W ? 2.0 * A.lam_s * w(i + 1) : 0.0;
-        cd[k] = y + 1 < H ? 2.0 * A.lam_s * w(i + W) : 0.0;
-        cl[k] = xx > 0 ? 2.0 * A.lam_s * w(i - 1) : 0.0;
-        cu[k] = y > 0 ? 2.0 * A.lam_s * w(i - W) : 0.0;
-        const double ds = A.Ds[i], dp = A.Dpre ? (double)A.Dpre[i] : 0.0;
-        const double wsp = ds > 0.0 ? 1.0 : 0.0, wst = dp > 0.0 ? 1.0 : 0.0;
-        dg[k] = A.lam_d * wsp + A.lam_s2 * wst + cr[k] + cd[k] + cl[k] + cu[k];
-        r[k] = A.lam_d * wsp * ds + A.lam_s2 * wst * dp;
-        id[k] = dg[k] > 0.0 ? 1.0 / dg[k] : 0.0;
+        const DzPixel c = dz_pixel(A.in, xx, y);
+        cr[k] = c.cr;
+        cd[k] = c.cd;
+        cl[k] = c.cl;
+        cu[k] = c.cu;
+        dg[k] = c.diag;
+        r[k] = c.b;
+        id[k] = c.id;
         rz += r[k] * r[k] * id[k];
         rr += r[k] * r[k];
     }
@@ -436,21 +485,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
     // Block sum of N values per thread in a fixed order, then published by one
     // thread as this tile's words at `at`.
     const auto publish = [&](auto& v, uint64_t* at, uint32_t epoch) {
-        constexpr int N = sizeof(v) / sizeof(double);
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            v[j] = lane_sum<true>(v[j]);
-            if ((t & 63) == 63) red[j][t >> 6] = v[j];
-        }
-        __syncthreads();
-        static_assert(kSolveWaves == 16, "one wavefront total per lane of a DPP row");
-        if (t < kSolveWaves) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                const double u = lane_sum<false>(red[j][t]);
-                if (t == kSolveWaves - 1) put_double(at + 2 * j, u, epoch);
-            }
-        }
+        tile_sums(v, red, [&](int j, double u) { put_double(at + 2 * j, u, epoch); });
     };
     // All tiles' sums (N doubles of every tile), added in a
     // fixed order, in every thread's v; with halo, also z of the thread's halo
@@ -475,16 +510,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
             zh = u[0];
         }
         if (!ok) gave_up = 1;
-        if (t < 256) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                v[j] = lane_sum<true>(v[j]);
-                if ((t & 63) == 63) all[j][t >> 6] = v[j];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < N; ++j) v[j] = (all[j][0] + all[j][1]) + (all[j][2] + all[j][3]);
+        over_tiles(v, all);
         const bool stop = gave_up != 0;
         __syncthreads();  // all[] may be reused
         return !stop;
@@ -574,42 +600,136 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
     }
 }
 
+// The same solve as a sequence of launches, a tile per workgroup as above: the state
+// between them in memory, a tile's sums in plain arrays.  dir and update are one
+// iteration; out makes D and the residual.
+struct DzTiles {
+    DzMem m;
+    double *q, *pq;
+    int W, H, tx, ntiles;
+    double tol2;
+};
+
+// body(i, x, y) for the thread's own pixels inside the image
+template <int K, typename Body>
+__device__ inline void tile_pixels(int W, int H, int tx, Body body) {
+    const int t = threadIdx.x, ty0 = blockIdx.x / tx, tx0 = blockIdx.x - ty0 * tx;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int x = tx0 * kTileW + (t & 31), y = (ty0 * K + k) * kTileRows + (t >> 5);
+        if (x < W && y < H) body(y * W + x, x, y);
+    }
+}
+
+// The sums over all tiles of N arrays of tile sums, in every thread.
+template <int N>
+__device__ inline void tiles_total(const double* const (&part)[N], int ntiles, double (&v)[N],
+                                   double (*all)[4]) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        v[j] = 0.0;
+        for (int i = t; i < ntiles && t < 256; i += 256) v[j] += part[j][i];
+    }
+    over_tiles(v, all);
+    __syncthreads();  // all[] may be reused
+}
+
+template <int K>
+__global__ __launch_bounds__(kSolveThreads) void k_dz_tile_setup(DzIn A, DzTiles s) {
+    __shared__ double red[2][kSolveWaves];
+    double v[2] = {0.0, 0.0};
+    tile_pixels<K>(A.W, A.H, s.tx, [&](int i, int x, int y) {
+        const DzPixel c = dz_pixel(A, x, y);
+        s.m.put(i, c);
+        v[0] += c.b * c.b * c.id;
+        v[1] += c.b * c.b;
+    });
+    double rz = 0.0;
+    tile_sums(v, red, [&](int j, double u) {
+        if (j == 0)
+            rz = u;
+        else
+            s.m.put_sums(blockIdx.x, rz, u);
+    });
+    if (blockIdx.x == 0 && threadIdx.x < 2) s.m.flags[threadIdx.x] = 0;
+}
+
+template <int K>
+__global__ __launch_bounds__(kSolveThreads) void k_dz_tile_dir(DzTiles s, const double* rz_new,
+                                                               const double* rz_old,
+                                                               const double* p_in, double* p_out) {
+    __shared__ double red[1][kSolveWaves];
+    __shared__ double all[2][4];
+    if (solve_done(s.m.flags)) return;
+    const double* const parts[2] = {rz_new, rz_old};
+    double rz[2], v[1] = {0.0};
+    tiles_total(parts, s.ntiles, rz, all);
+    const double beta = rz[0] / rz[1];
+    const DzMem& m = s.m;
+    const int W = s.W;
+    tile_pixels<K>(W, s.H, s.tx, [&](int i, int x, int y) {
+        const auto pn = [&](int j) { return m.r[j] * m.invdiag[j] + beta * p_in[j]; };
+        const double pc = pn(i);
+        double off = 0.0;
+        if (x + 1 < W) off += m.cr[i] * pn(i + 1);
+        if (x > 0) off += m.cr[i - 1] * pn(i - 1);
+        if (y + 1 < s.H) off += m.cd[i] * pn(i + W);
+        if (y > 0) off += m.cd[i - W] * pn(i - W);
+        const double qi = m.diag[i] * pc - off;
+        p_out[i] = pc;
+        s.q[i] = qi;
+        v[0] += pc * qi;
+    });
+    tile_sums(v, red, [&](int, double u) { s.pq[blockIdx.x] = u; });
+}
+
+template <int K>
+__global__ __launch_bounds__(kSolveThreads) void k_dz_tile_update(DzTiles s, const double* rz_in,
+                                                                  const double* rr_in,
+                                                                  const double* p, double* rz_out,
+                                                                  double* rr_out) {
+    __shared__ double red[2][kSolveWaves];
+    __shared__ double all[4][4];
+    if (solve_done(s.m.flags)) return;
+    const double* const parts[4] = {rr_in, s.m.bb, s.pq, rz_in};
+    double sums[4], v[2] = {0.0, 0.0};
+    tiles_total(parts, s.ntiles, sums, all);
+    if (sums[0] <= s.tol2 * sums[1]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) s.m.flags[0] = 1;
+        return;
+    }
+    const double alpha = sums[2] > 0.0 ? sums[3] / sums[2] : 0.0;
+    const DzMem& m = s.m;
+    tile_pixels<K>(s.W, s.H, s.tx, [&](int i, int, int) {
+        m.x[i] += alpha * p[i];
+        const double ri = m.r[i] - alpha * s.q[i];
+        m.r[i] = ri;
+        v[0] += ri * ri * m.invdiag[i];
+        v[1] += ri * ri;
+    });
+    tile_sums(v, red, [&](int j, double u) { (j ? rr_out : rz_out)[blockIdx.x] = u; });
+    if (blockIdx.x == 0 && threadIdx.x == 0) m.flags[1] += 1;
+}
+
+template <int K>
+__global__ __launch_bounds__(kSolveThreads) void k_dz_tile_out(DzTiles s, const double* rr_even,
+                                                               const double* rr_odd, float* D,
+                                                               double* res) {
+    __shared__ double all[2][4];
+    tile_pixels<K>(s.W, s.H, s.tx, [&](int i, int, int) { D[i] = (float)s.m.x[i]; });
+    if (blockIdx.x != 0) return;
+    const int it = s.m.flags[1];  // iteration k writes parity k & 1; setup parity 1
+    const double* const parts[2] = {it > 0 && ((it - 1) & 1) == 0 ? rr_even : rr_odd, s.m.bb};
+    double v[2];
+    tiles_total(parts, s.ntiles, v, all);
+    if (threadIdx.x < 2) res[threadIdx.x] = v[threadIdx.x];
+}
+
 }  // namespace
 
 int densify_blocks(int W, int H) {
     return (W * H + kDzThreads * kDzPix - 1) / (kDzThreads * kDzPix);
-}
-
-hipError_t launch_densify_setup(const DensifyBufs& b, const float* Ds, const float* Dpre,
-                                const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
-                                int H, double lam_d, double lam_s, double lam_s2, hipStream_t st) {
-    const int nb = densify_blocks(W, H);
-    hipLaunchKernelGGL(k_dz_setup, dim3(nb), dim3(kDzThreads), 0, st, Ds, Dpre, Bdp, Mfuse, MI, W,
-                       H, lam_d, lam_s, lam_s2, b.cr, b.cd, b.diag, b.invdiag, b.x, b.r, b.p[0],
-                       b.p[1], b.rz[1], b.rr[1], b.bb, b.rz[0], b.flags);
-    return hipGetLastError();
-}
-
-// Iterations [0, n) of one launch sequence; n even, so parities repeat.
-hipError_t launch_densify_iters(const DensifyBufs& b, int W, int H, double tol, int n,
-                                hipStream_t st) {
-    const int nb = densify_blocks(W, H);
-    DzState s{b.cr, b.cd, b.diag, b.invdiag, b.x, b.r, b.q, b.bb, b.flags, W, H, nb, tol * tol};
-    for (int it = 0; it < n; ++it) {
-        const int a = it & 1;  // rz[1 - a] is the newest r.z, rz[a] the one before
-        hipLaunchKernelGGL(k_dz_dir, dim3(nb), dim3(kDzThreads), 0, st, s, b.rz[1 - a], b.rz[a],
-                           b.p[a], b.p[1 - a], b.pq);
-        hipLaunchKernelGGL(k_dz_update, dim3(nb), dim3(kDzThreads), 0, st, s, b.rz[1 - a],
-                           b.rr[1 - a], b.pq, b.p[1 - a], b.rz[a], b.rr[a]);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_densify_out(const DensifyBufs& b, int W, int H, float* D, hipStream_t st) {
-    const int P = W * H;
-    hipLaunchKernelGGL(k_dz_out, dim3((P + kDzThreads - 1) / kDzThreads), dim3(kDzThreads), 0, st,
-                       b.x, P, D);
-    return hipGetLastError();
 }
 
 static int solve_tiles(int W, int H, int k) {
@@ -639,22 +759,105 @@ size_t densify_solve_words(int W, int H, int k) {
     return tiles * (2 * kLineWords + 2 * (size_t)(2 * kTileW + 2 * kTileRows * k));
 }
 
+// go(K) with the pixels per thread as a constant
+template <typename Go>
+static void with_tile_k(int k, Go go) {
+    switch (k) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        default: go(std::integral_constant<int, 4>{}); break;
+    }
+}
+
+static DzMem dz_mem(const DensifyBufs& b) {
+    return DzMem{b.cr, b.cd,    b.diag,  b.invdiag, b.x,     b.r,    b.p[0],
+                 b.p[1], b.rz[1], b.rr[1], b.bb,      b.rz[0], b.flags};
+}
+
+static DzTiles dz_tiles(const DensifyBufs& b, int k, int W, int H, double tol) {
+    return DzTiles{dz_mem(b), b.q, b.pq, W, H, (W + kTileW - 1) / kTileW, solve_tiles(W, H, k),
+                   tol * tol};
+}
+
+size_t densify_parts(int W, int H, int k) {
+    return k ? solve_tiles(W, H, k) : densify_blocks(W, H);
+}
+
+hipError_t launch_densify_setup(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
+                                const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
+                                int H, double lam_d, double lam_s, double lam_s2, hipStream_t st) {
+    const DzIn in{Ds, Dpre, Bdp, Mfuse, MI, W, H, lam_d, lam_s, lam_s2};
+    if (k) {
+        const DzTiles s = dz_tiles(b, k, W, H, 0.0);
+        with_tile_k(k, [&](auto K) {
+            hipLaunchKernelGGL(k_dz_tile_setup<decltype(K)::value>, dim3(s.ntiles),
+                               dim3(kSolveThreads), 0, st, in, s);
+        });
+    } else {
+        hipLaunchKernelGGL(k_dz_setup, dim3(densify_blocks(W, H)), dim3(kDzThreads), 0, st, in,
+                           dz_mem(b));
+    }
+    return hipGetLastError();
+}
+
+// Iterations [0, n) of one launch sequence; n even, so parities repeat.
+hipError_t launch_densify_iters(const DensifyBufs& b, int k, int W, int H, double tol, int n,
+                                hipStream_t st) {
+    const int nb = densify_blocks(W, H);
+    DzState s{b.cr, b.cd, b.diag, b.invdiag, b.x, b.r, b.q, b.bb, b.flags, W, H, nb, tol * tol};
+    const DzTiles t = k ? dz_tiles(b, k, W, H, tol) : DzTiles{};
+    for (int it = 0; it < n; ++it) {
+        const int a = it & 1;  // rz[1 - a] is the newest r.z, rz[a] the one before
+        if (k) {
+            with_tile_k(k, [&](auto K) {
+                hipLaunchKernelGGL(k_dz_tile_dir<decltype(K)::value>, dim3(t.ntiles),
+                                   dim3(kSolveThreads), 0, st, t, b.rz[1 - a], b.rz[a], b.p[a],
+                                   b.p[1 - a]);
+                hipLaunchKernelGGL(k_dz_tile_update<decltype(K)::value>, dim3(t.ntiles),
+                                   dim3(kSolveThreads), 0, st, t, b.rz[1 - a], b.rr[1 - a],
+                                   b.p[1 - a], b.rz[a], b.rr[a]);
+            });
+            continue;
+        }
+        hipLaunchKernelGGL(k_dz_dir, dim3(nb), dim3(kDzThreads), 0, st, s, b.rz[1 - a], b.rz[a],
+                           b.p[a], b.p[1 - a], b.pq);
+        hipLaunchKernelGGL(k_dz_update, dim3(nb), dim3(kDzThreads), 0, st, s, b.rz[1 - a],
+                           b.rr[1 - a], b.pq, b.p[1 - a], b.rz[a], b.rr[a]);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_densify_out(const DensifyBufs& b, int k, int W, int H, float* D,
+                              hipStream_t st) {
+    const int P = W * H;
+    if (k) {
+        const DzTiles t = dz_tiles(b, k, W, H, 0.0);
+        with_tile_k(k, [&](auto K) {
+            hipLaunchKernelGGL(k_dz_tile_out<decltype(K)::value>, dim3(t.ntiles),
+                               dim3(kSolveThreads), 0, st, t, b.rr[0], b.rr[1], D, b.res);
+        });
+    } else {
+        hipLaunchKernelGGL(k_dz_out, dim3((P + kDzThreads - 1) / kDzThreads), dim3(kDzThreads), 0,
+                           st, b.x, P, D);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
                                 const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
                                 int H, double lam_d, double lam_s, double lam_s2, double tol,
                                 int limit, uint64_t ticks, float* D, hipStream_t st) {
     const int tx = (W + kTileW - 1) / kTileW, tiles = solve_tiles(W, H, k);
-    SolveArgs A{Ds, Dpre, Bdp, Mfuse, MI, D, W, H, tx, tiles, limit, lam_d, lam_s, lam_s2,
+    SolveArgs A{{Ds, Dpre, Bdp, Mfuse, MI, W, H, lam_d, lam_s, lam_s2}, D, tx, tiles, limit,
                 tol * tol, ticks, b.words, b.words + (size_t)tiles * kLineWords,
                 b.words + 2 * (size_t)tiles * kLineWords, b.flags, b.res};
     const size_t n = densify_solve_words(W, H, k);
     hipLaunchKernelGGL(k_dz_clear, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, b.words, n,
                        b.flags);
-    switch (k) {
-        case 1: hipLaunchKernelGGL(k_dz_solve<1>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
-        case 2: hipLaunchKernelGGL(k_dz_solve<2>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
-        case 3: hipLaunchKernelGGL(k_dz_solve<3>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
-        default: hipLaunchKernelGGL(k_dz_solve<4>, dim3(tiles), dim3(kSolveThreads), 0, st, A); break;
-    }
+    with_tile_k(k, [&](auto K) {
+        hipLaunchKernelGGL(k_dz_solve<decltype(K)::value>, dim3(tiles), dim3(kSolveThreads), 0, st,
+                           A);
+    });
     return hipGetLastError();
 }

@@ -51,6 +51,12 @@ class Densifier:
         check(lib().dco_densify_stats(self._h, C.byref(it), C.byref(rel)))
         return it.value, rel.value
 
+    def launches(self):
+        """Launches of a group of iterations in the last solve (0: one launch)."""
+        n = C.c_int()
+        check(lib().dco_densify_launches(self._h, C.byref(n)))
+        return n.value
+
     def close(self):
         if self._h:
             lib().dco_densify_destroy(self._h)

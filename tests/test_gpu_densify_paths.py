@@ -1,0 +1,52 @@
+"""The two ways a densification solve runs on its tiles: as one launch, and as the
+sequence of launches that repeats a solve whose workgroups gave up waiting for each
+other (a wait bound of zero makes them).  Both form every value and every sum in the
+same order, so depth, iterations and residual are the same bits; the sequence is also
+held to the oracle's direct FP64 solve with the bound of test_gpu_densify.py, on
+inputs with varying texture, contour and stability maps."""
+import numpy as np
+import pytest
+
+from gpu_util import dev, host
+from oracle import densify as dz
+from test_gpu_densify_tiles import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def solve(W, H, a, **kw):
+    from paper_2203_02300_amd import Densifier
+    Ds, Dpre, B, Mf, MI = a
+    with Densifier(W, H, **kw) as z:
+        D = host(z.run(dev(Ds), dev(B), dev(Mf), dev(MI), Dpre=dev(Dpre)))
+        return D.view(np.uint32), z.stats(), z.launches()
+
+
+# one pixel per thread; two, three and four (edges of tiles, odd rows and columns)
+@pytest.mark.parametrize("W,H", [(200, 120), (33, 65), (257, 130), (640, 97), (1000, 200),
+                                 (639, 361), (1279, 129), (1100, 701)])
+def test_given_up_solve_has_the_same_bits(monkeypatch, W, H):
+    a = inputs(W, H, W + H)
+    print(f"densify paths {W}x{H}", flush=True)
+    one = solve(W, H, a)
+    monkeypatch.setenv("DCO_DENSIFY_WAIT", "0")
+    many = solve(W, H, a)
+    assert one[2] == 0 and many[2] > 0
+    assert np.array_equal(one[0], many[0]) and one[1] == many[1]
+    assert many[1][1] <= 1e-9 and 0 < many[1][0] < 400
+    if W * H < 200000:
+        want = dz.densify(*a)
+        assert np.abs(many[0].view(np.float32) - want).max() <= 1e-5 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("max_iters", [0, 2, 7])
+def test_iteration_limit_is_the_same(monkeypatch, max_iters):
+    W, H = 200, 120
+    a = inputs(W, H, 5)
+    kw = dict(max_iters=max_iters, iters_per_launch=2)
+    one = solve(W, H, a, **kw)
+    monkeypatch.setenv("DCO_DENSIFY_WAIT", "0")
+    many = solve(W, H, a, **kw)
+    assert many[2] == (max_iters + 1) // 2
+    assert np.array_equal(one[0], many[0]) and one[1] == many[1]
+    assert one[1][0] == 2 * ((max_iters + 1) // 2)
