@@ -50,3 +50,13 @@ def test_iteration_limit_is_the_same(monkeypatch, max_iters):
     assert many[2] == (max_iters + 1) // 2
     assert np.array_equal(one[0], many[0]) and one[1] == many[1]
     assert one[1][0] == 2 * ((max_iters + 1) // 2)
+
+
+def test_launches_of_a_large_grid():
+    """A grid beyond one launch: the linear kernels against the oracle."""
+    W, H = 1312, 832
+    a = inputs(W, H, 8)
+    D, (it, rel), launches = solve(W, H, a)
+    assert launches > 0 and rel <= 1e-9 and 0 < it < 400
+    want = dz.densify(*a)
+    assert np.abs(D.view(np.float32) - want).max() <= 1e-5 * np.abs(want).max()
