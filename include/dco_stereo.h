@@ -251,9 +251,9 @@ void dco_densify_destroy(dco_densify* h);
 
 /* One solve.  Ds (D_sparse, 0 = no data), Dpre (D_pre, 0 = none; NULL for
  * none), Mfuse, MI: H x W float; Bdp: H x W uint8 (nonzero = on the depth
- * contour); D: H x W float (out).  All device pointers.  Returns when the
- * solve has converged or used max_iters iterations, rounded up to whole
- * groups of iters_per_launch (grids of up to about a million pixels: one
+ * contour); D: H x W float (out; may lie on an input).  All device pointers.
+ * Returns when the solve has converged or used max_iters iterations, rounded up to
+ * whole groups of iters_per_launch (grids of up to about a million pixels: one
  * launch; larger ones: the host reads the convergence flag after every launch
  * of a group).  One-launch solves of a process take turns on a device. */
 dco_status dco_densify_run(dco_densify* h, const float* Ds, const float* Dpre, const uint8_t* Bdp,

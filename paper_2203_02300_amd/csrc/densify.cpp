@@ -157,6 +157,11 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
     return DCO_OK;
 }
 
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return a && b && x < y + nb && y < x + na;
+}
+
 extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const float* Dpre,
                                       const uint8_t* Bdp, const float* Mfuse, const float* MI,
                                       float* D) {
@@ -173,15 +178,23 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
         const long long groups = ((long long)p.max_iters + p.iters_per_launch - 1) /
                                  p.iters_per_launch;
         const long long limit = groups * p.iters_per_launch;
+        // D that lies on an input is written only once the solve is known to have
+        // ended: a solve given up at its last exchange may have written parts of it
+        const size_t P = (size_t)h->W * h->H, F = P * sizeof(float);
+        const bool aside = overlap(D, F, Ds, F) || overlap(D, F, Dpre, F) ||
+                           overlap(D, F, Bdp, P) || overlap(D, F, Mfuse, F) || overlap(D, F, MI, F);
         std::lock_guard<std::mutex> turn(g_solve_turn[h->device]);
         DCO_HIP_CHECK(launch_densify_solve(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
                                            p.lambda_d, p.lambda_s, p.lambda_s2, p.tol,
-                                           (int)(limit < INT_MAX ? limit : INT_MAX), h->ticks, D,
-                                           h->stream));
+                                           (int)(limit < INT_MAX ? limit : INT_MAX), h->ticks,
+                                           aside ? nullptr : D, h->stream));
         DCO_HIP_CHECK(hipMemcpyAsync(h->flags_host, h->b.flags, 3 * sizeof(int),
                                      hipMemcpyDeviceToHost, h->stream));
         DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
-        if (h->flags_host[2] == 0) return DCO_OK;
+        if (h->flags_host[2] == 0) {
+            if (aside) DCO_HIP_CHECK(launch_densify_out(h->b, 0, h->W, h->H, D, h->stream));
+            return DCO_OK;
+        }
         // given up: its workgroups could not all run (another process held the
         // CUs); the launches below need nothing to run at the same time, and give
         // the same bits

@@ -60,3 +60,21 @@ def test_launches_of_a_large_grid():
     assert launches > 0 and rel <= 1e-9 and 0 < it < 400
     want = dz.densify(*a)
     assert np.abs(D.view(np.float32) - want).max() <= 1e-5 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("wait", [None, "0"])
+@pytest.mark.parametrize("which", [0, 1, 3, 4])  # Ds, Dpre, Mfuse, MI
+def test_output_on_an_input(monkeypatch, which, wait):
+    """The inputs stay whole until the solve has ended, given up or not."""
+    from paper_2203_02300_amd import Densifier
+    W, H = 200, 120
+    a = inputs(W, H, 6)
+    want = solve(W, H, a)[0]
+    if wait:
+        monkeypatch.setenv("DCO_DENSIFY_WAIT", wait)
+    t = [dev(v) for v in a]
+    with Densifier(W, H) as z:
+        D = z.run(t[0], t[2], t[3], t[4], Dpre=t[1], out=t[which])
+        assert D.data_ptr() == t[which].data_ptr()
+        assert np.array_equal(host(D).view(np.uint32), want)
+        assert (z.launches() > 0) == bool(wait)
