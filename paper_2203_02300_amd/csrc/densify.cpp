@@ -9,6 +9,19 @@
 
 #include "dco_internal.h"
 
+// Longest wait of a one-launch solve's workgroups for each other, in 10 ns: 0.2 s.
+constexpr unsigned long long kSolveWait = 20000000;
+
+// The wait that the environment variable DCO_DENSIFY_WAIT asks for, which lets a test
+// force a solve to be given up: a whole number below kSolveWait; else kSolveWait.
+static unsigned long long solve_wait() {
+    const char* w = getenv("DCO_DENSIFY_WAIT");
+    if (!w || *w < '0' || *w > '9') return kSolveWait;
+    char* end = nullptr;
+    const unsigned long long v = strtoull(w, &end, 10);
+    return *end == '\0' && v < kSolveWait ? v : kSolveWait;
+}
+
 struct dco_densify {
     int W = 0, H = 0, nblk = 0;
     dco_densify_params p{};
@@ -19,10 +32,8 @@ struct dco_densify {
     int launches = 0;           // graph launches of the last run (0: one launch)
     int device = 0;
     int solve_k = 0;            // pixels per thread of the one-launch solve (0: not possible)
-    // longest wait of its workgroups for each other, in 10 ns (0.2 s); the
-    // environment variable DCO_DENSIFY_WAIT, read at create, lets a test
-    // force a solve to be given up
-    unsigned long long ticks = 20000000;
+    // longest wait of its workgroups for each other, in 10 ns
+    unsigned long long ticks = kSolveWait;
 };
 
 // One-launch solves of a process take turns on a device: two of them at once
@@ -112,7 +123,7 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
         dco_set_error("hipGetDevice failed: no usable GPU");
         return fail(DCO_ERR_HIP);
     }
-    if (const char* w = getenv("DCO_DENSIFY_WAIT")) h->ticks = strtoull(w, nullptr, 10);
+    h->ticks = solve_wait();
     h->solve_k = h->device < 64 ? densify_solve_k(W, H, cus) : 0;
     const size_t nb = densify_parts(W, H, h->solve_k);
     h->nblk = (int)nb;

@@ -78,3 +78,10 @@ def test_output_on_an_input(monkeypatch, which, wait):
         assert D.data_ptr() == t[which].data_ptr()
         assert np.array_equal(host(D).view(np.uint32), want)
         assert (z.launches() > 0) == bool(wait)
+
+
+@pytest.mark.parametrize("wait", ["", "abc", "-1", "0x", "1e9", " 0", "0 "])
+def test_wait_that_is_no_number_is_ignored(monkeypatch, wait):
+    W, H = 200, 120
+    monkeypatch.setenv("DCO_DENSIFY_WAIT", wait)
+    assert solve(W, H, inputs(W, H, 7))[2] == 0
