@@ -265,6 +265,11 @@ dco_status dco_densify_stats(dco_densify* h, int* iters, double* rel_residual);
 /* Launches of a group of iterations in the last solve, 0 if it ran as one launch
  * (diagnostics).  The two give the same bits. */
 dco_status dco_densify_launches(dco_densify* h, int* launches);
+/* One-launch solves of this handle that were given up after 20 ms because their
+ * workgroups could not all run (diagnostics).  Each is repeated as launches, and the
+ * next 16 solves (then 32, ... 1024, if further ones are given up) go as launches
+ * straight away. */
+dco_status dco_densify_given_up(dco_densify* h, int* solves);
 
 /* ---- Depth contour extraction given the optical flows (Sec. 5) ---- */
 

@@ -21,6 +21,7 @@ EXPORTS = (
     "dco_vote_refine",
     "dco_stereo_match_half", "dco_densify_default_params", "dco_densify_create",
     "dco_densify_destroy", "dco_densify_run", "dco_densify_stats", "dco_densify_launches",
+    "dco_densify_given_up",
     "dco_contour_default_params", "dco_contour_create", "dco_contour_destroy",
     "dco_contour_run", "dco_contour_launches",
     "dco_status_string", "dco_last_error", "dco_stereo_agg_slices", "dco_debug_fail_alloc",
@@ -105,6 +106,7 @@ def lib():
         "dco_densify_run": (st, [P, P, P, P, P, P, P]),
         "dco_densify_stats": (st, [P, C.POINTER(C.c_int), C.POINTER(C.c_double)]),
         "dco_densify_launches": (st, [P, C.POINTER(C.c_int)]),
+        "dco_densify_given_up": (st, [P, C.POINTER(C.c_int)]),
         "dco_contour_default_params": (st, [C.POINTER(ContourParams)]),
         "dco_contour_create": (st, [C.POINTER(P), i, i, C.POINTER(ContourParams), P]),
         "dco_contour_destroy": (None, [P]),

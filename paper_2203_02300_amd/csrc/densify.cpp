@@ -1,5 +1,6 @@
 // densify.cpp -- host side of the depth densification (Sec. 6, Eq. 13-20):
 // buffers, the captured iteration graph and the convergence loop.
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -9,8 +10,15 @@
 
 #include "dco_internal.h"
 
-// Longest wait of a one-launch solve's workgroups for each other, in 10 ns: 0.2 s.
-constexpr unsigned long long kSolveWait = 20000000;
+// Longest wait of a one-launch solve's workgroups for each other, in 10 ns: 20 ms.
+// An exchange takes 3 to 6 us, so a word that is not there then is that of a
+// workgroup which does not run.
+constexpr unsigned long long kSolveWait = 2000000;
+
+// Solves that run as launches after a given-up one before the next is tried as one
+// launch again: where the CUs stay taken (another process, a masked stream), a try
+// costs its wait, and twice as many launches pass before each further one.
+constexpr int kFirstPause = 16, kLongestPause = 1024;
 
 // The wait that the environment variable DCO_DENSIFY_WAIT asks for, which lets a test
 // force a solve to be given up: a whole number below kSolveWait; else kSolveWait.
@@ -34,6 +42,8 @@ struct dco_densify {
     int solve_k = 0;            // pixels per thread of the one-launch solve (0: not possible)
     // longest wait of its workgroups for each other, in 10 ns
     unsigned long long ticks = kSolveWait;
+    int given_up = 0;           // one-launch solves given up so far
+    int pause = 0, rest = 0;    // solves as launches after the last of them, and left of these
 };
 
 // One-launch solves of a process take turns on a device: two of them at once
@@ -184,7 +194,9 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
     DCO_TRY(need(D, "D"));
     const dco_densify_params& p = h->p;
     h->launches = 0;
-    if (h->solve_k) {
+    if (h->rest > 0) {
+        --h->rest;
+    } else if (h->solve_k) {
         // whole groups of iters_per_launch iterations, as the launches below run
         const long long groups = ((long long)p.max_iters + p.iters_per_launch - 1) /
                                  p.iters_per_launch;
@@ -203,12 +215,15 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
                                      hipMemcpyDeviceToHost, h->stream));
         DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
         if (h->flags_host[2] == 0) {
+            h->pause = 0;
             if (aside) DCO_HIP_CHECK(launch_densify_out(h->b, 0, h->W, h->H, D, h->stream));
             return DCO_OK;
         }
         // given up: its workgroups could not all run (another process held the
         // CUs); the launches below need nothing to run at the same time, and give
         // the same bits
+        ++h->given_up;
+        h->rest = h->pause = std::min(std::max(kFirstPause, 2 * h->pause), kLongestPause);
     }
     DCO_HIP_CHECK(launch_densify_setup(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
                                        p.lambda_d, p.lambda_s, p.lambda_s2, h->stream));
@@ -255,5 +270,12 @@ extern "C" dco_status dco_densify_launches(dco_densify* h, int* launches) {
     DCO_TRY(need(h, "handle"));
     DCO_TRY(need(launches, "launches"));
     *launches = h->launches;
+    return DCO_OK;
+}
+
+extern "C" dco_status dco_densify_given_up(dco_densify* h, int* solves) {
+    DCO_TRY(need(h, "handle"));
+    DCO_TRY(need(solves, "solves"));
+    *solves = h->given_up;
     return DCO_OK;
 }

@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kDzThreads) void k_dz_out(const double* __restrict_
 // turn.  Every workgroup adds all partial sums itself in the same order, so
 // all hold the same alpha and beta bits.
 //
-// A wait ends after `ticks` (0.2 s) without the awaited word (workgroups that do
+// A wait ends after `ticks` (20 ms) without the awaited word (workgroups that do
 // not run: another process holds the CUs): the workgroup raises an abort flag
 // that every wait looks at, all leave, and the host repeats the solve as a
 // sequence of launches on the same tiles (k_dz_tile_*), which form every value and

@@ -57,6 +57,12 @@ class Densifier:
         check(lib().dco_densify_launches(self._h, C.byref(n)))
         return n.value
 
+    def given_up(self):
+        """One-launch solves of this handle that were given up."""
+        n = C.c_int()
+        check(lib().dco_densify_given_up(self._h, C.byref(n)))
+        return n.value
+
     def close(self):
         if self._h:
             lib().dco_densify_destroy(self._h)

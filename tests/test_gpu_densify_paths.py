@@ -85,3 +85,18 @@ def test_wait_that_is_no_number_is_ignored(monkeypatch, wait):
     W, H = 200, 120
     monkeypatch.setenv("DCO_DENSIFY_WAIT", wait)
     assert solve(W, H, inputs(W, H, 7))[2] == 0
+
+
+def test_given_up_solves_are_remembered(monkeypatch):
+    """After one, 16 solves go as launches without a try; after the next, 32."""
+    from paper_2203_02300_amd import Densifier
+    W, H = 200, 120
+    monkeypatch.setenv("DCO_DENSIFY_WAIT", "0")
+    Ds, Dpre, B, Mf, MI = (dev(v) for v in inputs(W, H, 7))
+    with Densifier(W, H) as z:
+        tries = []
+        for _ in range(1 + 16 + 1 + 32 + 1):
+            z.run(Ds, B, Mf, MI, Dpre=Dpre)
+            assert z.launches() > 0
+            tries.append(z.given_up())
+    assert tries == [1] * 17 + [2] * 33 + [3]
