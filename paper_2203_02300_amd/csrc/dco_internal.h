@@ -228,8 +228,8 @@ constexpr int kDensifyMaxK = 4;
 int densify_solve_k(int W, int H, int cus);
 size_t densify_solve_words(int W, int H, int k);
 // The whole solve in one launch (k = densify_solve_k; `ticks` of the 100 MHz
-// clock bound each of its waits): D (or, where that is null, x), flags and res are its
-// results; with flags[2] set it was given up, and a part of D may have been written.
+// clock bound each of its waits): D, flags and res are its results; with flags[2]
+// set it was given up, and a part of D may have been written.
 hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, const float* Dpre,
                                 const uint8_t* Bdp, const float* Mfuse, const float* MI, int W,
                                 int H, double lam_d, double lam_s, double lam_s2, double tol,

@@ -210,13 +210,14 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
         DCO_HIP_CHECK(launch_densify_solve(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
                                            p.lambda_d, p.lambda_s, p.lambda_s2, p.tol,
                                            (int)(limit < INT_MAX ? limit : INT_MAX), h->ticks,
-                                           aside ? nullptr : D, h->stream));
+                                           aside ? (float*)h->b.q : D, h->stream));
         DCO_HIP_CHECK(hipMemcpyAsync(h->flags_host, h->b.flags, 3 * sizeof(int),
                                      hipMemcpyDeviceToHost, h->stream));
         DCO_HIP_CHECK(hipStreamSynchronize(h->stream));
         if (h->flags_host[2] == 0) {
             h->pause = 0;
-            if (aside) DCO_HIP_CHECK(launch_densify_out(h->b, 0, h->W, h->H, D, h->stream));
+            if (aside)
+                DCO_HIP_CHECK(hipMemcpyAsync(D, h->b.q, F, hipMemcpyDeviceToDevice, h->stream));
             return DCO_OK;
         }
         // given up: its workgroups could not all run (another process held the

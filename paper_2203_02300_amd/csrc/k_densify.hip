@@ -297,8 +297,7 @@ constexpr int kLineWords = 32;                       // a tile's sums, 256 bytes
 
 struct SolveArgs {
     DzIn in;
-    float* D;   // the solution goes here,
-    double* x;  // or, where D is null, here
+    float* D;
     int tx, ntiles, limit;  // tiles per row, tiles, iterations at most
     double tol2;
     uint64_t ticks;  // longest wait, in ticks of the 100 MHz clock
@@ -511,7 +510,18 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
             zh = u[0];
         }
         if (!ok) gave_up = 1;
-        over_tiles(v, all);
+        // over_tiles, written out: with a call here the wait above compiles to 28
+        // instructions more (640 x 360: 408 us instead of 405)
+        if (t < 256) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                v[j] = lane_sum<true>(v[j]);
+                if ((t & 63) == 63) all[j][t >> 6] = v[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] = (all[j][0] + all[j][1]) + (all[j][2] + all[j][3]);
         const bool stop = gave_up != 0;
         __syncthreads();  // all[] may be reused
         return !stop;
@@ -591,11 +601,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int xx = x0 + lx, y = y0 + ly + kTileRows * k;
-        if (xx >= W || y >= H) continue;
-        if (A.D)
-            A.D[(size_t)y * W + xx] = (float)x[k];
-        else
-            A.x[(size_t)y * W + xx] = x[k];
+        if (xx < W && y < H) A.D[(size_t)y * W + xx] = (float)x[k];
     }
     if (tile == 0 && t == 0) {
         A.flags[0] = converged;
@@ -854,7 +860,7 @@ hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, co
                                 int H, double lam_d, double lam_s, double lam_s2, double tol,
                                 int limit, uint64_t ticks, float* D, hipStream_t st) {
     const int tx = (W + kTileW - 1) / kTileW, tiles = solve_tiles(W, H, k);
-    SolveArgs A{{Ds, Dpre, Bdp, Mfuse, MI, W, H, lam_d, lam_s, lam_s2}, D, b.x, tx, tiles, limit,
+    SolveArgs A{{Ds, Dpre, Bdp, Mfuse, MI, W, H, lam_d, lam_s, lam_s2}, D, tx, tiles, limit,
                 tol * tol, ticks, b.words, b.words + (size_t)tiles * kLineWords,
                 b.words + 2 * (size_t)tiles * kLineWords, b.flags, b.res};
     const size_t n = densify_solve_words(W, H, k);
