@@ -85,7 +85,8 @@ struct DzIn {
 struct DzPixel {
     double cr, cd, cl, cu, diag, b, id;  // id = 1 / diag (0 where diag is 0)
 };
-__device__ inline DzPixel dz_pixel(const DzIn& A, int x, int y) {
+template <typename In>
+__device__ inline DzPixel dz_pixel(const In& A, int x, int y) {
     const int W = A.W, i = y * W + x;
     const double s = (double)A.Mfuse[i] * (double)A.MI[i];
     const int b = A.Bdp[i] != 0;
@@ -296,10 +297,12 @@ constexpr int kLineWords = 32;                       // a tile's sums, 256 bytes
                                                      // workgroup polls them
 
 struct SolveArgs {
-    DzIn in;
+    const float *Ds, *Dpre;
+    const uint8_t* Bdp;
+    const float *Mfuse, *MI;
     float* D;
-    int tx, ntiles, limit;  // tiles per row, tiles, iterations at most
-    double tol2;
+    int W, H, tx, ntiles, limit;  // tiles per row, tiles, iterations at most
+    double lam_d, lam_s, lam_s2, tol2;
     uint64_t ticks;  // longest wait, in ticks of the 100 MHz clock
     uint64_t* pq;    // ntiles lines: p.q (two words)
     uint64_t* rzr;   // ntiles lines: r.z, r.r (two words each)
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
     __shared__ int gave_up;
     const int t = threadIdx.x, lx = t & 31, ly = t >> 5;
     const int tile = blockIdx.x, ty0 = tile / A.tx, tx0 = tile - ty0 * A.tx;
-    const int x0 = tx0 * kTileW, y0 = ty0 * TH, W = A.in.W, H = A.in.H;
+    const int x0 = tx0 * kTileW, y0 = ty0 * TH, W = A.W, H = A.H;
     if (t == 0) gave_up = 0;
 
     // own pixels: rows ly + 32 k of the tile; outside the image all is zero
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
         const int xx = x0 + lx, y = y0 + ly + kTileRows * k;
         x[k] = r[k] = p[k] = id[k] = dg[k] = cr[k] = cd[k] = cl[k] = cu[k] = 0.0;
         if (xx >= W || y >= H) continue;
-        const DzPixel c = dz_pixel(A.in, xx, y);
+        const DzPixel c = dz_pixel(A, xx, y);
         cr[k] = c.cr;
         cd[k] = c.cd;
         cl[k] = c.cl;
@@ -511,7 +514,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_dz_solve(SolveArgs A) {
         }
         if (!ok) gave_up = 1;
         // over_tiles, written out: with a call here the wait above compiles to 28
-        // instructions more (640 x 360: 408 us instead of 405)
+        // instructions more
         if (t < 256) {
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -860,7 +863,7 @@ hipError_t launch_densify_solve(const DensifyBufs& b, int k, const float* Ds, co
                                 int H, double lam_d, double lam_s, double lam_s2, double tol,
                                 int limit, uint64_t ticks, float* D, hipStream_t st) {
     const int tx = (W + kTileW - 1) / kTileW, tiles = solve_tiles(W, H, k);
-    SolveArgs A{{Ds, Dpre, Bdp, Mfuse, MI, W, H, lam_d, lam_s, lam_s2}, D, tx, tiles, limit,
+    SolveArgs A{Ds, Dpre, Bdp, Mfuse, MI, D, W, H, tx, tiles, limit, lam_d, lam_s, lam_s2,
                 tol * tol, ticks, b.words, b.words + (size_t)tiles * kLineWords,
                 b.words + 2 * (size_t)tiles * kLineWords, b.flags, b.res};
     const size_t n = densify_solve_words(W, H, k);
