@@ -255,7 +255,9 @@ void dco_densify_destroy(dco_densify* h);
  * Returns when the solve has converged or used max_iters iterations, rounded up to
  * whole groups of iters_per_launch (grids of up to about a million pixels: one
  * launch; larger ones: the host reads the convergence flag after every launch
- * of a group).  One-launch solves of a process take turns on a device. */
+ * of a group).  One-launch solves of a process take turns on a device; one that
+ * has waited 2 ms for its turn goes as launches of a group instead, with the same
+ * bits. */
 dco_status dco_densify_run(dco_densify* h, const float* Ds, const float* Dpre, const uint8_t* Bdp,
                            const float* Mfuse, const float* MI, float* D);
 
@@ -263,7 +265,7 @@ dco_status dco_densify_run(dco_densify* h, const float* Ds, const float* Dpre, c
  * either may be NULL).  Synchronises the stream. */
 dco_status dco_densify_stats(dco_densify* h, int* iters, double* rel_residual);
 /* Launches of a group of iterations in the last solve, 0 if it ran as one launch
- * (diagnostics).  The two give the same bits. */
+ * (diagnostics). */
 dco_status dco_densify_launches(dco_densify* h, int* launches);
 /* One-launch solves of this handle that were given up after 20 ms because their
  * workgroups could not all run (diagnostics).  Each is repeated as launches, and the

@@ -1,6 +1,7 @@
 // densify.cpp -- host side of the depth densification (Sec. 6, Eq. 13-20):
 // buffers, the captured iteration graph and the convergence loop.
 #include <algorithm>
+#include <chrono>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -47,8 +48,11 @@ struct dco_densify {
 };
 
 // One-launch solves of a process take turns on a device: two of them at once
-// could each hold CUs that the other's workgroups wait for.
-static std::mutex g_solve_turn[64];
+// could each hold CUs that the other's workgroups wait for.  A turn lasts until the
+// solve has ended, with all that its stream holds before it, so a solve that has
+// waited longer than solves take (0.3 to 1 ms) goes as launches instead.
+static std::timed_mutex g_solve_turn[64];
+constexpr std::chrono::milliseconds kTurnWait{2};
 
 extern "C" dco_status dco_densify_default_params(dco_densify_params* out) {
     if (!out) {
@@ -194,9 +198,12 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
     DCO_TRY(need(D, "D"));
     const dco_densify_params& p = h->p;
     h->launches = 0;
-    if (h->rest > 0) {
+    std::unique_lock<std::timed_mutex> turn;
+    if (h->rest > 0)
         --h->rest;
-    } else if (h->solve_k) {
+    else if (h->solve_k)
+        turn = std::unique_lock<std::timed_mutex>(g_solve_turn[h->device], kTurnWait);
+    if (turn.owns_lock()) {
         // whole groups of iters_per_launch iterations, as the launches below run
         const long long groups = ((long long)p.max_iters + p.iters_per_launch - 1) /
                                  p.iters_per_launch;
@@ -206,7 +213,6 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
         const size_t P = (size_t)h->W * h->H, F = P * sizeof(float);
         const bool aside = overlap(D, F, Ds, F) || overlap(D, F, Dpre, F) ||
                            overlap(D, F, Bdp, P) || overlap(D, F, Mfuse, F) || overlap(D, F, MI, F);
-        std::lock_guard<std::mutex> turn(g_solve_turn[h->device]);
         DCO_HIP_CHECK(launch_densify_solve(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
                                            p.lambda_d, p.lambda_s, p.lambda_s2, p.tol,
                                            (int)(limit < INT_MAX ? limit : INT_MAX), h->ticks,
@@ -225,6 +231,7 @@ extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const flo
         // the same bits
         ++h->given_up;
         h->rest = h->pause = std::min(std::max(kFirstPause, 2 * h->pause), kLongestPause);
+        turn.unlock();
     }
     DCO_HIP_CHECK(launch_densify_setup(h->b, h->solve_k, Ds, Dpre, Bdp, Mfuse, MI, h->W, h->H,
                                        p.lambda_d, p.lambda_s, p.lambda_s2, h->stream));

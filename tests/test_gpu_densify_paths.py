@@ -100,3 +100,48 @@ def test_given_up_solves_are_remembered(monkeypatch):
             assert z.launches() > 0
             tries.append(z.given_up())
     assert tries == [1] * 17 + [2] * 33 + [3]
+
+
+def test_a_long_queue_holds_up_its_own_solve_only():
+    """A solve behind half a second of work on its stream; one on an idle stream,
+    started later, ends first."""
+    import threading
+    import time
+    import torch
+    from paper_2203_02300_amd import Densifier
+    W, H = 200, 120
+    a = [dev(v) for v in inputs(W, H, 9)]
+    slow, idle = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def sleep_ms(cycles):  # one thread of the GPU counts
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        torch.cuda._sleep(cycles)
+        e[1].record()
+        torch.cuda.synchronize()
+        return e[0].elapsed_time(e[1])
+
+    sleep_ms(1000)
+    cycles = int(1_000_000 * 500 / sleep_ms(1_000_000))
+    ended, queued = {}, threading.Event()
+
+    def run(stream, name, before):
+        with torch.cuda.stream(stream), Densifier(W, H) as z:
+            z.run(a[0], a[2], a[3], a[4], Dpre=a[1])
+            if before:
+                torch.cuda._sleep(before)
+                queued.set()
+            else:
+                queued.wait()
+                time.sleep(0.05)  # the other is in its solve
+            t = time.perf_counter()
+            z.run(a[0], a[2], a[3], a[4], Dpre=a[1])
+            ended[name] = time.perf_counter(), time.perf_counter() - t
+
+    ts = [threading.Thread(target=run, args=v) for v in ((slow, "slow", cycles), (idle, "idle", 0))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert ended["slow"][1] > 0.3
+    assert ended["idle"][0] < ended["slow"][0] and ended["idle"][1] < 0.1, ended
