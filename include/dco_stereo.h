@@ -140,7 +140,8 @@ dco_status dco_aggregate(dco_stereo* h, const float* cost, const uint8_t* arms_r
  *   valid(x, y) = x - dL >= 0 and |dL(x, y) - dR(x - dL, y)| <= lr_max_diff
  *   disp = dL + delta where valid, else 0
  * aggL, aggR: D x H x W float; disp: H x W float (out); valid: H x W uint8
- * (out); dL, dR: H x W int16 (out, optional: NULL to skip). */
+ * (out; both may lie on a volume); dL, dR: H x W int16 (out, optional: NULL to
+ * skip; not on a volume). */
 dco_status dco_wta_lrcheck(dco_stereo* h, const float* aggL, const float* aggR, float* disp,
                            uint8_t* valid, int16_t* dL, int16_t* dR);
 

@@ -402,8 +402,20 @@ extern "C" dco_status dco_wta_lrcheck(dco_stereo* h, const float* aggL, const fl
     DCO_TRY(need(valid, "valid"));
     int16_t* oL = dL ? dL : h->s.dint[0];
     int16_t* oR = dR ? dR : h->s.dint[1];
+    // a row's outputs are written while other rows of the volumes are read: outputs
+    // that lie on a volume go to the scratch of the packed pixels (16 bytes a pixel,
+    // used within a match only) and are copied
+    const size_t P = (size_t)h->W * h->H, F = P * sizeof(float);
+    const auto on_volume = [&](const void* p, size_t n) {
+        return overlap(p, n, aggL, F * h->D) || overlap(p, n, aggR, F * h->D);
+    };
+    const bool asideD = on_volume(disp, F), asideV = on_volume(valid, P);
+    float* d = asideD ? reinterpret_cast<float*>(h->s.pix[0]) : disp;
+    uint8_t* v = asideV ? reinterpret_cast<uint8_t*>(h->s.pix[1]) : valid;
     DCO_HIP_CHECK(launch_wta_lr(aggL, aggR, false, h->W, h->W, h->H, h->D, h->p.subpixel,
-                                h->p.lr_max_diff, oL, oR, disp, valid, HalfOut{}, h->stream));
+                                h->p.lr_max_diff, oL, oR, d, v, HalfOut{}, h->stream));
+    if (asideD) DCO_HIP_CHECK(hipMemcpyAsync(disp, d, F, hipMemcpyDeviceToDevice, h->stream));
+    if (asideV) DCO_HIP_CHECK(hipMemcpyAsync(valid, v, P, hipMemcpyDeviceToDevice, h->stream));
     return DCO_OK;
 }
 

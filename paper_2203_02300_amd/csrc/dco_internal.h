@@ -175,6 +175,12 @@ inline void pinned_free(void* p) {
     alloc_count(-1);
 }
 
+// Whether na bytes at a and nb bytes at b share memory (not where one is NULL).
+inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return a && b && x < y + nb && y < x + na;
+}
+
 // ---- host helpers shared by api.cpp and batch.cpp ----
 dco_status need(const void* ptr, const char* what);
 dco_status need_align(const void* ptr, size_t a, const char* what);

@@ -182,11 +182,6 @@ extern "C" dco_status dco_densify_create(dco_densify** out, int W, int H,
     return DCO_OK;
 }
 
-static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
-    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
-    return a && b && x < y + nb && y < x + na;
-}
-
 extern "C" dco_status dco_densify_run(dco_densify* h, const float* Ds, const float* Dpre,
                                       const uint8_t* Bdp, const float* Mfuse, const float* MI,
                                       float* D) {
