@@ -341,9 +341,11 @@ hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* 
                        int16_t* dv_out, const HalfOut& half, hipStream_t st) {
     const VoteOut o{agg, disp, valid_out, dv_out, half, pitch, W, H, D, subpixel, (int)paired};
     const dim3 grid((W + kVTW - 1) / kVTW, (H + kVTH - 1) / kVTH);
-    // the last pass makes the outputs, unless it is also the first: other tiles
-    // then still read the mask that valid_out may be
-    const bool fused = iters > 1;
+    // the last pass makes the outputs, unless it is also the first (other tiles then
+    // still read the mask that valid_out may be) or an output lies on the arms
+    const size_t P = (size_t)W * H;
+    const bool fused = iters > 1 && !overlap(disp, 4 * P, arms, 4 * P) &&
+                       !overlap(valid_out, P, arms, 4 * P) && !overlap(dv_out, 2 * P, arms, 4 * P);
     const int16_t* src = dL;
     const uint8_t* mask = valid;
     int16_t* bufs[2] = {buf0, buf1};
