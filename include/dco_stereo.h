@@ -422,7 +422,8 @@ dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_params* param
 /* Testing hooks for the error paths.  dco_debug_fail_alloc(k) makes the
  * k-th device or pinned allocation made by the library from now on fail
  * with DCO_ERR_OOM (k <= 0 disarms; DCO_FAIL_ALLOC=k in the environment arms
- * it when the library loads).  dco_debug_live_allocations() is the number
+ * it when the library loads); the call fails with it too, unless it has a
+ * smaller layout to try (volumes without padded rows).  dco_debug_live_allocations() is the number
  * of the library's device and pinned allocations not yet freed, so a test
  * can check that a failed create frees exactly what it allocated.
  * Process-wide; not meant for concurrent use with other calls. */

@@ -151,15 +151,19 @@ void build_tables(const dco_params& p, std::vector<float>& tabA, std::vector<flo
     build_tables_into(p, tabA.data(), tabC.data(), alpha.data(), beta.data());
 }
 
+static void free_scratch(dco_scratch& s) {
+    for (int v = 0; v < 2; ++v) {
+        void* ptrs[] = {s.pix[v],  s.arms[v], s.rec[v].b, s.rec[v].c,
+                        s.agg[v], s.dint[v], s.vote[v],  s.half[v]};
+        for (void* p : ptrs) dev_free(p);
+    }
+    s = dco_scratch{};
+}
+
 static void free_handle_memory(dco_stereo* h) {
+    free_scratch(h->s);
     void* ptrs[] = {h->tabA,         h->tabC,         h->alpha,        h->beta,
-                    h->alpha_soft,   h->s.pix[0],     h->s.pix[1],     h->s.arms[0],
-                    h->s.arms[1],    h->s.rec[0].b,   h->s.rec[0].c,
-                    h->s.rec[1].b,   h->s.rec[1].c,
-                    h->s.agg[0],     h->s.agg[1],     h->s.dint[0],
-                    h->s.dint[1],    h->s.vote[0],    h->s.vote[1],
-                    h->s.half[0],    h->s.half[1],
-                    h->soft.pix[0],  h->soft.pix[1],
+                    h->alpha_soft,   h->soft.pix[0],  h->soft.pix[1],
                     h->soft.arms,    h->soft.vrec,    h->soft.n2,
                     h->soft.tab,     h->soft.vol[0],  h->soft.vol[1],  h->soft.vol[2],
                     h->soft.partAC,  h->soft.partT};
@@ -178,10 +182,11 @@ dco_status alloc_records(AggRecords* r, int W, int H) {
     return DCO_OK;
 }
 
-static dco_status alloc_scratch(dco_stereo* h) {
+static dco_status alloc_scratch(dco_stereo* h, int pitch) {
     const size_t P = (size_t)h->W * h->H;
-    const size_t V = (size_t)agg_pitch(h->W, h->p.agg_iters) * h->H * h->D;
+    const size_t V = (size_t)pitch * h->H * h->D;
     dco_scratch& s = h->s;
+    s.pitch = pitch;
     for (int v = 0; v < 2; ++v) {
         DCO_TRY(dev_alloc(&s.arms[v], P));
         DCO_TRY(alloc_records(&s.rec[v], h->W, h->H));
@@ -251,7 +256,13 @@ extern "C" dco_status dco_stereo_create(dco_stereo** out, int W, int H, int D,
             return fail(DCO_ERR_HIP);
         }
     }
-    if ((st = alloc_scratch(h)) != DCO_OK) return fail(st);
+    const int pitch = agg_pitch(W, prm.agg_iters);
+    st = alloc_scratch(h, pitch);
+    if (st == DCO_ERR_OOM && pitch != W) {  // the padding of the rows may be what is too much
+        free_scratch(h->s);
+        st = alloc_scratch(h, W);
+    }
+    if (st != DCO_OK) return fail(st);
     *out = h;
     return DCO_OK;
 }
@@ -433,7 +444,7 @@ static dco_status match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
     }
     dco_scratch& s = h->s;
     const dco_params& p = h->p;
-    const int pitch = agg_pitch(h->W, p.agg_iters);
+    const int pitch = s.pitch;
     const uint8_t* img[2] = {rgbL, rgbR};
     DCO_TRY(prof_mark(h));
     DCO_HIP_CHECK(launch_front2(img[0], img[1], h->W, h->H, p.census_w, p.census_h, p.arm_L1,
@@ -536,7 +547,8 @@ extern "C" dco_status dco_stereo_agg_slices(dco_stereo* h, int view, int d0, int
     }
     const size_t P = (size_t)h->W * h->H;
     if (h->s.agg_paired)
-        DCO_HIP_CHECK(launch_unpair(h->s.agg[view], agg_pitch(h->W, 2), h->W, h->H, h->D, d0, n, out, h->stream));
+        DCO_HIP_CHECK(launch_unpair(h->s.agg[view], h->s.pitch, h->W, h->H, h->D, d0, n, out,
+                                    h->stream));
     else
         DCO_HIP_CHECK(hipMemcpyAsync(out, h->s.agg[view] + (size_t)d0 * P,
                                      (size_t)n * P * sizeof(float), hipMemcpyDeviceToDevice,

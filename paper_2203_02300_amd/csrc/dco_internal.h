@@ -21,7 +21,8 @@ struct dco_scratch {
     AggRecords rec[2];
     uint4* pix[2];      // packed pixels of both views: census lo, census hi, RGB, 8 L_min
                         // (two stages: in planes, PixPlanes; pix_entries 16-byte words)
-    float* agg[2];      // aggregated volumes of both views (D x H x W)
+    float* agg[2];      // aggregated volumes of both views (D x H x pitch)
+    int pitch;          // columns of a row of them
     bool agg_paired;    // ... written in the paired layout (two-stage aggregation)
     int16_t* dint[2];
     int16_t* vote[2];   // ping-pong maps of the Eq. 4 vote passes
@@ -31,7 +32,8 @@ struct dco_scratch {
 // Columns of a row of a handle's own aggregated volumes with two stages: rows that
 // end within a quad cost the aggregation a second kind of store, and quads that
 // start anywhere cost the loads (one call at 1279 x 720, D = 128 760 us, 719 so;
-// 399 x 300, D = 40 87.8 and 83.9; multiples of four within 1 %).
+// 399 x 300, D = 40 87.8 and 83.9; multiples of four within 1 %).  Where the volumes
+// do not fit the card so, a handle's rows have W columns (dco_scratch::pitch).
 constexpr int agg_pitch(int W, int iters) { return iters == 2 ? (W + 15) & ~15 : W; }
 
 // Columns of a row of the soft path's volumes: whole 64-byte pieces, so that no
