@@ -575,13 +575,10 @@ static void free_soft(SoftScratch& f) {
     f = SoftScratch{};
 }
 
-static dco_status soft_reserve(dco_stereo* h, int B) {
+static dco_status soft_alloc(dco_stereo* h, int B, int pitch) {
     SoftScratch& f = h->soft;
-    if (f.cap >= B) return DCO_OK;
-    (void)hipStreamSynchronize(h->stream);
-    free_soft(f);
     const size_t P = (size_t)h->W * h->H;
-    const size_t V = (size_t)soft_pitch(h->W) * h->H * h->D * B;
+    const size_t V = (size_t)pitch * h->H * h->D * B;
     DCO_TRY(dev_alloc(&f.pix[0], P * B));
     DCO_TRY(dev_alloc(&f.pix[1], P * B));
     DCO_TRY(dev_alloc(&f.arms, P * B));
@@ -591,8 +588,21 @@ static dco_status soft_reserve(dco_stereo* h, int B) {
     for (int k = 0; k < 3; ++k) DCO_TRY(dev_alloc(&f.vol[k], V));
     DCO_TRY(dev_alloc(&f.partAC, 2 * (size_t)B * h->D * h->H));
     DCO_TRY(dev_alloc(&f.partT, (size_t)B * h->D * h->H + 3 * 256));  // + the block totals
+    f.pitch = pitch;
     f.cap = B;
     return DCO_OK;
+}
+
+static dco_status soft_reserve(dco_stereo* h, int B) {
+    SoftScratch& f = h->soft;
+    if (f.cap >= B) return DCO_OK;
+    (void)hipStreamSynchronize(h->stream);
+    free_soft(f);
+    const int pitch = soft_pitch(h->W);
+    const dco_status st = soft_alloc(h, B, pitch);
+    if (st != DCO_ERR_OOM || pitch == h->W) return st;
+    free_soft(f);  // the padding of the rows may be what is too much
+    return soft_alloc(h, B, h->W);
 }
 
 // Arms and packed pixels of every pair, the Eq. 1 tables for theta,
@@ -608,7 +618,8 @@ static dco_status soft_front(dco_stereo* h, int B, const uint8_t* L, const uint8
                                       h->stream));
     DCO_HIP_CHECK(soft_prepare(theta, f.tab, f.arms, B, h->W, h->H, h->D, f.vrec, f.n2,
                                h->stream));
-    *sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
+    *sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab,
+                      f.pitch};
     DCO_HIP_CHECK(
         soft_aggregate(*sb, B, h->W, h->H, h->D, f.vol[0], f.vol[1], f.vol[2], theta, dhat, lse,
                        h->stream));
@@ -692,7 +703,8 @@ extern "C" dco_status dco_soft_backward_reuse(dco_stereo* h, int B, const uint8_
     // and pixels as they are, so any number of backward calls can reuse them
     if (f.held && f.held_B == B && f.held_L == L && f.held_R == R && f.held_theta == theta &&
         f.held_stream == h->stream)
-        sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab};
+        sb = SoftBuffers{f.arms, f.vrec, f.n2, f.pix[0], f.pix[1], h->alpha, f.tab,
+                      f.pitch};
     else
         DCO_TRY(soft_front(h, B, L, R, theta, nullptr, nullptr, &sb));
     DCO_HIP_CHECK(soft_backward(sb, B, h->W, h->H, h->D, f.vol[0], theta, dhat, lse, grad_dhat,

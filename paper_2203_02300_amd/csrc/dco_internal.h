@@ -40,13 +40,15 @@ constexpr int agg_pitch(int W, int iters) { return iters == 2 ? (W + 15) & ~15 :
 // store ends within one and every row's 16-byte words are aligned.  A training
 // step on 8 pairs of 639 x 480, D = 63 took 2670 us with rows of W columns, 2154
 // so; 604 x 400, D = 40 1735 and 1610; 600 x 400, D = 48 1659, 1661 with rows of
-// whole 32 bytes, 1555 so, and 1557 with whole 128.
-__host__ __device__ constexpr int soft_pitch(int W) { return (W + 15) & ~15; }
+// whole 32 bytes, 1555 so, and 1557 with whole 128.  Where the volumes do not fit the
+// card so, their rows have W columns (SoftScratch::pitch).
+constexpr int soft_pitch(int W) { return (W + 15) & ~15; }
 
 // Soft-path scratch of a handle: per-pair maps of B pairs and three
-// B x D x H x soft_pitch(W) float volumes (grown on demand).
+// B x D x H x pitch float volumes (grown on demand).
 struct SoftScratch {
     int cap;               // pairs the buffers hold
+    int pitch;             // columns of a row of the volumes
     uint4* pix[2];         // packed pixels of left / right views (census lo, census
                            // hi, RGB, 8 L_min)
     uint32_t* arms;        // arms of the left views
@@ -78,6 +80,7 @@ struct SoftBuffers {
     const uint4* pixR;
     const float* alpha;
     const float* tab;
+    int pitch;
 };
 
 struct dco_stereo {

@@ -24,7 +24,7 @@
 // with fixed-order two-level reductions.  The only atomics are LDS adds that one
 // thread makes to its own column in program order.
 //
-// Layout: volumes are B x D x H x soft_pitch(W) float in handle scratch; arms and the
+// Layout: volumes are B x D x H x pitch float in handle scratch; arms and the
 // packed pixels (census, RGB, L_min) are per pair B x H x W.  The cost and row
 // passes run one wavefront per image row and 16 disparities (k_soft_mrow,
 // k_soft_wide); the column pass runs one thread per column, streaming down the
@@ -41,8 +41,8 @@ struct SoftGeom {
     const uint2* vrec;     // B x H x W column records (col_record, 1 / stage-1 region count)
     const float* n2;       // B x H x W stage-2 region counts
     int B, W, H, D;
-    __host__ __device__ int pitch() const { return soft_pitch(W); }  // of a volume's row
-    __host__ __device__ size_t plane() const { return (size_t)pitch() * H; }
+    int pitch;             // columns of a volume's row
+    __host__ __device__ size_t plane() const { return (size_t)pitch * H; }
 };
 
 __device__ inline int arm(uint32_t a, int k) { return (a >> (8 * k)) & 0xff; }
@@ -359,15 +359,20 @@ __device__ inline RowTask row_task(int block, int rows, int ng, int w, int nw) {
     return RowTask{min(row, rows - 1), w % ng, row < rows};
 }
 
+// How a volume's rows are stored.  Rows are whole 64-byte pieces (soft_pitch) and
+// their columns past the image's hold nothing; kPast: past the caches, which a large
+// volume only passes through (soft_stream).  kCut: rows of W columns, for volumes that
+// do not fit the card with more: the quad that a row's end cuts is stored as words.
+enum Rows { kWhole, kPast, kCut };
+
 // Stores the stage's 16 x 64 outputs: disparities d0 .. d0 + 15, columns x0 ..
-// x0 + 63, those inside the volume only; `out` is row y of disparity 0, P a
-// plane.  256 contiguous bytes per disparity, and four disparities per store.
-// Rows are whole 64-byte pieces (soft_pitch): the columns past the image's hold
-// nothing.  kStream: past the caches, which a large volume only passes through;
-// see soft_stream.
-template <bool kStream>
+// x0 + 63, those inside the volume (rows of W columns) only; `out` is row y of
+// disparity 0, P a plane.  256 contiguous bytes per disparity, and four disparities
+// per store.
+template <Rows kRows>
 __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, size_t P, int d0,
                                 int D, int x0, int W) {
+    typedef float v4fu __attribute__((ext_vector_type(4), aligned(4), may_alias));
     const int lane = threadIdx.x & 63;
     const int c = 4 * (lane & 15), x = x0 + c;
     asm volatile("" : "+s"(P));  // the row addresses are made here, not kept over the row
@@ -379,15 +384,22 @@ __device__ inline void put_rows(const uint32_t* stage, float* __restrict__ out, 
     for (int j = 0; j < 4; ++j) {
         const int d = d0 + 4 * j + (lane >> 4);
         if (x < 0 || x >= W || d >= D) continue;
-        v4f* p = reinterpret_cast<v4f*>(out + d * P + x);
-        if (kStream)
-            __builtin_nontemporal_store(o[j], p);
-        else
-            *p = o[j];
+        float* const q = out + d * P + x;
+        if constexpr (kRows == kPast) {
+            __builtin_nontemporal_store(o[j], reinterpret_cast<v4f*>(q));
+        } else if constexpr (kRows == kWhole) {
+            *reinterpret_cast<v4f*>(q) = o[j];
+        } else if (x + 4 <= W) {
+            *reinterpret_cast<v4fu*>(q) = o[j];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (x + k < W) q[k] = o[j][k];
+        }
     }
 }
 
-template <bool kShare, bool kStream>
+template <bool kShare, Rows kRows>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, SoftImg im,
                                                                 float* __restrict__ out,
                                                                 int seg_its) {
@@ -409,7 +421,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     const uint4* pl = im.pixL + pix;
     const uint4* pr = im.pixR + pix;
     const uint32_t* ar = g.arms + pix;
-    const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch();
+    const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch;
     uint32_t* stage = stages[w];
     int par = 0;
     for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
@@ -513,7 +525,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
                         v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
                 });
                 __builtin_amdgcn_wave_barrier();
-                put_rows<kStream>(stage, out + vol, Q, d0, D, X - 32, g.pitch());
+                put_rows<kRows>(stage, out + vol, Q, d0, D, X - 32, g.pitch);
                 __builtin_amdgcn_wave_barrier();
             }
 #pragma unroll
@@ -572,7 +584,7 @@ __device__ inline v4i band_bytes_t(const uint32_t* lp, const uint32_t* r, int e)
 
 enum WideKind { kMean, kSeed, kDot };
 
-template <WideKind kKind, bool kShare, bool kStream>
+template <WideKind kKind, bool kShare, Rows kRows>
 __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     SoftGeom g, SoftImg im, const float* __restrict__ in, const float* __restrict__ theta,
     float* __restrict__ dhat, float* __restrict__ lse, const float* __restrict__ gdhat,
@@ -596,7 +608,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     const int row = rt.row, y = row % g.H, b = row / g.H;
     const int it0 = blockIdx.y * seg_its, it1 = min(it0 + seg_its, (W + 95) >> 6);
     const size_t P = (size_t)W * g.H, pix = (size_t)b * P + (size_t)y * W;
-    const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch();
+    const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch;
     const float T = theta[2], invT = 1.0f / T;
     uint32_t* stage = stages[w];
     int par = 0;
@@ -791,7 +803,7 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
                     }
                     __builtin_amdgcn_wave_barrier();
                 }
-                put_rows<kStream>(stage, out + vol, Q, d0, D, X - 32, g.pitch());
+                put_rows<kRows>(stage, out + vol, Q, d0, D, X - 32, g.pitch);
                 __builtin_amdgcn_wave_barrier();
             }
 #pragma unroll
@@ -897,13 +909,13 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
     const int bd = blockIdx.y, b = bd / g.D;
     const size_t P = (size_t)g.W * g.H, Q = g.plane();
     const int r0 = blockIdx.z * seg_rows, r1 = min(r0 + seg_rows, g.H);
-    const uint32_t W4 = 4u * (uint32_t)g.pitch(), W8 = 8u * (uint32_t)g.W;
+    const uint32_t W4 = 4u * (uint32_t)g.pitch, W8 = 8u * (uint32_t)g.W;
     const auto src = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + (size_t)bd * Q),
                                                        (short)0, (int)(Q * 4), 0x00020000);
     const auto rec = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint2*>(g.vrec + (size_t)b * P), (short)0, (int)(P * 8), 0x00020000);
     const auto dst = __builtin_amdgcn_make_buffer_rsrc(
-        out + (size_t)bd * Q + (size_t)r0 * g.pitch(), (short)0,
+        out + (size_t)bd * Q + (size_t)r0 * g.pitch, (short)0,
         (int)((uint32_t)(r1 - r0) * W4), 0x00020000);
     const uint32_t x4 = x < g.W ? 4u * (uint32_t)x : kSoftDrop;
     const uint32_t t8 = 8u * t;
@@ -1070,7 +1082,7 @@ __global__ __launch_bounds__(256) void k_soft_argmin(SoftGeom g, const float* __
     const float invT = 1.0f / theta[2];
     const size_t Q = g.plane();
     const float* a = A2 + (size_t)b * g.D * Q + i +
-                     (uint32_t)i / (uint32_t)g.W * (uint32_t)(g.pitch() - g.W);
+                     (uint32_t)i / (uint32_t)g.W * (uint32_t)(g.pitch - g.W);
     float m = -INFINITY, z = 0.0f, zd = 0.0f;
     for (int d0 = 0; d0 < g.D; d0 += kArgBatch) {
         float v[kArgBatch];
@@ -1202,14 +1214,16 @@ static bool soft_stream(const SoftGeom& g) {
     return (long long)g.B * g.D * g.H * g.W > 16LL << 20;
 }
 
-// go(share, stream): the bools as types
+// go(share, rows): the values as types
 template <typename Go>
 static void with_row_kind(const RowGrid& rg, const SoftGeom& g, Go go) {
     const auto second = [&](auto share) {
-        if (soft_stream(g))
-            go(share, std::true_type{});
+        if (g.pitch != soft_pitch(g.W))
+            go(share, std::integral_constant<Rows, kCut>{});
+        else if (soft_stream(g))
+            go(share, std::integral_constant<Rows, kPast>{});
         else
-            go(share, std::false_type{});
+            go(share, std::integral_constant<Rows, kWhole>{});
     };
     if (rg.share)
         second(std::true_type{});
@@ -1219,8 +1233,8 @@ static void with_row_kind(const RowGrid& rg, const SoftGeom& g, Go go) {
 
 static void launch_mrow(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, float* out,
                         hipStream_t st) {
-    with_row_kind(rg, g, [&](auto share, auto stream) {
-        hipLaunchKernelGGL((k_soft_mrow<decltype(share)::value, decltype(stream)::value>), rg.grid,
+    with_row_kind(rg, g, [&](auto share, auto rows) {
+        hipLaunchKernelGGL((k_soft_mrow<decltype(share)::value, decltype(rows)::value>), rg.grid,
                            rg.block, 0, st, g, im, out, rg.seg);
     });
 }
@@ -1229,17 +1243,17 @@ template <WideKind kKind>
 static void launch_wide(const RowGrid& rg, const SoftGeom& g, const SoftImg& im, const float* in,
                         const float* theta, float* dhat, float* lse, const float* gdhat, float* out,
                         double* part, hipStream_t st) {
-    with_row_kind(rg, g, [&](auto share, auto stream) {
+    with_row_kind(rg, g, [&](auto share, auto rows) {
         // the dot products write no volume
-        constexpr bool kStream = kKind != kDot && decltype(stream)::value;
-        hipLaunchKernelGGL((k_soft_wide<kKind, decltype(share)::value, kStream>), rg.grid, rg.block,
+        constexpr Rows kRows = kKind == kDot ? kWhole : decltype(rows)::value;
+        hipLaunchKernelGGL((k_soft_wide<kKind, decltype(share)::value, kRows>), rg.grid, rg.block,
                            0, st, g, im, in, theta, dhat, lse, gdhat, out, part, rg.seg);
     });
 }
 
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,
                         int D, uint2* vrec, float* n2, hipStream_t st) {
-    SoftGeom g{arms, nullptr, nullptr, B, W, H, D};
+    SoftGeom g{arms, nullptr, nullptr, B, W, H, D, 0};
     hipLaunchKernelGGL(k_soft_counts, dim3((W + kCntTW - 1) / kCntTW, (H + kCntTH - 1) / kCntTH, B),
                        dim3(256), 0, st, g, theta, tab, vrec, n2);
     return hipGetLastError();
@@ -1250,7 +1264,7 @@ hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, in
 hipError_t soft_aggregate(const SoftBuffers& s, int B, int W, int H, int D, float* A2, float* t1,
                           float* t2, const float* theta, float* dhat, float* lse,
                           hipStream_t st) {
-    SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D, s.pitch};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const RowGrid rg = row_grid(g);
     launch_mrow(rg, g, im, t1, st);                                 // E1
@@ -1271,7 +1285,7 @@ hipError_t soft_backward(const SoftBuffers& s, int B, int W, int H, int D, const
                          const float* theta, const float* dhat, const float* lse,
                          const float* gdhat, float* t1, float* t2, double* partAC,
                          double* partT, float* grad, hipStream_t st) {
-    SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D};
+    SoftGeom g{s.arms, s.vrec, s.n2, B, W, H, D, s.pitch};
     SoftImg im{s.pixL, s.pixR, s.alpha, s.tab};
     const int nrows = B * D * H;
     const RowGrid rg = row_grid(g);

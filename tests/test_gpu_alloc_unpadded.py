@@ -73,3 +73,36 @@ def test_matcher_without_padding(W, H, D, vote):
     finally:
         L.dco_debug_fail_alloc(0)
     assert L.dco_debug_live_allocations() == base
+
+
+# less than a quad, a cut quad of one, two and three columns, one and several groups
+@pytest.mark.parametrize("W,H,D,B", [(11, 12, 5, 2), (97, 21, 20, 2), (130, 9, 40, 1),
+                                     (67, 30, 66, 1), (332, 8, 17, 1)])
+def test_soft_path_without_padding(W, H, D, B):
+    """Every allocation of the soft scratch failing once: the same bits."""
+    import torch
+    from paper_2203_02300_amd import StereoMatcher, _lib
+    from paper_2203_02300_amd.soft import soft_backward, soft_forward
+    D = min(D, W - 1)
+    L = _lib.lib()
+    rng = np.random.default_rng(W)
+    a = rng.integers(0, 256, (B, H, W, 3), dtype=np.uint8)
+    b = np.roll(a, -2, axis=2)
+    gd = dev(rng.normal(0, 1e-2, (B, H, W)).astype(np.float32))
+    a, b = dev(a), dev(b)
+    theta = torch.tensor([10.0, 30.0, 0.5], dtype=torch.float32, device="cuda")
+
+    def run(k):
+        with StereoMatcher(W, H, D) as m:
+            L.dco_debug_fail_alloc(k)
+            try:
+                dh, lse = soft_forward(m, a, b, theta)
+            finally:
+                L.dco_debug_fail_alloc(0)
+            g = soft_backward(m, a, b, theta, dh, lse, gd, reuse=True)
+            return [host(t) for t in (dh, lse, g)]
+
+    want = run(0)
+    for k in (1, 7, 8, 9, 11):  # maps, the three volumes, partial sums
+        for g, w in zip(run(k), want):
+            assert np.isfinite(w).all() and np.array_equal(g, w), k
