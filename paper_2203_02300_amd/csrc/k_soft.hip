@@ -157,7 +157,7 @@ __device__ inline int xcd_block(int b, int n) {
 // A cost that is not finite makes the outputs from its block on NaN.
 //
 // A workgroup takes one image row (or one of `segs` parts of it), a wavefront
-// 16 of its disparities (in rounds where there are more than 64), and they walk
+// 16 of its disparities (those past 64 are other workgroups'), and they walk
 // the row together in blocks of 64 columns:
 //   - bands: the 0/1 operand of the block, which all the row's wavefronts use,
 //     each building its share: a lane's 16 columns are the bits of one
@@ -182,7 +182,7 @@ __device__ inline int xcd_block(int b, int n) {
 // barrier, the halves' products one after the other and the last partners of a block
 // kept in LDS: 124 registers; without, 0.30 and more to spilling.
 constexpr int kMxWaves = 4;          // most wavefronts per workgroup
-constexpr int kMxSlots = 16 * 256;   // wavefronts of it the device holds at once
+constexpr int kMxSimds = 4 * 256;    // SIMDs of the device
 constexpr int kMxStride = 68;        // words per disparity of the stage
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4), may_alias));
@@ -424,115 +424,113 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_mrow(SoftGeom g, Soft
     const size_t Q = g.plane(), vol = (size_t)b * D * Q + (size_t)y * g.pitch;
     uint32_t* stage = stages[w];
     int par = 0;
-    for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
-        const int grp = g0 + rt.grp, d0 = 16 * grp, d = d0 + n;
-        const bool active = rt.on && grp < ng;
-        v4i bp[2][3];
+    const int grp = (kShare ? (int)blockIdx.z * nw : 0) + rt.grp, d0 = 16 * grp, d = d0 + n;
+    const bool active = rt.on && grp < ng;
+    v4i bp[2][3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
+    WideScale sc;
+    // Partners of a block's 16 disparities: the 64 pixels from column X - d0 on
+    // and the last 16 of the 64 before, through LDS (entry 16 + lane - j holds
+    // column X + lane - (d0 + j)).  They and the reference pixels are loaded a
+    // block ahead.
+    const auto pixel = [&](int x) {
+        const uint4* q = pr + min(max(x - d0, 0), W - 1);
+        return uint3{q->x, q->y, q->z};
+    };
+    uint3 rc{};
+    uint4 pn{};
+    if (active) {
+        const int X = 64 * max(it0 - 1, 0);
+        if (lane < 16) {
+            const uint3 r = pixel(X - 16 + lane);
+            cen[w][64 + lane] = uint2{r.x, r.y};
+            rgb[w][64 + lane] = r.z;
+        }
+        rc = pixel(X + lane);
+        pn = pl[min(X + lane, W - 1)];
+    }
+    // the block before a segment's first only gives its digits
+    for (int it = max(it0 - 1, 0); it < it1; ++it, par ^= 1) {
+        const int X = it << 6;
+        // bands of the four 16-column outputs over the block before and this one
+        const auto band = [&](int c) {
+            const int x = X - 32 + 16 * (c >> 1) + n;
+            const uint32_t a = ar[min(max(x, 0), W - 1)];
+            return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
+                              X - 64 + 64 * (c & 1) + 16 * kg);
+        };
+        if constexpr (kShare)
+            for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
+        v4i bc[2][3];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
-        WideScale sc;
-        // Partners of a block's 16 disparities: the 64 pixels from column X - d0 on
-        // and the last 16 of the 64 before, through LDS (entry 16 + lane - j holds
-        // column X + lane - (d0 + j)).  They and the reference pixels are loaded a
-        // block ahead.
-        const auto pixel = [&](int x) {
-            const uint4* q = pr + min(max(x - d0, 0), W - 1);
-            return uint3{q->x, q->y, q->z};
-        };
-        uint3 rc{};
-        uint4 pn{};
-        if (active) {
-            const int X = 64 * max(it0 - 1, 0);
-            if (lane < 16) {
-                const uint3 r = pixel(X - 16 + lane);
-                cen[w][64 + lane] = uint2{r.x, r.y};
-                rgb[w][64 + lane] = r.z;
+            for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
+        const int ex_old = sc.ex;
+        if (active && X < W) {
+            if (lane < 16) {  // the last 16 of the block before
+                cen[w][lane] = cen[w][64 + lane];
+                rgb[w][lane] = rgb[w][64 + lane];
             }
-            rc = pixel(X + lane);
-            pn = pl[min(X + lane, W - 1)];
-        }
-        // the block before a segment's first only gives its digits
-        for (int it = max(it0 - 1, 0); it < it1; ++it, par ^= 1) {
-            const int X = it << 6;
-            // bands of the four 16-column outputs over the block before and this one
-            const auto band = [&](int c) {
-                const int x = X - 32 + 16 * (c >> 1) + n;
-                const uint32_t a = ar[min(max(x, 0), W - 1)];
-                return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1,
-                                  X - 64 + 64 * (c & 1) + 16 * kg);
-            };
-            if constexpr (kShare)
-                for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
-            v4i bc[2][3];
+            __builtin_amdgcn_wave_barrier();
+            cen[w][16 + lane] = uint2{rc.x, rc.y};
+            rgb[w][16 + lane] = rc.z;
+            const uint4 pa = pn;
+            rc = pixel(X + 64 + lane);
+            pn = pl[min(X + 64 + lane, W - 1)];
+            __builtin_amdgcn_wave_barrier();
+            const float al = im.alpha[pa.w >> 3], be = 1.0f - al;
+            const bool in_row = X + lane < W;
+            float v[16];
+            const auto costs = [&](auto all_in) {
+                constexpr bool kIn = decltype(all_in)::value;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
-            const int ex_old = sc.ex;
-            if (active && X < W) {
-                if (lane < 16) {  // the last 16 of the block before
-                    cen[w][lane] = cen[w][64 + lane];
-                    rgb[w][lane] = rgb[w][64 + lane];
+                for (int j = 0; j < 16; ++j) {
+                    const uint2 cb = cen[w][16 + lane - j];
+                    const uint32_t s = __builtin_amdgcn_sad_u8(pa.z, rgb[w][16 + lane - j], 0u);
+                    const int hm = __popc(pa.x ^ cb.x) + __popc(pa.y ^ cb.y);
+                    const float c = al * tab[s] + be * tab[kCenTab + hm];
+                    v[j] = kIn || (in_row && X + lane - d0 - j >= 0) ? c : 0.0f;
                 }
-                __builtin_amdgcn_wave_barrier();
-                cen[w][16 + lane] = uint2{rc.x, rc.y};
-                rgb[w][16 + lane] = rc.z;
-                const uint4 pa = pn;
-                rc = pixel(X + 64 + lane);
-                pn = pl[min(X + 64 + lane, W - 1)];
-                __builtin_amdgcn_wave_barrier();
-                const float al = im.alpha[pa.w >> 3], be = 1.0f - al;
-                const bool in_row = X + lane < W;
-                float v[16];
-                const auto costs = [&](auto all_in) {
-                    constexpr bool kIn = decltype(all_in)::value;
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        const uint2 cb = cen[w][16 + lane - j];
-                        const uint32_t s = __builtin_amdgcn_sad_u8(pa.z, rgb[w][16 + lane - j], 0u);
-                        const int hm = __popc(pa.x ^ cb.x) + __popc(pa.y ^ cb.y);
-                        const float c = al * tab[s] + be * tab[kCenTab + hm];
-                        v[j] = kIn || (in_row && X + lane - d0 - j >= 0) ? c : 0.0f;
-                    }
-                };
-                if (X >= d0 + 15 && X + 64 <= W)  // every column and partner is in the image
-                    costs(std::true_type{});
-                else
-                    costs(std::false_type{});
-                uint32_t lo[16];
-                put_wide(v, stage, lo, sc);
-                wide_planes(stage, lo, bc);
-            }
-            // the bands; the buffer's next writers pass the next one first
-            if (kShare) __syncthreads();
-            if (!active) continue;
-            if (it >= it0) {
-                const auto bands_of = [&](int c) { return kShare ? bands[par][c][lane] : band(c); };
-                wide_outputs(X, W, bp, bc, ex_old, sc, bands_of, [&](int i, int xb, double(&v)[4]) {
-                    if (xb - kLMax < d0 + 15) {  // ranges may hold columns left of d: c = 1
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int x = xb + 4 * kg + r;
-                            const uint32_t a = ar[min(x, W - 1)];
-                            const int len = arm(a, 0) + arm(a, 1) + 1;
-                            v[r] += (double)min(max(d - (x - arm(a, 0)), 0), len);
-                        }
-                    }
-                    // to the stage (free since the digits), one row per d
-                    *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
-                        v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-                });
-                __builtin_amdgcn_wave_barrier();
-                put_rows<kRows>(stage, out + vol, Q, d0, D, X - 32, g.pitch);
-                __builtin_amdgcn_wave_barrier();
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
+            };
+            if (X >= d0 + 15 && X + 64 <= W)  // every column and partner is in the image
+                costs(std::true_type{});
+            else
+                costs(std::false_type{});
+            uint32_t lo[16];
+            put_wide(v, stage, lo, sc);
+            wide_planes(stage, lo, bc);
         }
+        // the bands; the buffer's next writers pass the next one first
+        if (kShare) __syncthreads();
+        if (!active) continue;
+        if (it >= it0) {
+            const auto bands_of = [&](int c) { return kShare ? bands[par][c][lane] : band(c); };
+            wide_outputs(X, W, bp, bc, ex_old, sc, bands_of, [&](int i, int xb, double(&v)[4]) {
+                if (xb - kLMax < d0 + 15) {  // ranges may hold columns left of d: c = 1
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int x = xb + 4 * kg + r;
+                        const uint32_t a = ar[min(x, W - 1)];
+                        const int len = arm(a, 0) + arm(a, 1) + 1;
+                        v[r] += (double)min(max(d - (x - arm(a, 0)), 0), len);
+                    }
+                }
+                // to the stage (free since the digits), one row per d
+                *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
+                    v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+            });
+            __builtin_amdgcn_wave_barrier();
+            put_rows<kRows>(stage, out + vol, Q, d0, D, X - 32, g.pitch);
+            __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
     }
 }
 
@@ -612,220 +610,218 @@ __global__ __launch_bounds__(64 * kMxWaves, 4) void k_soft_wide(
     const float T = theta[2], invT = 1.0f / T;
     uint32_t* stage = stages[w];
     int par = 0;
-    for (int g0 = 0; g0 < (kShare ? ng : 1); g0 += nw) {
-        const int grp = g0 + rt.grp, d0 = 16 * grp;
-        const bool active = rt.on && grp < ng;
-        v4i bp[2][3];
+    const int grp = (kShare ? (int)blockIdx.z * nw : 0) + rt.grp, d0 = 16 * grp;
+    const bool active = rt.on && grp < ng;
+    v4i bp[2][3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
+    double acc = 0.0, acc2 = 0.0;
+    WideScale sc;
+    // the block before a segment's first only gives its digits
+    const auto merge = [&](int it, int buf) {
+        // dhat and lse of block it's columns from the wavefronts' sums
+        const int x = (it << 6) - 32 + lane;
+        float m = -INFINITY, z = 0.0f, zd = 0.0f;
+        const auto* r = soft[buf] + (w - rt.grp);  // the row's wavefronts
+        for (int k = 0; k < ng; ++k) m = fmaxf(m, r[k][0][lane]);
+        for (int k = 0; k < ng; ++k) {
+            const float sc = exp_e(r[k][0][lane] - m);
+            z += sc * r[k][1][lane];
+            zd += sc * r[k][2][lane];
+        }
+        if (rt.on && x >= 0 && x < W) {
+            dhat[pix + x] = zd / z;
+            lse[pix + x] = m + logf(z);
+        }
+    };
+    for (int it = max(it0 - 1, 0), first = it; it < it1; ++it, par ^= 1) {
+        const int X = it << 6;
+        const int xc = min(X + lane, W - 1);
+        const bool in_row = X + lane < W;
+        if constexpr (kAdj) {
+            const uint32_t a = X < W ? g.arms[pix + xc] : 0u;
+            reinterpret_cast<uint8_t*>(arml[w][it & 1])[lane] = (uint8_t)(arm(a, 0) + 1);
+            reinterpret_cast<uint8_t*>(armr[w][it & 1])[lane] = (uint8_t)arm(a, 1);
+            if (it == first) {  // no block before (its digits are zero)
+                reinterpret_cast<uint8_t*>(arml[w][~it & 1])[lane] = 1;
+                reinterpret_cast<uint8_t*>(armr[w][~it & 1])[lane] = 0;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        const auto band = [&](int c) {
+            const int k = c & 1;  // 0: the block before, 1: this one
+            const int x = X - 32 + 16 * (c >> 1) + n;
+            if constexpr (kAdj) {
+                return band_bytes_t(arml[w][(it + 1 + k) & 1] + 4 * kg,
+                                    armr[w][(it + 1 + k) & 1] + 4 * kg,
+                                    X - 64 + 64 * k + 16 * kg - x);
+            } else {
+                const uint32_t a = g.arms[pix + min(max(x, 0), W - 1)];
+                return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1, X - 64 + 64 * k + 16 * kg);
+            }
+        };
+        if constexpr (kShare)
+            for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
+        v4i bc[2][3];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) bp[h][k] = v4i{0, 0, 0, 0};
-        double acc = 0.0, acc2 = 0.0;
-        WideScale sc;
-        // the block before a segment's first only gives its digits
-        const auto merge = [&](int it, int buf) {
-            // dhat and lse of block it's columns from the wavefronts' sums
-            const int x = (it << 6) - 32 + lane;
-            float m = -INFINITY, z = 0.0f, zd = 0.0f;
-            const auto* r = soft[buf] + (w - rt.grp);  // the row's wavefronts
-            for (int k = 0; k < ng; ++k) m = fmaxf(m, r[k][0][lane]);
-            for (int k = 0; k < ng; ++k) {
-                const float sc = exp_e(r[k][0][lane] - m);
-                z += sc * r[k][1][lane];
-                zd += sc * r[k][2][lane];
-            }
-            if (rt.on && x >= 0 && x < W) {
-                dhat[pix + x] = zd / z;
-                lse[pix + x] = m + logf(z);
-            }
-        };
-        for (int it = max(it0 - 1, 0), first = it; it < it1; ++it, par ^= 1) {
-            const int X = it << 6;
-            const int xc = min(X + lane, W - 1);
-            const bool in_row = X + lane < W;
-            if constexpr (kAdj) {
-                const uint32_t a = X < W ? g.arms[pix + xc] : 0u;
-                reinterpret_cast<uint8_t*>(arml[w][it & 1])[lane] = (uint8_t)(arm(a, 0) + 1);
-                reinterpret_cast<uint8_t*>(armr[w][it & 1])[lane] = (uint8_t)arm(a, 1);
-                if (it == first) {  // no block before (its digits are zero)
-                    reinterpret_cast<uint8_t*>(arml[w][~it & 1])[lane] = 1;
-                    reinterpret_cast<uint8_t*>(armr[w][~it & 1])[lane] = 0;
+            for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
+        const int ex_old = sc.ex;
+        if (active && X < W) {
+            const float gp = kKind == kSeed && in_row ? gdhat[pix + xc] : 0.0f;
+            const float dh = kKind == kSeed ? dhat[pix + xc] : 0.0f;
+            const float ls = kKind == kSeed ? lse[pix + xc] : 0.0f;
+            const float g1 =
+                kKind == kSeed ? gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc]) : 0.0f;
+            const float dh0 = dh - (float)d0;
+            float G[16];
+            double t = 0.0;
+            size_t Pv = Q;
+            asm volatile("" : "+s"(Pv));  // else 16 row addresses live in registers
+            const float* a2 = in + vol + (size_t)d0 * Pv + xc;
+            const auto seed = [&](auto full) {
+                constexpr bool kFull = decltype(full)::value;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    G[j] = *a2;
+                    if (kFull || d0 + j + 1 < D) a2 += Pv;
                 }
-                __builtin_amdgcn_wave_barrier();
-            }
-            const auto band = [&](int c) {
-                const int k = c & 1;  // 0: the block before, 1: this one
-                const int x = X - 32 + 16 * (c >> 1) + n;
-                if constexpr (kAdj) {
-                    return band_bytes_t(arml[w][(it + 1 + k) & 1] + 4 * kg,
-                                        armr[w][(it + 1 + k) & 1] + 4 * kg,
-                                        X - 64 + 64 * k + 16 * kg - x);
-                } else {
-                    const uint32_t a = g.arms[pix + min(max(x, 0), W - 1)];
-                    return band_bytes(x - arm(a, 0), x + arm(a, 1) + 1, X - 64 + 64 * k + 16 * kg);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const bool on = kFull || d0 + j < D;
+                    if constexpr (kKind == kSeed) {
+                        const float u = exp_e(-G[j] * invT - ls) * (dh0 - (float)j);
+                        t += (double)(on ? gp * u * G[j] : 0.0f);
+                        G[j] = on ? g1 * u : 0.0f;
+                    } else {
+                        G[j] = in_row && on ? G[j] : 0.0f;
+                    }
                 }
             };
-            if constexpr (kShare)
-                for (int c = w; c < 8; c += nw) bands[par][c][lane] = band(c);
-            v4i bc[2][3];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) bc[h][k] = v4i{0, 0, 0, 0};
-            const int ex_old = sc.ex;
-            if (active && X < W) {
-                const float gp = kKind == kSeed && in_row ? gdhat[pix + xc] : 0.0f;
-                const float dh = kKind == kSeed ? dhat[pix + xc] : 0.0f;
-                const float ls = kKind == kSeed ? lse[pix + xc] : 0.0f;
-                const float g1 =
-                    kKind == kSeed ? gp * invT * __builtin_amdgcn_rcpf(g.n2[pix + xc]) : 0.0f;
-                const float dh0 = dh - (float)d0;
-                float G[16];
-                double t = 0.0;
-                size_t Pv = Q;
-                asm volatile("" : "+s"(Pv));  // else 16 row addresses live in registers
-                const float* a2 = in + vol + (size_t)d0 * Pv + xc;
-                const auto seed = [&](auto full) {
-                    constexpr bool kFull = decltype(full)::value;
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        G[j] = *a2;
-                        if (kFull || d0 + j + 1 < D) a2 += Pv;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        const bool on = kFull || d0 + j < D;
-                        if constexpr (kKind == kSeed) {
-                            const float u = exp_e(-G[j] * invT - ls) * (dh0 - (float)j);
-                            t += (double)(on ? gp * u * G[j] : 0.0f);
-                            G[j] = on ? g1 * u : 0.0f;
-                        } else {
-                            G[j] = in_row && on ? G[j] : 0.0f;
-                        }
-                    }
-                };
-                if (d0 + 16 <= D)
-                    seed(std::true_type{});
-                else
-                    seed(std::false_type{});
-                if (kKind == kSeed && it >= it0) acc -= t;
-                uint32_t lo[16];
-                put_wide(G, stage, lo, sc);
-                wide_planes(stage, lo, bc);
+            if (d0 + 16 <= D)
+                seed(std::true_type{});
+            else
+                seed(std::false_type{});
+            if (kKind == kSeed && it >= it0) acc -= t;
+            uint32_t lo[16];
+            put_wide(G, stage, lo, sc);
+            wide_planes(stage, lo, bc);
+        }
+        // the bands and the softmax sums; the buffers' next writers pass the next
+        // one first
+        if (kShare || (!kAdj && dhat)) __syncthreads();
+        if (!kAdj && dhat && it > it0 && rt.grp == it % ng) merge(it - 1, par ^ 1);
+        if (!active) continue;
+        const auto bands_of = [&](int c) { return kShare ? bands[par][c][lane] : band(c); };
+        if (kKind == kDot && it >= it0) {
+            // the outputs' pixels and their partners, on the stage: reference
+            // columns X - 32 .. X + 31, partner columns X - 47 - d0 .. X + 31 - d0
+            uint32_t* const rx = stage;            // census of the reference pixels
+            uint32_t* const ry = stage + 64;
+            uint32_t* const rz = stage + 128;      // their colours
+            float* const ra = reinterpret_cast<float*>(stage + 192);  // their alphas
+            uint2* const px = reinterpret_cast<uint2*>(stage + 256);  // partners: census
+            uint32_t* const pz = stage + 416;                         // colours
+            // 0 <= x - d < span: the disparity is one, column and partner in the image
+            const int xd = X - 32 - (d0 + n);
+            const uint32_t span = d0 + n < D ? (uint32_t)(W - (d0 + n)) : 0u;
+            const auto at = [&](const uint4* p, int x) {
+                return p[pix + min(max(x, 0), W - 1)];
+            };
+            const uint4 r = at(im.pixL, X - 32 + lane);
+            const uint4 q0 = at(im.pixR, X - 47 - d0 + lane);
+            const uint4 q1 = at(im.pixR, X + 17 - d0 + (lane & 15));
+            rx[lane] = r.x;
+            ry[lane] = r.y;
+            rz[lane] = r.z;
+            ra[lane] = im.alpha[r.w >> 3];
+            px[lane] = uint2{q0.x, q0.y};
+            pz[lane] = q0.z;
+            if (lane < 16) {
+                px[64 + lane] = uint2{q1.x, q1.y};
+                pz[64 + lane] = q1.z;
             }
-            // the bands and the softmax sums; the buffers' next writers pass the next
-            // one first
-            if (kShare || (!kAdj && dhat)) __syncthreads();
-            if (!kAdj && dhat && it > it0 && rt.grp == it % ng) merge(it - 1, par ^ 1);
-            if (!active) continue;
-            const auto bands_of = [&](int c) { return kShare ? bands[par][c][lane] : band(c); };
-            if (kKind == kDot && it >= it0) {
-                // the outputs' pixels and their partners, on the stage: reference
-                // columns X - 32 .. X + 31, partner columns X - 47 - d0 .. X + 31 - d0
-                uint32_t* const rx = stage;            // census of the reference pixels
-                uint32_t* const ry = stage + 64;
-                uint32_t* const rz = stage + 128;      // their colours
-                float* const ra = reinterpret_cast<float*>(stage + 192);  // their alphas
-                uint2* const px = reinterpret_cast<uint2*>(stage + 256);  // partners: census
-                uint32_t* const pz = stage + 416;                         // colours
-                // 0 <= x - d < span: the disparity is one, column and partner in the image
-                const int xd = X - 32 - (d0 + n);
-                const uint32_t span = d0 + n < D ? (uint32_t)(W - (d0 + n)) : 0u;
-                const auto at = [&](const uint4* p, int x) {
-                    return p[pix + min(max(x, 0), W - 1)];
-                };
-                const uint4 r = at(im.pixL, X - 32 + lane);
-                const uint4 q0 = at(im.pixR, X - 47 - d0 + lane);
-                const uint4 q1 = at(im.pixR, X + 17 - d0 + (lane & 15));
-                rx[lane] = r.x;
-                ry[lane] = r.y;
-                rz[lane] = r.z;
-                ra[lane] = im.alpha[r.w >> 3];
-                px[lane] = uint2{q0.x, q0.y};
-                pz[lane] = q0.z;
-                if (lane < 16) {
-                    px[64 + lane] = uint2{q1.x, q1.y};
-                    pz[64 + lane] = q1.z;
+            __builtin_amdgcn_wave_barrier();
+            wide_outputs(X, W, bp, bc, ex_old, sc, bands_of, [&](int i, int, double(&v)[4]) {
+                int c = 16 * i + 4 * kg;
+                asm volatile("" : "+v"(c));  // the addresses are made here, not kept
+                const v4u cx = *reinterpret_cast<const v4u*>(rx + c);
+                const v4u cy = *reinterpret_cast<const v4u*>(ry + c);
+                const v4u cz = *reinterpret_cast<const v4u*>(rz + c);
+                const v4f al = *reinterpret_cast<const v4f*>(ra + c);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int e = c + k + 15 - n;
+                    const uint2 q = px[e];
+                    const uint32_t s = __builtin_amdgcn_sad_u8(cz[k], pz[e], 0u);
+                    const int hm = __popc(cx[k] ^ q.x) + __popc(cy[k] ^ q.y);
+                    const float da = al[k] * tab[s], dc = (1.0f - al[k]) * tab[kCenTab + hm];
+                    const bool on = (uint32_t)(xd + c + k) < span;
+                    acc = __builtin_fma(v[k], (double)(on ? da : 0.0f), acc);
+                    acc2 = __builtin_fma(v[k], (double)(on ? dc : 0.0f), acc2);
+                }
+            });
+            __builtin_amdgcn_wave_barrier();
+        } else if (it >= it0) {
+            wide_outputs(X, W, bp, bc, ex_old, sc, bands_of,
+                         [&](int i, int, double(&v)[4]) {
+                             *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
+                                 v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+                         });
+            __builtin_amdgcn_wave_barrier();
+            if constexpr (!kAdj) {
+                // A2 = sum / N2, and the softmax sums of the wavefront's 16
+                // disparities for each column
+                const float rn = __builtin_amdgcn_rcpf(
+                    g.n2[pix + min(max(X - 32 + lane, 0), W - 1)]);
+                float v[16], m = -INFINITY, z = 0.0f, zd = 0.0f;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    uint32_t* q = stage + j * kMxStride + lane;
+                    const float a = __builtin_bit_cast(float, *q) * rn;
+                    *q = __builtin_bit_cast(uint32_t, a);
+                    v[j] = -a * invT;
+                }
+                if (dhat) {
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) m = d0 + j < D ? fmaxf(m, v[j]) : m;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        const float e = d0 + j < D ? exp_e(v[j] - m) : 0.0f;
+                        z += e;
+                        zd += (float)j * e;
+                    }
+                    soft[par][w][0][lane] = m;
+                    soft[par][w][1][lane] = z;
+                    soft[par][w][2][lane] = zd + (float)d0 * z;
                 }
                 __builtin_amdgcn_wave_barrier();
-                wide_outputs(X, W, bp, bc, ex_old, sc, bands_of, [&](int i, int, double(&v)[4]) {
-                    int c = 16 * i + 4 * kg;
-                    asm volatile("" : "+v"(c));  // the addresses are made here, not kept
-                    const v4u cx = *reinterpret_cast<const v4u*>(rx + c);
-                    const v4u cy = *reinterpret_cast<const v4u*>(ry + c);
-                    const v4u cz = *reinterpret_cast<const v4u*>(rz + c);
-                    const v4f al = *reinterpret_cast<const v4f*>(ra + c);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int e = c + k + 15 - n;
-                        const uint2 q = px[e];
-                        const uint32_t s = __builtin_amdgcn_sad_u8(cz[k], pz[e], 0u);
-                        const int hm = __popc(cx[k] ^ q.x) + __popc(cy[k] ^ q.y);
-                        const float da = al[k] * tab[s], dc = (1.0f - al[k]) * tab[kCenTab + hm];
-                        const bool on = (uint32_t)(xd + c + k) < span;
-                        acc = __builtin_fma(v[k], (double)(on ? da : 0.0f), acc);
-                        acc2 = __builtin_fma(v[k], (double)(on ? dc : 0.0f), acc2);
-                    }
-                });
-                __builtin_amdgcn_wave_barrier();
-            } else if (it >= it0) {
-                wide_outputs(X, W, bp, bc, ex_old, sc, bands_of,
-                             [&](int i, int, double(&v)[4]) {
-                                 *reinterpret_cast<v4f*>(stage + n * kMxStride + 16 * i + 4 * kg) =
-                                     v4f{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-                             });
-                __builtin_amdgcn_wave_barrier();
-                if constexpr (!kAdj) {
-                    // A2 = sum / N2, and the softmax sums of the wavefront's 16
-                    // disparities for each column
-                    const float rn = __builtin_amdgcn_rcpf(
-                        g.n2[pix + min(max(X - 32 + lane, 0), W - 1)]);
-                    float v[16], m = -INFINITY, z = 0.0f, zd = 0.0f;
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        uint32_t* q = stage + j * kMxStride + lane;
-                        const float a = __builtin_bit_cast(float, *q) * rn;
-                        *q = __builtin_bit_cast(uint32_t, a);
-                        v[j] = -a * invT;
-                    }
-                    if (dhat) {
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) m = d0 + j < D ? fmaxf(m, v[j]) : m;
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) {
-                            const float e = d0 + j < D ? exp_e(v[j] - m) : 0.0f;
-                            z += e;
-                            zd += (float)j * e;
-                        }
-                        soft[par][w][0][lane] = m;
-                        soft[par][w][1][lane] = z;
-                        soft[par][w][2][lane] = zd + (float)d0 * z;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-                put_rows<kRows>(stage, out + vol, Q, d0, D, X - 32, g.pitch);
-                __builtin_amdgcn_wave_barrier();
             }
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
+            put_rows<kRows>(stage, out + vol, Q, d0, D, X - 32, g.pitch);
+            __builtin_amdgcn_wave_barrier();
         }
-        if (!kAdj && dhat) {
-            __syncthreads();
-            if (rt.grp == 0) merge(it1 - 1, par ^ 1);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) bp[h][k] = bc[h][k];
+    }
+    if (!kAdj && dhat) {
+        __syncthreads();
+        if (rt.grp == 0) merge(it1 - 1, par ^ 1);
+    }
+    if (kAdj && active) {
+        for (int off = 32; off > 0; off >>= 1) {  // fixed-order wavefront reduction
+            acc += __shfl_down(acc, off, 64);
+            if (kKind == kDot) acc2 += __shfl_down(acc2, off, 64);
         }
-        if (kAdj && active) {
-            for (int off = 32; off > 0; off >>= 1) {  // fixed-order wavefront reduction
-                acc += __shfl_down(acc, off, 64);
-                if (kKind == kDot) acc2 += __shfl_down(acc2, off, 64);
-            }
-            const size_t k = ((size_t)row * gridDim.y + blockIdx.y) * ng + grp;
-            if (lane == 0 && kKind == kSeed) part[k] = acc * (double)(invT * invT);
-            if (lane == 0 && kKind == kDot) {
-                part[2 * k] = acc;
-                part[2 * k + 1] = acc2;
-            }
+        const size_t k = ((size_t)row * gridDim.y + blockIdx.y) * ng + grp;
+        if (lane == 0 && kKind == kSeed) part[k] = acc * (double)(invT * invT);
+        if (lane == 0 && kKind == kDot) {
+            part[2 * k] = acc;
+            part[2 * k + 1] = acc2;
         }
     }
 }
@@ -1185,9 +1181,15 @@ static void launch_vv(const SoftGeom& g, const float* in, float* out, hipStream_
                        dim3(kSoftCols), 0, st, g, in, out, seg);
 }
 
-// Launch shape of the matrix-core row passes (RowTask).  Rows are split in parts
-// (each computes one more block) while they leave the device's slots empty; the
-// partial sums have room for D values per row.
+// Launch shape of the matrix-core row passes (RowTask): the groups that a workgroup
+// has no wavefronts for go to further workgroups (grid z), and rows are split in parts
+// (each computes one more block).  A block takes a SIMD's lone wavefront about as long
+// as four wavefronts issue in, so the split with the least blocks times wavefronts per
+// SIMD (four at least) is taken; the partial sums have room for D values per row.
+// Forwards, with the groups in rounds of one workgroup and parts of two blocks at
+// least: 1 x 128 x 100, D = 80 75 us, 57 so; 4 x 200 x 150, D = 128 172 and 157; 4 x
+// 154 x 61, D = 23 57 and 48.  With a lone wavefront's block counted as two instead of
+// four 1 x 320 x 240, D = 32 takes 63, 60 so.
 struct RowGrid {
     bool share;
     int seg, parts;  // blocks per part of a row, values in all
@@ -1197,13 +1199,21 @@ struct RowGrid {
 static RowGrid row_grid(const SoftGeom& g) {
     const int ng = (g.D + 15) / 16, rows = g.B * g.H, its = (g.W + 95) / 64;
     const bool share = ng > 2;
-    // shared: wavefronts for the groups in as few turns as possible, evenly
-    const int turns = (ng + kMxWaves - 1) / kMxWaves;
+    // shared: wavefronts for the groups in as few workgroups as possible, evenly
+    const int turns = (ng + kMxWaves - 1) / kMxWaves, zs = share ? turns : 1;
     const int nw = share ? (ng + turns - 1) / turns : kMxWaves;
     const int blocks = share ? rows : (rows + kMxWaves / ng - 1) / (kMxWaves / ng);
-    const int most = std::max(1, std::min({its / 2, g.D / ng, kMxSlots / (blocks * nw)}));
-    const int seg = (its + most - 1) / most, segs = (its + seg - 1) / seg;
-    return RowGrid{share, seg, rows * segs * ng, dim3(blocks, segs), dim3(64 * nw)};
+    int seg = its;
+    long long least = -1;
+    for (int n = 1; n <= std::min(its, g.D / ng); ++n) {
+        const int len = (its + n - 1) / n, parts = (its + len - 1) / len;
+        const long long waves = (long long)blocks * nw * zs * parts;
+        const long long cost =
+            (parts > 1 ? len + 1 : len) * std::max(4LL, (waves + kMxSimds - 1) / kMxSimds);
+        if (least < 0 || cost < least) least = cost, seg = len;
+    }
+    const int segs = (its + seg - 1) / seg;
+    return RowGrid{share, seg, rows * segs * ng, dim3(blocks, segs, zs), dim3(64 * nw)};
 }
 
 // Large volumes are written past the caches.  8 pairs of 640 x 480, D = 64: forward
