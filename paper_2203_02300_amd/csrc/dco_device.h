@@ -1430,7 +1430,7 @@ __device__ inline void wta_quad_step(float v, int d, float& best, int& bd, float
 // Four consecutive pixels from i on of a D-slice volume, with one 16-byte load
 // per slice and eight slices in flight.
 template <bool kSub, bool kNarrow>
-__device__ inline WtaQuad wta_quad(const float* __restrict__ agg, int P, int D, int i, int n,
+__device__ inline __attribute__((always_inline)) WtaQuad wta_quad(const float* __restrict__ agg, int P, int D, int i, int n,
                                    int subpixel) {
     // each volume is read once: non-temporal loads keep it from evicting
     // reused data from the caches
@@ -1531,7 +1531,7 @@ __device__ inline float wta_pair_delta_tr(const float* __restrict__ vol, int P, 
 // Four consecutive pixels from i on: one 16-byte load per even slice, 21 slices
 // in flight.  kSub: the left view, with the parabola's offset.
 template <bool kSub, bool kNarrow>
-__device__ inline WtaQuad wta_pairs_quad(const float* __restrict__ vol, int P, int D, int i, int n,
+__device__ inline __attribute__((always_inline)) WtaQuad wta_pairs_quad(const float* __restrict__ vol, int P, int D, int i, int n,
                                          int subpixel) {
     const int G = (D + 1) / 2;
     const uint32_t* __restrict__ s = reinterpret_cast<const uint32_t*>(vol) + i;
@@ -1585,7 +1585,7 @@ __device__ inline WtaQuad wta_pairs_quad(const float* __restrict__ vol, int P, i
 
 // Either layout.
 template <bool kPaired, bool kSub, bool kNarrow>
-__device__ inline WtaQuad wta_any(const float* __restrict__ vol, int P, int D, int i, int n,
+__device__ inline __attribute__((always_inline)) WtaQuad wta_any(const float* __restrict__ vol, int P, int D, int i, int n,
                                   int subpixel) {
     if constexpr (kPaired)
         return wta_pairs_quad<kSub, kNarrow>(vol, P, D, i, n, subpixel);

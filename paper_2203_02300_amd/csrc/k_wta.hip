@@ -1,7 +1,7 @@
 // k_wta.hip -- winner-take-all over the aggregated volumes (Eq. 3) with
 // parabola sub-pixel refinement, and the left-right consistency check, in one
-// launch.  On volumes in the paired layout (dco::paired_at) only the even slices
-// are read; for the sub-pixel step the winner's pair partner is gathered and,
+// launch (two for long rows).  On volumes in the paired layout (dco::paired_at) only
+// the even slices are read; for the sub-pixel step the winner's pair partner is gathered and,
 // when it is not the adjacent pair's minimum kept from the scan, its other
 // neighbour.  A thread takes four consecutive pixels with 16-byte loads and
 // walks d = 0 .. D-1; loads of one slice are coalesced across the row, so each
@@ -12,14 +12,14 @@
 
 namespace {
 
-constexpr int kWtaThreads = 1024;  // most threads of a row
+constexpr int kWtaThreads = 1024;          // most threads of a row
+constexpr int kRowCols = 2 * kWtaThreads;  // longest row that k_wta_row takes
 
 // One workgroup per image row: its second half takes the right view's quads of
 // four pixels, the first half the left view's; the right disparities go to LDS
 // for the left-right check, which the left view's threads make on their own
-// quads.  A row of more quads than half a workgroup has threads: the right
-// view's in turns, the left view's rest by all threads after the barrier.  The
-// last quad of a row is moved back to end with it (rows of less than four
+// quads: a row has no more of them than half a workgroup has threads (kRowCols).
+// The last quad of a row is moved back to end with it (rows of less than four
 // pixels: kNarrow), so quads may start at any pixel.
 //
 // Bound by the volumes' bytes at large frames (1280 x 720, D = 128: 472 MB read
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
     };
     dco::WtaQuad l{};
     if (t >= nt) {
-        for (int q = t - nt; q < nq; q += nt) {
-            const int x = start(q);
+        if (t - nt < nq) {
+            const int x = start(t - nt);
             const dco::WtaQuad r =
                 dco::wta_any<kPaired, false, kNarrow>(aggR, P, D, vrow + x, W, subpixel);
             dco::put_bd<kNarrow>(right + x, r, W);
@@ -81,7 +81,51 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
     }
     __syncthreads();
     if (t < nt && t < nq) check(t, l);
-    for (int q = nt + t; q < nq; q += blockDim.x) check(q, left(q));
+}
+
+// Rows past kRowCols: WTA as a launch of a quad per thread, whatever row it is in, the
+// left view (blockIdx.y = 0) with disp = its disparity before the check, and the check
+// as a launch after it.  With the rest of such a row in turns of k_wta_row, 8192 x 16,
+// D = 64 took 68.1 us (staged volumes 78.2), as two launches 17.6 (20.2): a few long
+// rows left most CUs idle; 2100 x 400 67.2 (93.2), now 56.5 (77.8); 2560 x 600 110.5
+// (153.1), now 92.1 (142.6); 3840 x 1080 257.0 (389.9), now 243.0 (386.1).  Up to
+// kRowCols the row kernel is one turn and saves the check's launch, 4 to 5 us at
+// small frames.
+template <bool kPaired>
+__global__ __launch_bounds__(256) void k_wta_quads(const float* __restrict__ aggL,
+                                                   const float* __restrict__ aggR, int pitch,
+                                                   int P, int W, int H, int D, int subpixel,
+                                                   int16_t* __restrict__ dL,
+                                                   int16_t* __restrict__ dR,
+                                                   float* __restrict__ disp) {
+    const int nq = (W + 3) / 4, k = blockIdx.x * 256 + threadIdx.x, y = k / nq;
+    if (y >= H) return;
+    const int x = min(4 * (k - y * nq), W - 4), i = y * W + x, v = y * pitch + x;
+    if (blockIdx.y == 0) {
+        const dco::WtaQuad l = dco::wta_any<kPaired, true, false>(aggL, P, D, v, W, subpixel);
+        dco::put_bd<false>(dL + i, l, W);
+        dco::wta_store<false, dco::f32x4u>(disp + i, (float)l.bd[0] + l.del[0],
+                                           (float)l.bd[1] + l.del[1], (float)l.bd[2] + l.del[2],
+                                           (float)l.bd[3] + l.del[3], W);
+    } else {
+        dco::put_bd<false>(dR + i, dco::wta_any<kPaired, false, false>(aggR, P, D, v, W, subpixel),
+                           W);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_lrcheck(const int16_t* __restrict__ dL,
+                                                 const int16_t* __restrict__ dR, int W,
+                                                 int P, int maxdiff, float* __restrict__ disp,
+                                                 uint8_t* __restrict__ valid, HalfOut half) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= P) return;
+    const int x = i % W, d = dL[i], xr = x - d;
+    const bool ok = xr >= 0 && abs(d - (int)dR[i - d]) <= maxdiff;
+    float v = ok ? disp[i] : 0.0f;
+    if (half.on) v *= 2.0f;
+    if (half.depth) half.depth[i] = v > 0.0f ? half.fB / v : 0.0f;
+    disp[i] = v;
+    valid[i] = ok ? 1 : 0;
 }
 
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded to n x P.
@@ -98,12 +142,22 @@ __global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, i
 }  // namespace
 
 hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int pitch, int W,
-                         int H, int D, int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
-                         uint8_t* valid, const HalfOut& half, hipStream_t st) {
+                         int H, int D, int subpixel, int maxdiff, int16_t* dL, int16_t* dR,
+                         float* disp, uint8_t* valid, const HalfOut& half, hipStream_t st) {
+    if (W > kRowCols) {
+        const auto quads = paired ? k_wta_quads<true> : k_wta_quads<false>;
+        const unsigned n = (unsigned)H * ((W + 3) / 4);
+        hipLaunchKernelGGL(quads, dim3((n + 255) / 256, 2), dim3(256), 0, st, aggL, aggR, pitch,
+                           pitch * H, W, H, D, subpixel, dL, dR, disp);
+        hipLaunchKernelGGL(k_lrcheck, dim3((unsigned)(W * H + 255) / 256), dim3(256), 0, st, dL, dR,
+                           W, W * H, maxdiff, disp, valid, half);
+        return hipGetLastError();
+    }
     const int nt = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(H), dim3(2 * nt), (size_t)W * sizeof(int16_t), st, aggL,
-                           aggR, pitch, pitch * H, W, D, subpixel, maxdiff, dL, dR, disp, valid, half);
+                           aggR, pitch, pitch * H, W, D, subpixel, maxdiff, dL, dR, disp, valid,
+                           half);
     };
     if (W < 4)
         paired ? go(k_wta_row<true, true>) : go(k_wta_row<false, true>);
@@ -112,8 +166,8 @@ hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int 
     return hipGetLastError();
 }
 
-hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d0, int n, float* out,
-                         hipStream_t st) {
+hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d0, int n,
+                         float* out, hipStream_t st) {
     const size_t total = (size_t)n * W * H;
     hipLaunchKernelGGL(k_unpair, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, vol,
                        pitch, W, H, D, d0, n, out);
