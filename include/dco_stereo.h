@@ -80,7 +80,9 @@ dco_status dco_default_params(dco_params* out);
  * Requires 1 <= D < W, W >= census_w, H >= census_h, W, H <= 16384,
  * W * H <= 2^27 and W * H * D < 2^31 (else DCO_ERR_SHAPE).  Copies *p
  * (NULL = defaults), builds the Eq. 1 tables on the host in double precision
- * and uploads them, and allocates the scratch that dco_stereo_match needs.
+ * and uploads them, and allocates the scratch that dco_stereo_match needs:
+ * about 8 W H D bytes, with the rows of two-stage volumes padded to a
+ * multiple of 16 columns where that fits in memory.
  * Synchronous.  On failure *out is NULL. */
 dco_status dco_stereo_create(dco_stereo** out, int W, int H, int D, const dco_params* p,
                              void* stream);
@@ -213,8 +215,10 @@ dco_status dco_stereo_last_disparities(dco_stereo* h, int16_t* dL, int16_t* dR);
  * stage s < n, ms[s] = total milliseconds over the recorded calls, and
  * *calls = the number of recorded calls.  Stages: 0 census + arms + region
  * counts of both views, 1 cost + aggregation of both views (one launch),
- * 2 WTA of both views, 3 LR check, 4 Eq. 4 vote and its sub-pixel output
- * (0 ms when vote_iters = 0).  ms: host array of n floats. */
+ * 2 WTA of both views with the LR check (one launch, two where rows have more
+ * than 2048 columns), 3 nothing more (the check was a stage of its own; the
+ * events alone are left), 4 Eq. 4 vote and its sub-pixel output (the events
+ * alone when vote_iters = 0).  ms: host array of n floats. */
 #define DCO_NUM_STAGES 5
 dco_status dco_stereo_profile(dco_stereo* h, int enable);
 dco_status dco_stereo_stage_times(dco_stereo* h, float* ms, int n, int* calls);
@@ -423,9 +427,10 @@ dco_status dco_stereo_match_noalloc(int W, int H, int D, const dco_params* param
  * k-th device or pinned allocation made by the library from now on fail
  * with DCO_ERR_OOM (k <= 0 disarms; DCO_FAIL_ALLOC=k in the environment arms
  * it when the library loads); the call fails with it too, unless it has a
- * smaller layout to try (volumes without padded rows).  dco_debug_live_allocations() is the number
- * of the library's device and pinned allocations not yet freed, so a test
- * can check that a failed create frees exactly what it allocated.
+ * smaller layout to try (volumes without padded rows).
+ * dco_debug_live_allocations() is the number of the library's device and
+ * pinned allocations not yet freed, so a test can check that a failed create
+ * frees exactly what it allocated.
  * Process-wide; not meant for concurrent use with other calls. */
 void dco_debug_fail_alloc(int k);
 long dco_debug_live_allocations(void);

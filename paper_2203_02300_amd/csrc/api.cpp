@@ -459,11 +459,11 @@ static dco_status match(dco_stereo* h, const uint8_t* rgbL, const uint8_t* rgbR,
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
     // from the even slices (each pair's minimum) when the volumes are paired
-    DCO_HIP_CHECK(launch_wta_lr(s.agg[0], s.agg[1], s.agg_paired, pitch, h->W, h->H, h->D, p.subpixel,
-                                p.lr_max_diff, s.dint[0], s.dint[1], disp, valid,
+    DCO_HIP_CHECK(launch_wta_lr(s.agg[0], s.agg[1], s.agg_paired, pitch, h->W, h->H, h->D,
+                                p.subpixel, p.lr_max_diff, s.dint[0], s.dint[1], disp, valid,
                                 p.vote_iters > 0 ? HalfOut{} : half, h->stream));
     DCO_TRY(prof_mark(h));
-    DCO_TRY(prof_mark(h));  // the left-right check is part of the launch above
+    DCO_TRY(prof_mark(h));  // the left-right check is part of the stage above
     DCO_TRY(prof_mark(h));
     DCO_TRY(prof_mark(h));
     if (p.vote_iters > 0)
@@ -524,9 +524,9 @@ extern "C" dco_status dco_vote_refine(dco_stereo* h, const uint8_t* armsL, const
         dco_set_error("handle has no scratch");
         return DCO_ERR_STATE;
     }
-    DCO_HIP_CHECK(launch_vote(dL, valid, reinterpret_cast<const uint32_t*>(armsL), aggL, false, h->W,
-                              h->W, h->H, h->D, iters, h->p.subpixel, h->s.vote[0], h->s.vote[1],
-                              disp, valid_out, dvote, HalfOut{}, h->stream));
+    DCO_HIP_CHECK(launch_vote(dL, valid, reinterpret_cast<const uint32_t*>(armsL), aggL, false,
+                              h->W, h->W, h->H, h->D, iters, h->p.subpixel, h->s.vote[0],
+                              h->s.vote[1], disp, valid_out, dvote, HalfOut{}, h->stream));
     return DCO_OK;
 }
 

@@ -114,8 +114,8 @@ __device__ inline uint64_t census_code_any(const Lds& S, int tx, int ty, int hw,
 }
 
 // One 64 x TH tile at (x0, y0), NT threads, each 64 TH / NT pixels.  The tile plus
-// a kLMax apron (edge-clamped) is staged in LDS as RGB fields; grey levels of the tile plus the census apron go to a
-// second array.
+// a kLMax apron (edge-clamped) is staged in LDS as RGB fields; grey levels of the
+// tile plus the census apron go to a second array.
 //   grey:   Y = (77 R + 150 G + 29 B + 128) >> 8
 //   census: bit k = Y(q_k) < Y(p), neighbours row-major without the centre
 //   arms:   steps j = 1.. while inside, j <= L1 and max channel |diff| < tau1
@@ -794,13 +794,13 @@ __device__ inline void agg_stream(const AggArgs& A, int d, int strip, int y0, in
 // store is one 16-byte word; in a row of any length only the quad that the
 // border cuts is stored as what is left of it (stored and, in the staged call,
 // read as single words wherever W % 4 != 0, a frame of 1279 x 720, D = 128 took
-// 0.865 ms, now 0.764, a staged one of 295 x 717, D = 41 0.312 and 0.255).  The apron is 36 rather than 2 kLMax = 34, and
-// the strip 184 rather than 188, so that those quads are aligned to the
-// image's.  The first and last strip have no apron at the image's border and
-// take 20 columns more, so that narrower strips do not mean more of them (960
-// columns are five strips, not six: 960 x 540 with D = 96 and two vote passes
-// takes 0.445 ms instead of 0.491).  Every LDS word holds the two slices' values
-// of one column (one 64-bit access serves both).
+// 0.865 ms, now 0.764, a staged one of 295 x 717, D = 41 0.312 and 0.255).  The
+// apron is 36 rather than 2 kLMax = 34, and the strip 184 rather than 188, so that
+// those quads are aligned to the image's.  The first and last strip have no apron
+// at the image's border and take 20 columns more, so that narrower strips do not
+// mean more of them (960 columns are five strips, not six: 960 x 540 with D = 96
+// and two vote passes takes 0.445 ms instead of 0.491).  Every LDS word holds the
+// two slices' values of one column (one 64-bit access serves both).
 //  * Prefix rows are exclusive (entry i is the sum of the columns before i),
 //    so a range sum over [x - l, x + r] is entry x + r + 1 minus entry x - l
 //    and no entry is needed before the first column.
@@ -961,8 +961,8 @@ __device__ inline void ws_scan(uint32_t (&v)[kWsSlices][4]) {
 // prefixes are modular and every range of a stored output ends inside the
 // image (arms stop at the border), so neither reaches a stored output.
 template <bool kFused>
-__device__ inline void ws_cost_phase(const WsItem& I, const WsCostLane& ln, const WsCostIn& in, uint2* row,
-                                     AggLdsWs& S) {
+__device__ inline void ws_cost_phase(const WsItem& I, const WsCostLane& ln, const WsCostIn& in,
+                                     uint2* row, AggLdsWs& S) {
     uint32_t q[kWsSlices][4];
     if constexpr (kFused) {
         const uint32_t rlo[4] = {in.ref[0].x, in.ref[0].y, in.ref[0].z, in.ref[0].w};
@@ -1430,8 +1430,8 @@ __device__ inline void wta_quad_step(float v, int d, float& best, int& bd, float
 // Four consecutive pixels from i on of a D-slice volume, with one 16-byte load
 // per slice and eight slices in flight.
 template <bool kSub, bool kNarrow>
-__device__ inline __attribute__((always_inline)) WtaQuad wta_quad(const float* __restrict__ agg, int P, int D, int i, int n,
-                                   int subpixel) {
+__device__ inline __attribute__((always_inline)) WtaQuad wta_quad(
+    const float* __restrict__ agg, int P, int D, int i, int n, int subpixel) {
     // each volume is read once: non-temporal loads keep it from evicting
     // reused data from the caches
     const uint32_t* __restrict__ a = reinterpret_cast<const uint32_t*>(agg) + i;
@@ -1531,8 +1531,8 @@ __device__ inline float wta_pair_delta_tr(const float* __restrict__ vol, int P, 
 // Four consecutive pixels from i on: one 16-byte load per even slice, 21 slices
 // in flight.  kSub: the left view, with the parabola's offset.
 template <bool kSub, bool kNarrow>
-__device__ inline __attribute__((always_inline)) WtaQuad wta_pairs_quad(const float* __restrict__ vol, int P, int D, int i, int n,
-                                         int subpixel) {
+__device__ inline __attribute__((always_inline)) WtaQuad wta_pairs_quad(
+    const float* __restrict__ vol, int P, int D, int i, int n, int subpixel) {
     const int G = (D + 1) / 2;
     const uint32_t* __restrict__ s = reinterpret_cast<const uint32_t*>(vol) + i;
     const size_t st = (size_t)P * 2;  // two slices
@@ -1583,10 +1583,11 @@ __device__ inline __attribute__((always_inline)) WtaQuad wta_pairs_quad(const fl
     return r;
 }
 
-// Either layout.
+// Either layout.  Inlined always: as a call its loads were flat ones and its registers
+// spilled (1280 x 720, D = 128: 119 us instead of 85).
 template <bool kPaired, bool kSub, bool kNarrow>
-__device__ inline __attribute__((always_inline)) WtaQuad wta_any(const float* __restrict__ vol, int P, int D, int i, int n,
-                                  int subpixel) {
+__device__ inline __attribute__((always_inline)) WtaQuad wta_any(
+    const float* __restrict__ vol, int P, int D, int i, int n, int subpixel) {
     if constexpr (kPaired)
         return wta_pairs_quad<kSub, kNarrow>(vol, P, D, i, n, subpixel);
     else

@@ -216,8 +216,8 @@ struct HalfOut {
 // valid) from the voted map and the aggregated costs, dv_out (optional) the map
 // itself, -1 where invalid.
 hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* arms,
-                       const float* agg, bool paired, int pitch, int W, int H, int D, int iters, int subpixel,
-                       int16_t* buf0, int16_t* buf1, float* disp, uint8_t* valid_out,
+                       const float* agg, bool paired, int pitch, int W, int H, int D, int iters,
+                       int subpixel, int16_t* buf0, int16_t* buf1, float* disp, uint8_t* valid_out,
                        int16_t* dv_out, const HalfOut& half, hipStream_t st);
 // Quarter-size front end: 2 x 2 block means of both full images (row length
 // W2 pixels) into W x H x 3 outputs.
@@ -318,8 +318,8 @@ hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int 
                          int subpixel, int maxdiff, int16_t* dL, int16_t* dR, float* disp,
                          uint8_t* valid, const HalfOut& half, hipStream_t st);
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded into out (n x H x W).
-hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d0, int n, float* out,
-                         hipStream_t st);
+hipError_t launch_unpair(const float* vol, int pitch, int W, int H, int D, int d0, int n,
+                         float* out, hipStream_t st);
 
 // k_soft.hip
 hipError_t soft_prepare(const float* theta, float* tab, const uint32_t* arms, int B, int W, int H,

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(1024) void k_geometry(const uint32_t* __restrict__ 
                                                    int iters, AggRecords rec) {
     __shared__ dco::GeomLds S;
     dco::geometry_tile(arms, W, H, iters, rec, blockIdx.x * dco::kGeoTW,
-                             blockIdx.y * dco::kGeoTH, S);
+                       blockIdx.y * dco::kGeoTH, S);
 }
 
 // Both views of the one-call path in one launch each (blockIdx.z = view);
@@ -35,9 +35,9 @@ __global__ __launch_bounds__(64 * TH) __attribute__((amdgpu_waves_per_eu(8))) vo
     uint4* __restrict__ pixL, uint4* __restrict__ pixR, bool planes) {
     __shared__ dco::CensusLdsOf<TH> S;
     const bool r = blockIdx.z != 0;
-    dco::census_tile<64 * TH, TH>(r ? rgbR : rgbL, W, H, cw, ch, L1, tau1, nullptr, r ? armsR : armsL,
-                           nullptr, r ? pixR : pixL, planes, blockIdx.x * dco::kCenTW,
-                           blockIdx.y * TH, S);
+    dco::census_tile<64 * TH, TH>(r ? rgbR : rgbL, W, H, cw, ch, L1, tau1, nullptr,
+                                  r ? armsR : armsL, nullptr, r ? pixR : pixL, planes,
+                                  blockIdx.x * dco::kCenTW, blockIdx.y * TH, S);
 }
 
 __global__ __launch_bounds__(1024) void k_geometry2(const uint32_t* __restrict__ armsL,
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(1024) void k_geometry2(const uint32_t* __restrict__
                                                    AggRecords recR) {
     __shared__ dco::GeomLds S;
     const bool r = blockIdx.z != 0;
-    dco::geometry_tile(r ? armsR : armsL, W, H, iters, r ? recR : recL,
-                             blockIdx.x * dco::kGeoTW, blockIdx.y * dco::kGeoTH, S);
+    dco::geometry_tile(r ? armsR : armsL, W, H, iters, r ? recR : recL, blockIdx.x * dco::kGeoTW,
+                       blockIdx.y * dco::kGeoTH, S);
 }
 
 // Every view of a batch of pairs in one launch (blockIdx.z = 2 * pair + view),
@@ -61,8 +61,8 @@ __global__ __launch_bounds__(64 * TH) __attribute__((amdgpu_waves_per_eu(8))) vo
     const bool r = (blockIdx.z & 1) != 0;
     const size_t P = (size_t)W * H, o = P * (blockIdx.z >> 1);
     dco::census_tile<64 * TH, TH>((r ? rgbR : rgbL) + 3 * o, W, H, cw, ch, L1, tau1, nullptr,
-                           (r ? armsR : armsL) + o, nullptr, (r ? pixR : pixL) + o, false,
-                           blockIdx.x * dco::kCenTW, blockIdx.y * TH, S);
+                                  (r ? armsR : armsL) + o, nullptr, (r ? pixR : pixL) + o, false,
+                                  blockIdx.x * dco::kCenTW, blockIdx.y * TH, S);
 }
 
 // Rows of a census tile.  A tile of 16 rows is least work per pixel (its apron is

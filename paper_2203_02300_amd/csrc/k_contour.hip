@@ -197,7 +197,8 @@ __device__ inline int sobel_tile(const uint8_t* __restrict__ rgb, int W, int H, 
     } else {
         for (int k = t; k < kSobRH * kSobRW; k += 256) {
             const int ry = k / kSobRW, c = k - ry * kSobRW;
-            const int xx = dco::clampi(x0 + c - 2, 0, W - 1), yy = dco::clampi(y0 + ry - 1, 0, H - 1);
+            const int xx = dco::clampi(x0 + c - 2, 0, W - 1);
+            const int yy = dco::clampi(y0 + ry - 1, 0, H - 1);
             const size_t q = 3 * ((size_t)yy * W + xx);
             S.Y[ry][c] = (int)dco::grey_of((uint32_t)rgb[q] | (uint32_t)rgb[q + 1] << 8 |
                                            (uint32_t)rgb[q + 2] << 16);
@@ -377,7 +378,8 @@ __global__ __launch_bounds__(256) void k_hyst(const unsigned long long* __restri
                                               int* __restrict__ changed,
                                               uint8_t* __restrict__ B) {
     const int nw = plane_words(W);
-    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), y = blockIdx.y * kHystRows + (threadIdx.x & 63);
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int y = blockIdx.y * kHystRows + (threadIdx.x & 63);
     // the same values for every thread of every block
     const bool final_state = prev && *prev == 0;
     if (final_state) {

@@ -939,8 +939,8 @@ __global__ __launch_bounds__(kSoftCols) void k_soft_vv(SoftGeom g, const float* 
         h1[k] = l1[k] = h2[k] = l2[k] = 0.0;
     }
     double acc1 = 0.0, acc2 = 0.0;
-    const auto up = [&](uint32_t q) { return (q & 0x3e00u) | t8; };           // 512 dn + 8 t
-    const auto dn = [&](uint32_t q) { return (q << 5 & 0x3e00u) | t8; };      // 512 (kLMax - u) + 8 t
+    const auto up = [&](uint32_t q) { return (q & 0x3e00u) | t8; };       // 512 dn + 8 t
+    const auto dn = [&](uint32_t q) { return (q << 5 & 0x3e00u) | t8; };  // 512 (kLMax - u) + 8 t
     const auto at = [](char* r, uint32_t o) { return reinterpret_cast<double*>(r + o); };
     for (int y0 = first - kSoftLead * kSoftPre; y0 < last; y0 += kSoftRing) {
 #pragma unroll
@@ -1166,7 +1166,8 @@ static int soft_segments(int W, int H, int planes) {
     for (int s = 1; s <= 8; ++s) {
         const int rows = (H + s - 1) / s;
         const int head = s > 1 ? 2 * kLMax : 0;
-        const int turns = (kSoftLead * kSoftPre + head + rows + kSoftLag + kSoftRing - 1) / kSoftRing;
+        const int walked = kSoftLead * kSoftPre + head + rows + kSoftLag;
+        const int turns = (walked + kSoftRing - 1) / kSoftRing;
         const long long cost = (wgs * s + kSoftSlots - 1) / kSoftSlots * turns;
         if (least < 0 || cost < least) least = cost, best = s;
     }

@@ -27,13 +27,15 @@
 // running maximum keeps the smallest disparity among equal counts.  All counts
 // are integers, so the result does not depend on the order of the additions.
 //
-// Bound by the chain of loads and LDS steps of a tile, not by issue or memory: a
-// pass over 640 x 360 (480 tiles, one round) takes 12.0 us, over 960 x 540, D =
-// 96 (1080 tiles, three per CU) 25.5.  With the rows coded by a thread each, the
-// prefixes by a quarter of the threads, windows of 16 over the range and two
-// tiles per CU they took 19.4 and 50.  The last pass makes the outputs itself
-// (3.5 us more; as a launch 5.2 to 5.9, and 5 for the depth of the quarter-size
-// front end).
+// Bound by the chain of loads and LDS steps of a tile, not by issue or memory, and
+// longer with more runs in the tile's rows.  Pairs of a slanted background and six
+// boxes, noise of two grey levels: a pass over 640 x 360 (480 tiles, one round) takes
+// 12.4 us, over 960 x 540, D = 96 (1080 tiles, three per CU) 23.7.  With the rows coded
+// by a thread each, the prefixes by a quarter of the threads, windows of 16 over the
+// range and two tiles per CU they took 19.4 and 50.  (Ten slanted planes and two boxes
+// at 1280 x 720, reduced to 640 x 360: 23.6 us.)  The last pass makes the outputs
+// itself (2.8 to 3.5 us more; as a launch 5.2 to 5.9, and 5 for the depth of the
+// quarter-size front end).
 #include "dco_device.h"
 
 namespace {
@@ -360,6 +362,7 @@ hipError_t launch_vote(const int16_t* dL, const uint8_t* valid, const uint32_t* 
         hipLaunchKernelGGL(k_vote<true>, grid, dim3(kVThreads), 0, st, src, mask, arms, W, H, D,
                            (int16_t*)nullptr, o);
     else
-        hipLaunchKernelGGL(k_vote_finish, dim3((W * H + 255) / 256), dim3(256), 0, st, src, mask, o);
+        hipLaunchKernelGGL(k_vote_finish, dim3((W * H + 255) / 256), dim3(256), 0, st, src, mask,
+                           o);
     return hipGetLastError();
 }

@@ -1,9 +1,9 @@
 // k_wta.hip -- winner-take-all over the aggregated volumes (Eq. 3) with
 // parabola sub-pixel refinement, and the left-right consistency check, in one
-// launch (two for long rows).  On volumes in the paired layout (dco::paired_at) only
-// the even slices are read; for the sub-pixel step the winner's pair partner is gathered and,
-// when it is not the adjacent pair's minimum kept from the scan, its other
-// neighbour.  A thread takes four consecutive pixels with 16-byte loads and
+// launch (two for long rows).  On volumes in the paired layout (dco::paired_at)
+// only the even slices are read; for the sub-pixel step the winner's pair partner
+// is gathered and, when it is not the adjacent pair's minimum kept from the scan,
+// its other neighbour.  A thread takes four consecutive pixels with 16-byte loads and
 // walks d = 0 .. D-1; loads of one slice are coalesced across the row, so each
 // volume is read exactly once.  The stage bodies live in dco_device.h.
 #include <algorithm>
