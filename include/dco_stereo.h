@@ -215,8 +215,8 @@ dco_status dco_stereo_last_disparities(dco_stereo* h, int16_t* dL, int16_t* dR);
  * stage s < n, ms[s] = total milliseconds over the recorded calls, and
  * *calls = the number of recorded calls.  Stages: 0 census + arms + region
  * counts of both views, 1 cost + aggregation of both views (one launch),
- * 2 WTA of both views with the LR check (one launch, two where rows have more
- * than 2048 columns), 3 nothing more (the check was a stage of its own; the
+ * 2 WTA of both views with the LR check (one launch; two for very long, many
+ * short or few deep rows), 3 nothing more (the check was a stage of its own; the
  * events alone are left), 4 Eq. 4 vote and its sub-pixel output (the events
  * alone when vote_iters = 0).  ms: host array of n floats. */
 #define DCO_NUM_STAGES 5

@@ -1,6 +1,6 @@
 // k_wta.hip -- winner-take-all over the aggregated volumes (Eq. 3) with
 // parabola sub-pixel refinement, and the left-right consistency check, in one
-// launch (two for long rows).  On volumes in the paired layout (dco::paired_at)
+// launch (two where rows suit workgroups badly).  On volumes in the paired layout (dco::paired_at)
 // only the even slices are read; for the sub-pixel step the winner's pair partner
 // is gathered and, when it is not the adjacent pair's minimum kept from the scan,
 // its other neighbour.  A thread takes four consecutive pixels with 16-byte loads and
@@ -83,14 +83,9 @@ __global__ __launch_bounds__(kWtaThreads) void k_wta_row(
     if (t < nt && t < nq) check(t, l);
 }
 
-// Rows past kRowCols: WTA as a launch of a quad per thread, whatever row it is in, the
-// left view (blockIdx.y = 0) with disp = its disparity before the check, and the check
-// as a launch after it.  With the rest of such a row in turns of k_wta_row, 8192 x 16,
-// D = 64 took 68.1 us (staged volumes 78.2), as two launches 17.6 (20.2): a few long
-// rows left most CUs idle; 2100 x 400 67.2 (93.2), now 56.5 (77.8); 2560 x 600 110.5
-// (153.1), now 92.1 (142.6); 3840 x 1080 257.0 (389.9), now 243.0 (386.1).  Up to
-// kRowCols the row kernel is one turn and saves the check's launch, 4 to 5 us at
-// small frames.
+// Rows that suit workgroups badly (by_quads): WTA as a launch of a quad per thread,
+// whatever row it is in, the left view (blockIdx.y = 0) with disp = its disparity
+// before the check, and the check as a launch after it, which costs 2 to 5 us.
 template <bool kPaired>
 __global__ __launch_bounds__(256) void k_wta_quads(const float* __restrict__ aggL,
                                                    const float* __restrict__ aggR, int pitch,
@@ -128,6 +123,29 @@ __global__ __launch_bounds__(256) void k_lrcheck(const int16_t* __restrict__ dL,
     valid[i] = ok ? 1 : 0;
 }
 
+// Where k_wta_quads and k_lrcheck are faster than k_wta_row.  Times of the row kernel,
+// then of the two launches, for paired volumes (whole ones in brackets):
+//   - rows past kRowCols, which k_wta_row would take in turns: 8192 x 16, D = 64 68.1 us
+//     (78.2), 17.6 (20.2); 2100 x 400 67.2 (93.2), 56.5 (77.8); 2560 x 600 110.5
+//     (153.1), 92.1 (142.6); 3840 x 1080 257.0 (389.9), 243.0 (386.1);
+//   - many short rows, whose idle lanes (of both views) would make more than 1536
+//     threads on each CU: 33 x 4000, D = 32 14.2 (20.7), 13.4 (12.2); 33 x 16000 42.8
+//     (64.8), 25.2 (28.8); 65 x 8000 25.8 (37.4), 22.5 (28.6); but 33 x 2384 10.9
+//     (13.6), 11.7 (11.0), 17 x 2300, D = 12 8.0 (7.1), 10.1 (7.5);
+//   - few long rows of many disparities, whose volumes are more than half of the CUs or
+//     fewer can read in that time: 2048 x 8, D = 128 20.1 (29.4), 12.7 (27.5); 2048 x
+//     100 24.2 (51.2), 22.8 (38.6); 1600 x 64 20.4 (35.4), 15.6 (30.4); but 2048 x 200
+//     34.3 (62.9), 43.9 (73.6), 1280 x 48 15.5 (27.3), 14.2 (28.6), 2048 x 32, D = 32
+//     9.6 (8.0), 9.7 (10.0).
+// Else the launch that the row kernel saves is worth more: 320 x 240, D = 32 5.9 (8.6),
+// 10.0 (11.0).
+constexpr int kCus = 256;
+bool by_quads(int W, int H, int D, int nt) {
+    const int idle = nt - (W + 3) / 4;  // of a view's threads in a row's workgroup
+    return W >= 4 && (W > kRowCols || 2LL * H * idle > kCus * 1536 ||
+                      (2 * H <= kCus && (long long)W * D > 192 * 1024));
+}
+
 // Slices d0 .. d0 + n - 1 of a paired-layout volume, decoded to n x P.
 __global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, int pitch, int W,
                                                 int H, int D, int d0, int n,
@@ -144,7 +162,8 @@ __global__ __launch_bounds__(256) void k_unpair(const float* __restrict__ vol, i
 hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int pitch, int W,
                          int H, int D, int subpixel, int maxdiff, int16_t* dL, int16_t* dR,
                          float* disp, uint8_t* valid, const HalfOut& half, hipStream_t st) {
-    if (W > kRowCols) {
+    const int nt = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
+    if (by_quads(W, H, D, nt)) {
         const auto quads = paired ? k_wta_quads<true> : k_wta_quads<false>;
         const unsigned n = (unsigned)H * ((W + 3) / 4);
         hipLaunchKernelGGL(quads, dim3((n + 255) / 256, 2), dim3(256), 0, st, aggL, aggR, pitch,
@@ -153,7 +172,6 @@ hipError_t launch_wta_lr(const float* aggL, const float* aggR, bool paired, int 
                            W, W * H, maxdiff, disp, valid, half);
         return hipGetLastError();
     }
-    const int nt = std::min(kWtaThreads / 2, ((W + 3) / 4 + 63) / 64 * 64);
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(H), dim3(2 * nt), (size_t)W * sizeof(int16_t), st, aggL,
                            aggR, pitch, pitch * H, W, D, subpixel, maxdiff, dL, dR, disp, valid,

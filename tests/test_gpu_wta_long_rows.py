@@ -1,6 +1,7 @@
-"""WTA and left-right check of rows past 2048 columns (two launches of quads) and at
-that edge (one workgroup per row): against a plain scan of the volumes, every element,
-at rows that end anywhere within a quad and at workgroups that span several rows."""
+"""WTA and left-right check where they are two launches of quads: rows past 2048
+columns, many short rows, few deep ones, and the shapes next to those (one workgroup
+per row).  Against a plain scan of the volumes, every element, at rows that end
+anywhere within a quad and at workgroups that span several rows."""
 import numpy as np
 import pytest
 
@@ -24,10 +25,15 @@ def plain(aggL, aggR):
     return dL, dR, ok, np.where(ok, dL.astype(np.float32) + off, np.float32(0))
 
 
-# the longest row of one workgroup, the shortest past it, remainders of 1 to 3 pixels
+# the longest row of one workgroup, the shortest past it, remainders of 1 to 3 pixels;
+# short rows of 4 to 66 columns (33 x 3574: the last before the rule's edge); rows of
+# more and of fewer than 192 Ki costs
 @pytest.mark.parametrize("W,H,D", [(2047, 4, 9), (2048, 4, 9), (2049, 8, 5), (2052, 3, 64),
                                    (2050, 7, 257), (2081, 2, 1), (3001, 9, 300), (4099, 40, 17),
-                                   (8191, 7, 33), (4000, 257, 8), (16383, 7, 60), (2561, 2, 2000)])
+                                   (8191, 7, 33), (4000, 257, 8), (16383, 7, 60), (2561, 2, 2000),
+                                   (4, 3200, 3), (5, 3200, 4), (33, 3574, 7), (33, 3575, 7),
+                                   (17, 16384, 6), (66, 4301, 12), (2047, 7, 97), (2047, 7, 96),
+                                   (1801, 128, 110), (1801, 129, 110)])
 def test_long_rows(W, H, D):
     from paper_2203_02300_amd import StereoMatcher
     rng = np.random.default_rng(W + D)
@@ -46,7 +52,8 @@ def test_long_rows(W, H, D):
     assert np.array_equal(disp.view(np.uint32), want[3].view(np.uint32))
 
 
-@pytest.mark.parametrize("W,H,D", [(2048, 8, 5), (2049, 8, 5), (2309, 9, 40), (4099, 12, 17)])
+@pytest.mark.parametrize("W,H,D", [(2048, 8, 5), (2049, 8, 5), (2309, 9, 40), (4099, 12, 17),
+                                   (34, 3600, 7), (19, 9000, 8), (2046, 19, 98)])
 def test_long_rows_of_one_call(W, H, D):
     """The one call (paired volumes) against the staged calls."""
     from paper_2203_02300_amd import StereoMatcher
